@@ -1194,6 +1194,25 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
   // the workgroups of one XCD (round robin by workgroup) take one contiguous eighth of the chunks
   // (ranges aligned to groups of U chunks).
   int32_t cstart = wid * U, cend = nchunks, cstep = nwaves * U;
+  // A union's moves belong to the hypergraphs listed in the phase, and every chunk holds nets of one
+  // hypergraph: each wave takes a contiguous range of the listed hypergraphs' chunks and adds the
+  // metric change of one hypergraph at a time, with one atomic when the range crosses into the
+  // next.  (One atomic per net piled onto 96 addresses: 1,270 us per launch on 96 hypergraphs.)
+  const ActList *AL = un.vhg ? &un.act[want == kPhRb ? kActRb : want == kPhRoll ? kActRoll : kActJet] : nullptr;
+  int32_t li = 0, lend = nchunks, hg = 0, vshift = 0;  // list position, its end, hypergraph, virtual -> real
+  if (AL) {
+    const int32_t nv = AL->cpref[AL->cnt];
+    const int32_t per = ((nv + nwaves - 1) / nwaves + U - 1) / U * U;
+    cstart = min((int64_t)wid * per, (int64_t)nv);
+    cend = min((int64_t)cstart + per, (int64_t)nv);
+    cstep = U;
+    if (cstart < cend) {
+      li = act_find(AL->cpref, AL->cnt, cstart);
+      lend = AL->cpref[li + 1];
+      hg = AL->hg[li];
+      vshift = un.hch0[hg] - AL->cpref[li];
+    }
+  }
   if (xcd && !un.vhg && gridDim.x % 8 == 0) {
     const int32_t span = 4 * U, steps = (nchunks + span - 1) / span, per = (steps + 7) / 8;
     const int32_t x = (int32_t)(blockIdx.x % 8);
@@ -1201,10 +1220,25 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
     cend = min(nchunks, (x + 1) * per * span);
     cstep = (int32_t)(gridDim.x / 8) * span;
   }
-  for (int32_t c0 = cstart; c0 < cend; c0 += cstep) {  // wave-uniform trip count
+  for (int32_t c0 = cstart, cnext; c0 < cend; c0 = cnext) {  // wave-uniform trip count
+    int32_t gend = cend;  // end of this group's chunks
+    cnext = c0 + cstep;
+    if (AL) {
+      if (c0 >= lend) {  // the next hypergraph with chunks
+        const int64_t d = wave_sum(dk);
+        if (l == 0) add_km1_hg(st, hg, d);
+        dk = 0;
+        while (c0 >= AL->cpref[li + 1]) ++li;
+        lend = AL->cpref[li + 1];
+        hg = AL->hg[li];
+        vshift = un.hch0[hg] - AL->cpref[li];
+      }
+      gend = min(cend, lend);
+      cnext = min(cnext, gend);
+    }
     int4 cd[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) cd[u] = c0 + u < cend ? chunks[c0 + u] : make_int4(0, 0, 0, 0);
+    for (int u = 0; u < U; ++u) cd[u] = c0 + u < gend ? chunks[c0 + u + vshift] : make_int4(0, 0, 0, 0);
     int32_t v[U], j[U];
     bool act[U];
 #pragma unroll
@@ -1280,18 +1314,17 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
           if (a != wd[u][x]) nse[x] = a;
           if ((a & ~bb) != wd[u][NW + x]) nse[NW + x] = a & ~bb;
         }
-        if (lam_new != lam_old) {
-          const int64_t d = (int64_t)(lam_new - lam_old) * (nw ? nw[e] : 1);
-          if (un.nhg) add_km1_hg(st, un.nhg[e], d);
-          else dk += d;
-        }
+        if (lam_new != lam_old) dk += (int64_t)(lam_new - lam_old) * (nw ? nw[e] : 1);
       }
       wave_lds_sync();  // the LDS slots are reused by the next chunk
       if (act[u]) cnt[w][j[u]][nb[u] >> 2] = 0u;  // every nonzero counter word has a pin here
     }
   }  // chunk-group loop
   dk = wave_sum(dk);
-  if (l == 0) add_km1(st, wid, dk);
+  if (l == 0) {
+    if (AL) add_km1_hg(st, hg, dk);
+    else add_km1(st, wid, dk);
+  }
 }
 
 // Net-centric, larger nets: one block per net; per-block count changes gathered in LDS, then the
@@ -1313,6 +1346,7 @@ __global__ __launch_bounds__(THREADS) void k_apply_nets(const int64_t *__restric
   int64_t dk = 0;  // metric change of this block's nets (thread 0)
   for (int32_t bi = blockIdx.x; bi < nnets; bi += gridDim.x) {  // block-uniform trip count
   const int32_t e = nets[bi];
+  if (u.lcs && u.lcs[u.nhg[e]].phase != want) continue;  // union: no move of an idle hypergraph
   const int64_t q0 = off[e], q1 = off[e + 1];
   for (int b = threadIdx.x; b < k; b += blockDim.x) delta[b] = 0;
   if (threadIdx.x == 0) any = 0;

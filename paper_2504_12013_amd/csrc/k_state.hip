@@ -78,14 +78,6 @@ __global__ __launch_bounds__(256) void k_build_ns(const T *__restrict__ phi, int
 __global__ __launch_bounds__(256) void k_block_weights(const int32_t *__restrict__ part,
                                                        const int32_t *__restrict__ vw, int32_t n, int32_t k,
                                                        DevStatus *st, Union u) {
-  if (u.vhg) {  // union: one atomic per vertex into its hypergraph's segment
-    for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-      const int64_t sg = (int64_t)u.vhg[v] * k + part[v];
-      atomicAdd((unsigned long long *)&st->bw[sg], (unsigned long long)(vw ? vw[v] : 1));
-      atomicAdd(&st->bcnt[sg], 1);
-    }
-    return;
-  }
   __shared__ unsigned long long sw[kMaxK];
   __shared__ int32_t sc[kMaxK];
   for (int b = threadIdx.x; b < k; b += blockDim.x) {
@@ -93,6 +85,38 @@ __global__ __launch_bounds__(256) void k_block_weights(const int32_t *__restrict
     sc[b] = 0;
   }
   __syncthreads();
+  if (u.vhg) {
+    // union: a workgroup takes a contiguous range of tiles (every tile holds one hypergraph's
+    // vertices) and adds its sums to the segments where the range crosses into the next hypergraph
+    // (an atomic per vertex on the few segments took 540 us for 96 hypergraphs)
+    const int64_t nt = (n + kUnionTile - 1) / kUnionTile, per = (nt + gridDim.x - 1) / gridDim.x;
+    const int64_t t0 = (int64_t)blockIdx.x * per, t1 = min(nt, t0 + per);
+    for (int64_t t = t0; t < t1; ++t) {  // block-uniform trip count
+      const int64_t v = t * kUnionTile + threadIdx.x;
+      const int32_t hg = u.vhg[t * kUnionTile];
+      const bool mine = v < n && u.vhg[v] == hg;
+      if (mine) {
+        const int32_t b = part[v];
+        atomicAdd(&sw[b], (unsigned long long)(vw ? vw[v] : 1));
+        atomicAdd(&sc[b], 1);
+      } else if (v < n) {  // padding: the pseudo-hypergraph's segments
+        const int64_t sg = (int64_t)u.vhg[v] * k + part[v];
+        atomicAdd((unsigned long long *)&st->bw[sg], (unsigned long long)(vw ? vw[v] : 1));
+        atomicAdd(&st->bcnt[sg], 1);
+      }
+      if (t + 1 < t1 && u.vhg[(t + 1) * kUnionTile] == hg) continue;
+      __syncthreads();
+      for (int b = threadIdx.x; b < k; b += blockDim.x) {
+        const int64_t sg = (int64_t)hg * k + b;
+        if (sw[b]) atomicAdd((unsigned long long *)&st->bw[sg], sw[b]);
+        if (sc[b]) atomicAdd(&st->bcnt[sg], sc[b]);
+        sw[b] = 0;
+        sc[b] = 0;
+      }
+      __syncthreads();
+    }
+    return;
+  }
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
     const int32_t b = part[v];
     atomicAdd(&sw[b], (unsigned long long)(vw ? vw[v] : 1));
@@ -109,13 +133,43 @@ template <int NW>
 __global__ __launch_bounds__(256) void k_km1(const uint64_t *__restrict__ ns, const int32_t *__restrict__ nw,
                                              int32_t m, DevStatus *st, Union u) {
   int64_t s = 0;
+  if (u.nhg) {
+    // union: a wave takes a contiguous range of nets (nets are numbered by hypergraph) and adds its
+    // sum where the range crosses into the next hypergraph; a step of 64 nets that spans two adds
+    // per net (an atomic per net on the few addresses took 2.1 ms for 96 hypergraphs)
+    const int64_t nwv = (int64_t)gridDim.x * (blockDim.x / kWave);
+    const int64_t per = ((m + nwv - 1) / nwv + kWave - 1) / kWave * kWave;
+    const int64_t e0 = ((int64_t)blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave) * per;
+    const int64_t e1 = min((int64_t)m, e0 + per);
+    int32_t hg = -1;
+    for (int64_t eb = e0; eb < e1; eb += kWave) {  // wave-uniform trip count
+      const int64_t e = eb + lane_id();
+      const int32_t h0 = u.nhg[eb], h1 = u.nhg[min(e1, eb + kWave) - 1];
+      int64_t d = 0;
+      if (e < e1) {
+        int lam = 0;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) lam += __popcll(ns[e * 2 * NW + w]);
+        d = (int64_t)(lam - 1) * (nw ? nw[e] : 1);
+      }
+      if (h0 != hg || h0 != h1) {
+        s = wave_sum(s);
+        if (lane_id() == 0 && hg >= 0) add_km1_hg(st, hg, s);
+        s = 0;
+        hg = h0;
+      }
+      if (h0 == h1) s += d;
+      else if (e < e1) add_km1_hg(st, u.nhg[e], d);
+    }
+    s = wave_sum(s);
+    if (lane_id() == 0 && hg >= 0) add_km1_hg(st, hg, s);
+    return;
+  }
   for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < m; e += (int64_t)gridDim.x * blockDim.x) {
     int lam = 0;
 #pragma unroll
     for (int w = 0; w < NW; ++w) lam += __popcll(ns[e * 2 * NW + w]);
-    const int64_t d = (int64_t)(lam - 1) * (nw ? nw[e] : 1);
-    if (u.nhg) add_km1_hg(st, u.nhg[e], d);  // union: per hypergraph
-    else s += d;
+    s += (int64_t)(lam - 1) * (nw ? nw[e] : 1);
   }
   s = wave_sum(s);
   if (lane_id() == 0) add_km1(st, blockIdx.x * (blockDim.x / kWave) + threadIdx.x / kWave, s);
