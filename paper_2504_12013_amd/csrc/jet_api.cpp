@@ -1403,8 +1403,10 @@ int make_union(const std::vector<HostHg> &hh, const std::vector<int32_t> &ids, h
   c.H = (int32_t)ids.size();
   // every hypergraph's vertices start on a tile; the padding vertices up to the next start belong
   // to the pseudo-hypergraph H (no nets, block 0, never in a phase)
+  // (a lone hypergraph of its k is a plain context: no padding, its record is the gate record)
+  const bool lone = ids.size() == 1;
   int64_t v0 = 0, e0 = 0;
-  any_vw = true;  // padding vertices need a weight of their own: every vertex gets one
+  any_vw = any_vw || !lone;  // padding vertices need a weight of their own: every vertex gets one
   for (size_t h = 0; h < ids.size(); ++h) {
     const HostHg &g = hh[ids[h]];
     c.hg_v0.push_back((int32_t)v0);
@@ -1415,7 +1417,7 @@ int make_union(const std::vector<HostHg> &hh, const std::vector<int32_t> &ids, h
     if (any_nw)
       for (int32_t e = 0; e < g.m; ++e) nw.push_back(g.nw.empty() ? 1 : g.nw[e]);
     for (int32_t v = 0; v < g.n; ++v) vw.push_back(g.vw.empty() ? 1 : g.vw[v]);
-    const int64_t padded = (g.n + jet::kUnionTile - 1) / jet::kUnionTile * jet::kUnionTile;
+    const int64_t padded = lone ? g.n : (g.n + jet::kUnionTile - 1) / jet::kUnionTile * jet::kUnionTile;
     for (int64_t v = g.n; v < padded; ++v) vw.push_back(1);
     vhg.insert(vhg.end(), (size_t)g.n, (uint16_t)h);
     vhg.insert(vhg.end(), (size_t)(padded - g.n), (uint16_t)ids.size());
@@ -1435,7 +1437,7 @@ int make_union(const std::vector<HostHg> &hh, const std::vector<int32_t> &ids, h
   c.hg_e0.push_back((int32_t)e0);
   int rc = init_impl(c, (int32_t)n, (int32_t)m, p, off.data(), pins.data(), any_nw ? nw.data() : nullptr,
                      any_vw ? vw.data() : nullptr);
-  if (rc == JET_OK) {
+  if (rc == JET_OK && !lone) {
     hipError_t e = dalloc(&c.vhg, vhg.size());
     if (e == hipSuccess) e = dalloc(&c.nhg, nhg.size());
     if (e == hipSuccess) e = hipMemcpy(c.vhg, vhg.data(), sizeof(uint16_t) * vhg.size(), hipMemcpyHostToDevice);
