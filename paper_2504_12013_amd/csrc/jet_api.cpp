@@ -556,8 +556,6 @@ int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_sta
   fill_record(c.hlcs[0], *prm, rb_only, trace_cap, c.lmax, dz, c.A);
   HIP_OR_FAIL(&c, hipMemcpyAsync(c.lcs, c.hlcs, sizeof(jet::LoopCtl), hipMemcpyHostToDevice, c.stream));
   HIP_OR_FAIL(&c, jet::launch_loop_init(c));
-  if (!rb_only)
-    HIP_OR_FAIL(&c, hipMemcpyAsync(c.best, c.cpart, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.stream));
   if (c.use_graph) {
     rc = ensure_graphs(c);
     if (rc != JET_OK) return rc;
@@ -1604,8 +1602,6 @@ int jet_batch_refine(jet_batch *b, int32_t *const *parts, const jet_params *para
     }
     hipError_t e = hipMemcpyAsync(c.lcs, c.hlcs, sizeof(jet::LoopCtl) * (size_t)c.H, hipMemcpyHostToDevice, s);
     if (e == hipSuccess) e = jet::launch_loop_init(c);
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(c.best, c.cpart, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, s);
     if (e != hipSuccess) return batch_fail(b, JET_EHIP, std::string("loop set-up: ") + hipGetErrorString(e));
   }
   // the whole batch's iteration as one graph: every union context's launches, one after another

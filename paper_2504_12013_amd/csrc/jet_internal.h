@@ -83,10 +83,10 @@ struct LoopCtl {
   int32_t lock_was_any;   // lock_any as it was when the current iteration began
   int32_t n_cand, n_moved;          // the current iteration's Jet phase
   int32_t rb_rounds, rb_moved;      // the current iteration's rebalancing rounds
-  int32_t improved;       // the iteration just ended improved the key: snapshot wanted
+  int32_t improved;       // the current partition is the round's best and not in `best` yet: the next
+                          // candidate pass copies it, a rollback has nothing to undo
   int32_t ntrace;         // iteration records written (counted beyond the capacity too)
   int32_t iterations, rebalance_rounds, moves_executed;  // totals of the call
-  int32_t ticks;          // replays that found work
   int64_t km1;            // exact metric of the current partition
   int64_t best_ovl, best_km1;
   int64_t km1_in;
@@ -122,7 +122,7 @@ struct ActList {
   int32_t tpref[kMaxH + 2];
   int32_t cpref[kMaxH + 2];
 };
-enum : int { kActJet = 0, kActRb = 1, kActRoll = 2, kActImproved = 3, kActLists = 4 };
+enum : int { kActJet = 0, kActRb = 1, kActRoll = 2, kActLists = 3 };
 
 // The hypergraphs of a union context as the kernels see them; lcs == nullptr for a context of one
 // hypergraph (its record is the gate record, segments are blocks).
@@ -473,12 +473,12 @@ hipError_t launch_import_candidates(Ctx &c, const int32_t *part, const int32_t *
 // expects n_ovf == 0 (cleared by launch_candidates or launch_reset_counters)
 hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc = nullptr);
 enum : int32_t { kResetCandidates = 1, kResetMoves = 2 };
-hipError_t launch_reset_counters(Ctx &c, int32_t what, const LoopCtl *lc = nullptr, int32_t want = kPhAny);
+hipError_t launch_reset_counters(Ctx &c, int32_t what);
 hipError_t launch_afterburner_overflow(Ctx &c, RgSink sink, const LoopCtl *lc);  // k_ab_large.hip
 hipError_t launch_select_moves(Ctx &c, const int32_t *part, int32_t stamp, const LoopCtl *lc = nullptr);
 // wide: size the net-centric grids for that path (a performance hint; the device decides the path)
 hipError_t launch_apply_moves(Ctx &c, int32_t *part, bool wide, const LoopCtl *lc = nullptr, int32_t want = kPhAny);
-hipError_t launch_diff_moves(Ctx &c, const int32_t *part, const int32_t *target, const LoopCtl *lc = nullptr);
+hipError_t launch_diff_moves(Ctx &c, const int32_t *part, const int32_t *target, const LoopCtl *lc);
 
 // rebalancing (k_rebal.hip)
 hipError_t launch_rebalance_round(Ctx &c, const int32_t *part, int64_t dz, int32_t *sel_target,
@@ -492,6 +492,8 @@ hipError_t launch_tick(Ctx &c, int kind);
 // loop records for a call: the host wrote each hypergraph's parameters into c.lcs; this completes
 // them from the status block (metric, overload, first phase) and sets the gate record
 hipError_t launch_loop_init(Ctx &c);
+// zeroes the candidate bits where the candidate kernel of this context only sets them
+hipError_t launch_clear_candidate_bits(Ctx &c);
 hipError_t launch_fill_u32(Ctx &c, uint32_t *p, int64_t count, uint32_t value, const LoopCtl *lc, int32_t want);
 
 // k_graph.hip: graph-specialised afterburner (every net of two pins)

@@ -49,12 +49,14 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw,
     const int32_t *__restrict__ lockstamp, int32_t locked_stamp, const uint8_t *__restrict__ lock_bytes, int32_t n,
-    int32_t tau_q, uint64_t *__restrict__ rec, uint32_t *__restrict__ inm, DevStatus *st, const LoopCtl *lc,
-    Union u) {
+    int32_t tau_q, uint64_t *__restrict__ rec, uint32_t *__restrict__ inm, int32_t *__restrict__ best, DevStatus *st,
+    const LoopCtl *lc, Union u) {
   JET_GATE(lc, kPhJet);
+  bool snap = false;  // the partition is the round's best so far: the rollback point (Algorithm 1)
   if (lc && !u.lcs) {
     locked_stamp = lc->stamp - 1;
     tau_q = lc->tau_q;
+    snap = lc->improved != 0;
   }
   constexpr int BLOCK = (G == 16) ? 512 : 256;
   constexpr int VPB = BLOCK / G;
@@ -87,13 +89,15 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
       q1 = voff[v + 1];
       hub = q1 - q0 > kHubDegree;
       int32_t ls = locked_stamp;
-      bool off = false;
+      bool off = false, sn = snap;
       if (u.lcs) {  // the vertex's own hypergraph decides (union)
         const LoopCtl &h = u.lcs[u.vhg[v]];
         off = h.phase != kPhJet;
         ls = h.stamp - 1;
         tq = h.tau_q;
+        sn = !off && h.improved != 0;
       }
+      if (sn && lg == 0) best[v] = s;
       const bool locked = lock_bytes ? (lock_bytes[v] != 0) : (lockstamp[v] == ls);
       skip = locked || hub || off;
     }
@@ -151,12 +155,14 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw, const int32_t *__restrict__ lockstamp,
     int32_t locked_stamp, const uint8_t *__restrict__ lock_bytes, int32_t n, int32_t tau_q,
-    uint64_t *__restrict__ rec, uint32_t *__restrict__ inm, DevStatus *st, const LoopCtl *lc, Union u,
-    int32_t xcd) {
+    uint64_t *__restrict__ rec, uint32_t *__restrict__ inm, int32_t *__restrict__ best, DevStatus *st,
+    const LoopCtl *lc, Union u, int32_t xcd) {
   JET_GATE(lc, kPhJet);
+  bool snap = false;  // the partition is the round's best so far: the rollback point (Algorithm 1)
   if (lc && !u.lcs) {
     locked_stamp = lc->stamp - 1;
     tau_q = lc->tau_q;
+    snap = lc->improved != 0;
   }
   constexpr int VPW = kWave / G;  // vertices per wave and step
   __shared__ unsigned long long wscan[4];
@@ -194,13 +200,15 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
       q1 = voff[v + 1];
       hub = q1 - q0 > kHubDegree;
       int32_t ls = locked_stamp;
-      bool off = false;
+      bool off = false, sn = snap;
       if (u.lcs) {  // the vertex's own hypergraph decides (union)
         const LoopCtl &h = u.lcs[u.vhg[v]];
         off = h.phase != kPhJet;
         ls = h.stamp - 1;
         tq = h.tau_q;
+        sn = !off && h.improved != 0;
       }
+      if (sn && lg == 0) best[v] = s;
       const bool locked = lock_bytes ? (lock_bytes[v] != 0) : (lockstamp[v] == ls);
       skip = locked || hub || off;
     }
@@ -944,9 +952,14 @@ __global__ __launch_bounds__(kSelBlock) void k_diff_moves(const int32_t *__restr
                                                           int32_t *__restrict__ bigmv, const LoopCtl *lc,
                                                           Union u) {
   JET_GATE(lc, kPhRoll);
-  // union: only the hypergraphs whose round ended roll back
+  // union: only the hypergraphs whose round ended roll back; a partition that is its round's best
+  // without a snapshot yet stays (target holds an older one)
+  const bool stay = !u.lcs && lc && lc->improved != 0;
   auto pred = [&](int64_t v) {
-    return part[v] != target[v] && (!u.lcs || u.lcs[u.vhg[v]].phase == kPhRoll);
+    if (stay || part[v] == target[v]) return false;
+    if (!u.lcs) return true;
+    const LoopCtl &h = u.lcs[u.vhg[v]];
+    return h.phase == kPhRoll && h.improved == 0;
   };
   auto emit = [&](int64_t v, int32_t pos) -> unsigned long long {
     moves[pos] = make_int4((int32_t)v, part[v], target[v], vw ? vw[v] : 1);
@@ -1418,6 +1431,9 @@ inline unsigned grid_for(int64_t work, int block, int64_t cap) {
 }
 
 
+// unit net weights, k <= 64: a group of lanes per vertex instead of one lane
+inline bool cand_groups(const Ctx &c) { return c.p_low >= (int64_t)c.lane_degree * c.n_low; }
+
 template <int G, bool UNIT>
 hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const uint8_t *lock_bytes, int32_t tau_q,
                        const LoopCtl *lc) {
@@ -1431,21 +1447,23 @@ hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const 
   int tok = prof_begin(c, kProfCandidates, lc, want);
   // unit net weights, k <= 64: bit-sliced counts, one lane per vertex while the vertices are light
   // (mean degree below lane_degree), eight otherwise
-  if (UNIT && c.k <= 64 && c.p_low < (int64_t)c.lane_degree * c.n_low) {
+  if (UNIT && c.k <= 64 && !cand_groups(c)) {
     hipLaunchKernelGGL(k_candidates_bits<1>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 255) / 256)),
                        dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.st, lc, union_of(c), c.cand_xcd);
+                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
   } else if (UNIT && c.k <= 64) {
-    // the groups OR their bits into cleared words (a fill kernel: no memset node in a captured graph)
-    const int64_t words = ((int64_t)c.n + 255) / 256 * 8;
-    hipError_t fe = launch_fill_u32(c, c.inm, words, 0u, lc, want);
-    if (fe != hipSuccess) return fe;
+    // the groups OR their bits into cleared words: in the loop the selection leaves every word it
+    // walks at zero (launch_clear_candidate_bits before the first iteration)
+    if (!lc) {
+      const hipError_t fe = launch_clear_candidate_bits(c);
+      if (fe != hipSuccess) return fe;
+    }
     hipLaunchKernelGGL(k_candidates_bits<8>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 31) / 32)),
                        dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.st, lc, union_of(c), c.cand_xcd);
+                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
   } else
     hipLaunchKernelGGL((k_candidates<G, UNIT>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
-                       c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.st, lc,
+                       c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc,
                        union_of(c));
   prof_end(c, tok, lc, want, 18.0 * c.n_low, per_inc);  // plus per_inc per scanned incidence (device count)
   if (c.nhubs > 0) {
@@ -1472,11 +1490,9 @@ constexpr int kApplyGrid = 2048;
 
 }  // namespace
 
-// One launch clears the per-iteration counters (instead of a fill per field).
-__global__ void k_reset_counters(DevStatus *st, int32_t what, const LoopCtl *lc, int32_t want, int32_t H) {
-  JET_GATE(lc, want);
-  if ((what & kResetMoves) && H > 1)  // union: per-hypergraph move counts
-    for (int32_t i = threadIdx.x; i < H; i += blockDim.x) st->hmoves[i] = 0;
+// One launch clears the per-iteration counters (instead of a fill per field) of a launch outside the
+// loop.
+__global__ void k_reset_counters(DevStatus *st, int32_t what) {
   if (threadIdx.x != 0) return;
   if (what & kResetCandidates) {
     st->n_cand = 0;
@@ -1492,16 +1508,25 @@ __global__ void k_reset_counters(DevStatus *st, int32_t what, const LoopCtl *lc,
   }
 }
 
-hipError_t launch_reset_counters(Ctx &c, int32_t what, const LoopCtl *lc, int32_t want) {
-  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(256), 0, c.stream, c.st, what, lc, want, c.H);
+hipError_t launch_reset_counters(Ctx &c, int32_t what) {
+  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, c.stream, c.st, what);
   return hipGetLastError();
+}
+
+hipError_t launch_clear_candidate_bits(Ctx &c) {
+  if (!(c.unit_nw && c.k <= 64 && cand_groups(c))) return hipSuccess;  // the kernel writes whole words
+  const int64_t words = ((int64_t)c.n + 255) / 256 * 8;
+  return launch_fill_u32(c, c.inm, words, 0u, nullptr, kPhAny);
 }
 
 hipError_t launch_candidates(Ctx &c, const int32_t *part, int32_t locked_stamp, const uint8_t *lock_bytes,
                              int32_t tau_q, const LoopCtl *lc) {
-  // every counter of the iteration (candidates, afterburner overflow list, move list) starts at 0
-  hipError_t e = launch_reset_counters(c, kResetCandidates | kResetMoves, lc, lc ? (int32_t)kPhJet : (int32_t)kPhAny);
-  if (e != hipSuccess) return e;
+  // every counter of the iteration (candidates, afterburner overflow list, move list) starts at 0: in
+  // the loop the control kernel that enters the phase clears them
+  if (!lc) {
+    const hipError_t e = launch_reset_counters(c, kResetCandidates | kResetMoves);
+    if (e != hipSuccess) return e;
+  }
   return c.unit_nw ? cand_dispatch<true>(c, part, locked_stamp, lock_bytes, tau_q, lc)
                    : cand_dispatch<false>(c, part, locked_stamp, lock_bytes, tau_q, lc);
 }
@@ -1606,9 +1631,8 @@ hipError_t launch_select_moves(Ctx &c, const int32_t *part, int32_t stamp, const
   return hipGetLastError();
 }
 
+// only in the loop: the control kernel that enters the rollback cleared the move counters
 hipError_t launch_diff_moves(Ctx &c, const int32_t *part, const int32_t *target, const LoopCtl *lc) {
-  hipError_t e = launch_reset_counters(c, kResetMoves, lc, lc ? (int32_t)kPhRoll : (int32_t)kPhAny);
-  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_diff_moves, dim3(grid_for(c.n, kSelBlock * kCompactPer, c.grid_cap)), dim3(kSelBlock), 0, c.stream,
                      part, target, c.vw,
                      c.n, c.moves, c.mvto, c.voff, c.st, c.bigmv, lc, union_of(c));

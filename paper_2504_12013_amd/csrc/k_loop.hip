@@ -1,14 +1,19 @@
 // The Jet loop of Algorithm 1 kept on the device.  The decisions of the loop (rebalance or not,
 // strict improvement of the key (overload, metric), snapshot, iteration limit, fixed point, end of a
-// temperature round and rollback to its best partition) are taken by small control kernels on a
-// loop record (LoopCtl); every kernel of the iteration returns at once unless the record is in the
-// phase it belongs to.  One iteration's launches -- the Jet phase, rb_slots rebalancing rounds, the
-// end of the iteration and the rollback -- form a "tick"; the host captures a tick in a HIP graph
-// once per context and replays it several times between two looks at the record.  Ticks after the
-// loop finished do nothing.  The sequence of states is exactly that of the host loop it replaces
-// (one Jet phase, then rebalancing rounds while a block is overloaded, a round moved something
-// and the cap allows, then the key), so results and per-iteration records do not depend on how
-// many ticks run between polls.
+// temperature round and rollback to its best partition) are taken by one small control kernel after
+// each phase on a loop record (LoopCtl); every kernel of the iteration returns at once unless the
+// record is in the phase it belongs to.  One iteration's launches -- the Jet phase, rb_slots
+// rebalancing rounds and the rollback, each followed by its control kernel -- form a "tick"; the host
+// captures a tick in a HIP graph once per context and replays it several times between two looks at
+// the record.  Ticks after the loop finished do nothing.  The sequence of states is exactly that of
+// the host loop it replaces (one Jet phase, then rebalancing rounds while a block is overloaded, a
+// round moved something and the cap allows, then the key), so results and per-iteration records do
+// not depend on how many ticks run between polls.
+//
+// The control kernel that leaves a phase also enters the next one (iteration stamp, counters, the
+// round's needs and list regions), and the next Jet phase's candidate pass, which reads every
+// vertex's block anyway, takes the snapshot of an improving iteration.  A launch costs 2 to 5 us here
+// even when its gate is closed, so a rebalancing round of 2,000 vertices went from 15 launches to 9.
 #include <algorithm>
 
 #include "dev_util.h"
@@ -18,111 +23,272 @@ namespace jet {
 
 namespace {
 
-// Per-hypergraph views of the status block: one hypergraph (H == 1) keeps its metric in st->km1
-// plus spread slots and its move count in st->n_moves; a union keeps them per hypergraph.
-struct HgStatus {
-  DevStatus *st;
-  int32_t H, k;
+// ------------------------------------------------------------------ the loop's decisions
 
-  __device__ int64_t overload(int32_t hg, int64_t lmax) const {
-    int64_t worst = 0;
-    const int64_t *bw = st->bw + (int64_t)hg * k;
-    for (int b = 0; b < k; ++b) worst = max(worst, bw[b] - lmax);
-    return worst;
-  }
-  // the metric after folding the changes accumulated since the last fold
-  __device__ int64_t fold(LoopCtl &r, int32_t hg) const {
-    if (H == 1) {
-      int64_t s = st->km1;
-      for (int i = 0; i < kKm1Slots; ++i) {
-        s += st->km1_slot[i];
-        st->km1_slot[i] = 0;
-      }
-      st->km1 = s;
-      r.km1 = s;
-    } else {
-      r.km1 += st->hkm1[hg];
-      st->hkm1[hg] = 0;
-    }
-    return r.km1;
-  }
-  __device__ int32_t moves(int32_t hg) const { return H == 1 ? st->n_moves : st->hmoves[hg]; }
-  __device__ int32_t cand() const { return H == 1 ? st->n_cand : 0; }
-};
+// Start of a Jet phase: a new iteration stamp, so the vertices moved by the previous iteration's
+// Jet phase (stamped stamp - 1) are the locked ones.
+__device__ __forceinline__ void begin_jet(LoopCtl &r) {
+  r.stamp += 1;
+  r.lock_was_any = r.lock_any;
+  set_phase(r, kPhJet);
+}
 
-constexpr int kCtlThreads = 256;
+// Completes the record the host wrote (parameters, limits, stamp) from the state build_state left
+// (metric, block weights): the first round's key and the first phase.
+__device__ __forceinline__ void first_phase(LoopCtl &r, int64_t ovl, int64_t km1) {
+  r.km1 = km1;
+  r.km1_in = km1;
+  r.best_ovl = ovl;
+  r.best_km1 = km1;
+  r.improved = 1;  // the start is the first round's best: the first candidate pass takes the snapshot
+  if (r.rb_only) set_phase(r, (ovl > 0 && r.max_rb > 0) ? kPhRb : kPhDone);  // jet_rebalance
+  else begin_jet(r);
+}
 
-// Union: the lists of hypergraphs per phase (and of those whose iteration improved), with the
-// prefix sums of their tiles and chunks, in hypergraph order (one workgroup, block scans).
-__device__ __forceinline__ void build_lists(const LoopCtl *lcs, int32_t H, ActList *act, const int32_t *ht0,
-                                            const int32_t *hch0) {
-  __shared__ int32_t sm[kCtlThreads / kWave + 1];
-  __shared__ int32_t cn[kActLists], ct[kActLists], cc[kActLists];
-  const int tid = threadIdx.x;
-  if (tid < kActLists) cn[tid] = ct[tid] = cc[tid] = 0;
-  __syncthreads();
-  for (int32_t base = 0; base < H; base += kCtlThreads) {  // block-uniform trip count
-    const int32_t hg = base + tid;
-    const bool valid = hg < H;
-    int32_t ph = kPhDone, imp = 0, tcnt = 0, ccnt = 0;
-    if (valid) {
-      ph = lcs[hg].phase;
-      imp = lcs[hg].improved;
-      tcnt = ht0[hg + 1] - ht0[hg];
-      ccnt = hch0[hg + 1] - hch0[hg];
-    }
-    for (int L = 0; L < kActLists; ++L) {
-      const bool in = valid && (L == kActImproved ? imp != 0 : ph == (L == kActJet ? kPhJet : L == kActRb ? kPhRb : kPhRoll));
-      int32_t tn, tt, tc;
-      const int32_t rn = block_excl_scan<kCtlThreads>(in ? 1 : 0, sm, &tn);
-      const int32_t rt = block_excl_scan<kCtlThreads>(in ? tcnt : 0, sm, &tt);
-      const int32_t rc = block_excl_scan<kCtlThreads>(in ? ccnt : 0, sm, &tc);
-      if (in) {
-        act[L].hg[cn[L] + rn] = hg;
-        act[L].tpref[cn[L] + rn] = ct[L] + rt;
-        act[L].cpref[cn[L] + rn] = cc[L] + rc;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        cn[L] += tn;
-        ct[L] += tt;
-        cc[L] += tc;
-      }
-      __syncthreads();
-    }
+// End of an iteration: the key (overload, metric) against the round's best (strict, lexicographic),
+// the iteration record, the limit of non-improving iterations, the round's cap and the fixed point.
+__device__ __forceinline__ void end_iteration(LoopCtl &r, int64_t ovl, jet_trace *trace) {
+  const int64_t km1 = r.km1;
+  r.it += 1;
+  r.round += 1;
+  if (ovl < r.best_ovl || (ovl == r.best_ovl && km1 < r.best_km1)) {
+    r.best_ovl = ovl;
+    r.best_km1 = km1;
+    r.improved = 1;
+    r.round = 0;
   }
-  if (tid < kActLists) {
-    act[tid].cnt = cn[tid];
-    act[tid].tpref[cn[tid]] = ct[tid];
-    act[tid].cpref[cn[tid]] = cc[tid];
+  r.iterations += 1;
+  r.rebalance_rounds += r.rb_rounds;
+  if (trace && r.ntrace < r.trace_cap) {
+    jet_trace t;
+    t.km1 = km1;
+    t.overload = ovl;
+    t.n_cand = r.n_cand;
+    t.n_moved = r.n_moved;
+    t.rb_rounds = r.rb_rounds;
+    t.rb_moved = r.rb_moved;
+    trace[r.ntrace] = t;
+  }
+  r.ntrace += 1;
+  // nothing moved, nothing rebalanced and nothing was locked: the next iteration would repeat it
+  const bool fixed = r.n_moved == 0 && r.rb_moved == 0 && r.lock_was_any == 0;
+  if (r.round >= r.limit || r.it >= r.max_iters || fixed) set_phase(r, kPhRoll);
+  else begin_jet(r);
+}
+
+// After the Jet phase's moves are applied: its counts, the locks it leaves, and whether a
+// rebalancing round follows (Algorithm 1: rebalance while a block is overloaded).  The candidate
+// pass has taken the previous improvement's snapshot.
+__device__ __forceinline__ void after_jet(LoopCtl &r, int64_t ovl, int64_t km1, int32_t moved, int32_t cand,
+                                          jet_trace *trace) {
+  r.km1 = km1;
+  r.improved = 0;
+  r.n_cand = cand;
+  r.n_moved = moved;
+  r.lock_any = moved > 0 ? 1 : 0;
+  r.moves_executed += moved;
+  r.rb_rounds = 0;
+  r.rb_moved = 0;
+  if (ovl > 0 && r.max_rb > 0) set_phase(r, kPhRb);
+  else end_iteration(r, ovl, trace);
+}
+
+// After a rebalancing round's moves are applied: another round while a block is still overloaded,
+// the round moved a vertex and the cap allows (Section 4.3).
+__device__ __forceinline__ void after_rb(LoopCtl &r, int64_t ovl, int64_t km1, int32_t moved, jet_trace *trace) {
+  r.km1 = km1;
+  r.rb_rounds += 1;
+  r.rb_moved += moved;
+  if (ovl != 0 && r.rb_rounds < r.max_rb && moved != 0) return;
+  if (r.rb_only) {
+    r.rebalance_rounds += r.rb_rounds;
+    set_phase(r, kPhDone);
+  } else {
+    end_iteration(r, ovl, trace);
   }
 }
 
-// Runs f(record, hg) for every hypergraph (one workgroup striding over them), then sets the gate
-// record's phase mask and snapshot flag from all records (a union's gate is a record of its own)
-// and rebuilds the union's lists.
-template <typename F>
-__device__ __forceinline__ void for_each_hg(LoopCtl *lcs, int32_t H, LoopCtl *gate, Union u, F f) {
-  __shared__ int32_t smask, simp;
-  if (threadIdx.x == 0) {
-    smask = 0;
-    simp = 0;
+// After the rollback's moves are applied: the next temperature round starts from the round's
+// best partition with no locks, or the loop is done.
+__device__ __forceinline__ void after_roll(LoopCtl &r, int64_t ovl, int64_t km1) {
+  r.km1 = km1;
+  r.tau_r += 1;
+  if (r.tau_r >= r.num_tau) {
+    set_phase(r, kPhDone);
+    return;
+  }
+  r.tau_q = r.tau_qs[r.tau_r];
+  r.stamp += 2;  // the round's first iteration sees no lock
+  r.round = 0;
+  r.it = 0;
+  r.lock_any = 0;
+  r.best_ovl = ovl;
+  r.best_km1 = km1;
+  begin_jet(r);
+}
+
+// want: the phase just executed, kPhAny at the start of a call
+__device__ __forceinline__ void advance(LoopCtl &r, int32_t want, int64_t ovl, int64_t km1, int32_t moved,
+                                        int32_t cand, jet_trace *trace) {
+  if (want == kPhJet) after_jet(r, ovl, km1, moved, cand, trace);
+  else if (want == kPhRb) after_rb(r, ovl, km1, moved, trace);
+  else if (want == kPhRoll) after_roll(r, ovl, km1);
+  else first_phase(r, ovl, km1);
+}
+
+// ------------------------------------------------------------------ control kernels
+
+// The counters of a phase start at zero.
+__device__ __forceinline__ void clear_counters(DevStatus *st) {
+  st->n_cand = 0;
+  st->n_moves = 0;
+  st->n_ovf = 0;
+  st->n_bigmv = 0;
+  st->inc_low = 0;
+  st->inc_hub = 0;
+  st->ab_inc = 0;
+  st->mv_inc = 0;
+  st->rb_inc = 0;
+  st->rb_elig = 0;
+  st->rb_ent = 0;
+  st->rb_nlist = 0;
+  st->rb_nhub = 0;
+}
+
+// One hypergraph: one thread per block.  Record, block weights and metric slots are loaded at
+// once and the decision runs on the copy in LDS: a single thread walking them in global memory took
+// 7 us at k = 64 and 12 us at k = 128, this takes 3 us.  When a rebalancing round follows, its needs
+// (bw - Lmax) and list regions are set here.
+constexpr int kCtlOne = 128;
+static_assert(kCtlOne >= kMaxK && kCtlOne >= kKm1Slots && kKm1Slots == kWave, "one thread per block and slot");
+__global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st, int32_t k, int64_t lmax,
+                                                     int32_t want, jet_trace *trace) {
+  __shared__ LoopCtl r;
+  __shared__ int64_t s_ovl[kCtlOne / kWave], s_cnt[kCtlOne / kWave], s_km1;
+  const int b = threadIdx.x, w = b / kWave;
+  for (int i = b; i < (int)(sizeof(LoopCtl) / 4); i += kCtlOne)
+    reinterpret_cast<int32_t *>(&r)[i] = reinterpret_cast<const int32_t *>(lc)[i];
+  const int64_t bw = b < k ? st->bw[b] : 0;
+  const int32_t bc = b < k ? st->bcnt[b] : 0;
+  int64_t slot = b < kKm1Slots ? st->km1_slot[b] : 0;
+  const int64_t km1_base = st->km1;
+  const int32_t moved = st->n_moves, cand = st->n_cand;
+  const int64_t over = b < k ? max(bw - lmax, (int64_t)0) : 0;
+  int64_t mx = over;
+#pragma unroll
+  for (int o = kWave / 2; o >= 1; o >>= 1) mx = max(mx, (int64_t)__shfl_xor(mx, o, kWave));
+  slot = wave_sum(slot);
+  const int64_t cnt = over > 0 ? bc : 0, incl = wave_incl_scan(cnt);
+  if (lane_id() == kWave - 1) {
+    s_ovl[w] = mx;
+    s_cnt[w] = incl;
+    if (w == 0) s_km1 = km1_base + slot;
   }
   __syncthreads();
-  int32_t m = 0, imp = 0;
-  for (int32_t hg = threadIdx.x; hg < H; hg += blockDim.x) {
-    f(lcs[hg], hg);
-    m |= lcs[hg].phase_mask;
-    imp |= lcs[hg].improved;
+  if (want != kPhAny && r.phase != want) return;  // block-uniform
+  __syncthreads();  // every thread has read the phase
+  if (b == 0) {
+    advance(r, want, max(s_ovl[0], s_ovl[1]), s_km1, moved, cand, trace);
+    st->km1 = s_km1;
+    clear_counters(st);
+  }
+  if (b < kKm1Slots) st->km1_slot[b] = 0;
+  __syncthreads();
+  if (r.phase == kPhRb && b < k) {
+    st->rb_need[b] = over;
+    st->rb_count[b] = 0;
+    st->rb_kept[b] = 0;
+    st->rb_off[b] = incl - cnt + (w ? s_cnt[0] : 0);
+    if (b == 0) st->rb_off[k] = s_cnt[0] + s_cnt[1];
+  }
+  for (int i = b; i < (int)(sizeof(LoopCtl) / 4); i += kCtlOne)
+    reinterpret_cast<int32_t *>(lc)[i] = reinterpret_cast<const int32_t *>(&r)[i];
+}
+
+constexpr int kCtlThreads = 256;
+
+// Union: the lists of hypergraphs per phase, with the prefix sums of their tiles and chunks, in
+// hypergraph order (one workgroup; hypergraphs, tiles and chunks packed into one block scan: at most
+// 4,096 hypergraphs, 2^23 tiles of 256 vertices and 2^27 chunks).
+__device__ __forceinline__ void build_lists(const LoopCtl *lcs, int32_t H, ActList *act, const int32_t *ht0,
+                                            const int32_t *hch0) {
+  __shared__ unsigned long long sm[kCtlThreads / kWave + 1];
+  const int tid = threadIdx.x;
+  unsigned long long run[kActLists] = {};
+  constexpr int kTileSh = 13, kChunkSh = 37;
+  constexpr unsigned long long kTileMask = (1ull << (kChunkSh - kTileSh)) - 1ull;
+  for (int32_t base = 0; base < H; base += kCtlThreads) {  // block-uniform trip count
+    const int32_t hg = base + tid;
+    int32_t ph = kPhDone;
+    unsigned long long one = 0ull;
+    if (hg < H) {
+      ph = lcs[hg].phase;
+      one = 1ull | ((unsigned long long)(uint32_t)(ht0[hg + 1] - ht0[hg]) << kTileSh) |
+            ((unsigned long long)(uint32_t)(hch0[hg + 1] - hch0[hg]) << kChunkSh);
+    }
+#pragma unroll
+    for (int L = 0; L < kActLists; ++L) {
+      const bool in = hg < H && ph == (L == kActJet ? kPhJet : L == kActRb ? kPhRb : kPhRoll);
+      unsigned long long tot;
+      const unsigned long long at = run[L] + block_excl_scan<kCtlThreads>(in ? one : 0ull, sm, &tot);
+      if (in) {
+        const int32_t i = (int32_t)(at & ((1ull << kTileSh) - 1ull));
+        act[L].hg[i] = hg;
+        act[L].tpref[i] = (int32_t)((at >> kTileSh) & kTileMask);
+        act[L].cpref[i] = (int32_t)(at >> kChunkSh);
+      }
+      run[L] += tot;
+    }
+  }
+  if (tid == 0) {
+#pragma unroll
+    for (int L = 0; L < kActLists; ++L) {
+      const int32_t i = (int32_t)(run[L] & ((1ull << kTileSh) - 1ull));
+      act[L].cnt = i;
+      act[L].tpref[i] = (int32_t)((run[L] >> kTileSh) & kTileMask);
+      act[L].cpref[i] = (int32_t)(run[L] >> kChunkSh);
+    }
+  }
+}
+
+// Union: one thread per hypergraph, then the gate record's phase mask from all records (a union's
+// gate is a record of its own) and the lists.  The move counts start at zero for the next phase; the
+// rebalancing needs are set by the round's own preparation (one workgroup over all segments).
+__global__ __launch_bounds__(kCtlThreads) void k_control_union(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
+                                                               int32_t k, int32_t want, Union u) {
+  __shared__ int32_t smask;
+  if (threadIdx.x == 0) smask = 0;
+  __syncthreads();
+  int32_t m = 0;
+  for (int32_t hg = threadIdx.x; hg < H; hg += kCtlThreads) {
+    int32_t pm = lcs[hg].phase_mask;
+    if (want == kPhAny || (pm >> want) & 1) {
+      LoopCtl r = lcs[hg];
+      const int64_t *bw = st->bw + (int64_t)hg * k;
+      int64_t ovl = 0;
+      for (int32_t b0 = 0; b0 < k; b0 += 8) {  // eight loads in flight
+        int64_t x[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) x[j] = b0 + j < k ? bw[b0 + j] : 0;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) ovl = max(ovl, x[j] - r.lmax);
+      }
+      const int64_t km1 = (want == kPhAny ? 0 : r.km1) + st->hkm1[hg];
+      st->hkm1[hg] = 0;
+      advance(r, want, ovl, km1, st->hmoves[hg], 0, nullptr);
+      lcs[hg] = r;
+      pm = r.phase_mask;
+    }
+    st->hmoves[hg] = 0;
+    m |= pm;
   }
   if (m) atomicOr(&smask, m);
-  if (imp) atomicOr(&simp, imp);
   __syncthreads();
-  if (threadIdx.x == 0 && gate != lcs) {
+  if (threadIdx.x == 0) {
     gate->phase_mask = smask;
-    gate->improved = simp;
+    clear_counters(st);
   }
-  if (u.lcs) build_lists(lcs, H, const_cast<ActList *>(u.act), u.ht0, u.hch0);
+  build_lists(lcs, H, const_cast<ActList *>(u.act), u.ht0, u.hch0);
 }
 
 __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t count, uint32_t value, const LoopCtl *lc,
@@ -130,159 +296,6 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t count, uint32_t val
   JET_GATE(lc, want);
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < count; i += (int64_t)gridDim.x * blockDim.x)
     p[i] = value;
-}
-
-// Completes the records the host wrote (parameters, limits, stamp) from the state build_state left
-// (metric, block weights): the first round's key and the first phase.
-__global__ __launch_bounds__(kCtlThreads) void k_loop_init(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
-                                                           int32_t k, Union u) {
-  const HgStatus hs{st, H, k};
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t hg) {
-    if (H > 1) r.km1 = 0;
-    const int64_t km1 = hs.fold(r, hg);
-    const int64_t ovl = hs.overload(hg, r.lmax);
-    r.km1_in = km1;
-    r.best_ovl = ovl;
-    r.best_km1 = km1;
-    if (r.rb_only) set_phase(r, (ovl > 0 && r.max_rb > 0) ? kPhRb : kPhDone);  // jet_rebalance
-    else set_phase(r, kPhJet);
-  });
-}
-
-// Start of a piece: the snapshot flags of the previous piece are cleared.
-__global__ __launch_bounds__(kCtlThreads) void k_tick_begin(LoopCtl *lcs, int32_t H, LoopCtl *gate, Union u) {
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t) {
-    r.improved = 0;
-    if (r.phase != kPhDone) r.ticks += 1;
-  });
-}
-
-// Start of a Jet phase (launched only where the phase follows): a new iteration stamp, so the
-// vertices moved by the previous iteration's Jet phase (stamped stamp - 1) are the locked ones.
-__global__ __launch_bounds__(kCtlThreads) void k_jet_begin(LoopCtl *lcs, int32_t H, LoopCtl *gate, Union u) {
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t) {
-    if (r.phase != kPhJet) return;
-    r.stamp += 1;
-    r.lock_was_any = r.lock_any;
-  });
-}
-
-// After the Jet phase's moves are applied: its counts, the locks it leaves, and whether a
-// rebalancing round follows (Algorithm 1: rebalance while a block is overloaded).
-__global__ __launch_bounds__(kCtlThreads) void k_jet_post(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
-                                                          int32_t k, Union u) {
-  const HgStatus hs{st, H, k};
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t hg) {
-    if (r.phase != kPhJet) return;
-    hs.fold(r, hg);
-    const int32_t moved = hs.moves(hg);
-    r.n_cand = hs.cand();
-    r.n_moved = moved;
-    r.lock_any = moved > 0 ? 1 : 0;
-    r.moves_executed += moved;
-    r.rb_rounds = 0;
-    r.rb_moved = 0;
-    set_phase(r, (hs.overload(hg, r.lmax) > 0 && r.max_rb > 0) ? kPhRb : kPhEnd);
-  });
-}
-
-// After a rebalancing round's moves are applied: another round while a block is still overloaded,
-// the round moved a vertex and the cap allows (Section 4.3).
-__global__ __launch_bounds__(kCtlThreads) void k_rb_post(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
-                                                         int32_t k, Union u) {
-  const HgStatus hs{st, H, k};
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t hg) {
-    if (r.phase != kPhRb) return;
-    hs.fold(r, hg);
-    const int32_t moved = hs.moves(hg);
-    r.rb_rounds += 1;
-    r.rb_moved += moved;
-    if (hs.overload(hg, r.lmax) == 0 || r.rb_rounds >= r.max_rb || moved == 0) {
-      if (r.rb_only) {
-        r.rebalance_rounds += r.rb_rounds;
-        set_phase(r, kPhDone);
-      } else {
-        set_phase(r, kPhEnd);
-      }
-    }
-  });
-}
-
-// End of an iteration: the key (overload, metric) against the round's best (strict, lexicographic),
-// the iteration record, the limit of non-improving iterations, the round's cap and the fixed point.
-__global__ __launch_bounds__(kCtlThreads) void k_iter_end(LoopCtl *lcs, int32_t H, LoopCtl *gate,
-                                                          const DevStatus *st, int32_t k, jet_trace *trace, Union u) {
-  const HgStatus hs{const_cast<DevStatus *>(st), H, k};
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t hg) {
-    if (r.phase != kPhEnd) return;
-    const int64_t ovl = hs.overload(hg, r.lmax), km1 = r.km1;
-    r.it += 1;
-    r.round += 1;
-    if (ovl < r.best_ovl || (ovl == r.best_ovl && km1 < r.best_km1)) {
-      r.best_ovl = ovl;
-      r.best_km1 = km1;
-      r.improved = 1;
-      r.round = 0;
-    }
-    r.iterations += 1;
-    r.rebalance_rounds += r.rb_rounds;
-    if (trace && H == 1 && r.ntrace < r.trace_cap) {
-      jet_trace t;
-      t.km1 = km1;
-      t.overload = ovl;
-      t.n_cand = r.n_cand;
-      t.n_moved = r.n_moved;
-      t.rb_rounds = r.rb_rounds;
-      t.rb_moved = r.rb_moved;
-      trace[r.ntrace] = t;
-    }
-    r.ntrace += 1;
-    // nothing moved, nothing rebalanced and nothing was locked: the next iteration would repeat it
-    const bool fixed = r.n_moved == 0 && r.rb_moved == 0 && r.lock_was_any == 0;
-    set_phase(r, (r.round >= r.limit || r.it >= r.max_iters || fixed) ? kPhRoll : kPhJet);
-  });
-}
-
-// The snapshot of an improving iteration (Algorithm 1's rollback point), per vertex of the
-// hypergraphs whose iteration improved.
-__global__ void k_snapshot(const int32_t *__restrict__ part, int32_t *__restrict__ best, int32_t n, const LoopCtl *lc,
-                           Union u) {
-  if (lc->improved == 0) return;
-  if (u.lcs) {  // union: the tiles of the hypergraphs whose iteration improved
-    const ActList &L = u.act[kActImproved];
-    const int32_t nt = L.tpref[L.cnt];
-    for (int32_t t = blockIdx.x; t < nt; t += gridDim.x) {
-      const int64_t v = act_tile_base(L, u.ht0, t) + threadIdx.x;
-      if (v < n) best[v] = part[v];
-    }
-    return;
-  }
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
-    best[v] = part[v];
-}
-
-// After the rollback's moves are applied: the next temperature round starts from the round's
-// best partition with no locks, or the loop is done.
-__global__ __launch_bounds__(kCtlThreads) void k_roll_post(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
-                                                           int32_t k, Union u) {
-  const HgStatus hs{st, H, k};
-  for_each_hg(lcs, H, gate, u, [&](LoopCtl &r, int32_t hg) {
-    if (r.phase != kPhRoll) return;
-    const int64_t km1 = hs.fold(r, hg);
-    r.tau_r += 1;
-    if (r.tau_r >= r.num_tau) {
-      set_phase(r, kPhDone);
-      return;
-    }
-    r.tau_q = r.tau_qs[r.tau_r];
-    r.stamp += 2;  // the round's first iteration sees no lock
-    r.round = 0;
-    r.it = 0;
-    r.lock_any = 0;
-    r.best_ovl = hs.overload(hg, r.lmax);
-    r.best_km1 = km1;
-    set_phase(r, kPhJet);
-  });
 }
 
 // Device timing marks of a kernel family: `end` == 0 stores the wall clock, `end` == 1 adds the
@@ -341,9 +354,19 @@ hipError_t launch_fill_u32(Ctx &c, uint32_t *p, int64_t count, uint32_t value, c
   return hipGetLastError();
 }
 
-hipError_t launch_loop_init(Ctx &c) {
-  hipLaunchKernelGGL(k_loop_init, dim3(1), dim3(kCtlThreads), 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, union_of(c));
+// The loop's decision after phase `want` (kPhAny: at the start of a call).
+static hipError_t launch_control(Ctx &c, int32_t want) {
+  if (c.H > 1)
+    hipLaunchKernelGGL(k_control_union, dim3(1), dim3(kCtlThreads), 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, want,
+                       union_of(c));
+  else
+    hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlOne), 0, c.stream, c.lc, c.st, c.k, c.lmax, want, c.dtrace);
   return hipGetLastError();
+}
+
+hipError_t launch_loop_init(Ctx &c) {
+  hipError_t e = launch_clear_candidate_bits(c);
+  return e == hipSuccess ? launch_control(c, kPhAny) : e;
 }
 
 hipError_t launch_tick(Ctx &c, int kind) {
@@ -351,42 +374,31 @@ hipError_t launch_tick(Ctx &c, int kind) {
   const bool jet = kind == kTickJet || kind == kTickJetRb || kind == kTickAll;
   const bool rb = kind == kTickJetRb || kind == kTickRb || kind == kTickAll;
   const bool roll = kind == kTickRoll || kind == kTickAll;
-  const dim3 one(1), ctl(kCtlThreads);
   hipError_t e = hipSuccess;
-  const Union u = union_of(c);
-  hipLaunchKernelGGL(k_tick_begin, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, u);
   if (jet) {
     // Jet phase: candidates, afterburner, kept moves (locks), their application
-    hipLaunchKernelGGL(k_jet_begin, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, u);
     e = launch_candidates(c, c.cpart, 0, nullptr, 0, lc);
     if (e == hipSuccess) e = launch_afterburner(c, c.cpart, lc);
     if (e == hipSuccess) e = launch_select_moves(c, c.cpart, 0, lc);
     if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhJet);
+    if (e == hipSuccess) e = launch_control(c, kPhJet);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_jet_post, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, u);
   }
   if (rb) {
     for (int r = 0; r < c.rb_slots; ++r) {
       e = launch_rebalance_round(c, c.cpart, 0, nullptr, lc);
       if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhRb);
+      if (e == hipSuccess) e = launch_control(c, kPhRb);
       if (e != hipSuccess) return e;
-      hipLaunchKernelGGL(k_rb_post, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, u);
     }
-  }
-  if (jet || rb) {
-    // end of the iteration, snapshot
-    hipLaunchKernelGGL(k_iter_end, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, c.dtrace, u);
-    hipLaunchKernelGGL(k_snapshot, dim3(grid_for(c.n, 256, 2048)), dim3(kUnionTile), 0, c.stream, c.cpart, c.best, c.n,
-                       lc, u);
   }
   if (roll) {
     // end of a temperature round: back to its best partition
     e = launch_diff_moves(c, c.cpart, c.best, lc);
     if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhRoll);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_roll_post, one, ctl, 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, u);
+    if (e == hipSuccess) e = launch_control(c, kPhRoll);
   }
-  return hipGetLastError();
+  return e;
 }
 
 }  // namespace jet

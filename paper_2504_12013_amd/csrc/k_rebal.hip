@@ -1,6 +1,7 @@
 // Deterministic rebalancing round (Section 4.3) on the device.
 //
-//  prepare : per overloaded block the weight that must leave (bw - Lmax) and its list region
+//  prepare : per overloaded block the weight that must leave (bw - Lmax) and its list region (in the
+//            loop the control kernel that enters the round does this)
 //  gain    : per vertex of an overloaded block that passes the heavy-vertex rule, the best valid
 //            target (balanced after adding v, not in the deadzone; adjacency not required; lowest
 //            block on ties) and an exact 160-bit order key
@@ -80,8 +81,8 @@ __device__ __forceinline__ void entry_key(int32_t g, int32_t c, int32_t v, int32
 // entry layout: 8 words = key[0..4], v, target, weight
 constexpr int kEntryWords = 8;
 
-__global__ void k_rb_prepare(int32_t k, int64_t lmax, DevStatus *st, const LoopCtl *lc) {
-  JET_GATE(lc, kPhRb);
+// Needs and list regions of one round outside the loop (inside it the control kernel sets them).
+__global__ void k_rb_prepare(int32_t k, int64_t lmax, DevStatus *st) {
   __shared__ int64_t cnts[kMaxK];
   const int b = threadIdx.x;
   if (b < k) {
@@ -1196,10 +1197,10 @@ hipError_t launch_rebalance_round(Ctx &c, const int32_t *part, int64_t dz, int32
   if (c.H > 1)
     hipLaunchKernelGGL(k_rb_prepare_union, dim3(1), dim3(kPrepThreads), 0, c.stream, c.k, c.H, c.st, lc,
                        union_of(c));
-  else
-    hipLaunchKernelGGL(k_rb_prepare, dim3(1), dim3(kMaxK), 0, c.stream, c.k, c.lmax, c.st, lc);
+  else if (!lc)
+    hipLaunchKernelGGL(k_rb_prepare, dim3(1), dim3(kMaxK), 0, c.stream, c.k, c.lmax, c.st);
   hipError_t e = hipGetLastError();
-  // k_rb_prepare cleared the move list and the gain-pass counters
+  // the preparation (in the loop: the control kernel) cleared the move list and the counters
   if (e != hipSuccess) return e;
   int tok = prof_begin(c, kProfRbGain, lc, want);
   e = c.unit_nw ? gain_dispatch<true>(c, part, dz, lc) : gain_dispatch<false>(c, part, dz, lc);

@@ -45,3 +45,24 @@ def test_batch_with_lone_hypergraphs(ks):
         assert np.array_equal(parts[i].cpu().numpy(), out), i
         for key in ("km1_in", "km1_out", "iterations", "rebalance_rounds", "moves_executed", "balanced"):
             assert stats[i][key] == ost[key], (i, key)
+
+
+@pytest.mark.parametrize("k", [2, 63, 64, 65, 128])
+@pytest.mark.parametrize("max_iters", [1, 1000])
+def test_loop_trace_at_block_counts(k, max_iters):
+    """Whole refinements and their iteration records where the control kernel's waves fill up, also
+    with rounds that end on their best partition (nothing to roll back) after one iteration."""
+    hg = W.random_hypergraph(1500, 2600, k, 90 + k, smin=2, smax=9, vw_max=3, eps=0.1)
+    part = W.part_roundrobin(hg.n, k, 3)
+    say(f"k = {k}, max_iters = {max_iters}")
+    kw = dict(tau=(0.75, 0.375, 0.0), limit=4, max_iters=max_iters)
+    ref, orc, ost, otr = O.refine(hg, part, **kw)
+    ctx = J().JetContext(hg)
+    d = torch.from_numpy(part).to("cuda")
+    rc, st, tr = ctx.refine(d, trace_cap=4096, **kw)
+    ctx.close()
+    assert rc == orc
+    assert np.array_equal(d.cpu().numpy(), ref)
+    for key in ("km1_in", "km1_out", "iterations", "rebalance_rounds", "moves_executed", "balanced"):
+        assert st[key] == ost[key], key
+    assert len(tr) == ost["iterations"]
