@@ -66,3 +66,22 @@ def test_loop_trace_at_block_counts(k, max_iters):
     for key in ("km1_in", "km1_out", "iterations", "rebalance_rounds", "moves_executed", "balanced"):
         assert st[key] == ost[key], key
     assert len(tr) == ost["iterations"]
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+@pytest.mark.parametrize("n,k", [(40, 2), (1030, 2), (4097, 2), (9000, 2), (13000, 3)])
+def test_rebalance_selection_list_lengths(n, k, order):
+    """Rebalancing with most vertices in one block: selections from lists of a few entries up to
+    past the 4,096 a workgroup keeps in registers, in all three orders, weighted vertices."""
+    rng = np.random.default_rng(n + k)
+    hg = W.random_hypergraph(n, 2 * n, k, 11 + n, smin=2, smax=5, vw_max=7, nw_max=2)
+    part = np.where(rng.random(n) < 0.93, 0, rng.integers(0, k, n)).astype(np.int32)
+    say(f"n = {n}, k = {k}, order {order}")
+    ref, orc, ost = O.rebalance(hg, part, rb_unweighted=order)[:3]
+    ctx = J().JetContext(hg)
+    d = torch.from_numpy(part).to("cuda")
+    rc, st = ctx.rebalance(d, rb_unweighted=order)
+    ctx.close()
+    assert rc == orc
+    assert np.array_equal(d.cpu().numpy(), ref)
+    assert st["rebalance_rounds"] == ost["rebalance_rounds"]
