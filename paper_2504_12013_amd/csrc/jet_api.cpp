@@ -180,7 +180,7 @@ void free_ctx(Ctx &c) {
   void *ptrs[] = {c.off,  c.pins, c.nw,   c.vw,        c.voff, c.inc,   c.sumw, c.adj,    c.chunks,    c.pnet, c.mid_nets,
                   c.big_nets, c.phi, c.phi16, c.ns, c.rec, c.inm, c.rg, c.lockstamp, c.best, c.moves, c.rb_keys,
                   c.rb_target, c.st, c.scan_tmp, c.ovf_list, c.ovf_off, c.ovf_ka, c.ovf_kb, c.ovf_ma,
-                  c.ovf_mb, c.hubs, c.mvto, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.rb_hacc,
+                  c.ovf_mb, c.hubs, c.mvfrom, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.rb_hacc,
                   c.rb_keys2, c.rb_gw, c.rb_gc};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -325,7 +325,7 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
       (sz > jet::kMediumNet ? big : mid).push_back({sz, e});
       continue;
     }
-    if (cur_cnt > 0 && cur_pins + sz > jet::kSmallNet) close();
+    if (cur_cnt > 0 && (cur_pins + sz > jet::kSmallNet || cur_cnt == jet::kChunkNets)) close();
     if (cur_cnt == 0) cur_first = e;
     cur_cnt += 1;
     cur_pins += sz;
@@ -424,13 +424,13 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
   HIP_OR_FAIL(&c, hipMemsetAsync(c.lockstamp, 0x80, sizeof(int32_t) * (size_t)n, c.stream));  // never moved
   HIP_OR_FAIL(&c, dalloc(&c.best, (size_t)n));
   HIP_OR_FAIL(&c, dalloc(&c.moves, (size_t)n));
-  HIP_OR_FAIL(&c, dalloc(&c.mvto, (size_t)n));
+  HIP_OR_FAIL(&c, dalloc(&c.mvfrom, (size_t)n));
   HIP_OR_FAIL(&c, dalloc(&c.bigmv, (size_t)n));
   HIP_OR_FAIL(&c, dalloc(&c.rb_list, (size_t)n));
   HIP_OR_FAIL(&c, dalloc(&c.rb_slot, (size_t)n));
   HIP_OR_FAIL(&c, dalloc(&c.lstat, 5));
   HIP_OR_FAIL(&c, dalloc(&c.tau_io, 17));
-  HIP_OR_FAIL(&c, hipMemsetAsync(c.mvto, 0xff, (size_t)n, c.stream));
+  HIP_OR_FAIL(&c, hipMemsetAsync(c.mvfrom, 0xff, (size_t)n, c.stream));
   HIP_OR_FAIL(&c, dalloc(&c.rb_keys, (size_t)n * 8));
   HIP_OR_FAIL(&c, dalloc(&c.rb_keys2, (size_t)n * 8));
   HIP_OR_FAIL(&c, dalloc(&c.rb_gw, (size_t)jet::kMaxK * 256));

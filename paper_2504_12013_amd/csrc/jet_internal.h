@@ -13,6 +13,7 @@ namespace jet {
 
 constexpr int kMaxK = 128;
 constexpr int kSmallNet = 64;      // nets up to this size are processed by one wave, several per wave
+constexpr int kChunkNets = 32;     // nets of one chunk at most (64 pins hold more only with single-pin nets)
 constexpr int kMediumNet = 1024;   // nets up to this size: one 64-thread workgroup, candidates in LDS
 constexpr int kMediumSmall = 256;  // medium nets up to this size use a smaller LDS list (more per CU)
 constexpr int kLaneDegree = 32;    // moves with more incident nets are applied by many threads
@@ -358,7 +359,7 @@ struct Ctx {
   int32_t *lockstamp = nullptr;  // [n] stamp of the iteration that last moved v
   int32_t *best = nullptr;    // [n] rollback snapshot
   int4 *moves = nullptr;      // [n] move list (v, from, to, weight)
-  uint8_t *mvto = nullptr;    // [n] target of a listed move, 0xff otherwise (kept 0xff between calls)
+  uint8_t *mvfrom = nullptr;  // [n] block a listed move left, 0xff otherwise (vertices the listing pass walked)
   int32_t *bigmv = nullptr;   // [n] positions in the move list of the moves counted by n_bigmv
   int32_t *rb_list = nullptr; // [n] non-hub vertices that may move in the current rebalancing round
   int32_t *rb_slot = nullptr; // [n] the entry slot of each listed vertex (its block's region)
@@ -475,13 +476,13 @@ hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc = n
 enum : int32_t { kResetCandidates = 1, kResetMoves = 2 };
 hipError_t launch_reset_counters(Ctx &c, int32_t what);
 hipError_t launch_afterburner_overflow(Ctx &c, RgSink sink, const LoopCtl *lc);  // k_ab_large.hip
-hipError_t launch_select_moves(Ctx &c, const int32_t *part, int32_t stamp, const LoopCtl *lc = nullptr);
+hipError_t launch_select_moves(Ctx &c, int32_t *part, int32_t stamp, const LoopCtl *lc = nullptr);
 // wide: size the net-centric grids for that path (a performance hint; the device decides the path)
 hipError_t launch_apply_moves(Ctx &c, int32_t *part, bool wide, const LoopCtl *lc = nullptr, int32_t want = kPhAny);
-hipError_t launch_diff_moves(Ctx &c, const int32_t *part, const int32_t *target, const LoopCtl *lc);
+hipError_t launch_diff_moves(Ctx &c, int32_t *part, const int32_t *target, const LoopCtl *lc);
 
 // rebalancing (k_rebal.hip)
-hipError_t launch_rebalance_round(Ctx &c, const int32_t *part, int64_t dz, int32_t *sel_target,
+hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *sel_target,
                                   const LoopCtl *lc = nullptr);
 
 // the device-resident loop (k_loop.hip)

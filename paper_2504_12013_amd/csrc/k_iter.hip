@@ -510,13 +510,13 @@ __global__ __launch_bounds__(256) void k_ab_chunks(const int32_t *__restrict__ p
   // union: only the chunks of the hypergraphs in their Jet phase
   const ActList *AL = u.lcs ? &u.act[kActJet] : nullptr;
   const int32_t nvc = AL ? AL->cpref[AL->cnt] : nchunks;
-  __shared__ uint32_t cnt[4][64][KW];
-  __shared__ uint32_t ncand[4][64];
+  __shared__ uint32_t cnt[4][kChunkNets][KW];
+  __shared__ uint32_t ncand[4][kChunkNets];
   const int l = lane_id();
   const int w = threadIdx.x / kWave;
   const int32_t wid = blockIdx.x * 4 + w, nwv = gridDim.x * 4;
-  for (int x = 0; x < 64 * KW; x += kWave) (&cnt[w][0][0])[x + l] = 0u;
-  ncand[w][l] = 0u;
+  for (int x = 0; x < kChunkNets * KW; x += kWave) (&cnt[w][0][0])[x + l] = 0u;
+  if (l < kChunkNets) ncand[w][l] = 0u;
   wave_lds_sync();
   auto fetch = [&](int32_t cc, int4 &d, int32_t &p, int32_t &j) {
     d = cc < nvc ? chunks[AL ? act_chunk(*AL, u.hch0, cc) : cc] : make_int4(0, 0, 0, 0);
@@ -885,13 +885,13 @@ __device__ __forceinline__ void block_compact(int64_t n, Pred pred, Emit emit, D
   if (tid == 0 && s_deg) atomicAdd((unsigned long long *)&st->mv_inc, s_deg);
 }
 
-__global__ __launch_bounds__(kSelBlock) void k_select_moves(const int32_t *__restrict__ part,
+__global__ __launch_bounds__(kSelBlock) void k_select_moves(int32_t *__restrict__ part,
                                                             uint32_t *__restrict__ inm,
                                                             const uint64_t *__restrict__ rec,
                                                             int32_t *__restrict__ rg,
                                                             const int32_t *__restrict__ vw, int32_t n, int32_t stamp,
                                                             int32_t *__restrict__ lockstamp,
-                                                            int4 *__restrict__ moves, uint8_t *__restrict__ mvto,
+                                                            int4 *__restrict__ moves, uint8_t *__restrict__ mvfrom,
                                                             const int64_t *__restrict__ voff, DevStatus *st,
                                                             int32_t *__restrict__ bigmv, const LoopCtl *lc,
                                                             Union u) {
@@ -899,15 +899,17 @@ __global__ __launch_bounds__(kSelBlock) void k_select_moves(const int32_t *__res
   if (lc && !u.lcs) stamp = lc->stamp;
   // recomputed gains start from zero in the next iteration: each candidate's entry is cleared here
   auto pred = [&](int64_t v) {
+    mvfrom[v] = 0xff;
     if (!inm_bit(inm, (int32_t)v)) return false;
     const int32_t g = rg[v];
     rg[v] = 0;
     return g > 0;
   };
   auto emit = [&](int64_t v, int32_t pos) -> unsigned long long {
-    const int32_t t = rec_target(rec[v]);
-    moves[pos] = make_int4((int32_t)v, part[v], t, vw ? vw[v] : 1);
-    mvto[v] = (uint8_t)t;
+    const int32_t t = rec_target(rec[v]), from = part[v];
+    moves[pos] = make_int4((int32_t)v, from, t, vw ? vw[v] : 1);
+    mvfrom[v] = (uint8_t)from;
+    part[v] = t;
     if (u.lcs) {  // union: the hypergraph's own stamp (its move count is added per sub-tile)
       lockstamp[v] = u.lcs[u.vhg[v]].stamp;
     } else {
@@ -944,10 +946,10 @@ __global__ __launch_bounds__(kSelBlock) void k_select_moves(const int32_t *__res
   else block_compact(n, pred, emit, st, bigmv, nullptr, nullptr, clear_bits);
 }
 
-__global__ __launch_bounds__(kSelBlock) void k_diff_moves(const int32_t *__restrict__ part,
+__global__ __launch_bounds__(kSelBlock) void k_diff_moves(int32_t *__restrict__ part,
                                                           const int32_t *__restrict__ target,
                                                           const int32_t *__restrict__ vw, int32_t n,
-                                                          int4 *__restrict__ moves, uint8_t *__restrict__ mvto,
+                                                          int4 *__restrict__ moves, uint8_t *__restrict__ mvfrom,
                                                           const int64_t *__restrict__ voff, DevStatus *st,
                                                           int32_t *__restrict__ bigmv, const LoopCtl *lc,
                                                           Union u) {
@@ -956,14 +958,17 @@ __global__ __launch_bounds__(kSelBlock) void k_diff_moves(const int32_t *__restr
   // without a snapshot yet stays (target holds an older one)
   const bool stay = !u.lcs && lc && lc->improved != 0;
   auto pred = [&](int64_t v) {
+    mvfrom[v] = 0xff;
     if (stay || part[v] == target[v]) return false;
     if (!u.lcs) return true;
     const LoopCtl &h = u.lcs[u.vhg[v]];
     return h.phase == kPhRoll && h.improved == 0;
   };
   auto emit = [&](int64_t v, int32_t pos) -> unsigned long long {
-    moves[pos] = make_int4((int32_t)v, part[v], target[v], vw ? vw[v] : 1);
-    mvto[v] = (uint8_t)target[v];
+    const int32_t from = part[v], t = target[v];
+    moves[pos] = make_int4((int32_t)v, from, t, vw ? vw[v] : 1);
+    mvfrom[v] = (uint8_t)from;
+    part[v] = t;
     return (unsigned long long)(voff[v + 1] - voff[v]);
   };
   if (u.lcs) block_compact(n, pred, emit, st, bigmv, &u.act[kActRoll], u.ht0);
@@ -972,13 +977,15 @@ __global__ __launch_bounds__(kSelBlock) void k_diff_moves(const int32_t *__restr
 
 // ------------------------------------------------------------------ applying a move list
 //
-// Two ways to bring pin counts, connectivity words, block weights and the metric up to date; the
-// device picks one from the number of listed moves (no host round trip):
+// The pass that lists the moves has written the moved vertices' new blocks to the partition and the
+// blocks they left to mvfrom (0xff for the other vertices it walked).  k_apply brings pin counts,
+// connectivity words, block weights and the metric up to date in one of two ways; the device picks
+// one from the number of listed moves (no host round trip):
 //
-// Many moves (>= n / kNetCentricDivisor): net-centric.  Every net is owned by one wave (small
-// nets, chunked) or one workgroup (larger nets), which recounts the blocks its moving pins leave
-// and enter and rewrites those counts, its connectivity words and its metric contribution with
-// plain stores; the partition entries are then updated from the move list.
+// Many moves (their incident nets, times the divisor, reach the number of pins): net-centric.  Every
+// net is owned by one wave (small nets, chunked) or one workgroup (larger nets), which recounts the
+// blocks its moving pins leave and enter and rewrites those counts, its connectivity words and its
+// metric contribution with plain stores.
 //
 // Few moves: vertex-centric.  Each move walks its incident nets and moves the counts by +-1 with
 // atomics.  The counter values of one (net, block) form a sequence of +-1 steps in the atomics'
@@ -986,6 +993,9 @@ __global__ __launch_bounds__(kSelBlock) void k_diff_moves(const int32_t *__restr
 // 1->0 step removes it (the sum telescopes to the exact change), and the bits [count > 0] (flips at
 // 0<->1) and [count == 1] (flips at 0<->1 and 1<->2) are kept by atomic XOR toggles, which commute.
 // A move with many incident nets gets a whole block whose threads stride over its nets.
+//
+// Both ways sit in one launch: with a launch each for chunks, medium and big nets, three grids that
+// find their path not taken cost 6 us each per application (of 20 us on a row-net level).
 
 // divisor 0: always vertex-centric; otherwise net-centric when the moves' incident nets, times the
 // divisor, reach the number of pins
@@ -1053,154 +1063,34 @@ __device__ __forceinline__ int64_t apply_nets_of_move(const int32_t *__restrict_
   return dk;
 }
 
-// Partition entries and block weights from the move list; in the vertex-centric case also the
-// incident nets of every move.
-constexpr int kApplyLanes = 8;
-template <int NW, typename T>
-__global__ __launch_bounds__(256) void k_apply(const int4 *__restrict__ moves, const int64_t *__restrict__ voff,
-                                               const int32_t *__restrict__ inc, const int32_t *__restrict__ nw,
-                                               int64_t p, int32_t k, int32_t *__restrict__ part,
-                                               T *__restrict__ phi, uint64_t *__restrict__ ns,
-                                               uint8_t *__restrict__ mvto, const int32_t *__restrict__ bigmv,
-                                               int32_t divisor, DevStatus *st, const LoopCtl *lc, int32_t want,
-                                               Union u, int32_t xcd) {
-  JET_GATE(lc, want);
-  __shared__ unsigned long long dw[kMaxK];
-  __shared__ int32_t dc[kMaxK];
-  __shared__ int64_t sdk[256 / kWave];
-  for (int b = threadIdx.x; b < k; b += blockDim.x) {
-    dw[b] = 0;
-    dc[b] = 0;
-  }
-  __syncthreads();
-  const int32_t cnt = st->n_moves;
-  const bool by_vertex = !net_centric(st, p, divisor);
-  int64_t dk = 0;
-  // kApplyLanes lanes per move, each taking every kApplyLanes-th incident net of a move with few
-  // nets, so a move's chain of dependent atomics is that many times shorter.  A union gives every
-  // workgroup a contiguous range of the list (moves are listed by vertex, so by hypergraph): the
-  // moves of the range's first hypergraph ("home") add into the workgroup's sums, the others (a
-  // range crossing into the next hypergraph) straight into their segments.
-  const int lg = threadIdx.x % kApplyLanes;
-  const bool un = u.vhg != nullptr;
-  int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kApplyLanes, i1 = cnt;
-  int64_t istep = (int64_t)gridDim.x * blockDim.x / kApplyLanes;
-  int32_t home = 0;
-  if (un) {
-    const int64_t per = ((int64_t)cnt + gridDim.x - 1) / gridDim.x;
-    const int64_t first = (int64_t)blockIdx.x * per;
-    i0 = first + threadIdx.x / kApplyLanes;
-    i1 = first + per < cnt ? first + per : cnt;
-    istep = blockDim.x / kApplyLanes;
-    if (first < cnt) home = u.vhg[moves[first].x];
-  } else if (xcd && gridDim.x % 8 == 0) {
-    // the workgroups of one XCD (round robin by workgroup) take one contiguous eighth of the list
-    // (moves are listed by vertex: neighbouring moves share nets' lines in that XCD's L2)
-    const int64_t span = blockDim.x / kApplyLanes, steps = (cnt + span - 1) / span, per = (steps + 7) / 8;
-    const int64_t x = blockIdx.x % 8;
-    i0 = (x * per + blockIdx.x / 8) * span + threadIdx.x / kApplyLanes;
-    i1 = min((int64_t)cnt, (x + 1) * per * span);
-    istep = (int64_t)(gridDim.x / 8) * span;
-  }
-  for (int64_t i = i0; i < i1; i += istep) {
-    const int4 mv = moves[i];
-    const int32_t hg = un ? (int32_t)u.vhg[mv.x] : 0;
-    const bool local = !un || hg == home;
-    if (lg == 0) {
-      part[mv.x] = mv.z;
-      mvto[mv.x] = 0xff;
-      if (local) {
-        atomicAdd(&dw[mv.y], (unsigned long long)(-(int64_t)mv.w));
-        atomicAdd(&dw[mv.z], (unsigned long long)mv.w);
-        atomicAdd(&dc[mv.y], -1);
-        atomicAdd(&dc[mv.z], 1);
-      } else {  // union: another hypergraph's segments
-        const int64_t sg = (int64_t)hg * k;
-        atomicAdd((unsigned long long *)&st->bw[sg + mv.y], (unsigned long long)(-(int64_t)mv.w));
-        atomicAdd((unsigned long long *)&st->bw[sg + mv.z], (unsigned long long)mv.w);
-        atomicAdd(&st->bcnt[sg + mv.y], -1);
-        atomicAdd(&st->bcnt[sg + mv.z], 1);
-      }
-    }
-    if (by_vertex) {
-      const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
-      if (q1 - q0 <= kLaneDegree) {
-        const int64_t d = apply_nets_of_move<NW>(inc, q0 + lg, q1, kApplyLanes, mv.y, mv.z, k, nw, phi, ns);
-        if (local) dk += d;
-        else add_km1_hg(st, hg, d);
-      }
-    }
-  }
-  if (by_vertex) {
-    // high-degree moves: an equal share of the grid each (several blocks per move while there are
-    // fewer such moves than blocks), the threads of the share striding over the move's nets
-    const int32_t nb = st->n_bigmv;
-    if (nb > 0 && nb <= (int32_t)gridDim.x) {
-      const int32_t per = (int32_t)gridDim.x / nb;
-      const int32_t j = (int32_t)blockIdx.x / per, sub = (int32_t)blockIdx.x % per;
-      if (j < nb) {
-        const int4 mv = moves[bigmv[j]];
-        const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
-        const int64_t d = apply_nets_of_move<NW>(inc, q0 + (int64_t)sub * blockDim.x + threadIdx.x, q1,
-                                                 (int64_t)per * blockDim.x, mv.y, mv.z, k, nw, phi, ns);
-        if (u.vhg) add_km1_hg(st, u.vhg[mv.x], d);
-        else dk += d;
-      }
-    } else {
-      for (int32_t j = blockIdx.x; j < nb; j += gridDim.x) {
-        const int4 mv = moves[bigmv[j]];
-        const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
-        const int64_t d = apply_nets_of_move<NW>(inc, q0 + threadIdx.x, q1, blockDim.x, mv.y, mv.z, k, nw, phi, ns);
-        if (u.vhg) add_km1_hg(st, u.vhg[mv.x], d);
-        else dk += d;
-      }
-    }
-  }
-  dk = wave_sum(dk);
-  if (lane_id() == 0) sdk[threadIdx.x / kWave] = dk;
-  __syncthreads();
-  if (threadIdx.x == 0) {
-    int64_t tt = 0;
-    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) tt += sdk[w];
-    if (un) add_km1_hg(st, home, tt);
-    else add_km1(st, blockIdx.x, tt);
-  }
-  const int64_t sg0 = (int64_t)home * k;  // segments of the home hypergraph (the blocks for one)
-  for (int b = threadIdx.x; b < k; b += blockDim.x) {
-    if (dw[b]) atomicAdd((unsigned long long *)&st->bw[sg0 + b], dw[b]);
-    if (dc[b]) atomicAdd(&st->bcnt[sg0 + b], dc[b]);
-  }
-}
-
-// Net-centric, small nets: one wave per chunk.  Each pin's new block is its move target or its
-// block; per net the new connectivity words come from LDS OR-accumulation (a second OR collects
-// blocks seen twice), and each moving pin rewrites the counts of the two blocks it touches from
-// the pins of its net now in them (no count is read): every pin adds one to a byte counter of
-// (its net, its new block) in the wave's LDS table, and a moving pin reads the two it needs.  A
-// chunk holds at most 64 pins, so a byte never carries; the pins clear their counter words again
-// once the chunk is done, so the table is zero between chunks.  A wave takes kApplyU chunks at a time and
-// issues each level of their dependent loads (descriptor, pin, move target, block and words) for
-// all of them before using any, so the latency chain is paid once per group.
+// Net-centric, small nets: one wave per chunk.  Per net the new connectivity words come from LDS
+// OR-accumulation over its pins' blocks (a second OR collects blocks seen twice), and each moving
+// pin rewrites the counts of the two blocks it touches from the pins of its net now in them (no
+// count is read): every pin adds one to a byte counter of (its net, its block) in the wave's LDS
+// table, and a moving pin reads the two it needs.  A chunk holds at most 64 pins, so a byte never
+// carries; the pins clear their counter words again once the chunk is done, so the table is zero
+// between chunks.  A wave takes kApplyU chunks at a time and issues each level of their dependent
+// loads (descriptor, pin, block left, block and words) for all of them before using any, so the
+// latency chain is paid once per group.
 constexpr int kApplyU = 4;
+constexpr int kApplyBlock = 256;
+template <int NW>
+struct ChunkLds {  // one wave's
+  unsigned long long once[kChunkNets][NW], twice[kChunkNets][NW];
+  uint32_t cnt[kChunkNets][16 * NW];  // byte counters of (chunk net, block)
+};
 
 template <int NW, typename T>
-__global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict__ off,
-                                                      const int32_t *__restrict__ pins,
-                                                      const int4 *__restrict__ chunks,
-                                                      const uint8_t *__restrict__ pnet, int32_t nchunks,
-                                                      const int32_t *__restrict__ nw,
-                                                      const int32_t *__restrict__ part,
-                                                      const uint8_t *__restrict__ mvto, int64_t p, int32_t k,
-                                                      T *__restrict__ phi, uint64_t *__restrict__ ns,
-                                                      int32_t divisor, DevStatus *st, const LoopCtl *lc,
-                                                      int32_t want, Union un, int32_t xcd) {
-  JET_GATE(lc, want);
+__device__ __forceinline__ void recount_chunks(const int32_t *__restrict__ pins, const int4 *__restrict__ chunks,
+                                               const uint8_t *__restrict__ pnet, int32_t nchunks,
+                                               const int32_t *__restrict__ nw, const int32_t *__restrict__ part,
+                                               const uint8_t *__restrict__ mvfrom, int32_t k, T *__restrict__ phi,
+                                               uint64_t *__restrict__ ns, DevStatus *st, int32_t want, const Union &un,
+                                               int32_t xcd, ChunkLds<NW> *lds) {
   constexpr int U = kApplyU;
-  __shared__ unsigned long long once[4][64][NW], twice[4][64][NW];
-  __shared__ uint32_t cnt[4][64][16 * NW];  // per wave: byte counters of (chunk net, block)
-  if (!net_centric(st, p, divisor)) return;
   const int w = threadIdx.x / kWave, l = lane_id();
-  for (int x = 0; x < 64 * 16 * NW; x += kWave) (&cnt[w][0][0])[x + l] = 0u;
+  ChunkLds<NW> &L = lds[w];
+  for (int x = 0; x < kChunkNets * 16 * NW; x += kWave) (&L.cnt[0][0])[x + l] = 0u;
   const int32_t wid = blockIdx.x * 4 + w, nwaves = gridDim.x * 4;
   int64_t dk = 0;
   // each wave walks its own groups of chunks; the LDS slots are private to the wave.  With xcd set,
@@ -1265,19 +1155,19 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
         v[u] = pins[q];
       }
     }
-    uint8_t mt[U];
+    uint8_t mf[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) mt[u] = act[u] ? mvto[v[u]] : (uint8_t)0xff;
+    for (int u = 0; u < U; ++u) mf[u] = act[u] ? mvfrom[v[u]] : (uint8_t)0xff;
     uint64_t movers[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) movers[u] = ballot(mt[u] != 0xff);
+    for (int u = 0; u < U; ++u) movers[u] = ballot(mf[u] != 0xff);
     // blocks of the pins and connectivity words of the nets in chunks with movers
     int32_t ob[U], nb[U];
     uint64_t wd[U][2 * NW];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      ob[u] = 0;
-      if (movers[u] && act[u]) ob[u] = part[v[u]];
+      nb[u] = 0;
+      if (movers[u] && act[u]) nb[u] = part[v[u]];
 #pragma unroll
       for (int x = 0; x < 2 * NW; ++x) wd[u][x] = 0ull;
       if (movers[u] && l < cd[u].y) {
@@ -1287,29 +1177,31 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
       }
     }
 #pragma unroll
-    for (int u = 0; u < U; ++u) nb[u] = mt[u] != 0xff ? (int32_t)mt[u] : ob[u];
+    for (int u = 0; u < U; ++u) ob[u] = mf[u] != 0xff ? (int32_t)mf[u] : nb[u];
 #pragma unroll
     for (int u = 0; u < U; ++u) {
       if (!movers[u]) continue;  // wave-uniform
-      const bool moved = mt[u] != 0xff;
+      const bool moved = mf[u] != 0xff;
 #pragma unroll
       for (int x = 0; x < NW; ++x) {
-        once[w][l][x] = 0ull;
-        twice[w][l][x] = 0ull;
+        if (l < kChunkNets) {
+          L.once[l][x] = 0ull;
+          L.twice[l][x] = 0ull;
+        }
       }
       wave_lds_sync();
       if (act[u]) {
         const unsigned long long bit = 1ull << (nb[u] & 63);
-        const unsigned long long old = atomicOr(&once[w][j[u]][nb[u] >> 6], bit);
-        if (old & bit) atomicOr(&twice[w][j[u]][nb[u] >> 6], bit);
-        atomicAdd(&cnt[w][j[u]][nb[u] >> 2], 1u << (8 * (nb[u] & 3)));
+        const unsigned long long old = atomicOr(&L.once[j[u]][nb[u] >> 6], bit);
+        if (old & bit) atomicOr(&L.twice[j[u]][nb[u] >> 6], bit);
+        atomicAdd(&L.cnt[j[u]][nb[u] >> 2], 1u << (8 * (nb[u] & 3)));
       }
       wave_lds_sync();
       // The whole net is in the wave, so the new counts of the two blocks a moving pin touches
       // are those of its net's counters: pins of the net whose new block is that block.
       if (moved) {
-        const int32_t co = (cnt[w][j[u]][ob[u] >> 2] >> (8 * (ob[u] & 3))) & 0xff;
-        const int32_t cn = (cnt[w][j[u]][nb[u] >> 2] >> (8 * (nb[u] & 3))) & 0xff;
+        const int32_t co = (L.cnt[j[u]][ob[u] >> 2] >> (8 * (ob[u] & 3))) & 0xff;
+        const int32_t cn = (L.cnt[j[u]][nb[u] >> 2] >> (8 * (nb[u] & 3))) & 0xff;
         const int64_t row = (int64_t)(cd[u].x + j[u]) * k;
         phi[row + ob[u]] = (T)co;
         phi[row + nb[u]] = (T)cn;
@@ -1321,7 +1213,7 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
         int lam_old = 0, lam_new = 0;
 #pragma unroll
         for (int x = 0; x < NW; ++x) {
-          const uint64_t a = once[w][l][x], bb = twice[w][l][x];
+          const uint64_t a = L.once[l][x], bb = L.twice[l][x];
           lam_old += __popcll(wd[u][x]);
           lam_new += __popcll(a);
           if (a != wd[u][x]) nse[x] = a;
@@ -1330,7 +1222,7 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
         if (lam_new != lam_old) dk += (int64_t)(lam_new - lam_old) * (nw ? nw[e] : 1);
       }
       wave_lds_sync();  // the LDS slots are reused by the next chunk
-      if (act[u]) cnt[w][j[u]][nb[u] >> 2] = 0u;  // every nonzero counter word has a pin here
+      if (act[u]) L.cnt[j[u]][nb[u] >> 2] = 0u;  // every nonzero counter word has a pin here
     }
   }  // chunk-group loop
   dk = wave_sum(dk);
@@ -1342,65 +1234,65 @@ __global__ __launch_bounds__(256) void k_apply_chunks(const int64_t *__restrict_
 
 // Net-centric, larger nets: one block per net; per-block count changes gathered in LDS, then the
 // block rewrites the changed counts, the connectivity words and its metric contribution.
-template <int NW, typename T, int THREADS>
-__global__ __launch_bounds__(THREADS) void k_apply_nets(const int64_t *__restrict__ off, const int32_t *__restrict__ pins,
-                                                    const int32_t *__restrict__ nets, int32_t nnets,
-                                                    const int32_t *__restrict__ nw,
-                                                    const int32_t *__restrict__ part,
-                                                    const uint8_t *__restrict__ mvto, int64_t p, int32_t k,
-                                                    T *__restrict__ phi, uint64_t *__restrict__ ns,
-                                                    int32_t divisor, DevStatus *st, const LoopCtl *lc,
-                                                    int32_t want, Union u) {
-  JET_GATE(lc, want);
-  __shared__ int32_t delta[kMaxK];
-  __shared__ unsigned long long words[2 * NW];
-  __shared__ int32_t any;
-  if (!net_centric(st, p, divisor)) return;
+template <int NW>
+struct NetLds {
+  int32_t delta[kMaxK];
+  unsigned long long words[2 * NW];
+  int32_t any;
+};
+
+template <int NW, typename T>
+__device__ __forceinline__ void recount_nets(const int64_t *__restrict__ off, const int32_t *__restrict__ pins,
+                                             const int32_t *__restrict__ nets, int32_t nnets,
+                                             const int32_t *__restrict__ nw, const int32_t *__restrict__ part,
+                                             const uint8_t *__restrict__ mvfrom, int32_t k, T *__restrict__ phi,
+                                             uint64_t *__restrict__ ns, DevStatus *st, int32_t want, const Union &u,
+                                             NetLds<NW> &L) {
   int64_t dk = 0;  // metric change of this block's nets (thread 0)
   for (int32_t bi = blockIdx.x; bi < nnets; bi += gridDim.x) {  // block-uniform trip count
   const int32_t e = nets[bi];
   if (u.lcs && u.lcs[u.nhg[e]].phase != want) continue;  // union: no move of an idle hypergraph
   const int64_t q0 = off[e], q1 = off[e + 1];
-  for (int b = threadIdx.x; b < k; b += blockDim.x) delta[b] = 0;
-  if (threadIdx.x == 0) any = 0;
-  if (threadIdx.x < 2 * NW) words[threadIdx.x] = ns[(int64_t)e * (2 * NW) + threadIdx.x];
+  for (int b = threadIdx.x; b < k; b += blockDim.x) L.delta[b] = 0;
+  if (threadIdx.x == 0) L.any = 0;
+  if (threadIdx.x < 2 * NW) L.words[threadIdx.x] = ns[(int64_t)e * (2 * NW) + threadIdx.x];
   __syncthreads();
-  // four slices of the net at a time, each level of their dependent loads (pin, move target,
-  // block) issued for all before any is used
-  for (int64_t qb = q0; qb < q1; qb += 4 * THREADS) {
-    int32_t v[4], pv[4];
-    uint8_t mt[4];
+  // four slices of the net at a time, each level of their dependent loads (pin, block
+  // left, block) issued for all before any is used
+  for (int64_t qb = q0; qb < q1; qb += 4 * kApplyBlock) {
+    int32_t v[4], nb[4];
+    uint8_t mf[4];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      const int64_t q = qb + u * THREADS + threadIdx.x;
+      const int64_t q = qb + u * kApplyBlock + threadIdx.x;
       v[u] = q < q1 ? pins[q] : -1;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) mt[u] = v[u] >= 0 ? mvto[v[u]] : (uint8_t)0xff;
+    for (int u = 0; u < 4; ++u) mf[u] = v[u] >= 0 ? mvfrom[v[u]] : (uint8_t)0xff;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) pv[u] = mt[u] != 0xff ? part[v[u]] : 0;
+    for (int u = 0; u < 4; ++u) nb[u] = mf[u] != 0xff ? part[v[u]] : 0;
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
-      if (mt[u] != 0xff) {
-        atomicSub(&delta[pv[u]], 1);
-        atomicAdd(&delta[mt[u]], 1);
-        any = 1;
+      if (mf[u] != 0xff) {
+        atomicSub(&L.delta[mf[u]], 1);
+        atomicAdd(&L.delta[nb[u]], 1);
+        L.any = 1;
       }
     }
   }
   __syncthreads();
-  if (any) {
+  if (L.any) {
   for (int b = threadIdx.x; b < k; b += blockDim.x) {
-    const int32_t d = delta[b];
+    const int32_t d = L.delta[b];
     if (d == 0) continue;
     const int64_t idx = (int64_t)e * k + b;
     const int32_t nv = (int32_t)phi[idx] + d;
     phi[idx] = (T)nv;
     const unsigned long long bit = 1ull << (b & 63);
-    if (nv > 0) atomicOr(&words[b >> 6], bit);
-    else atomicAnd(&words[b >> 6], ~bit);
-    if (nv == 1) atomicOr(&words[NW + (b >> 6)], bit);
-    else atomicAnd(&words[NW + (b >> 6)], ~bit);
+    if (nv > 0) atomicOr(&L.words[b >> 6], bit);
+    else atomicAnd(&L.words[b >> 6], ~bit);
+    if (nv == 1) atomicOr(&L.words[NW + (b >> 6)], bit);
+    else atomicAnd(&L.words[NW + (b >> 6)], ~bit);
   }
   __syncthreads();
   if (threadIdx.x == 0) {
@@ -1408,9 +1300,9 @@ __global__ __launch_bounds__(THREADS) void k_apply_nets(const int64_t *__restric
     int lam_old = 0, lam_new = 0;
     for (int x = 0; x < NW; ++x) {
       lam_old += __popcll(nse[x]);
-      lam_new += __popcll(words[x]);
+      lam_new += __popcll(L.words[x]);
     }
-    for (int x = 0; x < 2 * NW; ++x) nse[x] = words[x];
+    for (int x = 0; x < 2 * NW; ++x) nse[x] = L.words[x];
     if (lam_new != lam_old) {
       const int64_t d = (int64_t)(lam_new - lam_old) * (nw ? nw[e] : 1);
       if (u.nhg) add_km1_hg(st, u.nhg[e], d);
@@ -1421,6 +1313,133 @@ __global__ __launch_bounds__(THREADS) void k_apply_nets(const int64_t *__restric
   __syncthreads();  // LDS reused by the next net
   }  // net loop
   if (threadIdx.x == 0) add_km1(st, blockIdx.x, dk);
+}
+
+// Vertex-centric: the incident nets of every move.  kApplyLanes lanes per move, each taking every
+// kApplyLanes-th incident net of a move with few nets, so a move's chain of dependent atomics is
+// that many times shorter.
+constexpr int kApplyLanes = 8;
+template <int NW, typename T>
+__global__ __launch_bounds__(kApplyBlock) void k_apply(
+    const int4 *__restrict__ moves, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
+    const int64_t *__restrict__ off, const int32_t *__restrict__ pins, const int4 *__restrict__ chunks,
+    const uint8_t *__restrict__ pnet, int32_t nchunks, const int32_t *__restrict__ mid, int32_t nmid,
+    const int32_t *__restrict__ big, int32_t nbig, const int32_t *__restrict__ nw, int64_t p, int32_t k,
+    const int32_t *__restrict__ part, T *__restrict__ phi, uint64_t *__restrict__ ns,
+    const uint8_t *__restrict__ mvfrom, const int32_t *__restrict__ bigmv, int32_t divisor, DevStatus *st,
+    const LoopCtl *lc, int32_t want, Union u, int32_t xcd) {
+  JET_GATE(lc, want);
+  __shared__ unsigned long long dw[kMaxK];
+  __shared__ int32_t dc[kMaxK];
+  __shared__ int64_t sdk[kApplyBlock / kWave];
+  __shared__ ChunkLds<NW> chunk_lds[kApplyBlock / kWave];
+  __shared__ NetLds<NW> net_lds;
+  const int32_t cnt = st->n_moves;
+  if (cnt == 0) return;
+  const bool by_vertex = !net_centric(st, p, divisor);
+  for (int b = threadIdx.x; b < k; b += blockDim.x) {
+    dw[b] = 0;
+    dc[b] = 0;
+  }
+  __syncthreads();
+  if (!by_vertex) {
+    // larger nets first: they are the long ones
+    if (nbig > 0) recount_nets<NW, T>(off, pins, big, nbig, nw, part, mvfrom, k, phi, ns, st, want, u, net_lds);
+    if (nmid > 0) recount_nets<NW, T>(off, pins, mid, nmid, nw, part, mvfrom, k, phi, ns, st, want, u, net_lds);
+    if (nchunks > 0)
+      recount_chunks<NW, T>(pins, chunks, pnet, nchunks, nw, part, mvfrom, k, phi, ns, st, want, u, xcd, chunk_lds);
+  }
+  int64_t dk = 0;
+  // A union gives every workgroup a contiguous range of the list (moves are listed by vertex, so by
+  // hypergraph): the moves of the range's first hypergraph ("home") add into the workgroup's sums,
+  // the others (a range crossing into the next hypergraph) straight into their segments.
+  const int lg = threadIdx.x % kApplyLanes;
+  const bool un = u.vhg != nullptr;
+  int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kApplyLanes, i1 = cnt;
+  int64_t istep = (int64_t)gridDim.x * blockDim.x / kApplyLanes;
+  int32_t home = 0;
+  if (un) {
+    const int64_t per = ((int64_t)cnt + gridDim.x - 1) / gridDim.x;
+    const int64_t first = (int64_t)blockIdx.x * per;
+    i0 = first + threadIdx.x / kApplyLanes;
+    i1 = first + per < cnt ? first + per : cnt;
+    istep = blockDim.x / kApplyLanes;
+    if (first < cnt) home = u.vhg[moves[first].x];
+  } else if (xcd && gridDim.x % 8 == 0) {
+    // the workgroups of one XCD (round robin by workgroup) take one contiguous eighth of the list
+    // (moves are listed by vertex: neighbouring moves share nets' lines in that XCD's L2)
+    const int64_t span = blockDim.x / kApplyLanes, steps = (cnt + span - 1) / span, per = (steps + 7) / 8;
+    const int64_t x = blockIdx.x % 8;
+    i0 = (x * per + blockIdx.x / 8) * span + threadIdx.x / kApplyLanes;
+    i1 = min((int64_t)cnt, (x + 1) * per * span);
+    istep = (int64_t)(gridDim.x / 8) * span;
+  }
+  for (int64_t i = i0; i < i1; i += istep) {
+    const int4 mv = moves[i];
+    const int32_t hg = un ? (int32_t)u.vhg[mv.x] : 0;
+    const bool local = !un || hg == home;
+    if (lg == 0) {
+      if (local) {
+        atomicAdd(&dw[mv.y], (unsigned long long)(-(int64_t)mv.w));
+        atomicAdd(&dw[mv.z], (unsigned long long)mv.w);
+        atomicAdd(&dc[mv.y], -1);
+        atomicAdd(&dc[mv.z], 1);
+      } else {  // union: another hypergraph's segments
+        const int64_t sg = (int64_t)hg * k;
+        atomicAdd((unsigned long long *)&st->bw[sg + mv.y], (unsigned long long)(-(int64_t)mv.w));
+        atomicAdd((unsigned long long *)&st->bw[sg + mv.z], (unsigned long long)mv.w);
+        atomicAdd(&st->bcnt[sg + mv.y], -1);
+        atomicAdd(&st->bcnt[sg + mv.z], 1);
+      }
+    }
+    if (by_vertex) {
+      const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
+      if (q1 - q0 <= kLaneDegree) {
+        const int64_t d = apply_nets_of_move<NW>(inc, q0 + lg, q1, kApplyLanes, mv.y, mv.z, k, nw, phi, ns);
+        if (local) dk += d;
+        else add_km1_hg(st, hg, d);
+      }
+    }
+  }
+  if (by_vertex) {
+    // high-degree moves: an equal share of the grid each (several blocks per move while there are
+    // fewer such moves than blocks), the threads of the share striding over the move's nets
+    const int32_t nb = st->n_bigmv;
+    if (nb > 0 && nb <= (int32_t)gridDim.x) {
+      const int32_t per = (int32_t)gridDim.x / nb;
+      const int32_t j = (int32_t)blockIdx.x / per, sub = (int32_t)blockIdx.x % per;
+      if (j < nb) {
+        const int4 mv = moves[bigmv[j]];
+        const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
+        const int64_t d = apply_nets_of_move<NW>(inc, q0 + (int64_t)sub * blockDim.x + threadIdx.x, q1,
+                                                 (int64_t)per * blockDim.x, mv.y, mv.z, k, nw, phi, ns);
+        if (u.vhg) add_km1_hg(st, u.vhg[mv.x], d);
+        else dk += d;
+      }
+    } else {
+      for (int32_t j = blockIdx.x; j < nb; j += gridDim.x) {
+        const int4 mv = moves[bigmv[j]];
+        const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
+        const int64_t d = apply_nets_of_move<NW>(inc, q0 + threadIdx.x, q1, blockDim.x, mv.y, mv.z, k, nw, phi, ns);
+        if (u.vhg) add_km1_hg(st, u.vhg[mv.x], d);
+        else dk += d;
+      }
+    }
+  }
+  dk = wave_sum(dk);
+  if (lane_id() == 0) sdk[threadIdx.x / kWave] = dk;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int64_t tt = 0;
+    for (int w = 0; w < (int)(blockDim.x / kWave); ++w) tt += sdk[w];
+    if (un) add_km1_hg(st, home, tt);
+    else add_km1(st, blockIdx.x, tt);
+  }
+  const int64_t sg0 = (int64_t)home * k;  // segments of the home hypergraph (the blocks for one)
+  for (int b = threadIdx.x; b < k; b += blockDim.x) {
+    if (dw[b]) atomicAdd((unsigned long long *)&st->bw[sg0 + b], dw[b]);
+    if (dc[b]) atomicAdd(&st->bcnt[sg0 + b], dc[b]);
+  }
 }
 
 inline unsigned grid_for(int64_t work, int block, int64_t cap) {
@@ -1620,47 +1639,34 @@ hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc) {
   return err;
 }
 
-hipError_t launch_select_moves(Ctx &c, const int32_t *part, int32_t stamp, const LoopCtl *lc) {
+hipError_t launch_select_moves(Ctx &c, int32_t *part, int32_t stamp, const LoopCtl *lc) {
   // the move counters were cleared with the candidate counters
   const int32_t want = lc ? (int32_t)kPhJet : (int32_t)kPhAny;
   const int tok = prof_begin(c, kProfSelect, lc, want);
   hipLaunchKernelGGL(k_select_moves, dim3(grid_for(c.n, kSelBlock * kCompactPer, c.grid_cap)), dim3(kSelBlock), 0,
                      c.stream, part, c.inm, c.rec,
-                     c.rg, c.vw, c.n, stamp, c.lockstamp, c.moves, c.mvto, c.voff, c.st, c.bigmv, lc, union_of(c));
+                     c.rg, c.vw, c.n, stamp, c.lockstamp, c.moves, c.mvfrom, c.voff, c.st, c.bigmv, lc, union_of(c));
   prof_end(c, tok, lc, want, 8.5 * c.n, 0.0);
   return hipGetLastError();
 }
 
 // only in the loop: the control kernel that enters the rollback cleared the move counters
-hipError_t launch_diff_moves(Ctx &c, const int32_t *part, const int32_t *target, const LoopCtl *lc) {
+hipError_t launch_diff_moves(Ctx &c, int32_t *part, const int32_t *target, const LoopCtl *lc) {
   hipLaunchKernelGGL(k_diff_moves, dim3(grid_for(c.n, kSelBlock * kCompactPer, c.grid_cap)), dim3(kSelBlock), 0, c.stream,
                      part, target, c.vw,
-                     c.n, c.moves, c.mvto, c.voff, c.st, c.bigmv, lc, union_of(c));
+                     c.n, c.moves, c.mvfrom, c.voff, c.st, c.bigmv, lc, union_of(c));
   return hipGetLastError();
 }
 
 template <int NW, typename T>
 void apply_launch(Ctx &c, int32_t *part, bool wide, T *phi, const LoopCtl *lc, int32_t want) {
-  // The net-centric kernels read the old blocks, so they run before k_apply writes the new ones.
-  // The device decides which path runs; `wide` only sizes their grids: one wave per chunk and one
-  // block per net when the host expects the net-centric path, a small grid that exits at once
-  // otherwise (either grid gives the same result).
-  const unsigned cap = wide ? 0x7fffffffu : 2048u;
-  if (c.nchunks > 0)
-    hipLaunchKernelGGL((k_apply_chunks<NW, T>),
-                       dim3(std::min(cap, (unsigned)((c.nchunks + 4 * kApplyU - 1) / (4 * kApplyU)))), dim3(256), 0,
-                       c.stream, c.off, c.pins, c.chunks, c.pnet, c.nchunks, c.nw, part, c.mvto, c.p, c.k, phi, c.ns,
-                       c.apply_divisor, c.st, lc, want, union_of(c), c.apply_xcd);
-  if (c.nmid > 0)
-    hipLaunchKernelGGL((k_apply_nets<NW, T, 128>), dim3(std::min(cap, (unsigned)c.nmid)), dim3(128), 0, c.stream,
-                       c.off, c.pins, c.mid_nets, c.nmid, c.nw, part, c.mvto, c.p, c.k, phi, c.ns, c.apply_divisor,
-                       c.st, lc, want, union_of(c));
-  if (c.nbig > 0)
-    hipLaunchKernelGGL((k_apply_nets<NW, T, 256>), dim3(std::min(cap, (unsigned)c.nbig)), dim3(256), 0, c.stream,
-                       c.off, c.pins, c.big_nets, c.nbig, c.nw, part, c.mvto, c.p, c.k, phi, c.ns, c.apply_divisor,
-                       c.st, lc, want, union_of(c));
-  hipLaunchKernelGGL((k_apply<NW, T>), dim3(kApplyGrid), dim3(256), 0, c.stream, c.moves, c.voff, c.inc, c.nw, c.p, c.k,
-                     part, phi, c.ns, c.mvto, c.bigmv, c.apply_divisor, c.st, lc, want, union_of(c), c.apply_xcd);
+  // `wide` only sizes the grid: one wave per group of chunks when the host expects the net-centric
+  // path (either grid gives the same result)
+  const int64_t groups = ((int64_t)c.nchunks + 4 * kApplyU - 1) / (4 * kApplyU);
+  const unsigned grid = wide ? (unsigned)std::max<int64_t>(kApplyGrid, std::min<int64_t>(groups, 1 << 20)) : kApplyGrid;
+  hipLaunchKernelGGL((k_apply<NW, T>), dim3(grid), dim3(kApplyBlock), 0, c.stream, c.moves, c.voff, c.inc, c.off,
+                     c.pins, c.chunks, c.pnet, c.nchunks, c.mid_nets, c.nmid, c.big_nets, c.nbig, c.nw, c.p, c.k, part,
+                     phi, c.ns, c.mvfrom, c.bigmv, c.apply_divisor, c.st, lc, want, union_of(c), c.apply_xcd);
 }
 
 hipError_t launch_apply_moves(Ctx &c, int32_t *part, bool wide, const LoopCtl *lc, int32_t want) {

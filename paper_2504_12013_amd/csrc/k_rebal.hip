@@ -176,7 +176,8 @@ __global__ __launch_bounds__(kUnionTile) void k_rb_list_union(const int32_t *__r
                                                               const int32_t *__restrict__ vw,
                                                               const int64_t *__restrict__ voff, int32_t n, int32_t k,
                                                               DevStatus *st, int32_t *__restrict__ list,
-                                                              int32_t *__restrict__ slot, const LoopCtl *lctl,
+                                                              int32_t *__restrict__ slot,
+                                                              uint8_t *__restrict__ mvfrom, const LoopCtl *lctl,
                                                               Union u) {
   JET_GATE(lctl, kPhRb);
   constexpr int T = 8;  // tiles per workgroup step
@@ -217,6 +218,7 @@ __global__ __launch_bounds__(kUnionTile) void k_rb_list_union(const int32_t *__r
       loc[j] = 0;
       const int64_t v = s_vb[j] + tid;
       if (s_vb[j] >= n || v >= n) continue;
+      mvfrom[v] = 0xff;
       const int32_t s = part[v];
       const int64_t bs = sbw[j][s];
       if (bs <= s_lmax[j] || u.vhg[v] != s_hg[j]) continue;  // not overloaded, or a padding vertex
@@ -267,7 +269,7 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
                                                         const int64_t *__restrict__ voff, int32_t n, int32_t k,
                                                         int64_t lmax, int64_t A, DevStatus *st,
                                                         int32_t *__restrict__ list, int32_t *__restrict__ slot,
-                                                        const LoopCtl *lctl) {
+                                                        uint8_t *__restrict__ mvfrom, const LoopCtl *lctl) {
   JET_GATE(lctl, kPhRb);
   __shared__ int64_t bw[kMaxK];
   __shared__ int32_t lc[kMaxK], lbase[kMaxK];
@@ -285,6 +287,7 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
   for (int j = 0; j < kListPer; ++j) {
     const int64_t v = r0 + j * kListBlock;
     pv[j] = v < n ? part[v] : -1;
+    if (v < n) mvfrom[v] = 0xff;
   }
   // vertices of overloaded blocks: weight and degree (loaded only for them)
   bool over[kListPer];
@@ -764,11 +767,13 @@ __device__ __forceinline__ uint32_t digit_of(const uint32_t *key, int d) {
   return (key[d >> 2] >> (8 * (3 - (d & 3)))) & 0xffu;
 }
 
-// Writes one selected entry as a move of vertex ent[5] from block `from` to ent[6].
+// Writes one selected entry as a move of vertex ent[5] from block `from` to ent[6], and the vertex's
+// new block.
 __device__ __forceinline__ void put_move(const uint32_t *ent, int32_t from, int32_t pos, int4 *moves,
-                                         int32_t *sel_target, uint8_t *mvto) {
+                                         int32_t *sel_target, int32_t *part, uint8_t *mvfrom) {
   moves[pos] = make_int4((int32_t)ent[5], from, (int32_t)ent[6], (int32_t)ent[7]);
-  mvto[ent[5]] = (uint8_t)ent[6];
+  part[ent[5]] = (int32_t)ent[6];
+  mvfrom[ent[5]] = (uint8_t)from;
   if (sel_target) sel_target[ent[5]] = (int32_t)ent[6];
 }
 
@@ -872,8 +877,8 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_hist(const uint32_t *_
 __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
     const uint32_t *__restrict__ entries, uint32_t *__restrict__ keep2, DevStatus *st,
     const unsigned long long *__restrict__ gw, const uint32_t *__restrict__ gc, int4 *__restrict__ moves,
-    int32_t *__restrict__ sel_target, uint8_t *__restrict__ mvto, const int64_t *__restrict__ voff,
-    int32_t *__restrict__ bigmv, const LoopCtl *lc) {
+    int32_t *__restrict__ sel_target, int32_t *__restrict__ part, uint8_t *__restrict__ mvfrom,
+    const int64_t *__restrict__ voff, int32_t *__restrict__ bigmv, const LoopCtl *lc) {
   JET_GATE(lc, kPhRb);
   __shared__ unsigned long long hw[256];
   __shared__ int32_t hc[256];
@@ -928,7 +933,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
       int64_t d = 0;
       if (e) {
         d = voff[ent[j][5] + 1] - voff[ent[j][5]];
-        put_move(ent[j], b, pos, moves, sel_target, mvto);
+        put_move(ent[j], b, pos, moves, sel_target, part, mvfrom);
       }
       push_big_move(d > kLaneDegree, pos, st, bigmv);
       pos += e ? 1 : 0;
@@ -957,7 +962,8 @@ constexpr int kRegPer = 4;  // entries per thread of the selection in registers
 // Starts at key byte d with `need` weight to select; every thread of the block calls it.
 __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
                                                  int32_t b, DevStatus *st, int4 *__restrict__ moves,
-                                                 int32_t *__restrict__ sel_target, uint8_t *__restrict__ mvto,
+                                                 int32_t *__restrict__ sel_target, int32_t *__restrict__ part,
+                                                 uint8_t *__restrict__ mvfrom,
                                                  const int64_t *__restrict__ voff, int32_t *__restrict__ bigmv,
                                                  int32_t *hmoves) {
   __shared__ unsigned long long rhw[2][256];
@@ -1075,7 +1081,7 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
       uint32_t ent[kEntryWords];
       load_entry(list + (int64_t)(j * kSelThreads + tid) * kEntryWords, ent);
       dg = voff[ent[5] + 1] - voff[ent[5]];
-      put_move(ent, b, pos, moves, sel_target, mvto);
+      put_move(ent, b, pos, moves, sel_target, part, mvfrom);
     }
     push_big_move(dg > kLaneDegree, pos, st, bigmv);
     pos += e ? 1 : 0;
@@ -1099,7 +1105,8 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
 // pass kept in keep2 (nothing is left to do when it completed the selection).
 __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__restrict__ entries, DevStatus *st,
                                                int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
-                                               uint8_t *__restrict__ mvto, const int64_t *__restrict__ voff,
+                                               int32_t *__restrict__ part, uint8_t *__restrict__ mvfrom,
+                                               const int64_t *__restrict__ voff,
                                                int32_t *__restrict__ bigmv, unsigned long long *__restrict__ gw,
                                                uint32_t *__restrict__ gc, uint32_t *__restrict__ keep2, int32_t k,
                                                const Union &u) {
@@ -1172,7 +1179,7 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
         const bool e = (emit >> j) & 1u;
         if (e) {
           d = voff[ent[j][5] + 1] - voff[ent[j][5]];
-          put_move(ent[j], b, pos, moves, sel_target, mvto);
+          put_move(ent[j], b, pos, moves, sel_target, part, mvfrom);
         }
         push_big_move(d > kLaneDegree, pos, st, bigmv);
         pos += e ? 1 : 0;
@@ -1203,7 +1210,7 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
     __syncthreads();  // every thread has finished reading the previous pass's histogram
     len = s_len;
     if (len <= kSelThreads * kRegPer) {  // block-uniform: the rest of the list fits the registers
-      select_registers(list, len, d, s_need, b, st, moves, sel_target, mvto, voff, bigmv,
+      select_registers(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
                        u.lcs ? &st->hmoves[sgm / k] : nullptr);
       break;
     }
@@ -1266,7 +1273,8 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
 // walk the segments of the hypergraphs in their rebalancing phase.
 __global__ __launch_bounds__(kSelThreads) void k_rb_select(uint32_t *__restrict__ entries, DevStatus *st,
                                                            int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
-                                                           uint8_t *__restrict__ mvto,
+                                                           int32_t *__restrict__ part,
+                                                           uint8_t *__restrict__ mvfrom,
                                                            const int64_t *__restrict__ voff,
                                                            int32_t *__restrict__ bigmv,
                                                            unsigned long long *__restrict__ gw,
@@ -1275,7 +1283,8 @@ __global__ __launch_bounds__(kSelThreads) void k_rb_select(uint32_t *__restrict_
   JET_GATE(lc, kPhRb);
   const int32_t nseg = u.lcs ? st->rb_nseg : k;  // union: the overloaded segments the preparation listed
   for (int32_t x = blockIdx.x; x < nseg; x += gridDim.x) {  // block-uniform trip count
-    select_segment(u.lcs ? st->rb_seg[x] : x, entries, st, moves, sel_target, mvto, voff, bigmv, gw, gc, keep2, k, u);
+    select_segment(u.lcs ? st->rb_seg[x] : x, entries, st, moves, sel_target, part, mvfrom, voff, bigmv, gw, gc,
+                   keep2, k, u);
     __syncthreads();  // shared state is reused by the next segment
   }
 }
@@ -1294,11 +1303,11 @@ hipError_t gain_launch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *l
   const Union u = union_of(c);
   if (c.H > 1)
     hipLaunchKernelGGL(k_rb_list_union, dim3(grid_for(c.n, 8 * kUnionTile, c.grid_cap)), dim3(kUnionTile), 0, c.stream, part, c.vw, c.voff,
-                       c.n, c.k, c.st, c.rb_list, c.rb_slot, lc, u);
+                       c.n, c.k, c.st, c.rb_list, c.rb_slot, c.mvfrom, lc, u);
   else
     hipLaunchKernelGGL(k_rb_list, dim3((unsigned)((c.n + kListBlock * kListPer - 1) / (kListBlock * kListPer))),
                        dim3(kListBlock), 0, c.stream, part, c.vw, c.voff, c.n, c.k, c.lmax, c.A, c.st, c.rb_list,
-                       c.rb_slot, lc);
+                       c.rb_slot, c.mvfrom, lc);
   // the list length is known on the device only: a persistent grid walks it; unit net weights and
   // k <= 64 take the bit-sliced kernel (one lane per vertex on light levels, eight otherwise) on
   // a context of one hypergraph
@@ -1337,7 +1346,7 @@ hipError_t gain_dispatch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl 
 
 }  // namespace
 
-hipError_t launch_rebalance_round(Ctx &c, const int32_t *part, int64_t dz, int32_t *sel_target,
+hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *sel_target,
                                   const LoopCtl *lc) {
   const int32_t want = lc ? (int32_t)kPhRb : (int32_t)kPhAny;
   if (c.H > 1)
@@ -1363,11 +1372,11 @@ hipError_t launch_rebalance_round(Ctx &c, const int32_t *part, int64_t dz, int32
     hipLaunchKernelGGL(k_rb_sel_hist, dim3(S, (unsigned)c.k), dim3(kSplitThreads), 0, c.stream, c.rb_keys, c.st,
                        c.rb_gw, c.rb_gc, lc);
     hipLaunchKernelGGL(k_rb_sel_split, dim3(S, (unsigned)c.k), dim3(kSplitThreads), 0, c.stream, c.rb_keys,
-                       c.rb_keys2, c.st, c.rb_gw, c.rb_gc, c.moves, sel_target, c.mvto, c.voff, c.bigmv, lc);
+                       c.rb_keys2, c.st, c.rb_gw, c.rb_gc, c.moves, sel_target, part, c.mvfrom, c.voff, c.bigmv, lc);
   }
   hipLaunchKernelGGL(k_rb_select, dim3(c.H > 1 ? (unsigned)std::min<int64_t>(512, (int64_t)c.H * c.k) : (unsigned)c.k),
                      dim3(kSelThreads), 0, c.stream, c.rb_keys, c.st,
-                     c.moves, sel_target, c.mvto, c.voff, c.bigmv, split ? c.rb_gw : nullptr,
+                     c.moves, sel_target, part, c.mvfrom, c.voff, c.bigmv, split ? c.rb_gw : nullptr,
                      split ? c.rb_gc : nullptr, c.rb_keys2, lc, c.k, union_of(c));
   prof_end(c, tok, lc, want, 0.0, 0.0);  // bytes from the entry and move counts (device)
   return hipGetLastError();

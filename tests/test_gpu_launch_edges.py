@@ -85,3 +85,29 @@ def test_rebalance_selection_list_lengths(n, k, order):
     assert rc == orc
     assert np.array_equal(d.cpu().numpy(), ref)
     assert st["rebalance_rounds"] == ost["rebalance_rounds"]
+
+
+@pytest.mark.parametrize("divisor", [0, 16, 1 << 20])
+@pytest.mark.parametrize("k", [5, 64, 100])
+def test_application_paths(divisor, k):
+    """Both ways of applying a move list (per move, per net) and the switch between them, on nets of
+    one pin (chunks full by nets, not pins), of a chunk's 64 pins, just above, and above 1,024."""
+    rng = np.random.default_rng(k)
+    n = 3000
+    sizes = np.concatenate([np.ones(200, int), rng.integers(2, 9, 3000), [63, 64, 65, 66, 255, 256, 257, 1023, 1024,
+                                                                        1025, 2500]])
+    nets = [np.sort(rng.choice(n, s, replace=False)) for s in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    hg = W.Hypergraph(n=n, m=len(nets), off=off, pins=np.concatenate(nets).astype(np.int32), k=k, eps=0.05)
+    part = W.part_uniform(n, k, 5)
+    say(f"divisor {divisor}, k = {k}")
+    kw = dict(tau=(0.75, 0.0), limit=5)
+    ref, orc, ost, _ = O.refine(hg, part, **kw)
+    ctx = J().JetContext(hg)
+    ctx.set_option(J().JET_OPT_APPLY_DIVISOR, divisor)
+    d = torch.from_numpy(part).to("cuda")
+    rc, st, _ = ctx.refine(d, **kw)
+    assert rc == orc
+    assert np.array_equal(d.cpu().numpy(), ref)
+    assert st["km1_out"] == ost["km1_out"] == ctx.km1(d)
+    ctx.close()
