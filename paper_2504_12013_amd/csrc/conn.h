@@ -51,13 +51,22 @@ __device__ __forceinline__ void conn_accumulate(const int32_t *__restrict__ inc,
       if (e[u] >= 0) {
         w[u] = UNIT ? 1 : nw[e[u]];
         const uint64_t *nse = ns + (int64_t)e[u] * (2 * NW);
+        uint64_t one;
+        if (NW == 1) {  // mask and "one pin" word in one access
+          const ulonglong2 q = *reinterpret_cast<const ulonglong2 *>(nse);
+          lo[u][0] = (uint32_t)q.x;
+          hi[u][0] = (uint32_t)(q.x >> 32);
+          one = q.y;
+        } else {
 #pragma unroll
-        for (int x = 0; x < NW; ++x) {
-          const uint64_t m = nse[x];
-          lo[u][x] = (uint32_t)m;
-          hi[u][x] = (uint32_t)(m >> 32);
+          for (int x = 0; x < NW; ++x) {
+            const uint64_t m = nse[x];
+            lo[u][x] = (uint32_t)m;
+            hi[u][x] = (uint32_t)(m >> 32);
+          }
+          one = nse[NW + sw];
         }
-        own[u] = (nse[NW + sw] & sbit) ? w[u] : 0;  // v is this net's only pin in s
+        own[u] = (one & sbit) ? w[u] : 0;  // v is this net's only pin in s
       }
     }
 #pragma unroll
@@ -162,78 +171,199 @@ __device__ __forceinline__ void vertex_conn(const int32_t *__restrict__ inc, int
   else conn_accumulate<G, UNIT>(inc, q0, q1, stride, nw, ns, lg, s, conn, benefit);
 }
 
-// ---- bit-sliced counts (unit net weights, k <= 64) ----
-// conn(v, b) for all 64 blocks is kept in nine 64-bit planes: plane p holds bit p of every
-// block's count (a non-hub vertex has at most 256 incident nets, so nine bits suffice).  Adding a
-// net's mask is a carry-save step over the planes.
+// ---- bit-sliced counts (unit net weights) ----
+// conn(v, b) for all blocks is kept in N bit planes of HW 32-bit words (HW = 1, 2, 4 for k <= 32, 64,
+// 128): bit b of plane p is bit p of block b's count.  These passes are bound by vector instructions
+// (four cycles each) before the gathers, so the masks of four nets enter through a tree of full adders
+// (three instructions on a word: two XORs and a bit select), which is 23 instructions per word and four
+// nets with nine planes; rippling each mask through the planes took 72.
 
-__device__ __forceinline__ void plane_add(uint64_t pl[9], uint64_t c) {
+// p + a + b: the sum bit stays in p, the carry is returned
+__device__ __forceinline__ uint32_t full_add(uint32_t &p, uint32_t a, uint32_t b) {
+  const uint32_t x = p ^ a, c = (x & b) | (~x & p);
+  p = x ^ b;
+  return c;
+}
+
+template <int N>
+__device__ __forceinline__ void planes_add4(uint32_t (&pl)[N], uint32_t m0, uint32_t m1, uint32_t m2, uint32_t m3) {
+  const uint32_t c0 = full_add(pl[0], m0, m1), c1 = full_add(pl[0], m2, m3);
+  uint32_t d = full_add(pl[1], c0, c1);
 #pragma unroll
-  for (int p = 0; p < 9; ++p) {
-    const uint64_t t = pl[p] & c;
-    pl[p] ^= c;
-    c = t;
+  for (int p = 2; p < N; ++p) {
+    const uint32_t t = pl[p] & d;
+    pl[p] ^= d;
+    d = t;
   }
 }
 
-// Lane lg of a group of G lanes takes incidences q0 + lg, q0 + lg + G, ... (four in flight) and
-// accumulates their masks into pl; benefit counts the nets where s is marked as holding one pin.
-template <int G>
-__device__ __forceinline__ void planes_accumulate(const int32_t *__restrict__ inc, int64_t q0, int64_t q1,
-                                                  const uint64_t *__restrict__ ns, int lg, uint64_t sbit,
-                                                  uint64_t pl[9], int32_t &benefit) {
-  int64_t q = q0 + lg;
-  for (; q + 3 * G < q1; q += 4 * G) {
-    const int32_t e0 = inc[q], e1 = inc[q + G], e2 = inc[q + 2 * G], e3 = inc[q + 3 * G];
-    const uint64_t m0 = ns[(int64_t)e0 * 2], m1 = ns[(int64_t)e1 * 2], m2 = ns[(int64_t)e2 * 2],
-                   m3 = ns[(int64_t)e3 * 2];
-    const uint64_t o0 = ns[(int64_t)e0 * 2 + 1], o1 = ns[(int64_t)e1 * 2 + 1], o2 = ns[(int64_t)e2 * 2 + 1],
-                   o3 = ns[(int64_t)e3 * 2 + 1];
-    plane_add(pl, m0);
-    plane_add(pl, m1);
-    plane_add(pl, m2);
-    plane_add(pl, m3);
-    benefit += ((o0 & sbit) != 0) + ((o1 & sbit) != 0) + ((o2 & sbit) != 0) + ((o3 & sbit) != 0);
-  }
-  for (; q < q1; q += G) {
-    const int32_t e = inc[q];
-    plane_add(pl, ns[(int64_t)e * 2]);
-    benefit += (ns[(int64_t)e * 2 + 1] & sbit) != 0;
-  }
-}
-
-// Sums the planes and benefits of the G lanes of each group (butterfly over the group, ripple
-// adds of the bit-sliced numbers); every lane of the wave calls it.
-template <int G>
-__device__ __forceinline__ void planes_combine(uint64_t pl[9], int32_t &benefit) {
+// Incidences q, q + step, ... below q1 of one lane (four in flight, at most 2^N - 1 in all): the nets'
+// masks into the planes; benefit counts the nets where s is marked as holding one pin.
+template <int HW, int N>
+__device__ __forceinline__ void planes_accumulate(const int32_t *__restrict__ inc, int64_t q, int64_t q1, int64_t step,
+                                                  const uint64_t *__restrict__ ns, int32_t s, uint32_t (&pl)[HW][N],
+                                                  int32_t &benefit) {
+  const uint4 *words = reinterpret_cast<const uint4 *>(ns);  // HW <= 2: mask, one; HW == 4: mask, then one
+  const uint32_t sbit = 1u << (s & 31);
+  const int sw = s >> 5;
+  for (; q < q1; q += 4 * step) {
+    int32_t e[4];
+    uint4 a[4], b[4];
 #pragma unroll
-  for (int o = 1; o < G; o <<= 1) {
-    uint64_t carry = 0ull;
+    for (int u = 0; u < 4; ++u) e[u] = q + u * step < q1 ? inc[q + u * step] : -1;
 #pragma unroll
-    for (int p = 0; p < 9; ++p) {
-      const uint64_t x = pl[p], y = __shfl_xor(pl[p], o, G);
-      pl[p] = x ^ y ^ carry;
-      carry = (x & y) | (carry & (x ^ y));
+    for (int u = 0; u < 4; ++u) {
+      a[u] = make_uint4(0u, 0u, 0u, 0u);
+      b[u] = make_uint4(0u, 0u, 0u, 0u);
+      if (e[u] >= 0) {
+        if (HW == 4) {
+          a[u] = words[(int64_t)e[u] * 2];
+          b[u] = words[(int64_t)e[u] * 2 + 1];
+        } else {
+          a[u] = words[e[u]];
+        }
+      }
     }
-    benefit += __shfl_xor(benefit, o, G);
+    planes_add4(pl[0], a[0].x, a[1].x, a[2].x, a[3].x);
+    if (HW >= 2) planes_add4(pl[HW >= 2 ? 1 : 0], a[0].y, a[1].y, a[2].y, a[3].y);
+    if (HW == 4) {
+      planes_add4(pl[HW == 4 ? 2 : 0], a[0].z, a[1].z, a[2].z, a[3].z);
+      planes_add4(pl[HW == 4 ? 3 : 0], a[0].w, a[1].w, a[2].w, a[3].w);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const uint32_t o = HW == 1   ? a[u].z
+                         : HW == 2 ? (sw ? a[u].w : a[u].z)
+                                   : (sw & 2 ? (sw & 1 ? b[u].w : b[u].z) : (sw & 1 ? b[u].y : b[u].x));
+      benefit += (o & sbit) != 0u;
+    }
   }
 }
 
-// Lowest block of largest count among the blocks of mask (counts of zero included): the mask is
-// narrowed from the top plane down.  Returns the count, or -1 when mask is empty.
-__device__ __forceinline__ int32_t planes_best(const uint64_t pl[9], uint64_t mask, int32_t &block) {
-  block = 0;
-  if (!mask) return -1;
+// a += b over N planes, the last carry dropped (the caller's counts fit)
+template <int N>
+__device__ __forceinline__ void planes_sum(uint32_t (&a)[N], const uint32_t (&b)[N]) {
+  uint32_t c = 0u;
 #pragma unroll
-  for (int p = 8; p >= 0; --p) {
-    const uint64_t x = mask & pl[p];
-    if (x) mask = x;
+  for (int p = 0; p < N; ++p) {
+    uint32_t x = a[p];
+    c = full_add(x, b[p], c);
+    a[p] = x;
   }
-  block = __ffsll((unsigned long long)mask) - 1;
+}
+
+// Sums the planes of the lanes of each aligned group of GL lanes.  Every lane ends with one word of the
+// group's sums, out: lane bits 0.. choose it (bit 0 the upper or lower half of the words, bit 1 the
+// half of that half), so each of the first log2(HW) exchanges moves only the words the partner keeps.
+// Returns the word's index.  benefit is summed too.  M >= N planes hold the sums.
+template <int GL, int HW, int N, int M>
+__device__ __forceinline__ int planes_combine(uint32_t (&pl)[HW][N], uint32_t (&out)[M], int32_t &benefit, int lane) {
+  uint32_t w[HW][M];
+#pragma unroll
+  for (int x = 0; x < HW; ++x)
+#pragma unroll
+    for (int p = 0; p < M; ++p) w[x][p] = p < N ? pl[x][p] : 0u;
+  int word = 0, o = 1;
+  int have = HW;  // words still held (compile-time after unrolling)
+#pragma unroll
+  for (int step = 0; step < 2; ++step) {
+    if (have == 1 || o >= GL) break;
+    const int half = have / 2;
+    const bool up = (lane & o) != 0;  // keeps the upper half
+#pragma unroll
+    for (int x = 0; x < HW / 2; ++x) {
+      if (x >= half) break;
+      uint32_t mine[M], theirs[M];
+#pragma unroll
+      for (int p = 0; p < M; ++p) {
+        const uint32_t lo = w[x][p], hi = w[x + half < HW ? x + half : 0][p];
+        mine[p] = up ? hi : lo;
+        theirs[p] = (uint32_t)__shfl_xor((int)(up ? lo : hi), o, GL);
+      }
+      planes_sum<M>(mine, theirs);
+#pragma unroll
+      for (int p = 0; p < M; ++p) w[x][p] = mine[p];
+    }
+    word = 2 * word + (up ? 1 : 0);
+    benefit += __shfl_xor(benefit, o, GL);
+    have = half;
+    o <<= 1;
+  }
+#pragma unroll
+  for (int r = 0; r < 6; ++r) {
+    if (o >= GL) break;
+    uint32_t theirs[M];
+#pragma unroll
+    for (int p = 0; p < M; ++p) theirs[p] = (uint32_t)__shfl_xor((int)w[0][p], o, GL);
+    planes_sum<M>(w[0], theirs);
+    benefit += __shfl_xor(benefit, o, GL);
+    o <<= 1;
+  }
+#pragma unroll
+  for (int p = 0; p < M; ++p) out[p] = w[0][p];
+  return word;
+}
+
+// Lowest block of largest count among the blocks of mask in one word (counts of zero included): the
+// mask is narrowed from the top plane down.  Returns the count, -1 when the mask is empty.
+template <int M>
+__device__ __forceinline__ int32_t planes_best(const uint32_t (&pl)[M], uint32_t mask, int32_t &bit) {
+  bit = 0;
+  if (!mask) return -1;
   int32_t c = 0;
 #pragma unroll
-  for (int p = 0; p < 9; ++p) c |= (int32_t)((pl[p] >> block) & 1ull) << p;
+  for (int p = M - 1; p >= 0; --p) {
+    const uint32_t x = mask & pl[p];
+    mask = x ? x : mask;
+    c |= x ? 1 << p : 0;
+  }
+  bit = __ffs((int)mask) - 1;
   return c;
+}
+
+// blocks with a nonzero count
+template <int M>
+__device__ __forceinline__ uint32_t planes_any(const uint32_t (&pl)[M]) {
+  uint32_t any = 0u;
+#pragma unroll
+  for (int p = 0; p < M; ++p) any |= pl[p];
+  return any;
+}
+
+// The best block of a vertex whose counts a group of G lanes holds in pl: valid(word index, counts) is
+// the mask of allowed blocks of a word.  Every lane of the group returns the count (-1: none) and block
+// (lowest on ties); benefit becomes the group's sum.
+template <int G, int HW, int N, typename Valid>
+__device__ __forceinline__ int32_t planes_target(uint32_t (&pl)[HW][N], int32_t &benefit, int lane, int32_t &block,
+                                                 Valid valid) {
+  int32_t bestc = -1, bestb = 0;
+  if (G == 1) {
+#pragma unroll
+    for (int x = 0; x < HW; ++x) {
+      int32_t b;
+      const int32_t c = planes_best<N>(pl[x], valid(x, pl[x]), b);
+      if (c > bestc) {
+        bestc = c;
+        bestb = 32 * x + b;
+      }
+    }
+  } else {
+    static_assert(G == 1 || G >= HW, "a lane for every word");
+    uint32_t w[N];
+    const int x = planes_combine<G, HW, N, N>(pl, w, benefit, lane);
+    bestc = planes_best<N>(w, valid(x, w), bestb);
+    bestb += 32 * x;
+#pragma unroll
+    for (int o = 1; o < HW; o <<= 1) {  // the lanes that hold the other words
+      const int32_t oc = __shfl_xor(bestc, o, G), ob = __shfl_xor(bestb, o, G);
+      if (oc > bestc || (oc == bestc && ob < bestb)) {
+        bestc = oc;
+        bestb = ob;
+      }
+    }
+  }
+  block = bestb;
+  return bestc;
 }
 
 }  // namespace jet

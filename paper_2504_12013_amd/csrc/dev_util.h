@@ -44,20 +44,18 @@ __device__ __forceinline__ T block_excl_scan(T x, T *smem, T *total) {
   T inc = wave_incl_scan(x);
   if (l == kWave - 1) smem[w] = inc;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    T run = 0;
-    for (int i = 0; i < NW; ++i) {
-      T s = smem[i];
-      smem[i] = run;
-      run += s;
-    }
-    smem[NW] = run;
+  // every thread sums the wave totals itself: one thread walking them in LDS was a chain of 2 NW
+  // dependent accesses (2 us for 1,024 threads)
+  T off = 0, tot = 0;
+#pragma unroll
+  for (int i = 0; i < NW; ++i) {
+    const T s = smem[i];
+    off += i < w ? s : 0;
+    tot += s;
   }
+  *total = tot;
   __syncthreads();
-  T res = inc - x + smem[w];
-  *total = smem[NW];
-  __syncthreads();
-  return res;
+  return inc - x + off;
 }
 
 // read a 32-bit value held by lane `src` (wave-uniform src) into every lane

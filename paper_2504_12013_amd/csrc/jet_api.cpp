@@ -82,7 +82,7 @@ int map_device_error(Ctx &c, int32_t err, int32_t arg) {
 int read_status(Ctx &c) {
   HIP_OR_FAIL(&c, hipMemcpyAsync(c.hst, c.st, status_bytes(c), hipMemcpyDeviceToHost, c.stream));
   HIP_OR_FAIL(&c, hipStreamSynchronize(c.stream));
-  for (int i = 0; i < jet::kKm1Slots; ++i) c.hst->km1 += c.hst->km1_slot[i];  // the metric (host view)
+  for (int i = 0; i < jet::kKm1Slots; ++i) c.hst->km1 += c.hst->slot[i].km1;  // the metric (host view)
   if (c.hst->err != 0) {
     const int32_t err = c.hst->err, arg = c.hst->err_arg;
     (void)hipMemsetAsync(&c.st->err, 0, 2 * sizeof(int32_t), c.stream);
@@ -180,7 +180,8 @@ void free_ctx(Ctx &c) {
   void *ptrs[] = {c.off,  c.pins, c.nw,   c.vw,        c.voff, c.inc,   c.sumw, c.adj,    c.chunks,    c.pnet, c.mid_nets,
                   c.big_nets, c.phi, c.phi16, c.ns, c.rec, c.inm, c.rg, c.lockstamp, c.best, c.moves, c.rb_keys,
                   c.rb_target, c.st, c.scan_tmp, c.ovf_list, c.ovf_off, c.ovf_ka, c.ovf_kb, c.ovf_ma,
-                  c.ovf_mb, c.hubs, c.mvfrom, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.rb_hacc,
+                  c.ovf_mb, c.hubs, c.mvfrom, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.hub_rows,
+                  c.hub_done,
                   c.rb_keys2, c.rb_gw, c.rb_gc};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -282,6 +283,7 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
     std::vector<int32_t> hh;
     c.n_low = 0;
     c.p_low = 0;
+    c.max_low_degree = 0;
     for (int32_t v = 0; v < n; ++v) {
       const int64_t d = hvoff[v + 1] - hvoff[v];
       if (d > jet::kHubDegree) {
@@ -289,15 +291,18 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
       } else {
         c.n_low += 1;
         c.p_low += d;
+        c.max_low_degree = std::max(c.max_low_degree, d);
       }
     }
     c.nhubs = (int32_t)hh.size();
     HIP_OR_FAIL(&c, dalloc(&c.hubs, hh.size()));
     HIP_OR_FAIL(&c, dalloc(&c.rb_hlist, hh.size()));
-    HIP_OR_FAIL(&c, dalloc(&c.rb_hacc, hh.size() * (size_t)(c.k + 1)));
-    HIP_OR_FAIL(&c, hipMemsetAsync(c.rb_hacc, 0, sizeof(int32_t) * hh.size() * (size_t)(c.k + 1), c.stream));
-    if (!hh.empty())
+    HIP_OR_FAIL(&c, dalloc(&c.hub_rows, hh.empty() ? 0 : (size_t)jet::kHubGrid * (size_t)(c.k + 1)));
+    HIP_OR_FAIL(&c, dalloc(&c.hub_done, hh.size()));
+    if (!hh.empty()) {
       HIP_OR_FAIL(&c, hipMemcpyAsync(c.hubs, hh.data(), sizeof(int32_t) * hh.size(), hipMemcpyHostToDevice, c.stream));
+      HIP_OR_FAIL(&c, hipMemsetAsync(c.hub_done, 0, sizeof(int32_t) * hh.size(), c.stream));
+    }
   }
   // net schedule: chunks of consecutive small nets (<= 64 pins in total), medium and big net lists
   std::vector<int4> chunks;

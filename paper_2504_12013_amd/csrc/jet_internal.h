@@ -19,29 +19,34 @@ constexpr int kMediumSmall = 256;  // medium nets up to this size use a smaller 
 constexpr int kLaneDegree = 32;    // moves with more incident nets are applied by many threads
 constexpr int kBigCap = 4096;      // larger nets: one 256-thread workgroup, up to kBigCap candidates in LDS
 constexpr int kMaxSortedDegree = 8192;  // longer incidence lists are radix-sorted in global scratch
-constexpr int kHubDegree = 256;        // vertices with more incident nets get a whole workgroup
+constexpr int kHubDegree = 256;        // vertices with more incident nets take whole workgroups (k_hub.hip)
 
 // Device status block, read back by the host after each phase that needs a decision.
 constexpr int kKm1Slots = 64;
+// Counters that every workgroup of a pass adds to, spread over slots a cache line apart.  Atomics on one
+// address are served one after the other, about 10 ns each: the three counters of a gain pass over
+// 2,048 workgroups, all on one line, took 50 us; over 64 lines they take less than one.
+struct alignas(128) CtrSlot {
+  long long km1;      // metric changes since the last fold
+  long long n_cand;   // |M| of the candidate pass
+  long long inc_low, inc_hub;  // incidences scanned by the candidate pass (non-hub / hub vertices)
+  long long ab_inc;   // incidences of candidates scanned by the graph afterburner
+  long long rb_inc;   // incidences scanned by the rebalancing gain pass
+  long long rb_elig;  // vertices it examined in full
+  long long rb_ent;   // order-key entries it wrote
+};
 // A union context refines many hypergraphs with the same k at once (the batch): vertices and nets
 // are concatenated, and every per-block quantity is kept per segment hg * k + b.
 constexpr int kMaxH = 4096;    // hypergraphs in one union context
 constexpr int kMaxSeg = 16384; // segments (hypergraph, block) of one context
 
 struct DevStatus {
-  int64_t km1;            // current metric, maintained incrementally: km1 + sum of km1_slot
-  int64_t km1_slot[kKm1Slots];  // metric changes spread over slots (no single hot address)
-  int32_t n_cand;         // |M| of the last candidate pass
+  CtrSlot slot[kKm1Slots];
+  int64_t km1;            // current metric, maintained incrementally: km1 + sum over the slots
   int32_t n_moves;        // entries in the move list
   int32_t n_ovf;          // large nets handed to the global-scratch afterburner this iteration
   int32_t n_bigmv;        // listed moves with more than kLaneDegree incident nets
-  int64_t inc_low;        // incidences scanned by the last candidate pass (non-hub / hub vertices)
-  int64_t inc_hub;
-  int64_t ab_inc;         // incidences of candidates scanned by the graph afterburner
   int64_t mv_inc;         // incident nets of the listed moves (sum of their degrees)
-  int64_t rb_inc;         // incidences scanned by the last rebalancing gain pass
-  int64_t rb_elig;        // vertices it examined in full
-  int64_t rb_ent;         // order-key entries it wrote
   int32_t rb_nlist;       // vertices on the rebalancing candidate list of the round
   int32_t rb_nhub;        // hub vertices on the hub candidate list of the round
   int32_t rb_nseg;        // union: overloaded segments of the round (listed in rb_seg)
@@ -191,9 +196,12 @@ __device__ __forceinline__ void rg_add(const RgSink &s, uint32_t slot, int32_t v
   atomicAdd(&s.base[(size_t)(slot % (uint32_t)s.copies) * (size_t)s.n + (size_t)v], d);
 }
 
-// adds a metric change to one of the slots (chosen by the caller, e.g. from the block index)
+// adds to a counter of one of the slots (chosen by the caller, e.g. from the block index)
+__device__ __forceinline__ void count_add(DevStatus *st, uint32_t slot, long long CtrSlot::*field, long long d) {
+  if (d != 0) atomicAdd((unsigned long long *)&(st->slot[slot % kKm1Slots].*field), (unsigned long long)d);
+}
 __device__ __forceinline__ void add_km1(DevStatus *st, uint32_t slot, int64_t d) {
-  if (d != 0) atomicAdd((unsigned long long *)&st->km1_slot[slot % kKm1Slots], (unsigned long long)d);
+  count_add(st, slot, &CtrSlot::km1, d);
 }
 // union: the metric change of hypergraph hg
 __device__ __forceinline__ void add_km1_hg(DevStatus *st, int32_t hg, int64_t d) {
@@ -339,9 +347,10 @@ struct Ctx {
   int32_t nmid_large = 0;       // leading entries of mid_nets with |e| > kMediumSmall
   int32_t *big_nets = nullptr;  // nets with |e| > kMediumNet, largest first
   int32_t nbig = 0;
-  int32_t nbig_over = 0;
+  int32_t nbig_over = 0;        // leading entries of big_nets with |e| > kBigCap
   int32_t *hubs = nullptr;      // vertices with more than kHubDegree incident nets
-  int32_t nhubs = 0;        // leading entries of big_nets with |e| > kBigCap
+  int32_t nhubs = 0;
+  int32_t *hub_done = nullptr;  // [nhubs] workgroups of the running hub pass that stored their sums (zero between)
   int2 *ovf_list = nullptr;     // [nbig_over] (index into big_nets, net) needing the scratch path
   int64_t *ovf_off = nullptr;   // [nbig_over + 1] scratch offsets: 2 |e| event slots per net
   unsigned long long *ovf_ka = nullptr, *ovf_kb = nullptr;  // event keys (ping-pong)
@@ -363,8 +372,8 @@ struct Ctx {
   int32_t *bigmv = nullptr;   // [n] positions in the move list of the moves counted by n_bigmv
   int32_t *rb_list = nullptr; // [n] non-hub vertices that may move in the current rebalancing round
   int32_t *rb_slot = nullptr; // [n] the entry slot of each listed vertex (its block's region)
-  int32_t *rb_hlist = nullptr; // [nhubs] hub vertices that may move in the current rebalancing round
-  int32_t *rb_hacc = nullptr;  // [(k + 1) * nhubs] their connectivity and benefit sums, block-major (zero between rounds)
+  int32_t *rb_hlist = nullptr; // [nhubs] hubs (indices into hubs) that may move in the current rebalancing round
+  int32_t *hub_rows = nullptr; // [kHubGrid * (k + 1)] sums of the workgroups that share a hub in the running hub pass
   int64_t *lstat = nullptr;   // [5] level statistics scratch
   float *tau_io = nullptr;    // [17] learned temperature: features in, temperature out
 
@@ -418,11 +427,16 @@ struct Ctx {
   // instrumentation
   bool prof = false;
   int64_t n_low = 0, p_low = 0;  // vertices / incidences handled by the non-hub candidate kernel
+  int64_t max_low_degree = 0;    // largest degree among them
   uint32_t prof_mask = 0xffffffffu;       // families marked while profiling is on
   double wall_khz = 100000.0;             // device wall clock rate
 
   std::string last_error;
 };
+
+// Unit net weights: one lane per vertex (the candidate and rebalancing gain passes) instead of eight.
+// One lane is right while the vertices are light (mean degree below lane_degree).
+inline bool light_lanes(const Ctx &c) { return c.p_low < (int64_t)c.lane_degree * c.n_low; }
 
 // the union view of a context for the kernels
 inline Union union_of(const Ctx &c) {
@@ -496,6 +510,12 @@ hipError_t launch_loop_init(Ctx &c);
 // zeroes the candidate bits where the candidate kernel of this context only sets them
 hipError_t launch_clear_candidate_bits(Ctx &c);
 hipError_t launch_fill_u32(Ctx &c, uint32_t *p, int64_t count, uint32_t value, const LoopCtl *lc, int32_t want);
+
+// k_hub.hip: vertices with more than kHubDegree incident nets
+constexpr int kHubGrid = 2048;  // workgroups of a hub pass at most
+hipError_t launch_candidates_hub(Ctx &c, const int32_t *part, int32_t locked_stamp, const uint8_t *lock_bytes,
+                                 int32_t tau_q, const LoopCtl *lc);
+hipError_t launch_rb_hubs(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *lc);
 
 // k_graph.hip: graph-specialised afterburner (every net of two pins)
 hipError_t launch_build_adj(Ctx &c);

@@ -87,7 +87,7 @@ __global__ __launch_bounds__(kGraphBlock) void k_ab_graph(const int32_t *__restr
   if (threadIdx.x == 0) {
     unsigned long long t = 0ull;
     for (int i = 0; i < kGraphBlock / kWave; ++i) t += wsum[i];
-    if (t) atomicAdd((unsigned long long *)&st->ab_inc, t);
+    count_add(st, blockIdx.x, &CtrSlot::ab_inc, (long long)t);
   }
 }
 

@@ -24,27 +24,10 @@ namespace {
 // Every unlocked vertex v of block s picks the adjacent foreign block t of largest conn (lowest ID
 // on ties), i.e. of largest gain conn[t] - aff, and is a candidate iff
 //     65536 gain + tau_q aff >= 0        (gain >= -tau aff with tau = tau_q / 65536).
-// Vertices with at most kHubDegree incident nets: G lanes per vertex (conn.h).  Hubs: one
-// workgroup per vertex (k_candidates_hub).
+// Vertices with at most kHubDegree incident nets: G lanes per vertex (conn.h).  Hubs: k_hub.hip.
 
-__device__ __forceinline__ void finish_candidate(int32_t v, int32_t s, int32_t bestc, int32_t bestb, int32_t sumw_v,
-                                                 int32_t benefit, int32_t tau_q, uint64_t *__restrict__ rec,
-                                                 bool *cand_out) {
-  bool cand = false;
-  uint64_t r;
-  if (bestc > 0) {
-    const int32_t aff = sumw_v - benefit;
-    const int32_t g = bestc - aff;
-    cand = 65536ll * (int64_t)g + (int64_t)tau_q * (int64_t)aff >= 0;
-    r = pack_rec(g, bestb, s);
-  } else {
-    r = pack_rec(0, 0xff, s);
-  }
-  rec[v] = r;
-  *cand_out = cand;
-}
-
-template <int G, bool UNIT>
+// With net weights.
+template <int G>
 __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw,
@@ -105,7 +88,7 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
 #pragma unroll
     for (int j = 0; j < 8; ++j) conn[j] = 0;
     int32_t benefit = 0;
-    if (!skip) vertex_conn<G, UNIT>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
+    if (!skip) vertex_conn<G, false>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
     int32_t bestc = 0, bestb = INT32_MAX;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -139,18 +122,18 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
     __syncthreads();
   }
   if (threadIdx.x == 0) {
-    if (ncand) atomicAdd(&st->n_cand, ncand);
-    if (scanned) atomicAdd((unsigned long long *)&st->inc_low, scanned);
+    count_add(st, blockIdx.x, &CtrSlot::n_cand, ncand);
+    count_add(st, blockIdx.x, &CtrSlot::inc_low, (long long)scanned);
   }
 }
 
-// Unit net weights and k <= 64: G lanes per vertex (G = 1 on light levels), each accumulating
-// the bit-sliced counts of its share of the incident nets (conn.h), summed over the group at the
-// end.  The best target is the lowest block of largest count among the adjacent blocks other than
-// s.  Same records and flags as k_candidates (exact integer counts, same tie rule), with no
-// per-net shuffles and no barriers.  With G = 1 a wave writes its two candidate words itself;
-// otherwise it ORs its bits into a word cleared before the launch.
-template <int G>
+// Unit net weights: G lanes per vertex (G = 1 on light levels), each accumulating the bit-sliced
+// counts of its share of the incident nets (conn.h), summed over the group at the end.  The best
+// target is the lowest block of largest count among the adjacent blocks other than s.  Same records
+// and flags as k_candidates (exact integer counts, same tie rule), with no per-net shuffles and no
+// barriers.  With G = 1 a wave writes its two candidate words itself; otherwise it ORs its bits into
+// a word cleared before the launch.
+template <int G, int HW, int N>
 __global__ __launch_bounds__(256) void k_candidates_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw, const int32_t *__restrict__ lockstamp,
@@ -212,18 +195,13 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
       const bool locked = lock_bytes ? (lock_bytes[v] != 0) : (lockstamp[v] == ls);
       skip = locked || hub || off;
     }
-    uint64_t pl[9];
-#pragma unroll
-    for (int p = 0; p < 9; ++p) pl[p] = 0ull;
+    uint32_t pl[HW][N] = {};
     int32_t benefit = 0;
-    const uint64_t sbit = 1ull << s;
-    if (!skip) planes_accumulate<G>(inc, q0, q1, ns, lg, sbit, pl, benefit);
-    planes_combine<G>(pl, benefit);
-    uint64_t any = 0ull;
-#pragma unroll
-    for (int p = 0; p < 9; ++p) any |= pl[p];
-    int32_t bestb;
-    const int32_t bestc = planes_best(pl, any & ~sbit, bestb);  // adjacent blocks other than s
+    if (!skip) planes_accumulate<HW, N>(inc, q0 + lg, q1, G, ns, s, pl, benefit);
+    int32_t bestb;  // adjacent blocks other than s
+    const int32_t bestc = planes_target<G, HW, N>(pl, benefit, l, bestb, [&](int x, const uint32_t (&w)[N]) {
+      return planes_any<N>(w) & ~(x == (s >> 5) ? 1u << (s & 31) : 0u);
+    });
     bool cand = false;
     if (valid && !hub && lg == 0) {
       finish_candidate((int32_t)v, s, skip ? 0 : (bestc > 0 ? bestc : 0), bestb, sumw[v], benefit, tq, rec, &cand);
@@ -257,100 +235,8 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
       ts += wscan[i];
       tc += wcand[i];
     }
-    if (tc) atomicAdd(&st->n_cand, tc);
-    if (ts) atomicAdd((unsigned long long *)&st->inc_low, ts);
-  }
-}
-
-// max over 64 lanes of a 64-bit key
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, o, kWave);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), o, kWave);
-    const unsigned long long y = ((unsigned long long)hi << 32) | lo;
-    x = y > x ? y : x;
-  }
-  return x;
-}
-
-// One 256-thread workgroup per hub vertex: the incident nets are split over 256/G lane groups,
-// whose per-block sums are added in LDS.  Runs after k_candidates (which leaves hub bits clear).
-template <int G, bool UNIT>
-__global__ __launch_bounds__(256) void k_candidates_hub(
-    const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
-    const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw,
-    const int32_t *__restrict__ lockstamp, int32_t locked_stamp, const uint8_t *__restrict__ lock_bytes,
-    const int32_t *__restrict__ hubs, int32_t nhubs, int32_t k, int32_t tau_q, uint64_t *__restrict__ rec,
-    uint32_t *__restrict__ inm, DevStatus *st, const LoopCtl *lc, Union u) {
-  JET_GATE(lc, kPhJet);
-  if (lc && !u.lcs) {
-    locked_stamp = lc->stamp - 1;
-    tau_q = lc->tau_q;
-  }
-  constexpr int NG = 256 / G;
-  __shared__ int32_t cs[NG][8 * G];
-  __shared__ int32_t bsum[NG];
-  __shared__ unsigned long long wbest[4];
-  const int tid = threadIdx.x, gi = tid / G, lg = tid % G;
-  int32_t ncand = 0;
-  unsigned long long scanned = 0ull;
-  for (int32_t hi = blockIdx.x; hi < nhubs; hi += gridDim.x) {  // block-uniform trip count
-  const int32_t v = hubs[hi];
-  const int32_t s = part[v];
-  int32_t ls = locked_stamp, tq = tau_q;
-  bool off = false;
-  if (u.lcs) {  // the vertex's own hypergraph decides (union)
-    const LoopCtl &h = u.lcs[u.vhg[v]];
-    off = h.phase != kPhJet;
-    ls = h.stamp - 1;
-    tq = h.tau_q;
-  }
-  const bool locked = off || (lock_bytes ? (lock_bytes[v] != 0) : (lockstamp[v] == ls));
-  if (locked) {
-    if (tid == 0) rec[v] = pack_rec(0, 0xff, s);
-    continue;
-  }
-  int32_t conn[8];
-#pragma unroll
-  for (int j = 0; j < 8; ++j) conn[j] = 0;
-  int32_t benefit = 0;
-  if (G == 1) conn_accumulate_strided<G, UNIT>(inc, voff[v] + gi, voff[v + 1], NG, nw, ns, lg, s, conn, benefit);
-  else conn_accumulate<G, UNIT>(inc, voff[v] + (int64_t)gi * G, voff[v + 1], (int64_t)NG * G, nw, ns, lg, s, conn,
-                                benefit);
-#pragma unroll
-  for (int j = 0; j < 8; ++j) cs[gi][lg * 8 + j] = conn[j];
-  if ((s >> 3) == lg) bsum[gi] = benefit;
-  __syncthreads();
-  unsigned long long key = 0;
-  if (tid < k && tid != s) {
-    int32_t tot = 0;
-    for (int g = 0; g < NG; ++g) tot += cs[g][tid];
-    if (tot > 0) key = ((unsigned long long)(uint32_t)tot << 32) | (uint32_t)(0xffffffffu - (uint32_t)tid);
-  }
-  key = wave_max_u64(key);
-  if (lane_id() == 0) wbest[tid / kWave] = key;
-  __syncthreads();
-  if (tid == 0) {
-    unsigned long long bk = wbest[0];
-    for (int w = 1; w < 4; ++w) bk = wbest[w] > bk ? wbest[w] : bk;
-    int32_t ben = 0;
-    for (int g = 0; g < NG; ++g) ben += bsum[g];
-    const int32_t bestc = (int32_t)(uint32_t)(bk >> 32);
-    const int32_t bestb = (int32_t)(0xffffffffu - (uint32_t)bk);
-    bool cand = false;
-    finish_candidate(v, s, bestc, bestb, sumw[v], ben, tq, rec, &cand);
-    if (cand) {
-      atomicOr(&inm[v >> 5], 1u << (v & 31));
-      ncand += 1;
-    }
-    scanned += (unsigned long long)(voff[v + 1] - voff[v]);
-  }
-  __syncthreads();  // LDS reused by the next hub
-  }  // hub loop
-  if (tid == 0) {
-    if (ncand) atomicAdd(&st->n_cand, ncand);
-    if (scanned) atomicAdd((unsigned long long *)&st->inc_hub, scanned);
+    count_add(st, blockIdx.x, &CtrSlot::n_cand, tc);
+    count_add(st, blockIdx.x, &CtrSlot::inc_low, (long long)ts);
   }
 }
 
@@ -1319,6 +1205,7 @@ __device__ __forceinline__ void recount_nets(const int64_t *__restrict__ off, co
 // kApplyLanes-th incident net of a move with few nets, so a move's chain of dependent atomics is
 // that many times shorter.
 constexpr int kApplyLanes = 8;
+constexpr unsigned kWeightBlocks = 64;  // workgroups that sum the block weights of a list
 template <int NW, typename T>
 __global__ __launch_bounds__(kApplyBlock) void k_apply(
     const int4 *__restrict__ moves, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
@@ -1355,7 +1242,17 @@ __global__ __launch_bounds__(kApplyBlock) void k_apply(
   // the others (a range crossing into the next hypergraph) straight into their segments.
   const int lg = threadIdx.x % kApplyLanes;
   const bool un = u.vhg != nullptr;
-  int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kApplyLanes, i1 = cnt;
+  // One hypergraph: the block weights of the whole list from kWeightBlocks workgroups, as the moves of a
+  // rebalancing round all leave the same few blocks and every workgroup would add to their counters.
+  if (!un && blockIdx.x < kWeightBlocks)
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < cnt; i += (int64_t)kWeightBlocks * blockDim.x) {
+      const int4 mv = moves[i];
+      atomicAdd(&dw[mv.y], (unsigned long long)(-(int64_t)mv.w));
+      atomicAdd(&dw[mv.z], (unsigned long long)mv.w);
+      atomicAdd(&dc[mv.y], -1);
+      atomicAdd(&dc[mv.z], 1);
+    }
+  int64_t i0 = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kApplyLanes, i1 = by_vertex || un ? cnt : 0;
   int64_t istep = (int64_t)gridDim.x * blockDim.x / kApplyLanes;
   int32_t home = 0;
   if (un) {
@@ -1371,20 +1268,20 @@ __global__ __launch_bounds__(kApplyBlock) void k_apply(
     const int64_t span = blockDim.x / kApplyLanes, steps = (cnt + span - 1) / span, per = (steps + 7) / 8;
     const int64_t x = blockIdx.x % 8;
     i0 = (x * per + blockIdx.x / 8) * span + threadIdx.x / kApplyLanes;
-    i1 = min((int64_t)cnt, (x + 1) * per * span);
+    i1 = by_vertex ? min((int64_t)cnt, (x + 1) * per * span) : 0;
     istep = (int64_t)(gridDim.x / 8) * span;
   }
   for (int64_t i = i0; i < i1; i += istep) {
     const int4 mv = moves[i];
     const int32_t hg = un ? (int32_t)u.vhg[mv.x] : 0;
     const bool local = !un || hg == home;
-    if (lg == 0) {
+    if (un && lg == 0) {
       if (local) {
         atomicAdd(&dw[mv.y], (unsigned long long)(-(int64_t)mv.w));
         atomicAdd(&dw[mv.z], (unsigned long long)mv.w);
         atomicAdd(&dc[mv.y], -1);
         atomicAdd(&dc[mv.z], 1);
-      } else {  // union: another hypergraph's segments
+      } else {  // another hypergraph's segments
         const int64_t sg = (int64_t)hg * k;
         atomicAdd((unsigned long long *)&st->bw[sg + mv.y], (unsigned long long)(-(int64_t)mv.w));
         atomicAdd((unsigned long long *)&st->bw[sg + mv.z], (unsigned long long)mv.w);
@@ -1450,10 +1347,7 @@ inline unsigned grid_for(int64_t work, int block, int64_t cap) {
 }
 
 
-// unit net weights, k <= 64: a group of lanes per vertex instead of one lane
-inline bool cand_groups(const Ctx &c) { return c.p_low >= (int64_t)c.lane_degree * c.n_low; }
-
-template <int G, bool UNIT>
+template <int G>
 hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const uint8_t *lock_bytes, int32_t tau_q,
                        const LoopCtl *lc) {
   constexpr int BLOCK = (G == 16) ? 512 : 256;
@@ -1461,48 +1355,55 @@ hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const 
   const unsigned grid = (unsigned)std::min<int64_t>(c.grid_cap, (c.n + VPB - 1) / VPB);
   // algorithmic bytes: per vertex part, lock, offsets, record, flag; per incidence the net ID, one
   // pin count and the net's connectivity mask (and its weight when weighted)
-  const double per_inc = 8.0 + (c.k + 7) / 8 + (UNIT ? 0.0 : 4.0);
+  const double per_inc = 8.0 + (c.k + 7) / 8 + (c.unit_nw ? 0.0 : 4.0);
   const int32_t want = lc ? (int32_t)kPhJet : (int32_t)kPhAny;
   int tok = prof_begin(c, kProfCandidates, lc, want);
-  // unit net weights, k <= 64: bit-sliced counts, one lane per vertex while the vertices are light
-  // (mean degree below lane_degree), eight otherwise
-  if (UNIT && c.k <= 64 && !cand_groups(c)) {
-    hipLaunchKernelGGL(k_candidates_bits<1>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 255) / 256)),
-                       dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
-  } else if (UNIT && c.k <= 64) {
+  // unit net weights: bit-sliced counts, one lane per vertex while the vertices are light (mean degree
+  // below lane_degree), eight otherwise; five planes where every count fits them
+  if (c.unit_nw) {
     // the groups OR their bits into cleared words: in the loop the selection leaves every word it
     // walks at zero (launch_clear_candidate_bits before the first iteration)
     if (!lc) {
       const hipError_t fe = launch_clear_candidate_bits(c);
       if (fe != hipSuccess) return fe;
     }
-    hipLaunchKernelGGL(k_candidates_bits<8>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 31) / 32)),
-                       dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                       lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
+    const bool few = c.max_low_degree < 32;
+    const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
+    auto go = [&](auto kernel, int64_t per_block) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + per_block - 1) / per_block)),
+                         dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
+                         lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
+    };
+    if (!light_lanes(c)) {
+      if (hw == 1) few ? go(k_candidates_bits<8, 1, 5>, 32) : go(k_candidates_bits<8, 1, 9>, 32);
+      else if (hw == 2) few ? go(k_candidates_bits<8, 2, 5>, 32) : go(k_candidates_bits<8, 2, 9>, 32);
+      else few ? go(k_candidates_bits<8, 4, 5>, 32) : go(k_candidates_bits<8, 4, 9>, 32);
+    } else {
+      if (hw == 1) few ? go(k_candidates_bits<1, 1, 5>, 256) : go(k_candidates_bits<1, 1, 9>, 256);
+      else if (hw == 2) few ? go(k_candidates_bits<1, 2, 5>, 256) : go(k_candidates_bits<1, 2, 9>, 256);
+      else few ? go(k_candidates_bits<1, 4, 5>, 256) : go(k_candidates_bits<1, 4, 9>, 256);
+    }
   } else
-    hipLaunchKernelGGL((k_candidates<G, UNIT>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
+    hipLaunchKernelGGL((k_candidates<G>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
                        c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc,
                        union_of(c));
   prof_end(c, tok, lc, want, 18.0 * c.n_low, per_inc);  // plus per_inc per scanned incidence (device count)
   if (c.nhubs > 0) {
     tok = prof_begin(c, kProfCandidatesHub, lc, want);
-    hipLaunchKernelGGL((k_candidates_hub<G, UNIT>), dim3((unsigned)std::min<int64_t>(c.grid_cap, c.nhubs)),
-                       dim3(256), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                       lock_bytes, c.hubs, c.nhubs, c.k, tau_q, c.rec, c.inm, c.st, lc, union_of(c));
+    const hipError_t he = launch_candidates_hub(c, part, locked_stamp, lock_bytes, tau_q, lc);
+    if (he != hipSuccess) return he;
     prof_end(c, tok, lc, want, 18.0 * (c.n - c.n_low), per_inc);
   }
   return hipGetLastError();
 }
 
-template <bool UNIT>
 hipError_t cand_dispatch(Ctx &c, const int32_t *part, int32_t locked_stamp, const uint8_t *lock_bytes,
                          int32_t tau_q, const LoopCtl *lc) {
-  if (c.k <= 8) return cand_launch<1, UNIT>(c, part, locked_stamp, lock_bytes, tau_q, lc);
-  if (c.k <= 16) return cand_launch<2, UNIT>(c, part, locked_stamp, lock_bytes, tau_q, lc);
-  if (c.k <= 32) return cand_launch<4, UNIT>(c, part, locked_stamp, lock_bytes, tau_q, lc);
-  if (c.k <= 64) return cand_launch<8, UNIT>(c, part, locked_stamp, lock_bytes, tau_q, lc);
-  return cand_launch<16, UNIT>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  if (c.k <= 8) return cand_launch<1>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  if (c.k <= 16) return cand_launch<2>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  if (c.k <= 32) return cand_launch<4>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  if (c.k <= 64) return cand_launch<8>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  return cand_launch<16>(c, part, locked_stamp, lock_bytes, tau_q, lc);
 }
 
 constexpr int kApplyGrid = 2048;
@@ -1511,15 +1412,13 @@ constexpr int kApplyGrid = 2048;
 
 // One launch clears the per-iteration counters (instead of a fill per field) of a launch outside the
 // loop.
-__global__ void k_reset_counters(DevStatus *st, int32_t what) {
-  if (threadIdx.x != 0) return;
+__global__ __launch_bounds__(kKm1Slots) void k_reset_counters(DevStatus *st, int32_t what) {
   if (what & kResetCandidates) {
-    st->n_cand = 0;
-    st->inc_low = 0;
-    st->inc_hub = 0;
-    st->ab_inc = 0;
-    st->n_ovf = 0;
+    CtrSlot &c = st->slot[threadIdx.x];
+    c.n_cand = c.inc_low = c.inc_hub = c.ab_inc = 0;
   }
+  if (threadIdx.x != 0) return;
+  if (what & kResetCandidates) st->n_ovf = 0;
   if (what & kResetMoves) {
     st->n_moves = 0;
     st->n_bigmv = 0;
@@ -1528,12 +1427,12 @@ __global__ void k_reset_counters(DevStatus *st, int32_t what) {
 }
 
 hipError_t launch_reset_counters(Ctx &c, int32_t what) {
-  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(64), 0, c.stream, c.st, what);
+  hipLaunchKernelGGL(k_reset_counters, dim3(1), dim3(kKm1Slots), 0, c.stream, c.st, what);
   return hipGetLastError();
 }
 
 hipError_t launch_clear_candidate_bits(Ctx &c) {
-  if (!(c.unit_nw && c.k <= 64 && cand_groups(c))) return hipSuccess;  // the kernel writes whole words
+  if (!(c.unit_nw && !light_lanes(c))) return hipSuccess;  // the kernel writes whole words
   const int64_t words = ((int64_t)c.n + 255) / 256 * 8;
   return launch_fill_u32(c, c.inm, words, 0u, nullptr, kPhAny);
 }
@@ -1546,8 +1445,7 @@ hipError_t launch_candidates(Ctx &c, const int32_t *part, int32_t locked_stamp, 
     const hipError_t e = launch_reset_counters(c, kResetCandidates | kResetMoves);
     if (e != hipSuccess) return e;
   }
-  return c.unit_nw ? cand_dispatch<true>(c, part, locked_stamp, lock_bytes, tau_q, lc)
-                   : cand_dispatch<false>(c, part, locked_stamp, lock_bytes, tau_q, lc);
+  return cand_dispatch(c, part, locked_stamp, lock_bytes, tau_q, lc);
 }
 
 hipError_t launch_export_candidates(Ctx &c, int32_t *t, int32_t *g, uint8_t *in_m) {

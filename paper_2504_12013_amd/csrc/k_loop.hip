@@ -140,17 +140,10 @@ __device__ __forceinline__ void advance(LoopCtl &r, int32_t want, int64_t ovl, i
 
 // The counters of a phase start at zero.
 __device__ __forceinline__ void clear_counters(DevStatus *st) {
-  st->n_cand = 0;
   st->n_moves = 0;
   st->n_ovf = 0;
   st->n_bigmv = 0;
-  st->inc_low = 0;
-  st->inc_hub = 0;
-  st->ab_inc = 0;
   st->mv_inc = 0;
-  st->rb_inc = 0;
-  st->rb_elig = 0;
-  st->rb_ent = 0;
   st->rb_nlist = 0;
   st->rb_nhub = 0;
 }
@@ -170,14 +163,16 @@ __global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st,
     reinterpret_cast<int32_t *>(&r)[i] = reinterpret_cast<const int32_t *>(lc)[i];
   const int64_t bw = b < k ? st->bw[b] : 0;
   const int32_t bc = b < k ? st->bcnt[b] : 0;
-  int64_t slot = b < kKm1Slots ? st->km1_slot[b] : 0;
+  int64_t slot = b < kKm1Slots ? st->slot[b].km1 : 0;
+  int32_t cand = b < kKm1Slots ? (int32_t)st->slot[b].n_cand : 0;
   const int64_t km1_base = st->km1;
-  const int32_t moved = st->n_moves, cand = st->n_cand;
+  const int32_t moved = st->n_moves;
   const int64_t over = b < k ? max(bw - lmax, (int64_t)0) : 0;
   int64_t mx = over;
 #pragma unroll
   for (int o = kWave / 2; o >= 1; o >>= 1) mx = max(mx, (int64_t)__shfl_xor(mx, o, kWave));
   slot = wave_sum(slot);
+  cand = wave_sum(cand);  // the first wave's counts
   const int64_t cnt = over > 0 ? bc : 0, incl = wave_incl_scan(cnt);
   if (lane_id() == kWave - 1) {
     s_ovl[w] = mx;
@@ -192,7 +187,7 @@ __global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st,
     st->km1 = s_km1;
     clear_counters(st);
   }
-  if (b < kKm1Slots) st->km1_slot[b] = 0;
+  if (b < kKm1Slots) st->slot[b] = CtrSlot{};
   __syncthreads();
   if (r.phase == kPhRb && b < k) {
     st->rb_need[b] = over;
@@ -288,6 +283,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_control_union(LoopCtl *lcs, int
     gate->phase_mask = smask;
     clear_counters(st);
   }
+  if (threadIdx.x < kKm1Slots) st->slot[threadIdx.x] = CtrSlot{};
   build_lists(lcs, H, const_cast<ActList *>(u.act), u.ht0, u.hch0);
 }
 
@@ -304,26 +300,26 @@ __global__ void k_fill_u32(uint32_t *__restrict__ p, int64_t count, uint32_t val
 __global__ void k_prof_mark(DevProf *dp, const DevStatus *st, const LoopCtl *lc, int32_t want, int32_t fam,
                             int32_t end, double bytes, double per_inc) {
   JET_GATE(lc, want);
-  if (threadIdx.x != 0) return;
   const unsigned long long now = wall_clock64();
   if (!end) {
-    dp->t0[fam] = now;
+    if (threadIdx.x == 0) dp->t0[fam] = now;
     return;
   }
+  const CtrSlot &c = st->slot[threadIdx.x];  // one lane per slot
+  auto total = [&](long long x) { return (double)wave_sum(x); };
   double b = bytes;
   switch (fam) {
-  case kProfCandidates: b += per_inc * (double)st->inc_low; break;
-  case kProfCandidatesHub: b += per_inc * (double)st->inc_hub; break;
+  case kProfCandidates: b += per_inc * total(c.inc_low); break;
+  case kProfCandidatesHub: b += per_inc * total(c.inc_hub); break;
   case kProfAfterburner:  // per_inc is nonzero for the graph afterburner only
-    if (per_inc > 0.0) b += per_inc * (double)st->ab_inc + 24.0 * (double)st->n_cand;
+    if (per_inc > 0.0) b += per_inc * total(c.ab_inc) + 24.0 * total(c.n_cand);
     break;
   case kProfApply: b += 5.0 * st->n_moves + 20.0 * (double)st->mv_inc; break;
-  case kProfRbGain:
-    b += 4.0 * (double)st->rb_elig + 32.0 * (double)st->rb_ent + per_inc * (double)st->rb_inc;
-    break;
-  case kProfRbSelect: b += 32.0 * (double)st->rb_ent + 8.0 * st->n_moves; break;
+  case kProfRbGain: b += 4.0 * total(c.rb_elig) + 32.0 * total(c.rb_ent) + per_inc * total(c.rb_inc); break;
+  case kProfRbSelect: b += 32.0 * total(c.rb_ent) + 8.0 * st->n_moves; break;
   default: break;
   }
+  if (threadIdx.x != 0) return;
   dp->ticks[fam] += now - dp->t0[fam];
   dp->launches[fam] += 1;
   dp->bytes[fam] += b;

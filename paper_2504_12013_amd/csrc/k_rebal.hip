@@ -21,6 +21,7 @@
 
 #include "conn.h"
 #include "dev_util.h"
+#include "entry.h"
 #include "jet_internal.h"
 #include "moves.h"
 
@@ -28,63 +29,11 @@ namespace jet {
 
 namespace {
 
-__device__ __forceinline__ uint32_t mono_code(unsigned __int128 x) {
-  if (x == 0) return 0u;
-  const uint64_t hi = (uint64_t)(x >> 64), lo = (uint64_t)x;
-  const int L = hi ? 128 - __clzll(hi) : 64 - __clzll(lo);  // bit length, 1..128
-  uint32_t mant;
-  if (L - 1 >= 24) mant = (uint32_t)(x >> (L - 1 - 24)) & 0xffffffu;
-  else mant = (uint32_t)(x << (24 - (L - 1))) & 0xffffffu;
-  return ((uint32_t)L << 24) | mant;
-}
-
-__device__ __forceinline__ void order_key(int32_t g, int32_t c, int32_t v, uint32_t key[5]) {
-  const unsigned __int128 bias = (unsigned __int128)1 << 95;
-  unsigned __int128 U;
-  if (g >= 0) {
-    const unsigned __int128 gc = (unsigned __int128)((uint64_t)(uint32_t)g * (uint64_t)(uint32_t)c);
-    U = bias + gc;
-    key[0] = 0x80000000u | mono_code(gc);
-  } else {
-    const uint64_t a = (uint64_t)(-(int64_t)g), cc = (uint64_t)(uint32_t)c;
-    const uint64_t q0 = a / cc, r0 = a % cc;
-    const uint64_t x1 = r0 << 31, f1 = x1 / cc, r1 = x1 % cc;
-    const uint64_t x2 = r1 << 31, f2 = x2 / cc, r2 = x2 % cc;
-    const unsigned __int128 ce =
-        ((unsigned __int128)q0 << 62) + ((unsigned __int128)f1 << 31) + (unsigned __int128)f2 + (r2 != 0 ? 1 : 0);
-    U = bias - ce;
-    key[0] = 0x7fffffffu - mono_code(ce);
-  }
-  key[1] = (uint32_t)(U >> 64);
-  key[2] = (uint32_t)(U >> 32);
-  key[3] = (uint32_t)U;
-  key[4] = 0xffffffffu - (uint32_t)v;
-}
-
-// The key of an entry in the order jet_params.rb_unweighted names: 0 the priority of Section 4.3,
-// 1 the gain alone (the original Jet's priority), 2 the original's bucket order of the loss
-// (Section 4.3 contrasts it with the sort): a move that does not lose goes to bucket 0, a loss
-// L >= 1 to bucket 1 + floor(log2 L); lower buckets first, and inside a bucket vertex-ID order
-// stands in for the original's arrival order.  Bucket words: w0 = (255 - bucket) << 24,
-// w1..w3 = 0 (so the selection skips their passes), w4 = 0xffffffff - v as for the priorities.
-// The bucket words replace the others by selects, so the key stays in registers.
-__device__ __forceinline__ void entry_key(int32_t g, int32_t c, int32_t v, int32_t order, uint32_t key[5]) {
-  order_key(g, order ? 1 : c, v, key);
-  const bool bk = order == 2;
-  const int32_t bucket = g >= 0 ? 0 : 64 - __clzll((unsigned long long)(-(int64_t)g));
-  key[0] = bk ? (uint32_t)(255 - bucket) << 24 : key[0];
-  key[1] = bk ? 0u : key[1];
-  key[2] = bk ? 0u : key[2];
-  key[3] = bk ? 0u : key[3];
-}
-
-// entry layout: 8 words = key[0..4], v, target, weight
-constexpr int kEntryWords = 8;
-
 // Needs and list regions of one round outside the loop (inside it the control kernel sets them).
 __global__ void k_rb_prepare(int32_t k, int64_t lmax, DevStatus *st) {
   __shared__ int64_t cnts[kMaxK];
   const int b = threadIdx.x;
+  if (b < kKm1Slots) st->slot[b].rb_inc = st->slot[b].rb_elig = st->slot[b].rb_ent = 0;
   if (b < k) {
     const int64_t over = st->bw[b] - lmax;
     st->rb_need[b] = over > 0 ? over : 0;
@@ -103,9 +52,6 @@ __global__ void k_rb_prepare(int32_t k, int64_t lmax, DevStatus *st) {
     st->n_moves = 0;
     st->n_bigmv = 0;
     st->mv_inc = 0;
-    st->rb_inc = 0;
-    st->rb_elig = 0;
-    st->rb_ent = 0;
     st->rb_nlist = 0;
     st->rb_nhub = 0;
   }
@@ -121,6 +67,10 @@ __global__ __launch_bounds__(kPrepThreads) void k_rb_prepare_union(int32_t k, in
   __shared__ int64_t sm[kPrepThreads / kWave + 1];
   __shared__ int64_t carry, scarry;
   if (threadIdx.x == 0) carry = scarry = 0;
+  if (threadIdx.x < kKm1Slots) {
+    CtrSlot &c = st->slot[threadIdx.x];
+    c.rb_inc = c.rb_elig = c.rb_ent = 0;
+  }
   const int32_t nseg = H * k;
   for (int32_t base = 0; base < nseg; base += kPrepThreads) {  // block-uniform trip count
     const int32_t sg = base + threadIdx.x;
@@ -159,9 +109,6 @@ __global__ __launch_bounds__(kPrepThreads) void k_rb_prepare_union(int32_t k, in
     st->n_moves = 0;
     st->n_bigmv = 0;
     st->mv_inc = 0;
-    st->rb_inc = 0;
-    st->rb_elig = 0;
-    st->rb_ent = 0;
     st->rb_nlist = 0;
     st->rb_nhub = 0;
   }
@@ -269,7 +216,9 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
                                                         const int64_t *__restrict__ voff, int32_t n, int32_t k,
                                                         int64_t lmax, int64_t A, DevStatus *st,
                                                         int32_t *__restrict__ list, int32_t *__restrict__ slot,
-                                                        uint8_t *__restrict__ mvfrom, const LoopCtl *lctl) {
+                                                        uint8_t *__restrict__ mvfrom,
+                                                        const int32_t *__restrict__ hubs, int32_t nhubs,
+                                                        int32_t *__restrict__ hlist, const LoopCtl *lctl) {
   JET_GATE(lctl, kPhRb);
   __shared__ int64_t bw[kMaxK];
   __shared__ int32_t lc[kMaxK], lbase[kMaxK];
@@ -281,6 +230,22 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
     lc[b] = 0;
   }
   __syncthreads();
+  // hub vertices that may move, by their index in the hub list (k_hub.hip)
+  for (int32_t h0 = blockIdx.x * kListBlock; h0 < nhubs; h0 += gridDim.x * kListBlock) {  // block-uniform
+    const int32_t h = h0 + tid;
+    bool e = false;
+    if (h < nhubs) {
+      const int32_t v = hubs[h];
+      const int64_t hb = bw[part[v]], c = vw ? vw[v] : 1;
+      e = hb > lmax && 2 * c <= 3 * (hb - A);
+    }
+    const uint64_t mm = ballot(e);
+    if (!mm) continue;  // wave-uniform, no barrier in the loop
+    int32_t base = 0;
+    if (lane_id() == 0) base = atomicAdd(&st->rb_nhub, __popcll(mm));
+    base = __shfl(base, 0, kWave);
+    if (e) hlist[base + rank_below(mm)] = h;
+  }
   const int64_t r0 = (int64_t)blockIdx.x * (kListBlock * kListPer) + tid;
   int32_t pv[kListPer];
 #pragma unroll
@@ -340,33 +305,6 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
   }
 }
 
-// Entries are 32 bytes on a 32-byte boundary: two 16-byte accesses each.
-__device__ __forceinline__ void load_entry(const uint32_t *__restrict__ p, uint32_t ent[kEntryWords]) {
-  const uint4 a = reinterpret_cast<const uint4 *>(p)[0], b = reinterpret_cast<const uint4 *>(p)[1];
-  ent[0] = a.x;
-  ent[1] = a.y;
-  ent[2] = a.z;
-  ent[3] = a.w;
-  ent[4] = b.x;
-  ent[5] = b.y;
-  ent[6] = b.z;
-  ent[7] = b.w;
-}
-__device__ __forceinline__ void store_entry(uint32_t *__restrict__ p, const uint32_t ent[kEntryWords]) {
-  reinterpret_cast<uint4 *>(p)[0] = make_uint4(ent[0], ent[1], ent[2], ent[3]);
-  reinterpret_cast<uint4 *>(p)[1] = make_uint4(ent[4], ent[5], ent[6], ent[7]);
-}
-
-// One rebalancing entry: the exact order key, vertex, target and weight; a vertex without a valid
-// target leaves weight 0 (the selection skips such entries).
-// order: jet_params.rb_unweighted (entry_key); the entry keeps the real weight c
-__device__ __forceinline__ void write_entry(uint32_t *p, bool ok, int32_t g, int32_t c, int32_t v, int32_t t,
-                                            int32_t order) {
-  uint32_t ent[kEntryWords] = {0u, 0u, 0u, 0u, 0u, (uint32_t)v, ok ? (uint32_t)t : 0xffu, ok ? (uint32_t)c : 0u};
-  if (ok) entry_key(g, c, v, order, ent);
-  store_entry(p, ent);
-}
-
 // Adds the thread's counts (scanned incidences, examined vertices, written entries) to the status,
 // one atomic per workgroup and counter.  Every thread of the block calls it.
 template <int NWV>
@@ -390,14 +328,15 @@ __device__ __forceinline__ void flush_rb_counters(unsigned long long a, unsigned
       t2 += wsum[i][2];
     }
     if (t1) {
-      atomicAdd((unsigned long long *)&st->rb_inc, t0);
-      atomicAdd((unsigned long long *)&st->rb_elig, t1);
-      if (t2) atomicAdd((unsigned long long *)&st->rb_ent, t2);
+      count_add(st, blockIdx.x, &CtrSlot::rb_inc, (long long)t0);
+      count_add(st, blockIdx.x, &CtrSlot::rb_elig, (long long)t1);
+      count_add(st, blockIdx.x, &CtrSlot::rb_ent, (long long)t2);
     }
   }
 }
 
-template <int G, bool UNIT>
+// With net weights.
+template <int G>
 __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw,
@@ -451,7 +390,7 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
 #pragma unroll
     for (int j = 0; j < 8; ++j) conn[j] = 0;
     int32_t benefit = 0;
-    if (elig) vertex_conn<G, UNIT>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
+    if (elig) vertex_conn<G, false>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
     // best valid target by conn (gain = conn - aff), lowest block on ties; -1 = none
     int32_t bestc = -1, bestb = INT32_MAX;
     if (elig) {
@@ -486,39 +425,39 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
   flush_rb_counters<BLOCK / kWave>(scanned, examined, emitted, wsum, st);
 }
 
-// Unit net weights and k <= 64: G lanes per listed vertex (G = 1 on light levels), the block
-// counts conn(v, b) bit-sliced as in the candidate pass (conn.h).  The valid targets form a mask
-// (b != s, room for v's weight, outside the deadzone); the best is the lowest block of largest
-// count in it (counts of zero included, as for the lane-group kernel).
-template <int G>
+// Unit net weights: G lanes per listed vertex (G = 1 on light levels), the block counts conn(v, b)
+// bit-sliced as in the candidate pass (conn.h).  The valid targets form a mask (b != s, room for v's
+// weight, outside the deadzone); the best is the lowest block of largest count in it (counts of zero
+// included, as for the lane-group kernel).  k = 128 took 16 lanes per vertex with six exchanges and 24
+// instructions per net on each: 85 us per pass on 300,000 SAT-like vertices against SLICED us now.
+template <int G, int HW, int N>
 __global__ __launch_bounds__(256) void k_rb_gain_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw, const int32_t *__restrict__ vw,
     const int32_t *__restrict__ list, const int32_t *__restrict__ slot, int32_t k, int64_t lmax, int64_t dz,
-    DevStatus *st, uint32_t *__restrict__ entries, const LoopCtl *lc, int32_t xcd) {
+    DevStatus *st, uint32_t *__restrict__ entries, const LoopCtl *lc, Union u, int32_t xcd) {
   JET_GATE(lc, kPhRb);
-  if (lc) dz = lc->dz;  // one hypergraph (unions take the lane-group kernel)
-  const int32_t unw = lc ? lc->rb_unw : 0;
+  const bool un = u.lcs != nullptr;
+  if (lc && !un) dz = lc->dz;
+  const int32_t unw0 = lc && !un ? lc->rb_unw : 0;
   constexpr int VPW = kWave / G;
-  __shared__ int64_t slack[kMaxK];
-  __shared__ unsigned long long s_okdz;
+  __shared__ int64_t slack[32 * HW];
+  __shared__ uint32_t s_ok[HW];  // one hypergraph: blocks outside the deadzone
   __shared__ long long s_minslack;
   __shared__ unsigned long long wsum[4][3];
-  if (threadIdx.x == 0) {
-    s_okdz = 0ull;
-    s_minslack = LLONG_MAX;
-  }
+  if (threadIdx.x < HW) s_ok[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) s_minslack = LLONG_MAX;
   __syncthreads();
-  for (int b = threadIdx.x; b < k; b += 256) {
-    const int64_t bwb = st->bw[b];
-    slack[b] = lmax - bwb;
-    if (bwb < dz) {
-      atomicOr(&s_okdz, 1ull << b);
-      atomicMin(&s_minslack, (long long)(lmax - bwb));
+  if (!un)
+    for (int b = threadIdx.x; b < k; b += 256) {
+      const int64_t bwb = st->bw[b];
+      slack[b] = lmax - bwb;
+      if (bwb < dz) {
+        atomicOr(&s_ok[b >> 5], 1u << (b & 31));
+        atomicMin(&s_minslack, (long long)(lmax - bwb));
+      }
     }
-  }
   __syncthreads();
-  const uint64_t okdz = s_okdz;
   const int64_t minslack = s_minslack;
   const int64_t nl = st->rb_nlist;
   const int l = lane_id(), lg = l % G;
@@ -526,7 +465,7 @@ __global__ __launch_bounds__(256) void k_rb_gain_bits(
   // with xcd set, the workgroups of one XCD take one contiguous eighth of the list (as k_rb_gain)
   int64_t bstart = ((int64_t)blockIdx.x * 4 + threadIdx.x / kWave) * VPW, bend = nl;
   int64_t bstep = (int64_t)gridDim.x * 4 * VPW;
-  if (xcd && gridDim.x % 8 == 0) {
+  if (xcd && !un && gridDim.x % 8 == 0) {
     const int64_t span = 4 * VPW, steps = (nl + span - 1) / span, per = (steps + 7) / 8, x = blockIdx.x % 8;
     bstart = (x * per + blockIdx.x / 8) * span + (threadIdx.x / kWave) * VPW;
     bend = min(nl, (x + 1) * per * span);
@@ -535,34 +474,56 @@ __global__ __launch_bounds__(256) void k_rb_gain_bits(
   for (int64_t base = bstart; base < bend; base += bstep) {  // wave-uniform trip count
     const int64_t i = base + l / G;
     const bool elig = i < nl;
-    int32_t v = 0, s = 0, c = 1;
-    int64_t q0 = 0, q1 = 0;
+    int32_t v = 0, s = 0, c = 1, unw = unw0;
+    int64_t q0 = 0, q1 = 0, lm = lmax, dzz = dz, sg0 = 0;  // union: the vertex's hypergraph's limits and segments
     if (elig) {
       v = list[i];
       s = part[v];
       c = vw ? vw[v] : 1;
       q0 = voff[v];
       q1 = voff[v + 1];
+      if (un) {
+        const int32_t hg = u.vhg[v];
+        lm = u.lcs[hg].lmax;
+        dzz = u.lcs[hg].dz;
+        sg0 = (int64_t)hg * k;
+        unw = u.lcs[hg].rb_unw;
+      }
     }
-    const uint64_t sbit = 1ull << s;
-    uint64_t pl[9];
-#pragma unroll
-    for (int p = 0; p < 9; ++p) pl[p] = 0ull;
+    uint32_t pl[HW][N] = {};
     int32_t benefit = 0;
-    if (elig) planes_accumulate<G>(inc, q0, q1, ns, lg, sbit, pl, benefit);
-    planes_combine<G>(pl, benefit);
-    if (!elig || lg != 0) continue;
-    // valid targets: room for c (every block outside the deadzone has it when c <= the smallest
-    // slack there), outside the deadzone, not s
-    uint64_t valid = okdz;
-    if ((int64_t)c > minslack) {
-      valid = 0ull;
-      for (int b = 0; b < k; ++b)
-        if (slack[b] >= (int64_t)c) valid |= 1ull << b;
-      valid &= okdz;
-    }
+    if (elig) planes_accumulate<HW, N>(inc, q0 + lg, q1, G, ns, s, pl, benefit);
+    // valid targets of a word: room for c (every block outside the deadzone has it when c <= the
+    // smallest slack there), outside the deadzone, not s
     int32_t bestb;
-    const int32_t bestc = planes_best(pl, valid & ~sbit, bestb);
+    const int32_t bestc = planes_target<G, HW, N>(pl, benefit, l, bestb, [&](int x, const uint32_t (&)[N]) {
+      uint32_t ok = 0u;
+      if (un) {
+#pragma unroll 1
+        for (int b0 = 0; b0 < 32 && 32 * x + b0 < k; b0 += 8) {  // eight loads in flight
+          int64_t w8[8];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            const int b = 32 * x + b0 + j;
+            w8[j] = b < k ? st->bw[sg0 + b] : LLONG_MAX / 2;
+          }
+#pragma unroll
+          for (int j = 0; j < 8; ++j)
+            if (w8[j] + c <= lm && w8[j] < dzz) ok |= 1u << (b0 + j);
+        }
+      } else {
+        ok = s_ok[x];
+        if ((int64_t)c > minslack) {
+          uint32_t room = 0u;
+#pragma unroll 1
+          for (int b = 0; b < 32 && 32 * x + b < k; ++b)
+            if (slack[32 * x + b] >= (int64_t)c) room |= 1u << b;
+          ok &= room;
+        }
+      }
+      return ok & ~(x == (s >> 5) ? 1u << (s & 31) : 0u);
+    });
+    if (!elig || lg != 0) continue;
     write_entry(entries + (int64_t)slot[i] * kEntryWords, bestc >= 0, bestc - (sumw[v] - benefit), c, v, bestb,
                 unw);
     scanned += (unsigned long long)(q1 - q0);
@@ -570,193 +531,6 @@ __global__ __launch_bounds__(256) void k_rb_gain_bits(
     emitted += bestc >= 0 ? 1ull : 0ull;
   }
   flush_rb_counters<4>(scanned, examined, emitted, wsum, st);
-}
-
-// max over 64 lanes of a 64-bit key
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, o, kWave);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), o, kWave);
-    const unsigned long long y = ((unsigned long long)hi << 32) | lo;
-    x = y > x ? y : x;
-  }
-  return x;
-}
-
-// Hub vertices of overloaded blocks (more than kHubDegree incident nets).  A round has few of them
-// but each has many nets, so their nets are spread over the whole grid:
-//   k_rb_hub_list    lists the hubs the heavy-vertex rule lets move;
-//   k_rb_hub_accum   gives every listed hub an equal share of the workgroups, each summing the
-//                    per-block connectivity and the benefit of its slice of incident nets into the
-//                    hub's column of rb_hacc ([k + 1][nhubs], integer atomics: exact);
-//   k_rb_hub_finish  one thread per listed hub: best valid target from the column, order key,
-//                    entry (slots reserved per workgroup); clears the column for the next round.
-__global__ __launch_bounds__(256) void k_rb_hub_list(const int32_t *__restrict__ part,
-                                                     const int32_t *__restrict__ vw,
-                                                     const int32_t *__restrict__ hubs, int32_t nhubs,
-                                                     int64_t lmax, int64_t A, DevStatus *st,
-                                                     int32_t *__restrict__ hlist, const LoopCtl *lc, int32_t k, Union u) {
-  JET_GATE(lc, kPhRb);
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  bool e = false;
-  int32_t v = 0;
-  if (i < nhubs) {
-    v = hubs[i];
-    int64_t sg = part[v], lm = lmax, a = A;
-    bool on = true;
-    if (u.lcs) {  // union: the hub's hypergraph
-      const int32_t hg = u.vhg[v];
-      on = u.lcs[hg].phase == kPhRb;
-      sg += (int64_t)hg * k;
-      lm = u.lcs[hg].lmax;
-      a = u.lcs[hg].A;
-    }
-    const int64_t bs = st->bw[sg];
-    const int64_t c = vw ? vw[v] : 1;
-    e = on && bs > lm && 2 * c <= 3 * (bs - a);
-  }
-  const uint64_t mm = ballot(e);
-  if (!mm) return;
-  int32_t base = 0;
-  if (lane_id() == 0) base = atomicAdd(&st->rb_nhub, __popcll(mm));
-  base = __shfl(base, 0, kWave);
-  if (e) hlist[base + rank_below(mm)] = v;
-}
-
-template <int G, bool UNIT>
-__global__ __launch_bounds__(256) void k_rb_hub_accum(
-    const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
-    const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, const int32_t *__restrict__ hlist, int32_t k,
-    int32_t H, const DevStatus *st, int32_t *__restrict__ acc, const LoopCtl *lc) {
-  JET_GATE(lc, kPhRb);
-  constexpr int NG = 256 / G;
-  __shared__ int32_t cs[NG][8 * G];
-  __shared__ int32_t bsum[NG];
-  const int32_t nh = st->rb_nhub;
-  if (nh == 0) return;
-  const int tid = threadIdx.x, gi = tid / G, lg = tid % G;
-  const int32_t per = nh >= (int32_t)gridDim.x ? 1 : (int32_t)gridDim.x / nh;  // blocks per hub
-  const int32_t first = (int32_t)blockIdx.x / per, sub = (int32_t)blockIdx.x % per;
-  const int32_t step = nh >= (int32_t)gridDim.x ? (int32_t)gridDim.x : nh;
-  for (int32_t j = first; j < nh; j += step) {  // block-uniform trip count
-    const int32_t v = hlist[j];
-    const int32_t s = part[v];
-    int32_t conn[8];
-#pragma unroll
-    for (int x = 0; x < 8; ++x) conn[x] = 0;
-    int32_t benefit = 0;
-    const int64_t q0 = voff[v], q1 = voff[v + 1];
-    if (G == 1)
-      conn_accumulate_strided<G, UNIT>(inc, q0 + (int64_t)sub * NG + gi, q1, (int64_t)per * NG, nw, ns, lg, s, conn,
-                                       benefit);
-    else
-      conn_accumulate<G, UNIT>(inc, q0 + ((int64_t)sub * NG + gi) * G, q1, (int64_t)per * NG * G, nw, ns, lg, s,
-                               conn, benefit);
-#pragma unroll
-    for (int x = 0; x < 8; ++x) cs[gi][lg * 8 + x] = conn[x];
-    if ((s >> 3) == lg) bsum[gi] = benefit;
-    __syncthreads();
-    if (tid < k) {
-      int32_t tot = 0;
-      for (int g = 0; g < NG; ++g) tot += cs[g][tid];
-      if (tot) atomicAdd(&acc[(size_t)tid * H + j], tot);
-    }
-    if (tid == k) {
-      int32_t ben = 0;
-      for (int g = 0; g < NG; ++g) ben += bsum[g];
-      if (ben) atomicAdd(&acc[(size_t)k * H + j], ben);
-    }
-    __syncthreads();  // LDS reused by the next hub
-  }
-}
-
-__global__ __launch_bounds__(256) void k_rb_hub_finish(
-    const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ sumw,
-    const int32_t *__restrict__ vw, const int32_t *__restrict__ hlist, int32_t k, int32_t H, int64_t lmax, int64_t dz,
-    DevStatus *st, int32_t *__restrict__ acc, uint32_t *__restrict__ entries, const LoopCtl *lc, Union u) {
-  JET_GATE(lc, kPhRb);
-  if (lc && !u.lcs) dz = lc->dz;
-  __shared__ int64_t bw[kMaxK];
-  __shared__ int32_t lcnt[kMaxK], lbase[kMaxK];
-  __shared__ unsigned long long scanned, examined, emitted;
-  const int32_t nh = st->rb_nhub;
-  if (nh == 0) return;
-  const int tid = threadIdx.x;
-  for (int b = tid; b < k; b += 256) bw[b] = st->bw[b];
-  if (tid == 0) {
-    scanned = 0ull;
-    examined = 0ull;
-    emitted = 0ull;
-  }
-  const int32_t ntiles = (nh + 255) / 256;
-  for (int32_t tile = blockIdx.x; tile < ntiles; tile += gridDim.x) {  // block-uniform trip count
-    for (int b = tid; b < k; b += 256) lcnt[b] = 0;
-    __syncthreads();
-    const int32_t j = tile * 256 + tid;
-    const bool e = j < nh;
-    int32_t v = 0, s = 0, c = 1, ben = 0;
-    int64_t lm = lmax, dzz = dz, sg0 = 0;  // union: the hub's hypergraph's limits and segments
-    int32_t unw = (lc && !u.lcs) ? lc->rb_unw : 0;
-    // best valid target (balanced with v added, outside the deadzone) by conn, lowest block on ties
-    int32_t bestc = -1, bestb = 0;
-    if (e) {
-      v = hlist[j];
-      s = part[v];
-      c = vw ? vw[v] : 1;
-      if (u.lcs) {
-        const int32_t hg = u.vhg[v];
-        lm = u.lcs[hg].lmax;
-        dzz = u.lcs[hg].dz;
-        sg0 = (int64_t)hg * k;
-        unw = u.lcs[hg].rb_unw;
-      }
-      for (int32_t b0 = 0; b0 < k; b0 += 16) {  // 16 loads in flight before any is used
-        int32_t cb[16];
-#pragma unroll
-        for (int x = 0; x < 16; ++x) cb[x] = b0 + x < k ? acc[(size_t)(b0 + x) * H + j] : -1;
-#pragma unroll
-        for (int x = 0; x < 16; ++x) {
-          const int32_t b = b0 + x;
-          if (b < k) acc[(size_t)b * H + j] = 0;
-          const int64_t bwb = b < k ? (u.lcs ? st->bw[sg0 + b] : bw[b]) : 0;
-          if (b < k && b != s && bwb + c <= lm && bwb < dzz && cb[x] > bestc) {
-            bestc = cb[x];
-            bestb = b;
-          }
-        }
-      }
-      ben = acc[(size_t)k * H + j];
-      acc[(size_t)k * H + j] = 0;
-    }
-    const bool emit = e && bestc >= 0;
-    int32_t local = 0;
-    int64_t uslot = 0;
-    if (emit) {
-      if (u.lcs) uslot = st->rb_off[sg0 + s] + atomicAdd(&st->rb_count[sg0 + s], 1);  // union: per segment
-      else local = atomicAdd(&lcnt[s], 1);
-      atomicAdd(&emitted, 1ull);
-    }
-    if (e) {
-      atomicAdd(&scanned, (unsigned long long)(voff[v + 1] - voff[v]));
-      atomicAdd(&examined, 1ull);
-    }
-    __syncthreads();
-    for (int b = tid; b < k; b += 256)
-      if (lcnt[b]) lbase[b] = atomicAdd(&st->rb_count[b], lcnt[b]);
-    __syncthreads();
-    if (emit) {
-      const int32_t g = bestc - (sumw[v] - ben);
-      write_entry(entries + (u.lcs ? uslot : st->rb_off[s] + lbase[s] + local) * kEntryWords, true, g, c, v, bestb,
-                  unw);
-    }
-  }
-  __syncthreads();
-  if (tid == 0 && examined) {
-    atomicAdd((unsigned long long *)&st->rb_inc, scanned);
-    atomicAdd((unsigned long long *)&st->rb_elig, examined);
-    if (emitted) atomicAdd((unsigned long long *)&st->rb_ent, emitted);
-  }
 }
 
 constexpr int kSelThreads = 1024;
@@ -1296,7 +1070,7 @@ inline unsigned grid_for(int64_t work, int block, int64_t cap) {
   return (unsigned)g;
 }
 
-template <int G, bool UNIT>
+template <int G>
 hipError_t gain_launch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *lc) {
   constexpr int BLOCK = (G == 16) ? 512 : 256;
   constexpr int VPB = BLOCK / G;
@@ -1307,41 +1081,41 @@ hipError_t gain_launch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *l
   else
     hipLaunchKernelGGL(k_rb_list, dim3((unsigned)((c.n + kListBlock * kListPer - 1) / (kListBlock * kListPer))),
                        dim3(kListBlock), 0, c.stream, part, c.vw, c.voff, c.n, c.k, c.lmax, c.A, c.st, c.rb_list,
-                       c.rb_slot, c.mvfrom, lc);
-  // the list length is known on the device only: a persistent grid walks it; unit net weights and
-  // k <= 64 take the bit-sliced kernel (one lane per vertex on light levels, eight otherwise) on
-  // a context of one hypergraph
-  if (c.H == 1 && UNIT && c.k <= 64 && c.p_low < (int64_t)c.lane_degree * c.n_low) {
-    hipLaunchKernelGGL(k_rb_gain_bits<1>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 255) / 256)), dim3(256), 0,
-                       c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st,
-                       c.rb_keys, lc, c.rb_xcd);
-  } else if (c.H == 1 && UNIT && c.k <= 64) {
-    hipLaunchKernelGGL(k_rb_gain_bits<8>, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + 31) / 32)), dim3(256), 0,
-                       c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st,
-                       c.rb_keys, lc, c.rb_xcd);
+                       c.rb_slot, c.mvfrom, c.hubs, c.nhubs, c.rb_hlist, lc);
+  // the list length is known on the device only: a persistent grid walks it; unit net weights take the
+  // bit-sliced kernel (one lane per vertex on light levels, eight otherwise)
+  if (c.unit_nw) {
+    const bool few = c.max_low_degree < 32;
+    const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
+    auto go = [&](auto kernel, int64_t per_block) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + per_block - 1) / per_block)),
+                         dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k,
+                         c.lmax, dz, c.st, c.rb_keys, lc, u, c.rb_xcd);
+    };
+    if (light_lanes(c)) {
+      if (hw == 1) few ? go(k_rb_gain_bits<1, 1, 5>, 256) : go(k_rb_gain_bits<1, 1, 9>, 256);
+      else if (hw == 2) few ? go(k_rb_gain_bits<1, 2, 5>, 256) : go(k_rb_gain_bits<1, 2, 9>, 256);
+      else few ? go(k_rb_gain_bits<1, 4, 5>, 256) : go(k_rb_gain_bits<1, 4, 9>, 256);
+    } else {
+      if (hw == 1) few ? go(k_rb_gain_bits<8, 1, 5>, 32) : go(k_rb_gain_bits<8, 1, 9>, 32);
+      else if (hw == 2) few ? go(k_rb_gain_bits<8, 2, 5>, 32) : go(k_rb_gain_bits<8, 2, 9>, 32);
+      else few ? go(k_rb_gain_bits<8, 4, 5>, 32) : go(k_rb_gain_bits<8, 4, 9>, 32);
+    }
   } else {
     const unsigned grid = (unsigned)std::min<int64_t>(c.grid_cap, (c.n + VPB - 1) / VPB);
-    hipLaunchKernelGGL((k_rb_gain<G, UNIT>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
+    hipLaunchKernelGGL((k_rb_gain<G>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
                        c.sumw, c.vw, c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st, c.rb_keys, lc, u, c.rb_xcd);
   }
-  if (c.nhubs > 0) {
-    hipLaunchKernelGGL(k_rb_hub_list, dim3((unsigned)((c.nhubs + 255) / 256)), dim3(256), 0, c.stream, part, c.vw,
-                       c.hubs, c.nhubs, c.lmax, c.A, c.st, c.rb_hlist, lc, c.k, u);
-    hipLaunchKernelGGL((k_rb_hub_accum<G, UNIT>), dim3(2048), dim3(256), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
-                       c.rb_hlist, c.k, c.nhubs, c.st, c.rb_hacc, lc);
-    hipLaunchKernelGGL(k_rb_hub_finish, dim3(grid_for(c.nhubs, 256, 2048)), dim3(256), 0, c.stream, part, c.voff,
-                       c.sumw, c.vw, c.rb_hlist, c.k, c.nhubs, c.lmax, dz, c.st, c.rb_hacc, c.rb_keys, lc, u);
-  }
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? launch_rb_hubs(c, part, dz, lc) : e;
 }
 
-template <bool UNIT>
 hipError_t gain_dispatch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *lc) {
-  if (c.k <= 8) return gain_launch<1, UNIT>(c, part, dz, lc);
-  if (c.k <= 16) return gain_launch<2, UNIT>(c, part, dz, lc);
-  if (c.k <= 32) return gain_launch<4, UNIT>(c, part, dz, lc);
-  if (c.k <= 64) return gain_launch<8, UNIT>(c, part, dz, lc);
-  return gain_launch<16, UNIT>(c, part, dz, lc);
+  if (c.k <= 8) return gain_launch<1>(c, part, dz, lc);
+  if (c.k <= 16) return gain_launch<2>(c, part, dz, lc);
+  if (c.k <= 32) return gain_launch<4>(c, part, dz, lc);
+  if (c.k <= 64) return gain_launch<8>(c, part, dz, lc);
+  return gain_launch<16>(c, part, dz, lc);
 }
 
 }  // namespace
@@ -1358,7 +1132,7 @@ hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *se
   // the preparation (in the loop: the control kernel) cleared the move list and the counters
   if (e != hipSuccess) return e;
   int tok = prof_begin(c, kProfRbGain, lc, want);
-  e = c.unit_nw ? gain_dispatch<true>(c, part, dz, lc) : gain_dispatch<false>(c, part, dz, lc);
+  e = gain_dispatch(c, part, dz, lc);
   // 12 B per vertex, plus on the device: examined vertices, written entries, scanned incidences
   prof_end(c, tok, lc, want, 12.0 * c.n, 8.0 + (c.k + 7) / 8 + (c.unit_nw ? 0.0 : 4.0));
   if (e != hipSuccess) return e;

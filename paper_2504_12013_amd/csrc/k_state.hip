@@ -2,6 +2,8 @@
 // the connectivity set Lambda(e) (Section 2; tracked per net as in Section 4.2), block weights
 // c(V_b), and the (lambda - 1) metric.  All sums are integer and commutative, so the result does
 // not depend on scheduling.
+#include <stddef.h>
+
 #include "chunk.h"
 #include "dev_util.h"
 #include "jet_internal.h"
@@ -298,16 +300,17 @@ hipError_t launch_block_weights(Ctx &c, const int32_t *part) {
   hipError_t e = hipMemsetAsync(c.st->bw, 0, sizeof(int64_t) * nseg, c.stream);
   if (e == hipSuccess) e = hipMemsetAsync(c.st->bcnt, 0, sizeof(int32_t) * nseg, c.stream);
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_block_weights, dim3(grid_for(c.n, 256, 2048)), dim3(256), 0, c.stream, part, c.vw, c.n, c.k,
+  // few workgroups: each adds up to k weights and counts to the same addresses
+  hipLaunchKernelGGL(k_block_weights, dim3(grid_for(c.n, 256, c.H > 1 ? 2048 : 256)), dim3(256), 0, c.stream, part, c.vw, c.n, c.k,
                      c.st, union_of(c));
   return hipGetLastError();
 }
 
 hipError_t launch_km1_from_ns(Ctx &c) {
-  hipError_t e = hipMemsetAsync(&c.st->km1, 0, sizeof(int64_t) * (1 + kKm1Slots), c.stream);
+  hipError_t e = hipMemsetAsync(c.st->slot, 0, offsetof(DevStatus, km1) + sizeof(int64_t), c.stream);
   if (e == hipSuccess && c.H > 1) e = hipMemsetAsync(c.st->hkm1, 0, sizeof(int64_t) * (size_t)c.H, c.stream);
   if (e != hipSuccess) return e;
-  const unsigned g = grid_for(c.m, 256, 4096);
+  const unsigned g = grid_for(c.m, 256, c.H > 1 ? 4096 : 1024);
   if (c.nw_words == 1)
     hipLaunchKernelGGL(k_km1<1>, dim3(g), dim3(256), 0, c.stream, c.ns, c.nw, c.m, c.st, union_of(c));
   else

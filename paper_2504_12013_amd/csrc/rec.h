@@ -25,4 +25,23 @@ __device__ __forceinline__ unsigned long long order_key(int32_t g, int32_t v) {
   return ((unsigned long long)order_hi(g) << 32) | (uint32_t)v;
 }
 
+// The record of vertex v of block s from its best adjacent foreign block (bestc = its conn, 0: none)
+// and whether v is a candidate.
+__device__ __forceinline__ void finish_candidate(int32_t v, int32_t s, int32_t bestc, int32_t bestb, int32_t sumw_v,
+                                                 int32_t benefit, int32_t tau_q, uint64_t *__restrict__ rec,
+                                                 bool *cand_out) {
+  bool cand = false;
+  uint64_t r;
+  if (bestc > 0) {
+    const int32_t aff = sumw_v - benefit;
+    const int32_t g = bestc - aff;
+    cand = 65536ll * (int64_t)g + (int64_t)tau_q * (int64_t)aff >= 0;
+    r = pack_rec(g, bestb, s);
+  } else {
+    r = pack_rec(0, 0xff, s);
+  }
+  rec[v] = r;
+  *cand_out = cand;
+}
+
 }  // namespace jet

@@ -111,3 +111,41 @@ def test_application_paths(divisor, k):
     assert np.array_equal(d.cpu().numpy(), ref)
     assert st["km1_out"] == ost["km1_out"] == ctx.km1(d)
     ctx.close()
+
+
+@pytest.mark.parametrize("k,nw_max", [(2, 1), (7, 3), (16, 1), (33, 1), (64, 1), (64, 4), (128, 1)])
+@pytest.mark.parametrize("hubs", [1, 9, 700])
+def test_hub_vertices(hubs, k, nw_max):
+    """Vertices with more than 256 incident nets, few and many of them, beside light ones: candidates,
+    whole refinements and rebalancing from an overloaded start (waves share one hub, or take many)."""
+    rng = np.random.default_rng(hubs * 131 + k)
+    n, m = hubs + 500, 400 if hubs > 100 else 4000
+    nets = []
+    for e in range(m):
+        heavy = rng.choice(hubs, max(1, int(0.9 * hubs)), replace=False)
+        light = hubs + rng.choice(500, 3, replace=False)
+        nets.append(np.sort(np.concatenate([heavy, light])))
+    off = np.concatenate([[0], np.cumsum([len(e) for e in nets])]).astype(np.int64)
+    nw = rng.integers(1, nw_max + 1, m).astype(np.int32) if nw_max > 1 else None
+    vw = rng.integers(1, 4, n).astype(np.int32)
+    hg = W.Hypergraph(n=n, m=m, off=off, pins=np.concatenate(nets).astype(np.int32), k=k, eps=0.1, net_w=nw, vtx_w=vw)
+    part = W.part_uniform(n, k, 9)
+    say(f"{hubs} hubs, k = {k}, net weights up to {nw_max}")
+    ctx = J().JetContext(hg)
+    d = torch.from_numpy(part).to("cuda")
+    t, g, im = ctx.candidates(d, 24576)
+    ot, og, oim = O.candidates(hg, part, 24576)
+    assert np.array_equal(im.cpu().numpy(), oim)
+    assert np.array_equal(t.cpu().numpy(), ot)
+    sel = ot >= 0
+    assert np.array_equal(g.cpu().numpy()[sel], og[sel])
+    ref, orc, ost, _ = O.refine(hg, part, tau=(0.75, 0.0), limit=3)
+    rc, st, _ = ctx.refine(d, tau=(0.75, 0.0), limit=3)
+    assert rc == orc and np.array_equal(d.cpu().numpy(), ref)
+    over = np.where(rng.random(n) < 0.7, 0, part).astype(np.int32)
+    oref, orc, ost = O.rebalance(hg, over)[:3]
+    d = torch.from_numpy(over).to("cuda")
+    rc, st = ctx.rebalance(d)
+    ctx.close()
+    assert rc == orc and np.array_equal(d.cpu().numpy(), oref)
+    assert st["rebalance_rounds"] == ost["rebalance_rounds"]
