@@ -149,3 +149,24 @@ def test_hub_vertices(hubs, k, nw_max):
     ctx.close()
     assert rc == orc and np.array_equal(d.cpu().numpy(), oref)
     assert st["rebalance_rounds"] == ost["rebalance_rounds"]
+
+
+@pytest.mark.parametrize("B", [31, 32, 33, 2047, 2048, 2049, 5000])
+def test_network_batch_edges(B):
+    """Forward and gradient of the temperature network at the edges of the 32 samples a batch sum holds
+    in flight and of the 2,048 waves of a forward launch.  The batch sums run in sample order in FP32:
+    rounding grows at most with B half-ulps of terms of at most a few units."""
+    from oracle import mlp as M
+    rng = np.random.default_rng(B)
+    net = J().TauNet(seed=B)
+    th, mean, std = net.get()
+    X = (rng.normal(size=(B, 16)) * std + mean).astype(np.float32)
+    t = rng.uniform(0, 1, B).astype(np.float32)
+    say(f"network, batch of {B}")
+    y = net.forward(torch.from_numpy(X)).cpu().numpy()
+    assert np.max(np.abs(y - M.forward(th, M.standardise(X, mean, std))[0])) <= 1e-5
+    loss, g = net.grad(torch.from_numpy(X), torch.from_numpy(t))
+    ref_loss, ref_g = M.grad(th, M.standardise(X, mean, std), t)
+    tol = 4.0 * (B + 256) * 2.0 ** -24
+    assert abs(loss - ref_loss) <= tol
+    assert np.all(np.abs(g.cpu().numpy() - ref_g) <= tol * np.maximum(1.0, np.abs(ref_g)))
