@@ -683,6 +683,7 @@ int co_alloc(Ctx &c) {
   s.hdeg.resize(n);
   HIP_OR_FAIL(&c, hipMemcpyAsync(s.hdeg.data(), s.deg, sizeof(int64_t) * n, hipMemcpyDeviceToHost, c.stream));
   HIP_OR_FAIL(&c, hipStreamSynchronize(c.stream));
+  s.max_deg = *std::max_element(s.hdeg.begin(), s.hdeg.end());
   s.ready = true;
   return JET_OK;
 }
@@ -736,20 +737,34 @@ int co_reserve(Ctx &c, int64_t cap, int64_t ptab_len, int64_t slots) {
   return JET_OK;
 }
 
-// Sub-rounds `rounds` over the device list d_list (host copy hlist): table offsets, launches.
+// some vertex's rating table does not fit the LDS of the rating kernel
+bool co_large_tables(const Ctx &c) { return co_table(c.co->max_deg, c.n) > jet::kCoLdsTable; }
+
+// Sub-rounds `rounds` over the device list d_list (host copy hlist, needed if co_large_tables): offsets
+// of the tables in global scratch, launches.
 int co_run(Ctx &c, const int32_t *d_list, const std::vector<int32_t> &hlist,
            const std::vector<std::pair<int64_t, int64_t>> &rounds, int32_t *label, int64_t *cw, int64_t wmax,
            int32_t *t_out) {
   jet::CoState &s = *c.co;
+  int64_t biggest = 0, longest = 1;
+  for (const auto &r : rounds) longest = std::max(longest, r.second);
+  if (!co_large_tables(c)) {
+    const int rc = co_reserve(c, longest, 1, 1);
+    if (rc != JET_OK) return rc;
+    for (const auto &r : rounds) {
+      HIP_OR_FAIL(&c, jet::launch_co_rate(c, d_list, r.first, r.first + r.second, 0, label, cw, wmax));
+      HIP_OR_FAIL(&c, jet::launch_co_settle(c, d_list + r.first, r.second, label, cw, wmax, t_out));
+    }
+    return JET_OK;
+  }
   const int64_t len = (int64_t)hlist.size();
   std::vector<int64_t> P((size_t)len + 1, 0);
-  int64_t biggest = 0, longest = 1;
   for (int64_t i = 0; i < len; ++i) {
-    const int64_t t = co_table(s.hdeg[(size_t)hlist[(size_t)i]], c.n);
+    int64_t t = co_table(s.hdeg[(size_t)hlist[(size_t)i]], c.n);
+    if (t <= jet::kCoLdsTable) t = 0;
     P[(size_t)i + 1] = P[(size_t)i] + t;
     biggest = std::max(biggest, t);
   }
-  for (const auto &r : rounds) longest = std::max(longest, r.second);
   const int64_t slots = std::max<int64_t>(1, std::max(biggest, std::min(P[(size_t)len], c.co_slots)));
   int rc = co_reserve(c, longest, len + 1, slots);
   if (rc != JET_OK) return rc;
@@ -770,14 +785,15 @@ int co_run(Ctx &c, const int32_t *d_list, const std::vector<int32_t> &hlist,
   return JET_OK;
 }
 
-// list[len] (device) holds distinct vertex IDs; its host copy in *host
+// list[len] (device) holds distinct vertex IDs; its host copy in *host where co_run needs it
 int co_check_list(Ctx &c, const int32_t *list, int64_t len, const char *what, std::vector<int32_t> *host) {
   jet::CoState &s = *c.co;
   HIP_OR_FAIL(&c, jet::launch_co_check(c, list, len, s.ctr + 1));
   int32_t bad = 0;
-  host->resize((size_t)len);
+  const bool copy = co_large_tables(c);
+  host->resize(copy ? (size_t)len : 0);
   HIP_OR_FAIL(&c, hipMemcpyAsync(&bad, s.ctr + 1, sizeof(int32_t), hipMemcpyDeviceToHost, c.stream));
-  if (len > 0)
+  if (copy && len > 0)
     HIP_OR_FAIL(&c, hipMemcpyAsync(host->data(), list, sizeof(int32_t) * (size_t)len, hipMemcpyDeviceToHost,
                                    c.stream));
   HIP_OR_FAIL(&c, hipStreamSynchronize(c.stream));

@@ -246,6 +246,7 @@ struct CoState {
   uint64_t *qnet = nullptr;          // [m] floor(w(e) 2^32 / (|e| - 1)), 0 for single-pin nets
   int64_t *deg = nullptr;            // [n] sum over incident nets of (|e| - 1)
   std::vector<int64_t> hdeg;         // host copy
+  int64_t max_deg = 0;               // largest of them
   int64_t *cw = nullptr;             // [n] cluster weights of jet_coarsen's own clustering
   int32_t *tp = nullptr, *tt = nullptr;  // [n] proposals, targets after swap prevention
   int32_t *gcnt = nullptr, *gslot = nullptr, *newlab = nullptr, *flag = nullptr;  // [n]
@@ -257,7 +258,7 @@ struct CoState {
   int64_t *ptab = nullptr;           // [ptab_len] rating-table offsets over list positions
   int64_t tab_slots = 0;
   CoSlot *tab = nullptr;             // [tab_slots] rating tables of one launch
-  int32_t *ctr = nullptr;            // [4] device counters: groups, bad entries, clusters
+  int32_t *ctr = nullptr;            // [4] device counters: groups, bad entries, clusters, members placed
   int32_t *ngroups = nullptr;        // == ctr
 };
 
@@ -522,6 +523,7 @@ hipError_t launch_build_adj(Ctx &c);
 bool graph_afterburner(const Ctx &c);
 hipError_t launch_ab_graph(Ctx &c, const int32_t *part, const LoopCtl *lc, int32_t want);
 
+constexpr int64_t kCoLdsTable = 512;  // largest rating table (slots) that needs no global scratch
 // k_coarsen.hip: synchronous clustering (Section 6, Algorithm 4)
 hipError_t launch_co_prepare(Ctx &c);
 hipError_t launch_co_init(Ctx &c, int32_t *label, int64_t *cw);

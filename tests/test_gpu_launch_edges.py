@@ -170,3 +170,26 @@ def test_network_batch_edges(B):
     tol = 4.0 * (B + 256) * 2.0 ** -24
     assert abs(loss - ref_loss) <= tol
     assert np.all(np.abs(g.cpu().numpy() - ref_g) <= tol * np.maximum(1.0, np.abs(ref_g)))
+
+
+@pytest.mark.parametrize("members", [63, 64, 65, 300])
+@pytest.mark.parametrize("size", [32, 33, 34, 256, 257, 258])
+def test_coarsening_table_and_group_edges(size, members):
+    """Vertices whose rating table is the last of one size or the first of the next (a net of `size`
+    pins alone around them), beside a centre that `members` leaves propose to in one sub-round."""
+    star = [[0, i] for i in range(1, members + 1)]
+    n0 = members + 1
+    nets = star + [list(range(n0 + j * size, n0 + (j + 1) * size)) for j in range(6)]
+    n = n0 + 6 * size
+    off = np.concatenate([[0], np.cumsum([len(e) for e in nets])]).astype(np.int64)
+    vw = (np.arange(n) % 4 + 1).astype(np.int32)
+    hg = W.Hypergraph(n=n, m=len(nets), off=off, pins=np.concatenate(nets).astype(np.int32), k=2, eps=0.05, vtx_w=vw)
+    order = np.concatenate([[0], np.random.default_rng(size).permutation(np.arange(1, n))]).astype(np.int32)
+    say(f"net of {size} pins, group of {members}")
+    for wmax, first in ((20, 100), (members, 0)):
+        olab, ocnt = O.coarsen(hg, order, wmax, first, 1)
+        ctx = J().JetContext(hg)
+        lab, cnt = ctx.coarsen(torch.from_numpy(order).to("cuda"), wmax, first, 1)
+        ctx.close()
+        assert cnt == ocnt
+        assert np.array_equal(lab.cpu().numpy(), olab)
