@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <algorithm>
 #include <string>
 #include <vector>
 
@@ -434,6 +435,28 @@ struct Ctx {
 
   std::string last_error;
 };
+
+// Workgroups of kernel K that the card holds at once, a multiple of its eight XCDs.  A grid-stride
+// kernel launched with more leaves the rest for a second, mostly empty wave: 2,048 workgroups of a
+// kernel that fits 1,536 take as long as two rounds.
+template <auto K>
+int64_t resident_grid(int block) {
+  static const int64_t g = [](int b) {
+    int per_cu = 0, dev = 0, cus = 0;
+    if (hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
+        hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, K, b, 0) != hipSuccess || per_cu < 1)
+      return (int64_t)2048;
+    return std::max<int64_t>(8, (int64_t)per_cu * cus / 8 * 8);
+  }(block);
+  return g;
+}
+// Launches K with one workgroup per `blocks`, at most as many as are resident and c.grid_cap allows.
+template <auto K, typename... A>
+void launch_resident(Ctx &c, int64_t blocks, int block, A... args) {
+  const int64_t g = std::max<int64_t>(1, std::min<int64_t>({blocks, c.grid_cap, resident_grid<K>(block)}));
+  hipLaunchKernelGGL(K, dim3((unsigned)g), dim3((unsigned)block), 0, c.stream, args...);
+}
 
 // Unit net weights: one lane per vertex (the candidate and rebalancing gain passes) instead of eight.
 // One lane is right while the vertices are light (mean degree below lane_degree).

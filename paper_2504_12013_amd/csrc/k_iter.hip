@@ -1369,20 +1369,20 @@ hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const 
     }
     const bool few = c.max_low_degree < 32;
     const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
-    auto go = [&](auto kernel, int64_t per_block) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + per_block - 1) / per_block)),
-                         dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp,
-                         lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd);
-    };
+#define JET_CAND(GG, HW, N)                                                                                          \
+  launch_resident<k_candidates_bits<GG, HW, N>>(c, ((int64_t)c.n + 256 / GG - 1) / (256 / GG), 256, part, c.voff,    \
+                                                c.inc, c.ns, c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n,     \
+                                                tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd)
     if (!light_lanes(c)) {
-      if (hw == 1) few ? go(k_candidates_bits<8, 1, 5>, 32) : go(k_candidates_bits<8, 1, 9>, 32);
-      else if (hw == 2) few ? go(k_candidates_bits<8, 2, 5>, 32) : go(k_candidates_bits<8, 2, 9>, 32);
-      else few ? go(k_candidates_bits<8, 4, 5>, 32) : go(k_candidates_bits<8, 4, 9>, 32);
+      if (hw == 1) few ? JET_CAND(8, 1, 5) : JET_CAND(8, 1, 9);
+      else if (hw == 2) few ? JET_CAND(8, 2, 5) : JET_CAND(8, 2, 9);
+      else few ? JET_CAND(8, 4, 5) : JET_CAND(8, 4, 9);
     } else {
-      if (hw == 1) few ? go(k_candidates_bits<1, 1, 5>, 256) : go(k_candidates_bits<1, 1, 9>, 256);
-      else if (hw == 2) few ? go(k_candidates_bits<1, 2, 5>, 256) : go(k_candidates_bits<1, 2, 9>, 256);
-      else few ? go(k_candidates_bits<1, 4, 5>, 256) : go(k_candidates_bits<1, 4, 9>, 256);
+      if (hw == 1) few ? JET_CAND(1, 1, 5) : JET_CAND(1, 1, 9);
+      else if (hw == 2) few ? JET_CAND(1, 2, 5) : JET_CAND(1, 2, 9);
+      else few ? JET_CAND(1, 4, 5) : JET_CAND(1, 4, 9);
     }
+#undef JET_CAND
   } else
     hipLaunchKernelGGL((k_candidates<G>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
                        c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc,
@@ -1561,7 +1561,8 @@ void apply_launch(Ctx &c, int32_t *part, bool wide, T *phi, const LoopCtl *lc, i
   // `wide` only sizes the grid: one wave per group of chunks when the host expects the net-centric
   // path (either grid gives the same result)
   const int64_t groups = ((int64_t)c.nchunks + 4 * kApplyU - 1) / (4 * kApplyU);
-  const unsigned grid = wide ? (unsigned)std::max<int64_t>(kApplyGrid, std::min<int64_t>(groups, 1 << 20)) : kApplyGrid;
+  const int64_t fits = std::min<int64_t>(kApplyGrid, resident_grid<k_apply<NW, T>>(kApplyBlock));
+  const unsigned grid = (unsigned)(wide ? std::max<int64_t>(fits, std::min<int64_t>(groups, 1 << 20)) : fits);
   hipLaunchKernelGGL((k_apply<NW, T>), dim3(grid), dim3(kApplyBlock), 0, c.stream, c.moves, c.voff, c.inc, c.off,
                      c.pins, c.chunks, c.pnet, c.nchunks, c.mid_nets, c.nmid, c.big_nets, c.nbig, c.nw, c.p, c.k, part,
                      phi, c.ns, c.mvfrom, c.bigmv, c.apply_divisor, c.st, lc, want, union_of(c), c.apply_xcd);

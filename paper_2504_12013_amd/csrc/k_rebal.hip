@@ -19,6 +19,7 @@
 #include <algorithm>
 #include <climits>
 
+#include "chunk.h"
 #include "conn.h"
 #include "dev_util.h"
 #include "entry.h"
@@ -218,7 +219,8 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
                                                         int32_t *__restrict__ list, int32_t *__restrict__ slot,
                                                         uint8_t *__restrict__ mvfrom,
                                                         const int32_t *__restrict__ hubs, int32_t nhubs,
-                                                        int32_t *__restrict__ hlist, const LoopCtl *lctl) {
+                                                        int32_t *__restrict__ hlist, int32_t list_blocks,
+                                                        const LoopCtl *lctl) {
   JET_GATE(lctl, kPhRb);
   __shared__ int64_t bw[kMaxK];
   __shared__ int32_t lc[kMaxK], lbase[kMaxK];
@@ -230,9 +232,8 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
     lc[b] = 0;
   }
   __syncthreads();
-  // hub vertices that may move, by their index in the hub list (k_hub.hip)
-  for (int32_t h0 = blockIdx.x * kListBlock; h0 < nhubs; h0 += gridDim.x * kListBlock) {  // block-uniform
-    const int32_t h = h0 + tid;
+  if ((int32_t)blockIdx.x >= list_blocks) {  // hub vertices that may move, by their index in the hub list
+    const int32_t h = ((int32_t)blockIdx.x - list_blocks) * kListBlock + tid;
     bool e = false;
     if (h < nhubs) {
       const int32_t v = hubs[h];
@@ -240,11 +241,12 @@ __global__ __launch_bounds__(kListBlock) void k_rb_list(const int32_t *__restric
       e = hb > lmax && 2 * c <= 3 * (hb - A);
     }
     const uint64_t mm = ballot(e);
-    if (!mm) continue;  // wave-uniform, no barrier in the loop
+    if (!mm) return;  // wave-uniform, no barrier follows
     int32_t base = 0;
     if (lane_id() == 0) base = atomicAdd(&st->rb_nhub, __popcll(mm));
     base = __shfl(base, 0, kWave);
     if (e) hlist[base + rank_below(mm)] = h;
+    return;
   }
   const int64_t r0 = (int64_t)blockIdx.x * (kListBlock * kListPer) + tid;
   int32_t pv[kListPer];
@@ -429,7 +431,7 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
 // bit-sliced as in the candidate pass (conn.h).  The valid targets form a mask (b != s, room for v's
 // weight, outside the deadzone); the best is the lowest block of largest count in it (counts of zero
 // included, as for the lane-group kernel).  k = 128 took 16 lanes per vertex with six exchanges and 24
-// instructions per net on each: 85 us per pass on 300,000 SAT-like vertices against SLICED us now.
+// instructions per net on each: 85 us per pass on 300,000 SAT-like vertices against 30 us now.
 template <int G, int HW, int N>
 __global__ __launch_bounds__(256) void k_rb_gain_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
@@ -725,6 +727,117 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
   if (tid == 0 && s_deg) atomicAdd((unsigned long long *)&st->mv_inc, s_deg);
 }
 
+// The selection of at most kWaveEntries entries by the first wave of the workgroup alone: no barriers,
+// the same passes with a histogram of the wave's own.  Other threads return at once.  Such lists (nearly
+// all of a multilevel run's) are a chain of passes, each two barriers of sixteen waves in the version for
+// whole workgroups below.
+constexpr int kWavePer = 4;
+constexpr int kWaveEntries = kWave * kWavePer;
+__device__ __forceinline__ void select_wave(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
+                                            int32_t b, DevStatus *st, int4 *__restrict__ moves,
+                                            int32_t *__restrict__ sel_target, int32_t *__restrict__ part,
+                                            uint8_t *__restrict__ mvfrom, const int64_t *__restrict__ voff,
+                                            int32_t *__restrict__ bigmv, int32_t *hmoves) {
+  __shared__ unsigned long long whw[256];
+  __shared__ int32_t whc[256], w_thr, w_done;
+  __shared__ int64_t w_need;
+  if (threadIdx.x >= kWave) return;
+  const int l = lane_id();
+  uint32_t k0[kWavePer], k4[kWavePer], wt[kWavePer];
+  uint32_t alive = 0u, sel = 0u;
+#pragma unroll
+  for (int j = 0; j < kWavePer; ++j) {
+    const int32_t i = j * kWave + l;
+    k0[j] = k4[j] = wt[j] = 0u;
+    if (i < len) {
+      const uint32_t *p = list + (int64_t)i * kEntryWords;
+      k0[j] = p[0];
+      k4[j] = p[4];
+      wt[j] = p[7];
+    }
+    if (wt[j] != 0u) alive |= 1u << j;
+  }
+  if (l == 0) w_need = need;
+  bool done = false;
+#pragma unroll 1
+  for (int x = d >> 2; x < 5 && !done; ++x) {  // wave-uniform
+    uint32_t cur[kWavePer];
+    uint32_t an = 0xffffffffu, orr = 0u;
+#pragma unroll
+    for (int j = 0; j < kWavePer; ++j) {
+      cur[j] = x == 0 ? k0[j] : k4[j];
+      if ((alive >> j) & 1u) {
+        if (x >= 1 && x <= 3) cur[j] = list[(int64_t)(j * kWave + l) * kEntryWords + x];
+        an &= cur[j];
+        orr |= cur[j];
+      }
+    }
+#pragma unroll
+    for (int o = kWave / 2; o >= 1; o >>= 1) {
+      an &= (uint32_t)__shfl_xor((int)an, o, kWave);
+      orr |= (uint32_t)__shfl_xor((int)orr, o, kWave);
+    }
+    const uint32_t diff = an ^ orr;
+#pragma unroll 1
+    for (int y = x == (d >> 2) ? (d & 3) : 0; y < 4; ++y) {
+      const int sh = 8 * (3 - y);
+      if (((diff >> sh) & 0xffu) == 0u && !(x == 4 && y == 3)) continue;  // a shared byte changes nothing
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        whw[j * kWave + l] = 0ull;
+        whc[j * kWave + l] = 0;
+      }
+      wave_lds_sync();
+#pragma unroll
+      for (int j = 0; j < kWavePer; ++j) {
+        if (!((alive >> j) & 1u)) continue;
+        const uint32_t dg = (cur[j] >> sh) & 0xffu;
+        atomicAdd(&whw[dg], (unsigned long long)wt[j]);
+        atomicAdd(&whc[dg], 1);
+      }
+      wave_lds_sync();
+      pass_threshold(whw, whc, w_need, &w_thr, &w_need, &w_done);
+      wave_lds_sync();
+      const uint32_t thr = (uint32_t)w_thr;
+      done = w_done != 0;
+      wave_lds_sync();
+#pragma unroll
+      for (int j = 0; j < kWavePer; ++j) {
+        if (!((alive >> j) & 1u)) continue;
+        const uint32_t dg = (cur[j] >> sh) & 0xffu;
+        if (dg > thr || (dg == thr && done)) sel |= 1u << j;
+        if (dg != thr || done) alive &= ~(1u << j);
+      }
+      if (done) break;
+    }
+  }
+  const int32_t cnt = __popc(sel), incl = wave_incl_scan(cnt), tot = __shfl(incl, kWave - 1, kWave);
+  if (tot == 0) return;
+  int32_t base = 0;
+  if (l == 0) {
+    base = atomicAdd(&st->n_moves, tot);
+    if (hmoves) atomicAdd(hmoves, tot);
+  }
+  int32_t pos = __shfl(base, 0, kWave) + incl - cnt;
+  int64_t dsum = 0;
+#pragma unroll
+  for (int j = 0; j < kWavePer; ++j) {
+    const bool e = (sel >> j) & 1u;
+    int64_t dg = 0;
+    if (e) {
+      uint32_t ent[kEntryWords];
+      load_entry(list + (int64_t)(j * kWave + l) * kEntryWords, ent);
+      dg = voff[ent[5] + 1] - voff[ent[5]];
+      put_move(ent, b, pos, moves, sel_target, part, mvfrom);
+    }
+    push_big_move(dg > kLaneDegree, pos, st, bigmv);
+    pos += e ? 1 : 0;
+    dsum += dg;
+  }
+  dsum = wave_sum(dsum);
+  if (l == 0 && dsum) atomicAdd((unsigned long long *)&st->mv_inc, (unsigned long long)dsum);
+}
+
 constexpr int kRegPer = 4;  // entries per thread of the selection in registers
 
 // The selection of at most kSelThreads * kRegPer entries: every thread keeps its entries in
@@ -983,6 +1096,11 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
   for (int d = d0; d < 20; ++d) {
     __syncthreads();  // every thread has finished reading the previous pass's histogram
     len = s_len;
+    if (len <= kWaveEntries) {  // block-uniform: one wave
+      select_wave(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
+                  u.lcs ? &st->hmoves[sgm / k] : nullptr);
+      break;
+    }
     if (len <= kSelThreads * kRegPer) {  // block-uniform: the rest of the list fits the registers
       select_registers(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
                        u.lcs ? &st->hmoves[sgm / k] : nullptr);
@@ -1078,29 +1196,32 @@ hipError_t gain_launch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *l
   if (c.H > 1)
     hipLaunchKernelGGL(k_rb_list_union, dim3(grid_for(c.n, 8 * kUnionTile, c.grid_cap)), dim3(kUnionTile), 0, c.stream, part, c.vw, c.voff,
                        c.n, c.k, c.st, c.rb_list, c.rb_slot, c.mvfrom, lc, u);
-  else
-    hipLaunchKernelGGL(k_rb_list, dim3((unsigned)((c.n + kListBlock * kListPer - 1) / (kListBlock * kListPer))),
-                       dim3(kListBlock), 0, c.stream, part, c.vw, c.voff, c.n, c.k, c.lmax, c.A, c.st, c.rb_list,
-                       c.rb_slot, c.mvfrom, c.hubs, c.nhubs, c.rb_hlist, lc);
+  else {
+    // the first workgroups take the vertices, the others the hubs
+    const int32_t lb = (int32_t)(((int64_t)c.n + kListBlock * kListPer - 1) / (kListBlock * kListPer));
+    hipLaunchKernelGGL(k_rb_list, dim3((unsigned)(lb + (c.nhubs + kListBlock - 1) / kListBlock)), dim3(kListBlock), 0,
+                       c.stream, part, c.vw, c.voff, c.n, c.k, c.lmax, c.A, c.st, c.rb_list, c.rb_slot, c.mvfrom,
+                       c.hubs, c.nhubs, c.rb_hlist, lb, lc);
+  }
   // the list length is known on the device only: a persistent grid walks it; unit net weights take the
   // bit-sliced kernel (one lane per vertex on light levels, eight otherwise)
   if (c.unit_nw) {
     const bool few = c.max_low_degree < 32;
     const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
-    auto go = [&](auto kernel, int64_t per_block) {
-      hipLaunchKernelGGL(kernel, dim3((unsigned)std::min<int64_t>(c.grid_cap, (c.n + per_block - 1) / per_block)),
-                         dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k,
-                         c.lmax, dz, c.st, c.rb_keys, lc, u, c.rb_xcd);
-    };
+#define JET_GAIN(GG, HW, N)                                                                                         \
+  launch_resident<k_rb_gain_bits<GG, HW, N>>(c, ((int64_t)c.n + 256 / GG - 1) / (256 / GG), 256, part, c.voff,      \
+                                             c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st, \
+                                             c.rb_keys, lc, u, c.rb_xcd)
     if (light_lanes(c)) {
-      if (hw == 1) few ? go(k_rb_gain_bits<1, 1, 5>, 256) : go(k_rb_gain_bits<1, 1, 9>, 256);
-      else if (hw == 2) few ? go(k_rb_gain_bits<1, 2, 5>, 256) : go(k_rb_gain_bits<1, 2, 9>, 256);
-      else few ? go(k_rb_gain_bits<1, 4, 5>, 256) : go(k_rb_gain_bits<1, 4, 9>, 256);
+      if (hw == 1) few ? JET_GAIN(1, 1, 5) : JET_GAIN(1, 1, 9);
+      else if (hw == 2) few ? JET_GAIN(1, 2, 5) : JET_GAIN(1, 2, 9);
+      else few ? JET_GAIN(1, 4, 5) : JET_GAIN(1, 4, 9);
     } else {
-      if (hw == 1) few ? go(k_rb_gain_bits<8, 1, 5>, 32) : go(k_rb_gain_bits<8, 1, 9>, 32);
-      else if (hw == 2) few ? go(k_rb_gain_bits<8, 2, 5>, 32) : go(k_rb_gain_bits<8, 2, 9>, 32);
-      else few ? go(k_rb_gain_bits<8, 4, 5>, 32) : go(k_rb_gain_bits<8, 4, 9>, 32);
+      if (hw == 1) few ? JET_GAIN(8, 1, 5) : JET_GAIN(8, 1, 9);
+      else if (hw == 2) few ? JET_GAIN(8, 2, 5) : JET_GAIN(8, 2, 9);
+      else few ? JET_GAIN(8, 4, 5) : JET_GAIN(8, 4, 9);
     }
+#undef JET_GAIN
   } else {
     const unsigned grid = (unsigned)std::min<int64_t>(c.grid_cap, (c.n + VPB - 1) / VPB);
     hipLaunchKernelGGL((k_rb_gain<G>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
