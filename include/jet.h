@@ -198,8 +198,8 @@ int jet_afterburner(jet_ctx *ctx, const int32_t *part, const int32_t *t, const i
 int jet_rebalance_round(jet_ctx *ctx, int32_t *part, int32_t deadzone_ppm, int32_t *sel_target, int32_t *moved);
 
 /* Diagnostics of the context's last refinement or rebalancing call ([host], either may be NULL):
- * the times the host read the device loop record (one stream synchronisation each) and the
- * iteration pieces it launched (graph replays, or eager launches with JET_OPT_GRAPH 0). */
+ * the reports of the device loop the host looked at and the pieces of iterations it launched
+ * (graph replays, or eager launches with JET_OPT_GRAPH 0). */
 int jet_loop_counts(jet_ctx *ctx, int64_t *host_polls, int64_t *pieces);
 
 /* ---- synchronous clustering of the coarsening phase (Section 6, Algorithm 4) ----
@@ -309,15 +309,16 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * vertices, inside the one workgroup per block otherwise; default 2^18, 0 = always.  Results do
  * not depend on it. */
 #define JET_OPT_SEL_SPLIT_MIN 5
-/* 1 (default): the Jet loop (Algorithm 1) runs on the device from a captured HIP graph of one
- * iteration, replayed several times between two host looks at the loop's state; 0: the same
- * kernels are launched one by one (same results). */
+/* 1 (default): the Jet loop (Algorithm 1) runs on the device from captured HIP graphs of its
+ * pieces (Jet phase, rebalancing round, rollback), launched as the loop's state asks for them;
+ * 0: the same kernels are launched one by one (same results). */
 #define JET_OPT_GRAPH 6
-/* Rebalancing rounds (Section 4.3) a replayed iteration holds room for, 1..64, default 1; an
- * iteration that needs more continues in the next replay.  Results do not depend on it. */
+/* Rebalancing rounds (Section 4.3) a replayed iteration of a batch holds room for, 1..64, default 4;
+ * an iteration that needs more continues in the next replay.  A single hypergraph's rounds are
+ * launched one by one.  Results do not depend on it. */
 #define JET_OPT_RB_SLOTS 7
-/* Most replays of the iteration between two host looks at the loop's state, 1..1024, default 8.
- * Replays after the loop finished return at once.  Results do not depend on it. */
+/* Pieces of the loop in flight at once, 1..1024, default 2: one runs, one more (at most) waits
+ * behind it when the host can foresee which it will be.  Results do not depend on it. */
 #define JET_OPT_REPLAYS 8
 /* Workgroups of the persistent (grid-stride) kernels: candidates, afterburner chunks, move
  * selection, rebalancing gains; 64..65536, default 2048.  Results do not depend on it. */

@@ -9,6 +9,7 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
+#include <deque>
 #include <new>
 #include <string>
 #include <thread>
@@ -194,6 +195,7 @@ void free_ctx(Ctx &c) {
   if (c.lcs && c.lcs != c.lc) (void)hipFree(c.lcs);
   co_free(c);
   jet::flow_free(c);
+  if (c.mail) (void)hipHostFree(c.mail);
   if (c.hlc) (void)hipHostFree(c.hlc);
   if (c.hlcs && c.hlcs != c.hlc) (void)hipHostFree(c.hlcs);
 }
@@ -447,6 +449,8 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
   HIP_OR_FAIL(&c, hipMemsetAsync(c.lc, 0, sizeof(jet::LoopCtl), c.stream));
   HIP_OR_FAIL(&c, hipHostMalloc((void **)&c.hlc, sizeof(jet::LoopCtl)));
   std::memset(c.hlc, 0, sizeof(jet::LoopCtl));
+  HIP_OR_FAIL(&c, hipHostMalloc((void **)&c.mail, 64, hipHostMallocMapped | hipHostMallocCoherent));
+  *c.mail = 0ull;
   if (c.H == 1) {  // the record is the gate record (a union gets per-hypergraph records on top)
     c.lcs = c.lc;
     c.hlcs = c.hlc;
@@ -492,7 +496,7 @@ void fill_record(jet::LoopCtl &r, const jet_params &prm, bool rb_only, int32_t t
 }
 
 void drop_graph(Ctx &c) {
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < jet::kTickPieces; ++i) {
     if (c.gexec[i]) (void)hipGraphExecDestroy(c.gexec[i]);
     if (c.graph[i]) (void)hipGraphDestroy(c.graph[i]);
     c.gexec[i] = nullptr;
@@ -504,7 +508,7 @@ void drop_graph(Ctx &c) {
 // when an option or the instrumentation changes what they launch).
 int ensure_graphs(Ctx &c) {
   if (c.gexec[0]) return JET_OK;
-  for (int kind = 0; kind < 4; ++kind) {
+  for (int kind = 0; kind < jet::kTickPieces; ++kind) {
     hipStream_t user = c.stream;
     c.stream = c.gstream;
     hipError_t e = hipStreamBeginCapture(c.gstream, hipStreamCaptureModeThreadLocal);
@@ -529,15 +533,74 @@ int launch_piece(Ctx &c, int kind) {
   return JET_OK;
 }
 
+// Which piece the host launches ahead of the device: the phase that follows the current one.  The
+// number of rebalancing rounds of an iteration is guessed from the number of the iteration before it
+// (what followed that number last time); the guess is acted on while the last one of its kind was right.
+struct Ahead {
+  static constexpr int kKinds = 17;  // rounds of the iteration before: 0..15, more
+  int32_t guess[kKinds] = {};
+  bool sure[kKinds];
+  int32_t prev = 0;  // rounds of the last finished iteration
+  bool rb_only;      // rebalancing alone: another round is the likely thing
+  explicit Ahead(bool rb) : rb_only(rb) { std::fill(sure, sure + kKinds, true); }
+  static int slot(int32_t rounds) { return std::min<int32_t>(rounds, kKinds - 1); }
+  // an iteration with this many rounds has ended
+  void learn(int32_t rounds) {
+    const int s = slot(prev);
+    sure[s] = guess[s] == rounds;
+    guess[s] = rounds;
+    prev = rounds;
+  }
+  // the phase after the one running (its rounds done so far, the round's last chance), -1: wait and see
+  int32_t next(const jet::LoopMail &m) const {
+    if (rb_only) return jet::kPhRb;
+    const int s = slot(prev);
+    if (m.phase == jet::kPhJet) {
+      if (!sure[s]) return -1;
+      if (guess[s] > 0) return jet::kPhRb;
+      return m.last ? -1 : jet::kPhJet;
+    }
+    if (m.phase == jet::kPhRb) {
+      if (m.rb_rounds + 1 < guess[s]) return jet::kPhRb;
+      if (m.rb_rounds + 1 == guess[s] && sure[s] && !m.last) return jet::kPhJet;
+    }
+    return -1;
+  }
+};
+
+int piece_of(int32_t phase) {
+  return phase == jet::kPhJet ? jet::kTickJet : phase == jet::kPhRb ? jet::kTickRb : jet::kTickRoll;
+}
+
+// Waits until a control kernel after number `seen` has reported (JET_OK), or the stream has ended or
+// failed without one.
+int wait_mail(Ctx &c, uint32_t seen, jet::LoopMail *m) {
+  for (uint32_t spin = 1;; ++spin) {
+    *m = jet::read_mail(__atomic_load_n(c.mail, __ATOMIC_ACQUIRE));
+    if (m->seq != (seen & jet::kMailSeqMask)) return JET_OK;
+    if (spin % 4096 == 0) {
+      const hipError_t q = hipStreamQuery(c.stream);
+      if (q == hipErrorNotReady) {
+        (void)hipGetLastError();
+        std::this_thread::yield();
+        continue;
+      }
+      if (q != hipSuccess) return fail_hip(&c, q, "waiting for the device loop");
+      *m = jet::read_mail(__atomic_load_n(c.mail, __ATOMIC_ACQUIRE));
+      return m->seq != (seen & jet::kMailSeqMask) ? JET_OK : fail(&c, JET_EHIP, "the device loop did not report");
+    }
+    __builtin_ia32_pause();
+  }
+}
+
 // The Jet loop (Algorithm 1) for every temperature, or (rb_only) the rebalancing rounds alone, on
-// the device.  The host launches pieces of iterations and looks at the loop record between
-// batches of them; what it launches only decides how much work is in flight, never what is
-// computed: a piece whose phase the record is not in does nothing.
-//   phase Jet: min(limit - round, max_iters - it) iterations at least remain in the round (fewer
-//              only at a fixed point), up to `replays` of them are launched, each a Jet piece, or
-//              a Jet + rebalancing piece once this call has seen a rebalancing round;
-//   phase Rb:  rebalancing pieces, as many as the call's rounds per iteration so far suggest;
-//   phase Roll: the rollback piece (the next round starts at the next look).
+// the device.  The host launches pieces -- a Jet phase, a rebalancing round, a rollback -- and follows
+// the word each one's control kernel stores in pinned memory.  One piece runs, one more waits behind
+// it when Ahead can name it; what is launched only decides how much work is in flight, never what is
+// computed: a piece whose phase the record is not in does nothing, but its five to nine launches take
+// 15 to 40 us.  Iterations replayed in batches of eight with four rounds each, and a copy and a
+// synchronisation between batches, left two thirds of the launched rounds empty: 263 of 292 on a 4M
+// vertex mesh at k = 64, 9 of its 25 ms.
 int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_stats *out, jet_trace *trace,
              int32_t trace_cap, int32_t *trace_len) {
   int rc = check_params(c, prm, !rb_only);
@@ -559,50 +622,51 @@ int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_sta
   rc = build_state(c, c.cpart);
   if (rc != JET_OK) return rc;
   fill_record(c.hlcs[0], *prm, rb_only, trace_cap, c.lmax, dz, c.A);
+  *c.mail = 0ull;  // nothing of this context runs here
   HIP_OR_FAIL(&c, hipMemcpyAsync(c.lcs, c.hlcs, sizeof(jet::LoopCtl), hipMemcpyHostToDevice, c.stream));
   HIP_OR_FAIL(&c, jet::launch_loop_init(c));
   if (c.use_graph) {
     rc = ensure_graphs(c);
     if (rc != JET_OK) return rc;
   }
-  const int64_t piece_cap = (int64_t)(rb_only ? 1 : prm->num_tau) * ((int64_t)prm->max_iters + 2) *
-                                ((int64_t)prm->max_rebalance_rounds / std::max(1, c.rb_slots) + 3) + 16;
+  const double piece_cap = 2.0 * (rb_only ? 1 : prm->num_tau) * ((double)prm->max_iters + 2.0) *
+                               ((double)prm->max_rebalance_rounds + 3.0) + 16.0;
   int64_t pieces = 0;
   c.polls = 0;
-  int32_t phase = rb_only ? jet::kPhRb : jet::kPhJet;
-  int32_t left = 1, rb_left = 1;
-  bool rb_seen = false;
-  for (;;) {
-    if (phase == jet::kPhRoll) {
-      rc = launch_piece(c, jet::kTickRoll);
+  const size_t lead = (size_t)std::min<int32_t>(c.replays, 2);
+  Ahead guess(rb_only);
+  std::deque<int32_t> flight;  // phases of the launched pieces that have not reported
+  jet::LoopMail m{};           // the last report looked at; before the first one, what it is likely to say
+  m.phase = rb_only ? jet::kPhRb : jet::kPhJet;
+  uint32_t seen = 0;
+  flight.push_back(jet::kPhAny);  // the set-up's control kernel reports too
+  while (m.phase != jet::kPhDone && !m.err) {
+    // the piece of the current phase, then the one behind it
+    const bool has = std::find(flight.begin(), flight.end(), m.phase) != flight.end();
+    const int32_t add = !has ? m.phase : flight.size() < lead && flight.back() == m.phase ? guess.next(m) : -1;
+    if (add >= 0) {
+      rc = launch_piece(c, piece_of(add));
+      if (rc != JET_OK) return rc;
+      flight.push_back(add);
       pieces += 1;
-    } else if (phase == jet::kPhRb) {
-      for (int32_t g = 0; g < rb_left && rc == JET_OK; ++g) rc = launch_piece(c, jet::kTickRb);
-      pieces += rb_left;
-    } else {
-      const int kind = rb_seen ? jet::kTickJetRb : jet::kTickJet;
-      for (int32_t g = 0; g < left && rc == JET_OK; ++g) rc = launch_piece(c, kind);
-      pieces += left;
+      continue;
     }
+    if ((double)pieces > piece_cap) return fail(&c, JET_EHIP, "the device loop did not finish within its bound");
+    const jet::LoopMail was = m;
+    rc = wait_mail(c, seen, &m);
     if (rc != JET_OK) return rc;
-    HIP_OR_FAIL(&c, hipMemcpyAsync(c.hlc, c.lc, sizeof(jet::LoopCtl), hipMemcpyDeviceToHost, c.stream));
-    rc = read_status(c);
     c.polls += 1;
-    if (rc != JET_OK) return rc;
-    const jet::LoopCtl &h = *c.hlc;
-    phase = h.phase;
-    if (phase == jet::kPhDone) break;
-    if (pieces > piece_cap) return fail(&c, JET_EHIP, "the device loop did not finish within its bound");
-    rb_seen = rb_seen || h.rebalance_rounds > 0 || h.rb_rounds > 0;
-    left = 1;
-    if (phase == jet::kPhJet)
-      left = (int32_t)std::max<int64_t>(1, std::min<int64_t>({(int64_t)h.limit - h.round,
-                                                              (int64_t)h.max_iters - h.it, (int64_t)c.replays}));
-    // rounds per iteration so far, less the rounds this iteration already ran, in pieces
-    const int64_t per_it = h.iterations > 0 ? (h.rebalance_rounds + h.iterations - 1) / h.iterations : 1;
-    const int64_t want = std::max<int64_t>(1, per_it - h.rb_rounds);
-    rb_left = (int32_t)std::max<int64_t>(1, std::min<int64_t>((want + c.rb_slots - 1) / c.rb_slots, c.replays));
+    bool ran = false;  // a piece of the phase we knew of has run
+    for (uint32_t i = (m.seq - seen) & jet::kMailSeqMask; i > 0 && !flight.empty(); --i) {
+      ran = ran || flight.front() == was.phase;
+      flight.pop_front();
+    }
+    seen = m.seq;
+    if (ran && !rb_only && was.phase != jet::kPhRoll && m.phase != jet::kPhRb) guess.learn(m.rb_rounds);
   }
+  HIP_OR_FAIL(&c, hipMemcpyAsync(c.hlc, c.lc, sizeof(jet::LoopCtl), hipMemcpyDeviceToHost, c.stream));
+  rc = read_status(c);
+  if (rc != JET_OK) return rc;
   c.replays_done = pieces;
   HIP_OR_FAIL(&c, hipMemcpyAsync(part, c.cpart, sizeof(int32_t) * (size_t)c.n, hipMemcpyDeviceToDevice, c.stream));
   const jet::LoopCtl &h = *c.hlc;

@@ -92,6 +92,7 @@ struct LoopCtl {
   int32_t rb_rounds, rb_moved;      // the current iteration's rebalancing rounds
   int32_t improved;       // the current partition is the round's best and not in `best` yet: the next
                           // candidate pass copies it, a rollback has nothing to undo
+  uint32_t seq;           // control kernels run in this call
   int32_t ntrace;         // iteration records written (counted beyond the capacity too)
   int32_t iterations, rebalance_rounds, moves_executed;  // totals of the call
   int64_t km1;            // exact metric of the current partition
@@ -105,6 +106,22 @@ struct LoopCtl {
   int32_t trace_cap;
   int64_t lmax, dz, A;    // balance limit, deadzone threshold, ceil(W/k) of the hypergraph
 };
+
+// What the host follows of a running loop: one word per control kernel, stored by it in pinned memory.
+struct LoopMail {
+  uint32_t seq;       // low kMailSeqBits bits of LoopCtl::seq
+  int32_t phase;
+  int32_t rb_rounds;  // of the current iteration, once the next Jet phase runs of the last one (clipped)
+  bool last;          // the round ends with the current iteration unless that improves
+  bool err;           // a kernel reported an error
+};
+constexpr int kMailSeqBits = 24, kMailPhaseSh = 24, kMailRbSh = 27, kMailRbBits = 16, kMailLastSh = 43, kMailErrSh = 44;
+constexpr uint32_t kMailSeqMask = (1u << kMailSeqBits) - 1u;
+inline LoopMail read_mail(unsigned long long w) {
+  return LoopMail{(uint32_t)w & kMailSeqMask, (int32_t)((w >> kMailPhaseSh) & 7u),
+                  (int32_t)((w >> kMailRbSh) & ((1u << kMailRbBits) - 1u)), ((w >> kMailLastSh) & 1u) != 0,
+                  ((w >> kMailErrSh) & 1u) != 0};
+}
 
 // A launch of a phase returns at once unless some hypergraph of the gate record is in it.
 #define JET_GATE(lc, want)                                                      \
@@ -305,6 +322,10 @@ struct FlowState {
   int32_t *fcnt = nullptr;                    // [3] their sizes
 };
 
+// Pieces of an iteration that a single hypergraph's loop launches, and a union's tick of all phases.
+enum TickKind : int { kTickJet = 0, kTickRb = 1, kTickRoll = 2, kTickAll = 3 };
+constexpr int kTickPieces = 3;  // kinds of pieces of a single context
+
 struct Ctx {
   hipStream_t stream = nullptr;
   int32_t n = 0, m = 0, k = 0, nw_words = 1;  // nw_words = ceil(k/64) words per mask
@@ -404,17 +425,18 @@ struct Ctx {
   // device-resident loop
   LoopCtl *lc = nullptr;         // device loop record (the gate record of a union)
   LoopCtl *hlc = nullptr;        // pinned host mirror
+  unsigned long long *mail = nullptr;  // [1] pinned host memory the control kernel writes (read_mail)
   int32_t *cpart = nullptr;      // [n] the partition the loop works on (copied in and out per call)
   jet_trace *dtrace = nullptr;   // device iteration records
   int32_t dtrace_cap = 0;
   hipStream_t gstream = nullptr; // stream the iteration graph is captured on
   // captured pieces of an iteration (TickKind): Jet phase + end, Jet phase + rebalancing slots +
   // end, rebalancing slots + end, rollback
-  hipGraph_t graph[4] = {nullptr, nullptr, nullptr, nullptr};
-  hipGraphExec_t gexec[4] = {nullptr, nullptr, nullptr, nullptr};
+  hipGraph_t graph[kTickPieces] = {};
+  hipGraphExec_t gexec[kTickPieces] = {};
   bool use_graph = true;         // JET_OPT_GRAPH
-  int32_t rb_slots = 4;          // JET_OPT_RB_SLOTS: rebalancing rounds per replay
-  int32_t replays = 8;           // JET_OPT_REPLAYS: most replays per host poll
+  int32_t rb_slots = 4;          // JET_OPT_RB_SLOTS: rebalancing rounds of a union's tick
+  int32_t replays = 2;           // JET_OPT_REPLAYS: most pieces in flight
   int64_t polls = 0;             // host polls of the last call (diagnostic)
   int64_t replays_done = 0;      // graph replays or eager ticks of the last call
   DevProf *dprof = nullptr;      // device timing accumulators
@@ -526,7 +548,6 @@ hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *se
 // the device-resident loop (k_loop.hip)
 // the launches of one piece of an iteration (kTickAll: every phase, rb_slots rebalancing rounds),
 // gated by c.lc
-enum TickKind : int { kTickJet = 0, kTickJetRb = 1, kTickRb = 2, kTickRoll = 3, kTickAll = 4 };
 hipError_t launch_tick(Ctx &c, int kind);
 // loop records for a call: the host wrote each hypergraph's parameters into c.lcs; this completes
 // them from the status block (metric, overload, first phase) and sets the gate record

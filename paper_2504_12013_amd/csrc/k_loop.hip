@@ -2,18 +2,19 @@
 // strict improvement of the key (overload, metric), snapshot, iteration limit, fixed point, end of a
 // temperature round and rollback to its best partition) are taken by one small control kernel after
 // each phase on a loop record (LoopCtl); every kernel of the iteration returns at once unless the
-// record is in the phase it belongs to.  One iteration's launches -- the Jet phase, rb_slots
-// rebalancing rounds and the rollback, each followed by its control kernel -- form a "tick"; the host
-// captures a tick in a HIP graph once per context and replays it several times between two looks at
-// the record.  Ticks after the loop finished do nothing.  The sequence of states is exactly that of
-// the host loop it replaces (one Jet phase, then rebalancing rounds while a block is overloaded, a
-// round moved something and the cap allows, then the key), so results and per-iteration records do
-// not depend on how many ticks run between polls.
+// record is in the phase it belongs to.  The Jet phase, a rebalancing round and the rollback, each
+// followed by its control kernel, are the pieces of an iteration; the host captures each in a HIP
+// graph once per context and launches them by what the control kernel last reported in pinned memory.
+// A union of hypergraphs replays a "tick" of all of them (rb_slots rebalancing rounds) and looks at
+// the records in between.  Pieces and ticks after the loop finished do nothing.  The sequence of
+// states is exactly that of the host loop it replaces (one Jet phase, then rebalancing rounds while a
+// block is overloaded, a round moved something and the cap allows, then the key), so results and
+// per-iteration records do not depend on which pieces were launched ahead.
 //
 // The control kernel that leaves a phase also enters the next one (iteration stamp, counters, the
 // round's needs and list regions), and the next Jet phase's candidate pass, which reads every
 // vertex's block anyway, takes the snapshot of an improving iteration.  A launch costs 2 to 5 us here
-// even when its gate is closed, so a rebalancing round of 2,000 vertices went from 15 launches to 9.
+// even when its gate is closed, so a rebalancing round of 2,000 vertices went from 15 launches to 5.
 #include <algorithm>
 
 #include "dev_util.h"
@@ -148,6 +149,16 @@ __device__ __forceinline__ void clear_counters(DevStatus *st) {
   st->rb_nhub = 0;
 }
 
+// Tells the host where the loop is (one store to pinned memory).
+__device__ __forceinline__ void post(unsigned long long *mail, uint32_t seq, const LoopCtl &r, int32_t err) {
+  const unsigned long long rb = (unsigned long long)min(r.rb_rounds, (1 << kMailRbBits) - 1);
+  const unsigned long long last = r.round + 1 >= r.limit || r.it + 1 >= r.max_iters ? 1ull : 0ull;
+  __hip_atomic_store(mail,
+                     (unsigned long long)(seq & kMailSeqMask) | ((unsigned long long)r.phase << kMailPhaseSh) |
+                         (rb << kMailRbSh) | (last << kMailLastSh) | ((err != 0 ? 1ull : 0ull) << kMailErrSh),
+                     __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // One hypergraph: one thread per block.  Record, block weights and metric slots are loaded at
 // once and the decision runs on the copy in LDS: a single thread walking them in global memory took
 // 7 us at k = 64 and 12 us at k = 128, this takes 3 us.  When a rebalancing round follows, its needs
@@ -155,7 +166,7 @@ __device__ __forceinline__ void clear_counters(DevStatus *st) {
 constexpr int kCtlOne = 128;
 static_assert(kCtlOne >= kMaxK && kCtlOne >= kKm1Slots && kKm1Slots == kWave, "one thread per block and slot");
 __global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st, int32_t k, int64_t lmax,
-                                                     int32_t want, jet_trace *trace) {
+                                                     int32_t want, jet_trace *trace, unsigned long long *mail) {
   __shared__ LoopCtl r;
   __shared__ int64_t s_ovl[kCtlOne / kWave], s_cnt[kCtlOne / kWave], s_km1;
   const int b = threadIdx.x, w = b / kWave;
@@ -166,7 +177,7 @@ __global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st,
   int64_t slot = b < kKm1Slots ? st->slot[b].km1 : 0;
   int32_t cand = b < kKm1Slots ? (int32_t)st->slot[b].n_cand : 0;
   const int64_t km1_base = st->km1;
-  const int32_t moved = st->n_moves;
+  const int32_t moved = st->n_moves, err = st->err;
   const int64_t over = b < k ? max(bw - lmax, (int64_t)0) : 0;
   int64_t mx = over;
 #pragma unroll
@@ -180,10 +191,19 @@ __global__ __launch_bounds__(kCtlOne) void k_control(LoopCtl *lc, DevStatus *st,
     if (w == 0) s_km1 = km1_base + slot;
   }
   __syncthreads();
-  if (want != kPhAny && r.phase != want) return;  // block-uniform
+  const uint32_t seq = r.seq + 1;
+  if (want != kPhAny && r.phase != want) {  // block-uniform
+    if (b == 0) {
+      lc->seq = seq;
+      post(mail, seq, r, err);
+    }
+    return;
+  }
   __syncthreads();  // every thread has read the phase
   if (b == 0) {
     advance(r, want, max(s_ovl[0], s_ovl[1]), s_km1, moved, cand, trace);
+    r.seq = seq;
+    post(mail, seq, r, err);
     st->km1 = s_km1;
     clear_counters(st);
   }
@@ -356,7 +376,8 @@ static hipError_t launch_control(Ctx &c, int32_t want) {
     hipLaunchKernelGGL(k_control_union, dim3(1), dim3(kCtlThreads), 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, want,
                        union_of(c));
   else
-    hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlOne), 0, c.stream, c.lc, c.st, c.k, c.lmax, want, c.dtrace);
+    hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlOne), 0, c.stream, c.lc, c.st, c.k, c.lmax, want, c.dtrace,
+                       c.mail);
   return hipGetLastError();
 }
 
@@ -367,8 +388,8 @@ hipError_t launch_loop_init(Ctx &c) {
 
 hipError_t launch_tick(Ctx &c, int kind) {
   const LoopCtl *lc = c.lc;
-  const bool jet = kind == kTickJet || kind == kTickJetRb || kind == kTickAll;
-  const bool rb = kind == kTickJetRb || kind == kTickRb || kind == kTickAll;
+  const bool jet = kind == kTickJet || kind == kTickAll;
+  const bool rb = kind == kTickRb || kind == kTickAll;
   const bool roll = kind == kTickRoll || kind == kTickAll;
   hipError_t e = hipSuccess;
   if (jet) {
@@ -381,7 +402,7 @@ hipError_t launch_tick(Ctx &c, int kind) {
     if (e != hipSuccess) return e;
   }
   if (rb) {
-    for (int r = 0; r < c.rb_slots; ++r) {
+    for (int r = 0; r < (kind == kTickAll ? c.rb_slots : 1); ++r) {
       e = launch_rebalance_round(c, c.cpart, 0, nullptr, lc);
       if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhRb);
       if (e == hipSuccess) e = launch_control(c, kPhRb);

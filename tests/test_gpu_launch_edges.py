@@ -193,3 +193,27 @@ def test_coarsening_table_and_group_edges(size, members):
         ctx.close()
         assert cnt == ocnt
         assert np.array_equal(lab.cpu().numpy(), olab)
+
+
+@pytest.mark.parametrize("replays", [1, 2])
+@pytest.mark.parametrize("overloaded", [False, True])
+def test_loop_launches_what_the_loop_asks_for(replays, overloaded):
+    """One piece in flight: exactly a piece per Jet phase, rebalancing round and rollback; two: at most
+    one more per piece, and the same refinement."""
+    hg = W.random_hypergraph(3000, 5000, 6, 21, smin=2, smax=7, vw_max=3, eps=0.05)
+    part = W.part_roundrobin(hg.n, 6, 2)
+    if overloaded:
+        part[: hg.n // 3] = 0
+    kw = dict(tau=(0.75, 0.375, 0.0), limit=5)
+    say(f"pieces in flight {replays}, overloaded start {overloaded}")
+    ref, orc, ost, otr = O.refine(hg, part, **kw)
+    ctx = J().JetContext(hg)
+    ctx.set_option(J().JET_OPT_REPLAYS, replays)
+    d = torch.from_numpy(part).to("cuda")
+    rc, st, tr = ctx.refine(d, trace_cap=4096, **kw)
+    need = ost["iterations"] + ost["rebalance_rounds"] + 3
+    pieces = ctx.loop_counts()[1]
+    ctx.close()
+    assert rc == orc and tr == otr
+    assert np.array_equal(d.cpu().numpy(), ref)
+    assert pieces == need if replays == 1 else need <= pieces <= 2 * need
