@@ -727,125 +727,55 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
   if (tid == 0 && s_deg) atomicAdd((unsigned long long *)&st->mv_inc, s_deg);
 }
 
-// The selection of at most kWaveEntries entries by the first wave of the workgroup alone: no barriers,
-// the same passes with a histogram of the wave's own.  Other threads return at once.  Such lists (nearly
-// all of a multilevel run's) are a chain of passes, each two barriers of sixteen waves in the version for
-// whole workgroups below.
-constexpr int kWavePer = 4;
-constexpr int kWaveEntries = kWave * kWavePer;
-__device__ __forceinline__ void select_wave(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
-                                            int32_t b, DevStatus *st, int4 *__restrict__ moves,
-                                            int32_t *__restrict__ sel_target, int32_t *__restrict__ part,
-                                            uint8_t *__restrict__ mvfrom, const int64_t *__restrict__ voff,
-                                            int32_t *__restrict__ bigmv, int32_t *hmoves) {
-  __shared__ unsigned long long whw[256];
-  __shared__ int32_t whc[256], w_thr, w_done;
-  __shared__ int64_t w_need;
-  if (threadIdx.x >= kWave) return;
-  const int l = lane_id();
-  uint32_t k0[kWavePer], k4[kWavePer], wt[kWavePer];
-  uint32_t alive = 0u, sel = 0u;
-#pragma unroll
-  for (int j = 0; j < kWavePer; ++j) {
-    const int32_t i = j * kWave + l;
-    k0[j] = k4[j] = wt[j] = 0u;
-    if (i < len) {
-      const uint32_t *p = list + (int64_t)i * kEntryWords;
-      k0[j] = p[0];
-      k4[j] = p[4];
-      wt[j] = p[7];
-    }
-    if (wt[j] != 0u) alive |= 1u << j;
-  }
-  if (l == 0) w_need = need;
-  bool done = false;
-#pragma unroll 1
-  for (int x = d >> 2; x < 5 && !done; ++x) {  // wave-uniform
-    uint32_t cur[kWavePer];
-    uint32_t an = 0xffffffffu, orr = 0u;
-#pragma unroll
-    for (int j = 0; j < kWavePer; ++j) {
-      cur[j] = x == 0 ? k0[j] : k4[j];
-      if ((alive >> j) & 1u) {
-        if (x >= 1 && x <= 3) cur[j] = list[(int64_t)(j * kWave + l) * kEntryWords + x];
-        an &= cur[j];
-        orr |= cur[j];
-      }
-    }
-#pragma unroll
-    for (int o = kWave / 2; o >= 1; o >>= 1) {
-      an &= (uint32_t)__shfl_xor((int)an, o, kWave);
-      orr |= (uint32_t)__shfl_xor((int)orr, o, kWave);
-    }
-    const uint32_t diff = an ^ orr;
-#pragma unroll 1
-    for (int y = x == (d >> 2) ? (d & 3) : 0; y < 4; ++y) {
-      const int sh = 8 * (3 - y);
-      if (((diff >> sh) & 0xffu) == 0u && !(x == 4 && y == 3)) continue;  // a shared byte changes nothing
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        whw[j * kWave + l] = 0ull;
-        whc[j * kWave + l] = 0;
-      }
-      wave_lds_sync();
-#pragma unroll
-      for (int j = 0; j < kWavePer; ++j) {
-        if (!((alive >> j) & 1u)) continue;
-        const uint32_t dg = (cur[j] >> sh) & 0xffu;
-        atomicAdd(&whw[dg], (unsigned long long)wt[j]);
-        atomicAdd(&whc[dg], 1);
-      }
-      wave_lds_sync();
-      pass_threshold(whw, whc, w_need, &w_thr, &w_need, &w_done);
-      wave_lds_sync();
-      const uint32_t thr = (uint32_t)w_thr;
-      done = w_done != 0;
-      wave_lds_sync();
-#pragma unroll
-      for (int j = 0; j < kWavePer; ++j) {
-        if (!((alive >> j) & 1u)) continue;
-        const uint32_t dg = (cur[j] >> sh) & 0xffu;
-        if (dg > thr || (dg == thr && done)) sel |= 1u << j;
-        if (dg != thr || done) alive &= ~(1u << j);
-      }
-      if (done) break;
-    }
-  }
-  const int32_t cnt = __popc(sel), incl = wave_incl_scan(cnt), tot = __shfl(incl, kWave - 1, kWave);
-  if (tot == 0) return;
-  int32_t base = 0;
-  if (l == 0) {
-    base = atomicAdd(&st->n_moves, tot);
-    if (hmoves) atomicAdd(hmoves, tot);
-  }
-  int32_t pos = __shfl(base, 0, kWave) + incl - cnt;
-  int64_t dsum = 0;
-#pragma unroll
-  for (int j = 0; j < kWavePer; ++j) {
-    const bool e = (sel >> j) & 1u;
-    int64_t dg = 0;
-    if (e) {
-      uint32_t ent[kEntryWords];
-      load_entry(list + (int64_t)(j * kWave + l) * kEntryWords, ent);
-      dg = voff[ent[5] + 1] - voff[ent[5]];
-      put_move(ent, b, pos, moves, sel_target, part, mvfrom);
-    }
-    push_big_move(dg > kLaneDegree, pos, st, bigmv);
-    pos += e ? 1 : 0;
-    dsum += dg;
-  }
-  dsum = wave_sum(dsum);
-  if (l == 0 && dsum) atomicAdd((unsigned long long *)&st->mv_inc, (unsigned long long)dsum);
-}
+constexpr int kRegPer = 4;    // entries per thread of the selection in registers
+constexpr int kFinish = 64;   // entries a wave orders by comparing all pairs
 
-constexpr int kRegPer = 4;  // entries per thread of the selection in registers
+// Threshold of a histogram whose bins hold weight << 16 | count (at most kSelThreads * kRegPer entries,
+// so the counts never carry): as pass_threshold, and the number of entries on the threshold digit.
+__device__ __forceinline__ void packed_threshold(const unsigned long long *h, int64_t nr, int32_t *s_thr,
+                                                 int64_t *s_need, int32_t *s_done, int32_t *s_left) {
+  const int lane = lane_id();
+  const int g = kWave - 1 - lane;
+  int64_t v[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) v[j] = (int64_t)h[4 * g + j];
+  const int64_t sg = v[0] + v[1] + v[2] + v[3];
+  const int64_t suf = wave_incl_scan(sg);
+  const int64_t total = __shfl(suf, kWave - 1, kWave);
+  const uint64_t reach = ballot((suf >> 16) >= nr);
+  if ((total >> 16) <= nr) {
+    if (lane == 0) {
+      *s_thr = 0;
+      *s_done = 1;
+    }
+  } else if (lane == (int)__builtin_ctzll(reach)) {
+    int64_t cum = suf - sg, on = 0;
+    int thr = 4 * g;
+#pragma unroll
+    for (int j = 3; j >= 0; --j) {
+      on = v[j];
+      if (((cum + on) >> 16) >= nr) {
+        thr = 4 * g + j;
+        break;
+      }
+      cum += on;
+    }
+    const int64_t rem = nr - (cum >> 16);
+    *s_thr = thr;
+    *s_need = rem;
+    *s_left = (int32_t)(on & 0xffff);
+    *s_done = (on >> 16) == rem || (on & 0xffff) == 1 ? 1 : 0;
+  }
+}
 
 // The selection of at most kSelThreads * kRegPer entries: every thread keeps its entries in
 // registers, an entry above the threshold digit of a pass is marked selected, one below it is
 // dropped, and the moves are written once at the end, with one reservation.  Nothing is compacted
-// or read again, and bytes that all remaining entries share are skipped a word at a time (their
-// AND and OR over the workgroup).  What bounds it is the chain of barriers: two per pass that
-// splits.  The passes over the list in memory below took 24 us for 500 entries, this takes 9 us.
+// or read again.  A pass takes the highest eight of the bits in which the remaining entries differ
+// (their AND and OR over the workgroup); words 1..3 are skipped at once when they share them, and the
+// last kFinish entries are ordered by one wave, each lane summing the weight of the keys above its
+// own.  What bounds it is the chain of steps, about 1.5 us each: byte by byte through the key it took
+// 20 us for 500 entries (SELFIG).
 // Starts at key byte d with `need` weight to select; every thread of the block calls it.
 __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
                                                  int32_t b, DevStatus *st, int4 *__restrict__ moves,
@@ -853,16 +783,15 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
                                                  uint8_t *__restrict__ mvfrom,
                                                  const int64_t *__restrict__ voff, int32_t *__restrict__ bigmv,
                                                  int32_t *hmoves) {
-  __shared__ unsigned long long rhw[2][256];
-  __shared__ int32_t rhc[2][256];
-  __shared__ uint32_t s_and[5], s_or[5];
-  __shared__ int32_t r_thr, r_done, r_base;
+  __shared__ unsigned long long hist[2][256];
+  __shared__ uint32_t s_and[5], s_or[5], f_bits[kSelThreads * kRegPer / 32];
+  __shared__ int32_t r_thr, r_done, r_left, r_base, r_ref, r_differ, f_n, f_idx[kFinish];
   __shared__ int64_t r_need;
   __shared__ int32_t r_sm[kSelThreads / kWave + 1];
   __shared__ unsigned long long r_deg;
   const int tid = threadIdx.x;
   // the first and last key word and the weight stay in registers; words 1..3 (the exact rational)
-  // are read again in the rare rounds that reach them, the target only for selected entries
+  // are read again in the rare rounds that reach them, vertex and target only for selected entries
   uint32_t k0[kRegPer], k4[kRegPer], wt[kRegPer];
   uint32_t alive = 0u, sel = 0u;
 #pragma unroll
@@ -877,23 +806,41 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
     }
     if (wt[j] != 0u) alive |= 1u << j;  // a vertex without a valid target: dropped
   }
-  if (tid < 256) {
-    rhw[0][tid] = 0ull;
-    rhc[0][tid] = 0;
-  }
+  if (tid < 256) hist[0][tid] = hist[1][tid] = 0ull;
+  if (tid < kSelThreads * kRegPer / 32) f_bits[tid] = 0u;
   if (tid < 5) {
     s_and[tid] = 0xffffffffu;
     s_or[tid] = 0u;
   }
   if (tid == 0) {
     r_need = need;
+    r_done = 0;
+    r_left = len;
+    r_differ = 0;
+    f_n = 0;
     r_deg = 0ull;
   }
   __syncthreads();
   int buf = 0;
   bool done = false;
-  #pragma unroll 1
-  for (int x = d >> 2; x < 5 && !done; ++x) {  // block-uniform
+#pragma unroll 1
+  for (int x = d >> 2; x < 5 && !done && r_left > kFinish; ++x) {  // block-uniform
+    if (x == 1) {  // do the remaining entries share words 1..3?
+      if (alive) r_ref = tid + kSelThreads * __builtin_ctz(alive);  // any of them
+      __syncthreads();
+      const uint32_t *q = list + (int64_t)r_ref * kEntryWords;
+      const uint32_t q1 = q[1], q2 = q[2], q3 = q[3];
+      bool differ = false;
+#pragma unroll
+      for (int j = 0; j < kRegPer; ++j) {
+        if (!((alive >> j) & 1u)) continue;
+        const uint32_t *p = list + (int64_t)(j * kSelThreads + tid) * kEntryWords;
+        differ = differ || p[1] != q1 || p[2] != q2 || p[3] != q3;
+      }
+      if (ballot(differ) && lane_id() == 0) r_differ = 1;
+      __syncthreads();
+      if (!r_differ) x = 4;
+    }
     uint32_t cur[kRegPer];
     uint32_t an = 0xffffffffu, orr = 0u;
 #pragma unroll
@@ -917,25 +864,16 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
       }
     }
     __syncthreads();
-    const uint32_t diff = s_and[x] ^ s_or[x];  // bits in which the remaining entries differ
-    for (int y = x == (d >> 2) ? (d & 3) : 0; y < 4; ++y) {  // block-uniform
-      const int sh = 8 * (3 - y);
-      // a shared byte changes nothing; a selection that every remaining entry or the last byte
-      // completes is left to the last byte of the key
-      if (((diff >> sh) & 0xffu) == 0u && !(x == 4 && y == 3)) continue;
+    uint32_t diff = s_and[x] ^ s_or[x];  // bits in which the remaining entries differ
+    while (diff != 0u) {  // block-uniform
+      const int sh = max(0, 24 - __clz((int)diff));
 #pragma unroll
-      for (int j = 0; j < kRegPer; ++j) {
-        if (!((alive >> j) & 1u)) continue;
-        const uint32_t dg = (cur[j] >> sh) & 0xffu;
-        atomicAdd(&rhw[buf][dg], (unsigned long long)wt[j]);
-        atomicAdd(&rhc[buf][dg], 1);
-      }
-      if (tid < 256) {  // the next pass's histogram
-        rhw[buf ^ 1][tid] = 0ull;
-        rhc[buf ^ 1][tid] = 0;
-      }
+      for (int j = 0; j < kRegPer; ++j)
+        if ((alive >> j) & 1u)
+          atomicAdd(&hist[buf][(cur[j] >> sh) & 0xffu], ((unsigned long long)wt[j] << 16) | 1ull);
+      if (tid < 256) hist[buf ^ 1][tid] = 0ull;  // the next pass's histogram
       __syncthreads();
-      if (tid < kWave) pass_threshold(rhw[buf], rhc[buf], r_need, &r_thr, &r_need, &r_done);
+      if (tid < kWave) packed_threshold(hist[buf], r_need, &r_thr, &r_need, &r_done, &r_left);
       __syncthreads();
       const uint32_t thr = (uint32_t)r_thr;
       done = r_done != 0;
@@ -947,8 +885,51 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
         if (dg != thr || done) alive &= ~(1u << j);
       }
       buf ^= 1;
-      if (done) break;
+      if (done || r_left <= kFinish) break;
+      diff &= (1u << sh) - 1u;
     }
+  }
+  // r_done and r_left stay as they are from here on.  The last entries (distinct keys, so at most one is
+  // left otherwise): the first wave orders them
+  if (!done) {  // block-uniform
+#pragma unroll
+    for (int j = 0; j < kRegPer; ++j)
+      if ((alive >> j) & 1u) f_idx[atomicAdd(&f_n, 1)] = j * kSelThreads + tid;
+    __syncthreads();
+    if (tid < kWave) {
+      const int n = f_n;
+      uint32_t ent[kEntryWords] = {};
+      if (tid < n) load_entry(list + (int64_t)f_idx[tid] * kEntryWords, ent);
+      const uint64_t hi = ((uint64_t)ent[0] << 32) | ent[1], lo = ((uint64_t)ent[2] << 32) | ent[3];
+      int64_t above = 0;  // weight of the entries with larger keys
+      for (int i = 0; i < n; ++i) {
+        const uint32_t e0 = (uint32_t)__builtin_amdgcn_readlane((int)ent[0], i);
+        const uint32_t e1 = (uint32_t)__builtin_amdgcn_readlane((int)ent[1], i);
+        const uint32_t e2 = (uint32_t)__builtin_amdgcn_readlane((int)ent[2], i);
+        const uint32_t e3 = (uint32_t)__builtin_amdgcn_readlane((int)ent[3], i);
+        const uint32_t e4 = (uint32_t)__builtin_amdgcn_readlane((int)ent[4], i);
+        const uint32_t ew = (uint32_t)__builtin_amdgcn_readlane((int)ent[7], i);
+        const uint64_t ehi = ((uint64_t)e0 << 32) | e1, elo = ((uint64_t)e2 << 32) | e3;
+        const bool gt = ehi > hi || (ehi == hi && (elo > lo || (elo == lo && e4 > ent[4])));
+        above += gt ? (int64_t)ew : 0;
+      }
+      if (tid < n && above < r_need) atomicOr(&f_bits[f_idx[tid] >> 5], 1u << (f_idx[tid] & 31));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int j = 0; j < kRegPer; ++j) {
+      const int32_t i = j * kSelThreads + tid;
+      if (((alive >> j) & 1u) && ((f_bits[i >> 5] >> (i & 31)) & 1u)) sel |= 1u << j;
+    }
+  }
+  // vertices and degrees are read before the reservation, beside the scan
+  int32_t vtx[kRegPer], deg[kRegPer];
+#pragma unroll
+  for (int j = 0; j < kRegPer; ++j) {
+    vtx[j] = deg[j] = 0;
+    if (!((sel >> j) & 1u)) continue;
+    vtx[j] = (int32_t)list[(int64_t)(j * kSelThreads + tid) * kEntryWords + 5];
+    deg[j] = (int32_t)(voff[vtx[j] + 1] - voff[vtx[j]]);
   }
   int32_t tot;
   const int32_t rk = block_excl_scan<kSelThreads>((int32_t)__popc(sel), r_sm, &tot);
@@ -963,16 +944,14 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
 #pragma unroll
   for (int j = 0; j < kRegPer; ++j) {
     const bool e = (sel >> j) & 1u;
-    int64_t dg = 0;
     if (e) {
-      uint32_t ent[kEntryWords];
-      load_entry(list + (int64_t)(j * kSelThreads + tid) * kEntryWords, ent);
-      dg = voff[ent[5] + 1] - voff[ent[5]];
+      const uint32_t t = list[(int64_t)(j * kSelThreads + tid) * kEntryWords + 6];
+      const uint32_t ent[kEntryWords] = {0u, 0u, 0u, 0u, 0u, (uint32_t)vtx[j], t, wt[j]};
       put_move(ent, b, pos, moves, sel_target, part, mvfrom);
     }
-    push_big_move(dg > kLaneDegree, pos, st, bigmv);
+    push_big_move(deg[j] > kLaneDegree, pos, st, bigmv);
     pos += e ? 1 : 0;
-    dsum += dg;
+    dsum += deg[j];
   }
   dsum = wave_sum(dsum);
   if (lane_id() == 0 && dsum) atomicAdd(&r_deg, (unsigned long long)dsum);
@@ -1096,11 +1075,6 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
   for (int d = d0; d < 20; ++d) {
     __syncthreads();  // every thread has finished reading the previous pass's histogram
     len = s_len;
-    if (len <= kWaveEntries) {  // block-uniform: one wave
-      select_wave(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
-                  u.lcs ? &st->hmoves[sgm / k] : nullptr);
-      break;
-    }
     if (len <= kSelThreads * kRegPer) {  // block-uniform: the rest of the list fits the registers
       select_registers(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
                        u.lcs ? &st->hmoves[sgm / k] : nullptr);
