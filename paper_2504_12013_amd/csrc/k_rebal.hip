@@ -594,33 +594,56 @@ __device__ __forceinline__ void pass_threshold(const unsigned long long *hw, con
   }
 }
 
-// ---- the first radix pass over all CUs (large levels) ----
-// The first pass of the selection over an overloaded block's entries runs on S workgroups per
-// block (slice s of the block's list each, grid S x k; blocks without need exit at once):
-// k_rb_sel_hist adds the histogram of the first key byte into hist[b]; k_rb_sel_split derives the
-// same threshold from it in every workgroup, emits the entries above the threshold byte (and on
-// it, when that completes the selection) and compacts the entries on the threshold byte into the
-// block's region of keep2.  The single-workgroup selection then continues from the second byte
-// over the kept entries; it clears hist[b] again.
+// ---- the first pass over all CUs (large levels) ----
+// The first pass of the selection over an overloaded block's entries runs on up to S workgroups per
+// block (grid S x k, a workgroup has a tile of entries at least; blocks without need exit at once):
+// k_rb_sel_hist adds the histogram of the entries' split digit into hist[b]; k_rb_sel_split derives the
+// same threshold from it in every workgroup, emits the entries above the threshold digit (and on
+// it, when that completes the selection) and compacts the entries on the threshold digit into the
+// block's region of keep2.  The single-workgroup selection then continues over the kept entries, which
+// still differ anywhere in the key; it clears hist[b] again.
+// A block that holds half of 300,000 vertices took 140 us on the two slices that suit an average block;
+// now
+// 27 us, and a round's histogram and split 15 us on average (34).
 constexpr int kSplitThreads = 256;  // one thread per histogram bin
 
-__device__ __forceinline__ void slice_range(int32_t len, int s, int S, int32_t &lo, int32_t &hi) {
+constexpr int kSplitTile = kSplitThreads * kSplitPer;
+
+// The slice of a list of len entries for workgroup s of S: S only as far as slices hold `least` entries.
+__device__ __forceinline__ void slice_range(int32_t len, int s, int S, int32_t least, int32_t &lo, int32_t &hi) {
+  S = min(S, (len + least - 1) / least);
+  if (s >= S) {
+    lo = hi = 0;
+    return;
+  }
   lo = (int32_t)((int64_t)len * s / S);
   hi = (int32_t)((int64_t)len * (s + 1) / S);
 }
 
+// Split digit of an entry's first key word: monotone in it, and finer than its first byte (sign and bit
+// length of the priority, the same for nearly all moves) where priorities lie: three bits of mantissa for
+// losses per weight from 2^-7 up to 2^8 and for gains times weight below 2^15.
+// order 2 (buckets): the byte that holds the bucket.
+__device__ __forceinline__ uint32_t split_digit(uint32_t w0, int32_t order) {
+  if (order == 2) return w0 >> 24;
+  if (w0 >> 31) return 128u + min((w0 & 0x7fffffffu) >> 21, 127u);
+  const int32_t e = (int32_t)((0x7fffffffu - w0) >> 21) - 56 * 8;  // bit length 63: a loss of 1 per weight
+  return 127u - (uint32_t)min(max(e, 0), 127);
+}
+
 __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_hist(const uint32_t *__restrict__ entries,
                                                                const DevStatus *st, unsigned long long *__restrict__ gw,
-                                                               uint32_t *__restrict__ gc, const LoopCtl *lc) {
+                                                               uint32_t *__restrict__ gc, int32_t least, const LoopCtl *lc) {
   JET_GATE(lc, kPhRb);
   __shared__ unsigned long long hw[256];
   __shared__ uint32_t hc[256];
   const int b = blockIdx.y, tid = threadIdx.x;
   if (st->rb_need[b] <= 0) return;
   int32_t lo, hi;
-  slice_range(st->rb_count[b], blockIdx.x, gridDim.x, lo, hi);
+  slice_range(st->rb_count[b], blockIdx.x, gridDim.x, least, lo, hi);
   if (lo >= hi) return;
   const uint32_t *list = entries + st->rb_off[b] * kEntryWords;
+  const int32_t order = lc ? lc->rb_unw : 0;
   hw[tid] = 0ull;
   hc[tid] = 0u;
   __syncthreads();
@@ -639,8 +662,9 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_hist(const uint32_t *_
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       if (wt[u] == 0u) continue;  // a vertex without a valid target (or past the slice)
-      atomicAdd(&hw[k0[u] >> 24], (unsigned long long)wt[u]);
-      atomicAdd(&hc[k0[u] >> 24], 1u);
+      const uint32_t dg = split_digit(k0[u], order);
+      atomicAdd(&hw[dg], (unsigned long long)wt[u]);
+      atomicAdd(&hc[dg], 1u);
     }
   }
   __syncthreads();
@@ -654,7 +678,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
     const uint32_t *__restrict__ entries, uint32_t *__restrict__ keep2, DevStatus *st,
     const unsigned long long *__restrict__ gw, const uint32_t *__restrict__ gc, int4 *__restrict__ moves,
     int32_t *__restrict__ sel_target, int32_t *__restrict__ part, uint8_t *__restrict__ mvfrom,
-    const int64_t *__restrict__ voff, int32_t *__restrict__ bigmv, const LoopCtl *lc) {
+    const int64_t *__restrict__ voff, int32_t *__restrict__ bigmv, int32_t least, const LoopCtl *lc) {
   JET_GATE(lc, kPhRb);
   __shared__ unsigned long long hw[256];
   __shared__ int32_t hc[256];
@@ -666,7 +690,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
   const int64_t need = st->rb_need[b];
   if (need <= 0) return;
   int32_t lo, hi;
-  slice_range(st->rb_count[b], blockIdx.x, gridDim.x, lo, hi);
+  slice_range(st->rb_count[b], blockIdx.x, gridDim.x, least, lo, hi);
   if (lo >= hi) return;
   const uint32_t *list = entries + st->rb_off[b] * kEntryWords;
   uint32_t *kept = keep2 + st->rb_off[b] * kEntryWords;
@@ -678,6 +702,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
   __syncthreads();
   const uint32_t thr = (uint32_t)s_thr;
   const bool done = s_done != 0;
+  const int32_t order = lc ? lc->rb_unw : 0;
   unsigned long long deg = 0ull;
   for (int32_t tb = lo; tb < hi; tb += kSplitThreads * kSplitPer) {  // block-uniform trip count
     uint32_t ent[kSplitPer][kEntryWords];
@@ -688,7 +713,7 @@ __global__ __launch_bounds__(kSplitThreads) void k_rb_sel_split(
       if (i < hi) {
         load_entry(list + (int64_t)i * kEntryWords, ent[j]);
         if (ent[j][7] == 0u) continue;  // a vertex without a valid target: dropped
-        const uint32_t dg = ent[j][0] >> 24;
+        const uint32_t dg = split_digit(ent[j][0], order);
         if (dg > thr || (dg == thr && done)) emit |= 1u << j;
         else if (dg == thr) keep |= 1u << j;
       }
@@ -775,7 +800,7 @@ __device__ __forceinline__ void packed_threshold(const unsigned long long *h, in
 // (their AND and OR over the workgroup); words 1..3 are skipped at once when they share them, and the
 // last kFinish entries are ordered by one wave, each lane summing the weight of the keys above its
 // own.  What bounds it is the chain of steps, about 1.5 us each: byte by byte through the key it took
-// 20 us for 500 entries (SELFIG).
+// 20 us for 500 entries, now 16.
 // Starts at key byte d with `need` weight to select; every thread of the block calls it.
 __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
                                                  int32_t b, DevStatus *st, int4 *__restrict__ moves,
@@ -967,7 +992,7 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
 // skipped outright.  Emitted moves take their slots with one reservation per tile of the list,
 // and their incidence total is added to mv_inc once at the end.  With gw / gc (the first-byte
 // histograms of the grid-wide first pass) the first pass has already run: the kernel rederives
-// its threshold, clears the histogram, and continues from the second byte over the entries that
+// its threshold, clears the histogram, and continues over the entries that
 // pass kept in keep2 (nothing is left to do when it completed the selection).
 __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__restrict__ entries, DevStatus *st,
                                                int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
@@ -990,8 +1015,7 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
   if (need <= 0) return;
   uint32_t *list = entries + st->rb_off[sgm] * kEntryWords;
   int32_t len = st->rb_count[sgm];
-  int d0 = 0;
-  if (gw) {  // the first pass ran over all CUs: continue from the second byte over the kept entries
+  if (gw) {  // the first pass ran over all CUs: continue over the kept entries
     for (int i = tid; i < 256; i += kSelThreads) {
       hw[i] = gw[(int64_t)b * 256 + i];
       hc[i] = (int32_t)gc[(int64_t)b * 256 + i];
@@ -1005,7 +1029,6 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
     need = s_need;
     list = keep2 + st->rb_off[sgm] * kEntryWords;
     len = st->rb_kept[sgm];
-    d0 = 1;
     __syncthreads();  // every thread has read s_need and s_done before they are rewritten
   }
   if (len == 0) return;
@@ -1072,7 +1095,7 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
     s_need = need;
     s_len = len;
   }
-  for (int d = d0; d < 20; ++d) {
+  for (int d = 0; d < 20; ++d) {
     __syncthreads();  // every thread has finished reading the previous pass's histogram
     len = s_len;
     if (len <= kSelThreads * kRegPer) {  // block-uniform: the rest of the list fits the registers
@@ -1234,14 +1257,16 @@ hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *se
   tok = prof_begin(c, kProfRbSelect, lc, want);
   const bool split = c.H == 1 && c.n >= c.sel_split_min;
   if (split) {
-    // about 2,048 entries of an average block per workgroup (an overloaded block lists at most its
-    // vertices), or the set count (1..64); any S works, a workgroup whose slice is empty exits
+    // as many slices as some 2,048 workgroups allow (or the set count, 1..64): one block may list most
+    // of the vertices, and a workgroup without a full tile exits at once
     const unsigned S = c.sel_slices > 0 ? (unsigned)c.sel_slices
-                                        : (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, (c.n / c.k + 2047) / 2048));
+                                        : (unsigned)std::max<int64_t>(1, std::min<int64_t>(64, 2048 / c.k));
+    const int32_t least = c.sel_slices > 0 ? 1 : kSplitTile;
     hipLaunchKernelGGL(k_rb_sel_hist, dim3(S, (unsigned)c.k), dim3(kSplitThreads), 0, c.stream, c.rb_keys, c.st,
-                       c.rb_gw, c.rb_gc, lc);
+                       c.rb_gw, c.rb_gc, least, lc);
     hipLaunchKernelGGL(k_rb_sel_split, dim3(S, (unsigned)c.k), dim3(kSplitThreads), 0, c.stream, c.rb_keys,
-                       c.rb_keys2, c.st, c.rb_gw, c.rb_gc, c.moves, sel_target, part, c.mvfrom, c.voff, c.bigmv, lc);
+                       c.rb_keys2, c.st, c.rb_gw, c.rb_gc, c.moves, sel_target, part, c.mvfrom, c.voff, c.bigmv, least,
+                       lc);
   }
   hipLaunchKernelGGL(k_rb_select, dim3(c.H > 1 ? (unsigned)std::min<int64_t>(512, (int64_t)c.H * c.k) : (unsigned)c.k),
                      dim3(kSelThreads), 0, c.stream, c.rb_keys, c.st,

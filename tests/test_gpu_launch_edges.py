@@ -217,3 +217,24 @@ def test_loop_launches_what_the_loop_asks_for(replays, overloaded):
     assert rc == orc and tr == otr
     assert np.array_equal(d.cpu().numpy(), ref)
     assert pieces == need if replays == 1 else need <= pieces <= 2 * need
+
+
+@pytest.mark.parametrize("order", [0, 1, 2])
+@pytest.mark.parametrize("nw_max,vw_max", [(1, 1), (1, 1 << 17), (1 << 15, 1), (300, 300)])
+def test_split_selection_digits(nw_max, vw_max, order, monkeypatch):
+    """The grid-wide first pass on priorities inside and far outside the range its digit resolves, with
+    lists of a tile and of several per workgroup."""
+    monkeypatch.setenv("JET_SEL_SPLIT_MIN", "0")
+    rng = np.random.default_rng(nw_max + vw_max)
+    n, k = 12000, 3
+    hg = W.random_hypergraph(n, 2 * n, k, 5, smin=2, smax=5, vw_max=vw_max, nw_max=nw_max)
+    part = np.where(rng.random(n) < 0.9, 1, rng.integers(0, k, n)).astype(np.int32)
+    say(f"net weights to {nw_max}, vertex weights to {vw_max}, order {order}")
+    ref, orc, ost = O.rebalance(hg, part, rb_unweighted=order)[:3]
+    ctx = J().JetContext(hg)
+    d = torch.from_numpy(part).to("cuda")
+    rc, st = ctx.rebalance(d, rb_unweighted=order)
+    ctx.close()
+    assert rc == orc
+    assert np.array_equal(d.cpu().numpy(), ref)
+    assert st["rebalance_rounds"] == ost["rebalance_rounds"]
