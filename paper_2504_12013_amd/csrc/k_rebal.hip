@@ -536,12 +536,8 @@ __global__ __launch_bounds__(256) void k_rb_gain_bits(
 }
 
 constexpr int kSelThreads = 1024;
-constexpr int kSelPer = 2;    // list entries per thread and tile of the selection in memory (4: spills)
+constexpr int kSelPer = 2;    // list entries in flight per thread of the selection in memory (4: spills)
 constexpr int kSplitPer = 4;  // and of the grid-wide first pass
-
-__device__ __forceinline__ uint32_t digit_of(const uint32_t *key, int d) {
-  return (key[d >> 2] >> (8 * (3 - (d & 3)))) & 0xffu;
-}
 
 // Writes one selected entry as a move of vertex ent[5] from block `from` to ent[6], and the vertex's
 // new block.
@@ -801,8 +797,8 @@ __device__ __forceinline__ void packed_threshold(const unsigned long long *h, in
 // last kFinish entries are ordered by one wave, each lane summing the weight of the keys above its
 // own.  What bounds it is the chain of steps, about 1.5 us each: byte by byte through the key it took
 // 20 us for 500 entries, now 16.
-// Starts at key byte d with `need` weight to select; every thread of the block calls it.
-__device__ __forceinline__ void select_registers(const uint32_t *__restrict__ list, int32_t len, int d, int64_t need,
+// Every thread of the block calls it, with the weight to select.
+__device__ __forceinline__ void select_registers(const uint32_t *list, int32_t len, int64_t need,
                                                  int32_t b, DevStatus *st, int4 *__restrict__ moves,
                                                  int32_t *__restrict__ sel_target, int32_t *__restrict__ part,
                                                  uint8_t *__restrict__ mvfrom,
@@ -849,7 +845,7 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
   int buf = 0;
   bool done = false;
 #pragma unroll 1
-  for (int x = d >> 2; x < 5 && !done && r_left > kFinish; ++x) {  // block-uniform
+  for (int x = 0; x < 5 && !done && r_left > kFinish; ++x) {  // block-uniform
     if (x == 1) {  // do the remaining entries share words 1..3?
       if (alive) r_ref = tid + kSelThreads * __builtin_ctz(alive);  // any of them
       __syncthreads();
@@ -984,37 +980,42 @@ __device__ __forceinline__ void select_registers(const uint32_t *__restrict__ li
   if (tid == 0 && r_deg) atomicAdd((unsigned long long *)&st->mv_inc, r_deg);
 }
 
-// One block per overloaded block b: selects the minimal prefix of b's entries in key order whose
-// weight reaches rb_need[b] (all entries if their total falls short).  Radix selection over the
-// 20 key bytes, most significant first; each pass emits the entries above the threshold digit and
-// keeps those on it.  Passes whose digit is shared by every remaining entry change nothing and
-// only cost the histogram; when the remaining entries share words 1..3 those 12 passes are
-// skipped outright.  Emitted moves take their slots with one reservation per tile of the list,
-// and their incidence total is added to mv_inc once at the end.  With gw / gc (the first-byte
-// histograms of the grid-wide first pass) the first pass has already run: the kernel rederives
-// its threshold, clears the histogram, and continues over the entries that
-// pass kept in keep2 (nothing is left to do when it completed the selection).
-__device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__restrict__ entries, DevStatus *st,
+// The selection of one segment by a workgroup.  Lists of more than kSelThreads * kRegPer entries are
+// cut down in memory first: the highest eight of the bits in which the entries differ (AND and OR of all
+// key words) make the digit of a pass; it emits the entries above the threshold digit and keeps those on
+// it, in the other of the two entry regions.  The counts of the histogram give the moves' reservation, so
+// the waves place their entries with LDS counters and meet at no barrier inside a scan.  What bounds it is
+// one CU reading the list three times per pass; byte by byte, with barriers per tile of 2,048 entries, it
+// took 94 to 168 us on 1M
+// SAT-like vertices, now 30 to 60.  With gw / gc (the histograms of the grid-wide first pass) the first pass has already run:
+// the kernel rederives its threshold, clears the histogram, and continues over the entries that pass kept
+// in keep2 (nothing is left to do when it completed the selection).
+__device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *entries, DevStatus *st,
                                                int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
                                                int32_t *__restrict__ part, uint8_t *__restrict__ mvfrom,
                                                const int64_t *__restrict__ voff,
                                                int32_t *__restrict__ bigmv, unsigned long long *__restrict__ gw,
-                                               uint32_t *__restrict__ gc, uint32_t *__restrict__ keep2, int32_t k,
+                                               uint32_t *__restrict__ gc, uint32_t *keep2, int32_t k,
                                                const Union &u) {
   __shared__ unsigned long long hw[256];
   __shared__ int32_t hc[256];
-  __shared__ int32_t s_thr, s_done, s_len, s_same, s_base;
+  __shared__ uint32_t s_and[5], s_or[5];
+  __shared__ int32_t s_thr, s_done, s_emit, s_keep;
   __shared__ int64_t s_need;
   __shared__ unsigned long long s_deg;
-  __shared__ int32_t s_emitted;
-  __shared__ int32_t scan_sm[2][kSelThreads / kWave];
-  int parity = 0;
   const int32_t b = sgm % k;        // the block the selected vertices leave
   const int tid = threadIdx.x;
-  int64_t need = st->rb_need[sgm];
+  const int64_t need = st->rb_need[sgm];
   if (need <= 0) return;
-  uint32_t *list = entries + st->rb_off[sgm] * kEntryWords;
+  int32_t *hmoves = u.lcs ? &st->hmoves[sgm / k] : nullptr;  // union: per hypergraph
+  const int64_t at = st->rb_off[sgm] * kEntryWords;
+  const uint32_t *list = entries + at;
+  uint32_t *other = keep2 + at;
   int32_t len = st->rb_count[sgm];
+  if (tid == 0) {
+    s_need = need;
+    s_deg = 0ull;
+  }
   if (gw) {  // the first pass ran over all CUs: continue over the kept entries
     for (int i = tid; i < 256; i += kSelThreads) {
       hw[i] = gw[(int64_t)b * 256 + i];
@@ -1026,148 +1027,147 @@ __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *__re
     if (tid < kWave) pass_threshold(hw, hc, need, &s_thr, &s_need, &s_done);
     __syncthreads();
     if (s_done) return;  // the split pass emitted the whole selection
-    need = s_need;
-    list = keep2 + st->rb_off[sgm] * kEntryWords;
+    list = keep2 + at;
+    other = entries + at;
     len = st->rb_kept[sgm];
-    __syncthreads();  // every thread has read s_need and s_done before they are rewritten
   }
-  if (len == 0) return;
-  // One tile: kSelPer entries per thread (entry tb + j * kSelThreads + tid).  Emits those with
-  // bit j of `emit` set and compacts those with bit j of `keep` to list[out..]; returns the number
-  // kept.  Every thread of the block calls it, after loading its entries.
-  auto emit_keep = [&](uint32_t emit, uint32_t keep, const uint32_t (*ent)[kEntryWords], int32_t out) -> int32_t {
-    const int32_t ne = __popc(emit), nk = __popc(keep);
-    // block-wide exclusive scan with one barrier: the wave totals go to the half of scan_sm this
-    // tile owns (tiles alternate), so no barrier is needed before the next tile writes
-    const int32_t x = ne | (nk << 16);
-    const int32_t inc = wave_incl_scan(x);
-    int32_t *ws = scan_sm[parity];
-    parity ^= 1;
-    if (lane_id() == kWave - 1) ws[tid / kWave] = inc;
-    __syncthreads();
-    int32_t off = 0, tot = 0;
-#pragma unroll
-    for (int i = 0; i < kSelThreads / kWave; ++i) {
-      const int32_t v = ws[i];
-      off += i < tid / kWave ? v : 0;
-      tot += v;
+  __syncthreads();
+  while (len > kSelThreads * kRegPer) {  // block-uniform
+    if (tid < 5) {
+      s_and[tid] = 0xffffffffu;
+      s_or[tid] = 0u;
     }
-    const int32_t rk = inc - x + off;
-    const int32_t etot = tot & 0xffff;
-    if (etot) {  // block-uniform
-      if (tid == 0) {
-        s_base = atomicAdd(&st->n_moves, etot);
-        s_emitted += etot;
-      }
-      __syncthreads();
-      int32_t pos = s_base + (rk & 0xffff);
-      int64_t dsum = 0;
+    if (tid < 256) {
+      hw[tid] = 0ull;
+      hc[tid] = 0;
+    }
+    if (tid == 0) s_emit = s_keep = 0;
+    uint32_t an[5], orr[5];
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+      an[x] = 0xffffffffu;
+      orr[x] = 0u;
+    }
+    for (int32_t i0 = tid; i0 < len; i0 += kSelThreads * kSelPer) {
 #pragma unroll
       for (int j = 0; j < kSelPer; ++j) {
+        const int32_t i = i0 + j * kSelThreads;
+        uint32_t ent[kEntryWords] = {};
+        if (i < len) load_entry(list + (int64_t)i * kEntryWords, ent);
+        const bool valid = ent[7] != 0u;  // else a vertex without a valid target
+#pragma unroll
+        for (int x = 0; x < 5; ++x) {
+          an[x] &= valid ? ent[x] : 0xffffffffu;
+          orr[x] |= valid ? ent[x] : 0u;
+        }
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int x = 0; x < 5; ++x) {
+#pragma unroll
+      for (int o = kWave / 2; o >= 1; o >>= 1) {
+        an[x] &= (uint32_t)__shfl_xor((int)an[x], o, kWave);
+        orr[x] |= (uint32_t)__shfl_xor((int)orr[x], o, kWave);
+      }
+      if (lane_id() == 0) {
+        atomicAnd(&s_and[x], an[x]);
+        atomicOr(&s_or[x], orr[x]);
+      }
+    }
+    __syncthreads();
+    int x = 0;
+    while (x < 4 && (s_and[x] & s_or[x]) == s_or[x]) ++x;  // the first word in which entries differ
+    const uint32_t diff = s_or[x] & ~s_and[x];
+    const int sh = diff ? max(0, 24 - __clz((int)diff)) : 0;  // one valid entry or none: any digit will do
+    for (int32_t i0 = tid; i0 < len; i0 += kSelThreads * 4) {  // four entries' loads in flight
+      uint32_t wt[4], key[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const int32_t i = i0 + j * kSelThreads;
+        wt[j] = key[j] = 0u;
+        if (i < len) {
+          wt[j] = list[(int64_t)i * kEntryWords + 7];
+          key[j] = list[(int64_t)i * kEntryWords + x];
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (wt[j] == 0u) continue;
+        atomicAdd(&hw[(key[j] >> sh) & 0xffu], (unsigned long long)wt[j]);
+        atomicAdd(&hc[(key[j] >> sh) & 0xffu], 1);
+      }
+    }
+    __syncthreads();
+    if (tid < kWave) pass_threshold(hw, hc, s_need, &s_thr, &s_need, &s_done);
+    __syncthreads();
+    const int thr = s_thr;
+    const bool done = s_done != 0;
+    if (tid < 256 && hc[tid] && (tid > thr || (tid == thr && done))) atomicAdd(&s_emit, hc[tid]);
+    __syncthreads();
+    if (tid == 0 && s_emit) {  // from here on the next position of the move list
+      const int32_t n = s_emit;
+      s_emit = atomicAdd(&st->n_moves, n);
+      if (hmoves) atomicAdd(hmoves, n);
+    }
+    __syncthreads();
+    int64_t dsum = 0;
+    for (int32_t i0 = tid - lane_id(); i0 < len; i0 += kSelThreads * kSelPer) {  // wave-uniform
+      uint32_t ent[kSelPer][kEntryWords];
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) {
+        const int32_t i = i0 + j * kSelThreads + lane_id();
+        ent[j][7] = 0u;
+        if (i < len) load_entry(list + (int64_t)i * kEntryWords, ent[j]);
+      }
+#pragma unroll
+      for (int j = 0; j < kSelPer; ++j) {
+        uint32_t key = ent[j][0];
+#pragma unroll
+        for (int y = 1; y < 5; ++y) key = x == y ? ent[j][y] : key;
+        const int dg = (int)((key >> sh) & 0xffu);
+        const bool valid = ent[j][7] != 0u;
+        const bool e = valid && (dg > thr || (dg == thr && done)), kp = valid && dg == thr && !done;
+        const uint64_t me = ballot(e), mk = ballot(kp);
+        int32_t eb = 0, kb = 0;
+        if (lane_id() == 0) {
+          eb = me ? atomicAdd(&s_emit, __popcll(me)) : 0;
+          kb = mk ? atomicAdd(&s_keep, __popcll(mk)) : 0;
+        }
+        const int32_t pos = __shfl(eb, 0, kWave) + rank_below(me), kpos = __shfl(kb, 0, kWave) + rank_below(mk);
         int64_t d = 0;
-        const bool e = (emit >> j) & 1u;
         if (e) {
           d = voff[ent[j][5] + 1] - voff[ent[j][5]];
           put_move(ent[j], b, pos, moves, sel_target, part, mvfrom);
         }
         push_big_move(d > kLaneDegree, pos, st, bigmv);
-        pos += e ? 1 : 0;
         dsum += d;
-      }
-      const int64_t wd = wave_sum(dsum);
-      if (lane_id() == 0 && wd) atomicAdd(&s_deg, (unsigned long long)wd);
-    }
-    int32_t kp = out + (rk >> 16);
-#pragma unroll
-    for (int j = 0; j < kSelPer; ++j) {
-      if ((keep >> j) & 1u) {
-        store_entry(list + (int64_t)kp * kEntryWords, ent[j]);
-        ++kp;
+        if (kp) store_entry(other + (int64_t)kpos * kEntryWords, ent[j]);
       }
     }
-    // s_base is read above, before this thread reaches the next tile's barrier; the next tile reads
-    // list slots at or beyond this tile's end, which no thread of this tile writes
-    return tot >> 16;
-  };
-  if (tid == 0) {
-    s_deg = 0ull;
-    s_emitted = 0;
-    s_need = need;
-    s_len = len;
+    dsum = wave_sum(dsum);
+    if (lane_id() == 0 && dsum) atomicAdd(&s_deg, (unsigned long long)dsum);
+    __syncthreads();  // the kept entries are written, also for the other waves of the workgroup
+    len = done ? 0 : s_keep;
+    uint32_t *t = const_cast<uint32_t *>(list);
+    list = other;
+    other = t;
+    __syncthreads();  // every thread has read the counters
   }
-  for (int d = 0; d < 20; ++d) {
-    __syncthreads();  // every thread has finished reading the previous pass's histogram
-    len = s_len;
-    if (len <= kSelThreads * kRegPer) {  // block-uniform: the rest of the list fits the registers
-      select_registers(list, len, d, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv,
-                       u.lcs ? &st->hmoves[sgm / k] : nullptr);
-      break;
-    }
-    if (d == 4) {  // do the remaining entries share the exact rational part of the key?
-      if (tid == 0) s_same = 1;
-      __syncthreads();
-      const uint32_t r1 = list[1], r2 = list[2], r3 = list[3];
-      for (int32_t i = tid; i < len; i += kSelThreads) {
-        const uint32_t *ent = list + (int64_t)i * kEntryWords;
-        if (ent[1] != r1 || ent[2] != r2 || ent[3] != r3) s_same = 0;
-      }
-      __syncthreads();
-      if (s_same) d = 16;
-    }
-    for (int i = tid; i < 256; i += kSelThreads) {
-      hw[i] = 0;
-      hc[i] = 0;
-    }
-    __syncthreads();
-    for (int32_t i = tid; i < len; i += kSelThreads) {
-      const uint32_t *ent = list + (int64_t)i * kEntryWords;
-      if (ent[7] == 0u) continue;  // a vertex without a valid target
-      const uint32_t dg = digit_of(ent, d);
-      atomicAdd(&hw[dg], (unsigned long long)ent[7]);
-      atomicAdd(&hc[dg], 1);
-    }
-    __syncthreads();
-    if (tid < kWave) pass_threshold(hw, hc, s_need, &s_thr, &s_need, &s_done);
-    __syncthreads();
-    const uint32_t thr = (uint32_t)s_thr;
-    const bool done = s_done != 0;
-    if (!done && hc[thr] == len) continue;  // every entry on the threshold digit: nothing changes
-    // emit entries above the threshold digit, keep (or emit, when done) those on it
-    int32_t out = 0;
-    for (int32_t tb = 0; tb < len; tb += kSelThreads * kSelPer) {
-      uint32_t ent[kSelPer][kEntryWords];
-      uint32_t emit = 0, keep = 0;
-#pragma unroll
-      for (int j = 0; j < kSelPer; ++j) {
-        const int32_t i = tb + j * kSelThreads + tid;
-        if (i < len) {
-          load_entry(list + (int64_t)i * kEntryWords, ent[j]);
-          const uint32_t dg = digit_of(ent[j], d);
-          if (ent[j][7] == 0u) continue;  // a vertex without a valid target: dropped
-          if (dg > thr || (dg == thr && done)) emit |= 1u << j;
-          if (!done && dg == thr) keep |= 1u << j;
-        }
-      }
-      out += emit_keep(emit, keep, ent, out);
-    }
-    if (done) break;
-    if (tid == 0) s_len = out;
-  }
-  __syncthreads();
   if (tid == 0 && s_deg) atomicAdd((unsigned long long *)&st->mv_inc, s_deg);
-  if (tid == 0 && u.lcs && s_emitted) atomicAdd(&st->hmoves[sgm / k], s_emitted);  // union: per hypergraph
+  if (len > 0) select_registers(list, len, s_need, b, st, moves, sel_target, part, mvfrom, voff, bigmv, hmoves);
 }
 
 // One workgroup per overloaded block: the block's segment (one hypergraph).  A union's workgroups
 // walk the segments of the hypergraphs in their rebalancing phase.
-__global__ __launch_bounds__(kSelThreads) void k_rb_select(uint32_t *__restrict__ entries, DevStatus *st,
+__global__ __launch_bounds__(kSelThreads) void k_rb_select(uint32_t *entries, DevStatus *st,
                                                            int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
                                                            int32_t *__restrict__ part,
                                                            uint8_t *__restrict__ mvfrom,
                                                            const int64_t *__restrict__ voff,
                                                            int32_t *__restrict__ bigmv,
                                                            unsigned long long *__restrict__ gw,
-                                                           uint32_t *__restrict__ gc, uint32_t *__restrict__ keep2,
+                                                           uint32_t *__restrict__ gc, uint32_t *keep2,
                                                            const LoopCtl *lc, int32_t k, Union u) {
   JET_GATE(lc, kPhRb);
   const int32_t nseg = u.lcs ? st->rb_nseg : k;  // union: the overloaded segments the preparation listed
