@@ -313,9 +313,8 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * pieces (Jet phase, rebalancing round, rollback), launched as the loop's state asks for them;
  * 0: the same kernels are launched one by one (same results). */
 #define JET_OPT_GRAPH 6
-/* Rebalancing rounds (Section 4.3) a replayed iteration of a batch holds room for, 1..64, default 4;
- * an iteration that needs more continues in the next replay.  A single hypergraph's rounds are
- * launched one by one.  Results do not depend on it. */
+/* Rebalancing rounds (Section 4.3) launched at a time, 1..64, default 1.  Results do not depend on
+ * it. */
 #define JET_OPT_RB_SLOTS 7
 /* Pieces of the loop in flight at once, 1..1024, default 2: one runs, one more (at most) waits
  * behind it when the host can foresee which it will be.  Results do not depend on it. */
@@ -374,9 +373,10 @@ int jet_batch_set_option(jet_batch *b, int32_t option, int64_t value);
  * jet_refine would (Algorithm 1 per hypergraph, its own balance limit, key, limit and rollback):
  * the result of each hypergraph does not depend on the batch or on the options.  Every kernel
  * launch covers all hypergraphs of a union context, each hypergraph's vertices and nets taking part
- * only while its own loop is in the launch's phase; one captured HIP graph holds a whole iteration
- * of every union context and is replayed `replays` (1..1024) times between two host looks at the
- * loop records, until every hypergraph's loop is done.  Runs on the stream given to jet_batch_init.
+ * only while its own loop is in the launch's phase; the phases some hypergraph is in are launched
+ * (as captured HIP graphs) until every hypergraph's loop is done, the unions beside each other.
+ * `replays` (1..1024) bounds the steps of a union in flight; one is enough and more are not
+ * launched.  The caller's order holds on the stream given to jet_batch_init.
  * stats and rcs ([host][count], may be NULL) receive each hypergraph's statistics and return code.
  * Returns a negative code on failure, else JET_IMBALANCED if any hypergraph is, else JET_OK. */
 int jet_batch_refine(jet_batch *b, int32_t *const *parts, const jet_params *params, int32_t replays,

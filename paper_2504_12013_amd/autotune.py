@@ -2,12 +2,12 @@
 caches the choice as JSON keyed by (GPU architecture, shape bucket).
 
 Knobs (none of them changes any result, only the time):
-  replays        iterations of the whole batch's captured graph between two host polls;
+  replays        bound of a union's steps in flight (one is launched at a time, so more change nothing);
   grid           workgroups of the persistent kernels (tiles per workgroup = work / grid);
   lane_degree    lanes per vertex of the bit-sliced candidate kernel: one lane below this mean degree,
                  eight above (0: always eight);
   apply_divisor  switch point of move application from per-move atomics to per-net recounting;
-  rb_slots       rebalancing rounds a replayed iteration holds room for.
+  rb_slots       rebalancing rounds launched at a time.
 
 The sweep is coordinate descent from the library defaults: each knob in turn is timed at every
 value with the others fixed at their best so far (one refinement of copies of the batch's starting

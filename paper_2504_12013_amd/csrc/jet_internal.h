@@ -110,15 +110,18 @@ struct LoopCtl {
 // What the host follows of a running loop: one word per control kernel, stored by it in pinned memory.
 struct LoopMail {
   uint32_t seq;       // low kMailSeqBits bits of LoopCtl::seq
-  int32_t phase;
+  int32_t mask;       // phases the record (a union: any of its hypergraphs) is in
+  int32_t phase;      // the lowest of them
   int32_t rb_rounds;  // of the current iteration, once the next Jet phase runs of the last one (clipped)
   bool last;          // the round ends with the current iteration unless that improves
   bool err;           // a kernel reported an error
 };
-constexpr int kMailSeqBits = 24, kMailPhaseSh = 24, kMailRbSh = 27, kMailRbBits = 16, kMailLastSh = 43, kMailErrSh = 44;
+constexpr int kMailSeqBits = 24, kMailMaskSh = 24, kMailMaskBits = 5;
+constexpr int kMailRbSh = 29, kMailRbBits = 16, kMailLastSh = 45, kMailErrSh = 46;
 constexpr uint32_t kMailSeqMask = (1u << kMailSeqBits) - 1u;
 inline LoopMail read_mail(unsigned long long w) {
-  return LoopMail{(uint32_t)w & kMailSeqMask, (int32_t)((w >> kMailPhaseSh) & 7u),
+  const int32_t mask = (int32_t)((w >> kMailMaskSh) & ((1u << kMailMaskBits) - 1u));
+  return LoopMail{(uint32_t)w & kMailSeqMask, mask, mask ? __builtin_ctz((unsigned)mask) : 0,
                   (int32_t)((w >> kMailRbSh) & ((1u << kMailRbBits) - 1u)), ((w >> kMailLastSh) & 1u) != 0,
                   ((w >> kMailErrSh) & 1u) != 0};
 }
@@ -322,9 +325,9 @@ struct FlowState {
   int32_t *fcnt = nullptr;                    // [3] their sizes
 };
 
-// Pieces of an iteration that a single hypergraph's loop launches, and a union's tick of all phases.
-enum TickKind : int { kTickJet = 0, kTickRb = 1, kTickRoll = 2, kTickAll = 3 };
-constexpr int kTickPieces = 3;  // kinds of pieces of a single context
+// The pieces of an iteration: what the host launches for a phase.
+enum TickKind : int { kTickJet = 0, kTickRb = 1, kTickRoll = 2 };
+constexpr int kTickPieces = 3;
 
 struct Ctx {
   hipStream_t stream = nullptr;
@@ -435,7 +438,7 @@ struct Ctx {
   hipGraph_t graph[kTickPieces] = {};
   hipGraphExec_t gexec[kTickPieces] = {};
   bool use_graph = true;         // JET_OPT_GRAPH
-  int32_t rb_slots = 4;          // JET_OPT_RB_SLOTS: rebalancing rounds of a union's tick
+  int32_t rb_slots = 1;          // JET_OPT_RB_SLOTS: rounds of one rebalancing piece
   int32_t replays = 2;           // JET_OPT_REPLAYS: most pieces in flight
   int64_t polls = 0;             // host polls of the last call (diagnostic)
   int64_t replays_done = 0;      // graph replays or eager ticks of the last call

@@ -5,8 +5,8 @@
 // record is in the phase it belongs to.  The Jet phase, a rebalancing round and the rollback, each
 // followed by its control kernel, are the pieces of an iteration; the host captures each in a HIP
 // graph once per context and launches them by what the control kernel last reported in pinned memory.
-// A union of hypergraphs replays a "tick" of all of them (rb_slots rebalancing rounds) and looks at
-// the records in between.  Pieces and ticks after the loop finished do nothing.  The sequence of
+// A union's hypergraphs may be in several phases at once: a piece then works on those in its phase.
+// Pieces after the loop finished do nothing.  The sequence of
 // states is exactly that of the host loop it replaces (one Jet phase, then rebalancing rounds while a
 // block is overloaded, a round moved something and the cap allows, then the key), so results and
 // per-iteration records do not depend on which pieces were launched ahead.
@@ -150,13 +150,17 @@ __device__ __forceinline__ void clear_counters(DevStatus *st) {
 }
 
 // Tells the host where the loop is (one store to pinned memory).
-__device__ __forceinline__ void post(unsigned long long *mail, uint32_t seq, const LoopCtl &r, int32_t err) {
-  const unsigned long long rb = (unsigned long long)min(r.rb_rounds, (1 << kMailRbBits) - 1);
-  const unsigned long long last = r.round + 1 >= r.limit || r.it + 1 >= r.max_iters ? 1ull : 0ull;
+__device__ __forceinline__ void post(unsigned long long *mail, uint32_t seq, int32_t mask, int32_t rb_rounds,
+                                     bool last, int32_t err) {
+  const unsigned long long rb = (unsigned long long)min(rb_rounds, (1 << kMailRbBits) - 1);
   __hip_atomic_store(mail,
-                     (unsigned long long)(seq & kMailSeqMask) | ((unsigned long long)r.phase << kMailPhaseSh) |
-                         (rb << kMailRbSh) | (last << kMailLastSh) | ((err != 0 ? 1ull : 0ull) << kMailErrSh),
+                     (unsigned long long)(seq & kMailSeqMask) | ((unsigned long long)mask << kMailMaskSh) |
+                         (rb << kMailRbSh) | ((last ? 1ull : 0ull) << kMailLastSh) |
+                         ((err != 0 ? 1ull : 0ull) << kMailErrSh),
                      __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+__device__ __forceinline__ void post(unsigned long long *mail, uint32_t seq, const LoopCtl &r, int32_t err) {
+  post(mail, seq, r.phase_mask, r.rb_rounds, r.round + 1 >= r.limit || r.it + 1 >= r.max_iters, err);
 }
 
 // One hypergraph: one thread per block.  Record, block weights and metric slots are loaded at
@@ -270,7 +274,8 @@ __device__ __forceinline__ void build_lists(const LoopCtl *lcs, int32_t H, ActLi
 // gate is a record of its own) and the lists.  The move counts start at zero for the next phase; the
 // rebalancing needs are set by the round's own preparation (one workgroup over all segments).
 __global__ __launch_bounds__(kCtlThreads) void k_control_union(LoopCtl *lcs, int32_t H, LoopCtl *gate, DevStatus *st,
-                                                               int32_t k, int32_t want, Union u) {
+                                                               int32_t k, int32_t want, unsigned long long *mail,
+                                                               Union u) {
   __shared__ int32_t smask;
   if (threadIdx.x == 0) smask = 0;
   __syncthreads();
@@ -301,6 +306,8 @@ __global__ __launch_bounds__(kCtlThreads) void k_control_union(LoopCtl *lcs, int
   __syncthreads();
   if (threadIdx.x == 0) {
     gate->phase_mask = smask;
+    gate->seq += 1;
+    post(mail, gate->seq, smask, 0, false, st->err);
     clear_counters(st);
   }
   if (threadIdx.x < kKm1Slots) st->slot[threadIdx.x] = CtrSlot{};
@@ -374,7 +381,7 @@ hipError_t launch_fill_u32(Ctx &c, uint32_t *p, int64_t count, uint32_t value, c
 static hipError_t launch_control(Ctx &c, int32_t want) {
   if (c.H > 1)
     hipLaunchKernelGGL(k_control_union, dim3(1), dim3(kCtlThreads), 0, c.stream, c.lcs, c.H, c.lc, c.st, c.k, want,
-                       union_of(c));
+                       c.mail, union_of(c));
   else
     hipLaunchKernelGGL(k_control, dim3(1), dim3(kCtlOne), 0, c.stream, c.lc, c.st, c.k, c.lmax, want, c.dtrace,
                        c.mail);
@@ -388,11 +395,8 @@ hipError_t launch_loop_init(Ctx &c) {
 
 hipError_t launch_tick(Ctx &c, int kind) {
   const LoopCtl *lc = c.lc;
-  const bool jet = kind == kTickJet || kind == kTickAll;
-  const bool rb = kind == kTickRb || kind == kTickAll;
-  const bool roll = kind == kTickRoll || kind == kTickAll;
   hipError_t e = hipSuccess;
-  if (jet) {
+  if (kind == kTickJet) {
     // Jet phase: candidates, afterburner, kept moves (locks), their application
     e = launch_candidates(c, c.cpart, 0, nullptr, 0, lc);
     if (e == hipSuccess) e = launch_afterburner(c, c.cpart, lc);
@@ -401,15 +405,15 @@ hipError_t launch_tick(Ctx &c, int kind) {
     if (e == hipSuccess) e = launch_control(c, kPhJet);
     if (e != hipSuccess) return e;
   }
-  if (rb) {
-    for (int r = 0; r < (kind == kTickAll ? c.rb_slots : 1); ++r) {
+  if (kind == kTickRb) {
+    for (int r = 0; r < c.rb_slots; ++r) {
       e = launch_rebalance_round(c, c.cpart, 0, nullptr, lc);
       if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhRb);
       if (e == hipSuccess) e = launch_control(c, kPhRb);
       if (e != hipSuccess) return e;
     }
   }
-  if (roll) {
+  if (kind == kTickRoll) {
     // end of a temperature round: back to its best partition
     e = launch_diff_moves(c, c.cpart, c.best, lc);
     if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhRoll);

@@ -986,10 +986,10 @@ __device__ __forceinline__ void select_registers(const uint32_t *list, int32_t l
 // it, in the other of the two entry regions.  The counts of the histogram give the moves' reservation, so
 // the waves place their entries with LDS counters and meet at no barrier inside a scan.  What bounds it is
 // one CU reading the list three times per pass; byte by byte, with barriers per tile of 2,048 entries, it
-// took 94 to 168 us on 1M
-// SAT-like vertices, now 30 to 60.  With gw / gc (the histograms of the grid-wide first pass) the first pass has already run:
-// the kernel rederives its threshold, clears the histogram, and continues over the entries that pass kept
-// in keep2 (nothing is left to do when it completed the selection).
+// took 94 to 168 us on 1M SAT-like vertices, now 30 to 60.  With gw / gc (the histograms of the
+// grid-wide first pass) the first pass has already run: the kernel rederives its threshold, clears the
+// histogram, and continues over the entries that pass kept in keep2 (nothing is left to do when it
+// completed the selection).
 __device__ __forceinline__ void select_segment(const int32_t sgm, uint32_t *entries, DevStatus *st,
                                                int4 *__restrict__ moves, int32_t *__restrict__ sel_target,
                                                int32_t *__restrict__ part, uint8_t *__restrict__ mvfrom,
