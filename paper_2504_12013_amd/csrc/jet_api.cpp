@@ -189,6 +189,11 @@ void free_ctx(Ctx &c) {
   if (c.hst) (void)hipHostFree(c.hst);
   drop_graph(c);
   if (c.gstream) (void)hipStreamDestroy(c.gstream);
+  for (int i = 0; i < jet::kSides; ++i) {
+    if (c.side[i]) (void)hipStreamDestroy(c.side[i]);
+    if (c.join[i]) (void)hipEventDestroy(c.join[i]);
+  }
+  if (c.fork) (void)hipEventDestroy(c.fork);
   for (void *p : {(void *)c.lc, (void *)c.cpart, (void *)c.dtrace, (void *)c.dprof, (void *)c.vhg, (void *)c.nhg,
                   (void *)c.act, (void *)c.ht0, (void *)c.hch0})
     if (p) (void)hipFree(p);
@@ -461,6 +466,13 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
   HIP_OR_FAIL(&c, dalloc(&c.dprof, 1));
   HIP_OR_FAIL(&c, hipMemsetAsync(c.dprof, 0, sizeof(jet::DevProf), c.stream));
   HIP_OR_FAIL(&c, hipStreamCreateWithFlags(&c.gstream, hipStreamNonBlocking));
+  if (jet::ab_branches(c)) {
+    for (int i = 0; i < jet::kSides; ++i) {
+      HIP_OR_FAIL(&c, hipStreamCreateWithFlags(&c.side[i], hipStreamNonBlocking));
+      HIP_OR_FAIL(&c, hipEventCreateWithFlags(&c.join[i], hipEventDisableTiming));
+    }
+    HIP_OR_FAIL(&c, hipEventCreateWithFlags(&c.fork, hipEventDisableTiming));
+  }
   {
     int dev = 0, khz = 0;
     if (hipGetDevice(&dev) == hipSuccess &&

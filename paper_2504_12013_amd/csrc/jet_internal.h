@@ -328,6 +328,8 @@ struct FlowState {
 // The pieces of an iteration: what the host launches for a phase.
 enum TickKind : int { kTickJet = 0, kTickRb = 1, kTickRoll = 2 };
 constexpr int kTickPieces = 3;
+constexpr int kSides = 3;
+constexpr int64_t kForkPins = 1 << 19;  // pins from which the afterburner's kernels run beside each other
 
 struct Ctx {
   hipStream_t stream = nullptr;
@@ -435,6 +437,8 @@ struct Ctx {
   hipStream_t gstream = nullptr; // stream the iteration graph is captured on
   // captured pieces of an iteration (TickKind): Jet phase + end, Jet phase + rebalancing slots +
   // end, rebalancing slots + end, rollback
+  hipStream_t side[kSides] = {};  // branches of the afterburner beside `stream`
+  hipEvent_t fork = nullptr, join[kSides] = {};
   hipGraph_t graph[kTickPieces] = {};
   hipGraphExec_t gexec[kTickPieces] = {};
   bool use_graph = true;         // JET_OPT_GRAPH
@@ -539,6 +543,7 @@ hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc = n
 enum : int32_t { kResetCandidates = 1, kResetMoves = 2 };
 hipError_t launch_reset_counters(Ctx &c, int32_t what);
 hipError_t launch_afterburner_overflow(Ctx &c, RgSink sink, const LoopCtl *lc);  // k_ab_large.hip
+bool ab_branches(const Ctx &c);
 hipError_t launch_select_moves(Ctx &c, int32_t *part, int32_t stamp, const LoopCtl *lc = nullptr);
 // wide: size the net-centric grids for that path (a performance hint; the device decides the path)
 hipError_t launch_apply_moves(Ctx &c, int32_t *part, bool wide, const LoopCtl *lc = nullptr, int32_t want = kPhAny);

@@ -1479,19 +1479,30 @@ __global__ void k_rg_reduce(int32_t *__restrict__ rgx, int32_t copies, int32_t n
 }
 
 // Larger nets of the afterburner: 1,024-entry LDS lists for medium nets above 256 pins, 256-entry
-// ones below, and the big-net kernel with its global-scratch overflow list.
+// ones below, and the big-net kernel with its global-scratch overflow list, each on its stream.
 template <int NW, typename T>
-void ab_nets_launch(Ctx &c, RgSink sink, const T *phi, const LoopCtl *lc) {
-  if (c.nmid_large > 0)
-    hipLaunchKernelGGL((k_ab_nets<128, kMediumNet, NW, T>), dim3((unsigned)c.nmid_large), dim3(128), 0, c.stream, c.off,
-                       c.pins, c.mid_nets, c.nw, c.inm, c.rec, phi, c.ns, c.k, sink, c.st, (int2 *)nullptr, lc, union_of(c));
-  if (c.nmid > c.nmid_large)
-    hipLaunchKernelGGL((k_ab_nets<64, kMediumSmall, NW, T>), dim3((unsigned)(c.nmid - c.nmid_large)), dim3(64), 0,
-                       c.stream, c.off, c.pins, c.mid_nets + c.nmid_large, c.nw, c.inm, c.rec, phi, c.ns, c.k, sink,
-                       c.st, (int2 *)nullptr, lc, union_of(c));
+void ab_nets_launch(Ctx &c, RgSink sink, const T *phi, const LoopCtl *lc, const hipStream_t *on) {
   if (c.nbig > 0)
     hipLaunchKernelGGL((k_ab_nets<512, kBigCap, NW, T>), dim3((unsigned)c.nbig), dim3(512), 0, c.stream, c.off, c.pins,
                        c.big_nets, c.nw, c.inm, c.rec, phi, c.ns, c.k, sink, c.st, c.ovf_list, lc, union_of(c));
+  if (c.nmid_large > 0)
+    hipLaunchKernelGGL((k_ab_nets<128, kMediumNet, NW, T>), dim3((unsigned)c.nmid_large), dim3(128), 0, on[0], c.off,
+                       c.pins, c.mid_nets, c.nw, c.inm, c.rec, phi, c.ns, c.k, sink, c.st, (int2 *)nullptr, lc,
+                       union_of(c));
+  if (c.nmid > c.nmid_large)
+    hipLaunchKernelGGL((k_ab_nets<64, kMediumSmall, NW, T>), dim3((unsigned)(c.nmid - c.nmid_large)), dim3(64), 0,
+                       on[1], c.off, c.pins, c.mid_nets + c.nmid_large, c.nw, c.inm, c.rec, phi, c.ns, c.k, sink, c.st,
+                       (int2 *)nullptr, lc, union_of(c));
+}
+
+// The kernels of the net sizes run beside each other: a net of 10,000 pins keeps one workgroup busy for
+// 80 us while the others leave the chip, so it starts first.  On 1M row-net vertices at
+// k = 64 a full iteration's kernels took 314 us one after the other, 159 us beside each other.
+// Levels with few pins finish each within the 10 us that a fork and a join cost, and the unions of a
+// batch already run beside each other (166 ms for 96 hypergraphs, 195 ms with branches).
+bool ab_branches(const Ctx &c) {
+  const int kinds = (c.nchunks > 0) + (c.nbig > 0) + (c.nmid_large > 0) + (c.nmid > c.nmid_large);
+  return c.H == 1 && kinds > 1 && c.p >= kForkPins && !graph_afterburner(c);
 }
 
 hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc) {
@@ -1508,23 +1519,35 @@ hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc) {
     prof_end(c, tok, lc, want, 4.125 * c.n, 8.125 + (c.unit_nw ? 0.0 : 8.0));
     return e;
   }
+  const bool branch = c.fork && ab_branches(c);
+  hipStream_t on[kSides];
+  hipError_t err = branch ? hipEventRecord(c.fork, c.stream) : hipSuccess;
+  for (int i = 0; i < kSides; ++i) {
+    on[i] = branch ? c.side[i] : c.stream;
+    if (branch && err == hipSuccess) err = hipStreamWaitEvent(on[i], c.fork, 0);
+  }
+  if (err != hipSuccess) return err;
+  if (c.nw_words == 1) {
+    if (c.phi16) ab_nets_launch<1>(c, sink, c.phi16, lc, on);
+    else ab_nets_launch<1>(c, sink, c.phi, lc, on);
+  } else {
+    if (c.phi16) ab_nets_launch<2>(c, sink, c.phi16, lc, on);
+    else ab_nets_launch<2>(c, sink, c.phi, lc, on);
+  }
   if (c.nchunks > 0) {
     const dim3 grid((unsigned)std::min<int64_t>(c.grid_cap, (c.nchunks + 3) / 4));
     if (c.k <= 64)
-      hipLaunchKernelGGL(k_ab_chunks<16>, grid, dim3(256), 0, c.stream, c.pins, c.chunks, c.pnet, c.nchunks, c.nw,
+      hipLaunchKernelGGL(k_ab_chunks<16>, grid, dim3(256), 0, on[2], c.pins, c.chunks, c.pnet, c.nchunks, c.nw,
                          part, c.inm, c.rec, sink, lc, union_of(c), c.cand_xcd);
     else
-      hipLaunchKernelGGL(k_ab_chunks<kMaxK / 4>, grid, dim3(256), 0, c.stream, c.pins, c.chunks, c.pnet, c.nchunks,
+      hipLaunchKernelGGL(k_ab_chunks<kMaxK / 4>, grid, dim3(256), 0, on[2], c.pins, c.chunks, c.pnet, c.nchunks,
                          c.nw, part, c.inm, c.rec, sink, lc, union_of(c), c.cand_xcd);
   }
-  if (c.nw_words == 1) {
-    if (c.phi16) ab_nets_launch<1>(c, sink, c.phi16, lc);
-    else ab_nets_launch<1>(c, sink, c.phi, lc);
-  } else {
-    if (c.phi16) ab_nets_launch<2>(c, sink, c.phi16, lc);
-    else ab_nets_launch<2>(c, sink, c.phi, lc);
+  err = hipGetLastError();
+  for (int i = 0; i < kSides && branch; ++i) {
+    if (err == hipSuccess) err = hipEventRecord(c.join[i], on[i]);
+    if (err == hipSuccess) err = hipStreamWaitEvent(c.stream, c.join[i], 0);
   }
-  hipError_t err = hipGetLastError();
   if (err != hipSuccess) return err;
   err = launch_afterburner_overflow(c, sink, lc);
   if (err == hipSuccess && c.rg_copies > 1) {

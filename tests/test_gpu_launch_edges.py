@@ -238,3 +238,28 @@ def test_split_selection_digits(nw_max, vw_max, order, monkeypatch):
     assert rc == orc
     assert np.array_equal(d.cpu().numpy(), ref)
     assert st["rebalance_rounds"] == ost["rebalance_rounds"]
+
+
+@pytest.mark.parametrize("graph", [0, 1])
+def test_afterburner_branches(graph):
+    """Nets of every size class at the pin count from which their kernels run beside each other, from a
+    captured graph and launched one by one, twice on one context."""
+    rng = np.random.default_rng(17)
+    n, k = 20000, 9
+    sizes = np.concatenate([rng.integers(2, 9, 60000), np.full(300, 200), np.full(120, 900), np.full(20, 6000)])
+    nets = [np.sort(rng.choice(n, s, replace=False)) for s in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    hg = W.Hypergraph(n=n, m=len(nets), off=off, pins=np.concatenate(nets).astype(np.int32), k=k, eps=0.05)
+    assert hg.p >= 1 << 19
+    part = W.part_uniform(n, k, 4)
+    say(f"{hg.p} pins, graph {graph}")
+    kw = dict(tau=(0.75,), limit=3, max_iters=6)
+    ref, orc, ost, _ = O.refine(hg, part, **kw)
+    ctx = J().JetContext(hg)
+    ctx.set_option(J().JET_OPT_GRAPH, graph)
+    for _ in range(2):
+        d = torch.from_numpy(part).to("cuda")
+        rc, st, _ = ctx.refine(d, **kw)
+        assert rc == orc and st["km1_out"] == ost["km1_out"]
+        assert np.array_equal(d.cpu().numpy(), ref)
+    ctx.close()
