@@ -240,6 +240,37 @@ __device__ __forceinline__ void planes_accumulate(const int32_t *__restrict__ in
   }
 }
 
+// The same for a graph (every net has two pins, adj holds the other one): the neighbours' blocks instead of
+// the nets' words.  Only blocks other than s are added; benefit counts the neighbours outside s.  Inside
+// a block nothing is (wave-uniformly: nothing that any lane needs).
+template <int HW, int N>
+__device__ __forceinline__ void planes_accumulate_graph(const int32_t *__restrict__ adj, int64_t q, int64_t q1,
+                                                        const int32_t *__restrict__ part, int32_t s,
+                                                        uint32_t (&pl)[HW][N], int32_t &benefit) {
+  for (; q < q1; q += 8) {
+    int32_t v[8], b[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = q + u < q1 ? adj[q + u] : -1;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) b[u] = v[u] >= 0 ? part[v[u]] : s;
+    int32_t out = 0;
+#pragma unroll
+    for (int u = 0; u < 8; ++u) out += b[u] != s;
+    benefit += out;
+    if (!ballot(out != 0)) continue;
+    uint32_t m[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) m[u] = b[u] != s ? 1u << (b[u] & 31) : 0u;
+#pragma unroll
+    for (int x = 0; x < HW; ++x) {
+#pragma unroll
+      for (int h = 0; h < 8; h += 4)
+        planes_add4(pl[x], (b[h] >> 5) == x ? m[h] : 0u, (b[h + 1] >> 5) == x ? m[h + 1] : 0u,
+                    (b[h + 2] >> 5) == x ? m[h + 2] : 0u, (b[h + 3] >> 5) == x ? m[h + 3] : 0u);
+    }
+  }
+}
+
 // a += b over N planes, the last carry dropped (the caller's counts fit)
 template <int N>
 __device__ __forceinline__ void planes_sum(uint32_t (&a)[N], const uint32_t (&b)[N]) {
