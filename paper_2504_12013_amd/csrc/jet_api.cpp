@@ -135,12 +135,8 @@ int check_params(Ctx &c, const jet_params *p, bool loop) {
 // Builds pin counts, connectivity words, block weights and the metric from part.
 int build_state(Ctx &c, const int32_t *part) {
   if (!part) return fail(&c, JET_EINVAL, "part is NULL");
-  HIP_OR_FAIL(&c, jet::launch_check_part(c, part));
-  int rc = read_status(c);
-  if (rc != JET_OK) return rc;
-  HIP_OR_FAIL(&c, c.phi16 ? jet::launch_build_phi(c, part, c.phi16) : jet::launch_build_phi(c, part, c.phi));
-  HIP_OR_FAIL(&c, jet::launch_build_ns(c));
-  HIP_OR_FAIL(&c, jet::launch_block_weights(c, part));
+  HIP_OR_FAIL(&c, jet::launch_block_weights(c, part));  // checks the partition
+  HIP_OR_FAIL(&c, jet::launch_build_counts(c, part));
   HIP_OR_FAIL(&c, jet::launch_km1_from_ns(c));
   return read_status(c);
 }

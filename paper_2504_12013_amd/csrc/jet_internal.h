@@ -518,8 +518,8 @@ hipError_t launch_check_weights(Ctx &c);
 // state (k_state.hip)
 hipError_t launch_check_part(Ctx &c, const int32_t *part);
 hipError_t launch_build_phi(Ctx &c, const int32_t *part, int32_t *phi);
-hipError_t launch_build_phi(Ctx &c, const int32_t *part, uint16_t *phi);
-hipError_t launch_build_ns(Ctx &c);
+// the context's counts and connectivity words
+hipError_t launch_build_counts(Ctx &c, const int32_t *part);
 hipError_t launch_block_weights(Ctx &c, const int32_t *part);
 hipError_t launch_km1_from_ns(Ctx &c);
 // one network evaluation on the network's stream: raw features x (device [16]) -> *tau (host);

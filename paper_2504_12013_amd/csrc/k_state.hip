@@ -13,70 +13,137 @@ namespace jet {
 
 namespace {
 
+// Block of v; out of range is reported and counts as block 0.
+__device__ __forceinline__ int32_t checked_block(const int32_t *__restrict__ part, int64_t v, int32_t k,
+                                                 DevStatus *st) {
+  const int32_t b = part[v];
+  if ((uint32_t)b < (uint32_t)k) return b;
+  if (atomicCAS(&st->err, 0, kErrPartRange) == 0) st->err_arg = (int32_t)v;
+  return 0;
+}
+
 __global__ void k_check_part(const int32_t *__restrict__ part, int32_t n, int32_t k, DevStatus *st) {
-  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t b = part[v];
-    if (b < 0 || b >= k)
-      if (atomicCAS(&st->err, 0, kErrPartRange) == 0) st->err_arg = (int32_t)v;
+  for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x)
+    (void)checked_block(part, v, k, st);
+}
+
+// A block read before the check of the partition has been looked at: out of range counts as block 0.
+__device__ __forceinline__ int32_t safe_block(int32_t b, int32_t k) { return (uint32_t)b < (uint32_t)k ? b : 0; }
+
+// Four byte counters as four counts.
+__device__ __forceinline__ void store_counts(uint16_t *p, uint32_t c) {
+  *reinterpret_cast<uint2 *>(p) =
+      make_uint2((c & 0xffu) | ((c & 0xff00u) << 8), ((c >> 16) & 0xffu) | ((c >> 8) & 0xff0000u));
+}
+__device__ __forceinline__ void store_counts(int32_t *p, uint32_t c) {
+  *reinterpret_cast<int4 *>(p) =
+      make_int4((int)(c & 0xffu), (int)((c >> 8) & 0xffu), (int)((c >> 16) & 0xffu), (int)(c >> 24));
+}
+
+// Small nets, one wave per chunk, one pin per lane: byte counters of (net of the chunk, block) in LDS, from
+// which the wave writes the nets' rows of counts (consecutive nets: one run of memory, four counts per
+// lane where rows allow it) and, with ns, their connectivity words.  Bound by writing m x k counts once;
+// clearing the table, an atomic per pin and reading it back for the words took 2.75 ms on the 12.6M
+// edges of a mesh at k = 64, now 0.46 ms.
+template <int NW, typename T>
+__global__ __launch_bounds__(256) void k_state_chunks(const int32_t *__restrict__ pins, const int4 *__restrict__ chunks,
+                                                      const uint8_t *__restrict__ pnet, int32_t nchunks,
+                                                      const int32_t *__restrict__ part, int32_t k, T *__restrict__ phi,
+                                                      uint64_t *__restrict__ ns, int32_t vec) {
+  __shared__ uint32_t cnt[4][kChunkNets][16 * NW];
+  __shared__ unsigned long long some[4][kChunkNets][NW], one[4][kChunkNets][NW];
+  const int w = threadIdx.x / kWave, l = lane_id();
+  uint32_t(*C)[16 * NW] = cnt[w];
+  for (int x = l; x < kChunkNets * 16 * NW; x += kWave) (&C[0][0])[x] = 0u;
+  const int32_t nwv = gridDim.x * 4, per = vec ? k / 4 : k;  // stores per net
+  const uint32_t inv = (1u << 20) / (uint32_t)per + 1u;  // x / per == (x * inv) >> 20 for x < 4,096, per <= 128
+  auto fetch = [&](int32_t c, int4 &d, int32_t &p, int32_t &j) {
+    d = c < nchunks ? chunks[c] : make_int4(0, 0, 0, 0);
+    p = j = 0;
+    if (l < d.z) {
+      j = pnet[(int64_t)d.w + l];
+      p = pins[(int64_t)d.w + l];
+    }
+  };
+  int4 cd;
+  int32_t pin, j;
+  fetch(blockIdx.x * 4 + w, cd, pin, j);
+  for (int32_t c = blockIdx.x * 4 + w; c < nchunks; c += nwv) {  // wave-uniform
+    const bool act = l < cd.z;
+    const int32_t b = act ? safe_block(part[pin], k) : 0;
+    int4 ncd;
+    int32_t npin, nj;
+    fetch(c + nwv, ncd, npin, nj);  // the next chunk's loads overlap this chunk's work
+    if (l < kChunkNets) {
+#pragma unroll
+      for (int x = 0; x < NW; ++x) some[w][l][x] = one[w][l][x] = 0ull;
+    }
+    if (act) atomicAdd(&C[j][b >> 2], 1u << (8 * (b & 3)));
+    wave_lds_sync();
+    if (act && ns) {
+      const uint32_t mine = (C[j][b >> 2] >> (8 * (b & 3))) & 0xffu;
+      atomicOr(&some[w][j][b >> 6], 1ull << (b & 63));
+      if (mine == 1u) atomicOr(&one[w][j][b >> 6], 1ull << (b & 63));
+    }
+    T *row = phi + (int64_t)cd.x * k;
+    const int32_t total = cd.y * per;
+    for (int32_t i = l; i < total; i += kWave) {
+      const int32_t e = (int32_t)(((uint32_t)i * inv) >> 20), x = i - e * per;
+      if (vec) store_counts(row + 4 * (int64_t)i, C[e][x]);
+      else row[i] = (T)((C[e][x >> 2] >> (8 * (x & 3))) & 0xffu);
+    }
+    wave_lds_sync();
+    if (ns && l < cd.y) {
+      uint64_t *nse = ns + (int64_t)(cd.x + l) * (2 * NW);
+#pragma unroll
+      for (int x = 0; x < NW; ++x) {
+        nse[x] = some[w][l][x];
+        nse[NW + x] = one[w][l][x];
+      }
+    }
+    if (act) C[j][b >> 2] = 0u;  // every nonzero counter word has a pin here
+    wave_lds_sync();
+    cd = ncd;
+    pin = npin;
+    j = nj;
   }
 }
 
-// small nets: one wave per chunk, one pin per lane
-template <typename T>
-__global__ __launch_bounds__(256) void k_phi_chunks(const int64_t *__restrict__ off, const int32_t *__restrict__ pins,
-                                                    const int4 *__restrict__ chunks, const uint8_t *__restrict__ pnet,
-                                                    int32_t nchunks,
-                                                    const int32_t *__restrict__ part, int32_t k,
-                                                    T *__restrict__ phi) {
-  const int w = threadIdx.x / kWave;
-  const int32_t c = blockIdx.x * 4 + w;
-  const bool has = c < nchunks;
-  const int4 cd = has ? chunks[c] : make_int4(0, 0, 0, 0);
-  const ChunkLane cl = chunk_lane(cd, pnet, has);
-  if (cl.active) phi_atomic_add(phi, (int64_t)cl.net * k + part[pins[cl.q]], 1);
-}
-
-// larger nets: one block per net, histogram in LDS, then the block writes the row it owns
-template <typename T>
-__global__ __launch_bounds__(256) void k_phi_large(const int64_t *__restrict__ off, const int32_t *__restrict__ pins,
-                                                   const int32_t *__restrict__ nets, const int32_t *__restrict__ part,
-                                                   int32_t k, T *__restrict__ phi) {
+// Larger nets: one block per net (the big ones first), histogram in LDS, then the block writes the row it
+// owns and the words.
+template <int NW, typename T>
+__global__ __launch_bounds__(256) void k_state_large(const int64_t *__restrict__ off, const int32_t *__restrict__ pins,
+                                                     const int32_t *__restrict__ big, int32_t nbig,
+                                                     const int32_t *__restrict__ mid, const int32_t *__restrict__ part,
+                                                     int32_t k, T *__restrict__ phi, uint64_t *__restrict__ ns) {
   __shared__ int32_t hist[kMaxK];
-  const int32_t e = nets[blockIdx.x];
+  const int32_t e = (int32_t)blockIdx.x < nbig ? big[blockIdx.x] : mid[blockIdx.x - nbig];
+  const int64_t q0 = off[e], q1 = off[e + 1];
   for (int b = threadIdx.x; b < k; b += blockDim.x) hist[b] = 0;
   __syncthreads();
-  for (int64_t q = off[e] + threadIdx.x; q < off[e + 1]; q += blockDim.x) atomicAdd(&hist[part[pins[q]]], 1);
+  for (int64_t qb = q0 + threadIdx.x; qb < q1; qb += 4 * blockDim.x) {  // four pins' loads in flight
+    int32_t v[4], b[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) v[u] = qb + u * blockDim.x < q1 ? pins[qb + u * blockDim.x] : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u) b[u] = v[u] >= 0 ? safe_block(part[v[u]], k) : -1;
+#pragma unroll
+    for (int u = 0; u < 4; ++u)
+      if (b[u] >= 0) atomicAdd(&hist[b[u]], 1);
+  }
   __syncthreads();
-  for (int b = threadIdx.x; b < k; b += blockDim.x) phi[(int64_t)e * k + b] = (T)hist[b];
-}
-
-// Connectivity words from pin counts: mask bit b = (phi_e[b] > 0), single bit b = (phi_e[b] == 1).
-// Lane i of the flattened (net, padded block) index space reads one count; ballots form the words.
-template <int KP, typename T>
-__global__ __launch_bounds__(256) void k_build_ns(const T *__restrict__ phi, int32_t m, int32_t k,
-                                                  uint64_t *__restrict__ ns) {
-  constexpr int NW = KP > 64 ? 2 : 1;
-  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  const int64_t e = i / KP;
-  const int b = (int)(i % KP);
-  int32_t val = 0;
-  if (e < m && b < k) val = (int32_t)phi[e * k + b];
-  const uint64_t nz = ballot(val > 0), one = ballot(val == 1);
-  if (e >= m) return;
-  if (KP >= 64) {
-    if (lane_id() == 0) {
-      const int word = b / 64;
-      ns[e * 2 * NW + word] = nz;
-      ns[e * 2 * NW + NW + word] = one;
-    }
-  } else if (b == 0) {
-    const int sh = lane_id();  // this net's field starts at this lane
-    const uint64_t fm = (KP == 64) ? ~0ull : ((1ull << KP) - 1ull);
-    ns[e * 2] = (nz >> sh) & fm;
-    ns[e * 2 + 1] = (one >> sh) & fm;
+  const int b = threadIdx.x, x = threadIdx.x / kWave;
+  const int32_t h = b < k ? hist[b] : 0;
+  if (b < k) phi[(int64_t)e * k + b] = (T)h;
+  if (!ns || x >= NW) return;
+  const uint64_t some = ballot(h > 0), one = ballot(h == 1);
+  if (lane_id() == 0) {
+    ns[(int64_t)e * (2 * NW) + x] = some;
+    ns[(int64_t)e * (2 * NW) + NW + x] = one;
   }
 }
 
+// Block weights and sizes, and the check of the partition (every vertex is read here).
 __global__ __launch_bounds__(256) void k_block_weights(const int32_t *__restrict__ part,
                                                        const int32_t *__restrict__ vw, int32_t n, int32_t k,
                                                        DevStatus *st, Union u) {
@@ -98,11 +165,11 @@ __global__ __launch_bounds__(256) void k_block_weights(const int32_t *__restrict
       const int32_t hg = u.vhg[t * kUnionTile];
       const bool mine = v < n && u.vhg[v] == hg;
       if (mine) {
-        const int32_t b = part[v];
+        const int32_t b = checked_block(part, v, k, st);
         atomicAdd(&sw[b], (unsigned long long)(vw ? vw[v] : 1));
         atomicAdd(&sc[b], 1);
       } else if (v < n) {  // padding: the pseudo-hypergraph's segments
-        const int64_t sg = (int64_t)u.vhg[v] * k + part[v];
+        const int64_t sg = (int64_t)u.vhg[v] * k + checked_block(part, v, k, st);
         atomicAdd((unsigned long long *)&st->bw[sg], (unsigned long long)(vw ? vw[v] : 1));
         atomicAdd(&st->bcnt[sg], 1);
       }
@@ -120,7 +187,7 @@ __global__ __launch_bounds__(256) void k_block_weights(const int32_t *__restrict
     return;
   }
   for (int64_t v = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; v < n; v += (int64_t)gridDim.x * blockDim.x) {
-    const int32_t b = part[v];
+    const int32_t b = checked_block(part, v, k, st);
     atomicAdd(&sw[b], (unsigned long long)(vw ? vw[v] : 1));
     atomicAdd(&sc[b], 1);
   }
@@ -251,49 +318,34 @@ hipError_t launch_check_part(Ctx &c, const int32_t *part) {
 
 namespace {
 
-template <typename T>
-hipError_t build_phi(Ctx &c, const int32_t *part, T *phi) {
-  // 16-bit tables (the context's own) are cleared with their padding; an int32 table may be a
-  // caller's buffer of exactly m*k counts
-  const size_t entries = (size_t)c.m * c.k + (sizeof(T) == 2 ? 1 : 0);
-  hipError_t e = hipMemsetAsync(phi, 0, sizeof(T) * entries, c.stream);
-  if (e != hipSuccess) return e;
+// Counts of every net, and with ns the connectivity words.  Every row is written whole.
+template <int NW, typename T>
+hipError_t build_counts(Ctx &c, const int32_t *part, T *phi, uint64_t *ns) {
+  // four counts per store where rows begin on a multiple of it (a caller's table may begin anywhere)
+  const int32_t vec = c.k % 4 == 0 && reinterpret_cast<uintptr_t>(phi) % (4 * sizeof(T)) == 0 ? 1 : 0;
   if (c.nchunks > 0)
-    hipLaunchKernelGGL(k_phi_chunks<T>, dim3((unsigned)((c.nchunks + 3) / 4)), dim3(256), 0, c.stream, c.off, c.pins,
-                       c.chunks, c.pnet, c.nchunks, part, c.k, phi);
-  if (c.nmid > 0)
-    hipLaunchKernelGGL(k_phi_large<T>, dim3((unsigned)c.nmid), dim3(256), 0, c.stream, c.off, c.pins, c.mid_nets,
-                       part, c.k, phi);
-  if (c.nbig > 0)
-    hipLaunchKernelGGL(k_phi_large<T>, dim3((unsigned)c.nbig), dim3(256), 0, c.stream, c.off, c.pins, c.big_nets,
-                       part, c.k, phi);
+    launch_resident<k_state_chunks<NW, T>>(c, ((int64_t)c.nchunks + 3) / 4, 256, c.pins, c.chunks, c.pnet, c.nchunks,
+                                           part, c.k, phi, ns, vec);
+  if (c.nmid + c.nbig > 0)
+    hipLaunchKernelGGL((k_state_large<NW, T>), dim3((unsigned)(c.nmid + c.nbig)), dim3(256), 0, c.stream, c.off,
+                       c.pins, c.big_nets, c.nbig, c.mid_nets, part, c.k, phi, ns);
   return hipGetLastError();
 }
 
 template <typename T>
-hipError_t build_ns(Ctx &c, const T *phi) {
-  int kp = 1;
-  while (kp < c.k) kp <<= 1;
-  const int64_t threads = (int64_t)c.m * kp;
-  const unsigned g = grid_for(threads, 256, INT32_MAX);
-  switch (kp) {
-  case 2: hipLaunchKernelGGL((k_build_ns<2, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  case 4: hipLaunchKernelGGL((k_build_ns<4, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  case 8: hipLaunchKernelGGL((k_build_ns<8, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  case 16: hipLaunchKernelGGL((k_build_ns<16, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  case 32: hipLaunchKernelGGL((k_build_ns<32, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  case 64: hipLaunchKernelGGL((k_build_ns<64, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  default: hipLaunchKernelGGL((k_build_ns<128, T>), dim3(g), dim3(256), 0, c.stream, phi, c.m, c.k, c.ns); break;
-  }
-  return hipGetLastError();
+hipError_t build_counts(Ctx &c, const int32_t *part, T *phi, uint64_t *ns) {
+  return c.nw_words == 1 ? build_counts<1>(c, part, phi, ns) : build_counts<2>(c, part, phi, ns);
 }
 
 }  // namespace
 
-hipError_t launch_build_phi(Ctx &c, const int32_t *part, int32_t *phi) { return build_phi(c, part, phi); }
-hipError_t launch_build_phi(Ctx &c, const int32_t *part, uint16_t *phi) { return build_phi(c, part, phi); }
+hipError_t launch_build_phi(Ctx &c, const int32_t *part, int32_t *phi) {
+  return build_counts(c, part, phi, (uint64_t *)nullptr);
+}
 
-hipError_t launch_build_ns(Ctx &c) { return c.phi16 ? build_ns(c, c.phi16) : build_ns(c, c.phi); }
+hipError_t launch_build_counts(Ctx &c, const int32_t *part) {
+  return c.phi16 ? build_counts(c, part, c.phi16, c.ns) : build_counts(c, part, c.phi, c.ns);
+}
 
 hipError_t launch_block_weights(Ctx &c, const int32_t *part) {
   const size_t nseg = (c.H > 1 ? (size_t)c.H + 1 : 1) * (size_t)c.k;  // a union's padding has its own segments

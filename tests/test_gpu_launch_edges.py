@@ -263,3 +263,33 @@ def test_afterburner_branches(graph):
         assert rc == orc and st["km1_out"] == ost["km1_out"]
         assert np.array_equal(d.cpu().numpy(), ref)
     ctx.close()
+
+
+@pytest.mark.parametrize("k", [2, 3, 4, 63, 64, 65, 124, 128])
+def test_counts_where_rows_and_chunks_end(k):
+    """Pin counts (rows of every alignment, also in a caller's table at an odd offset) and the metric on
+    nets of one pin, of a chunk's 64 pins and above, and a partition out of range."""
+    rng = np.random.default_rng(k)
+    n = 3000
+    sizes = np.concatenate([np.ones(70, int), np.full(40, 2), rng.integers(2, 20, 900), [63, 64, 65, 1023, 1024, 1025]])
+    nets = [np.sort(rng.choice(n, s, replace=False)) for s in sizes]
+    off = np.concatenate([[0], np.cumsum(sizes)]).astype(np.int64)
+    hg = W.Hypergraph(n=n, m=len(nets), off=off, pins=np.concatenate(nets).astype(np.int32), k=k, eps=0.05)
+    part = W.part_uniform(n, k, 8)
+    say(f"k = {k}")
+    ref = np.zeros((hg.m, k), np.int64)
+    np.add.at(ref, (np.repeat(np.arange(hg.m), sizes), part[hg.pins]), 1)
+    ctx = J().JetContext(hg)
+    d = torch.from_numpy(part).to("cuda")
+    assert np.array_equal(ctx.phi(d).cpu().numpy().reshape(hg.m, k), ref)
+    odd = torch.full((hg.m * k + 2,), -7, dtype=torch.int32, device="cuda")
+    J().jet_phi(ctx.h, d, odd[1:-1])
+    assert np.array_equal(odd[1:-1].cpu().numpy().reshape(hg.m, k), ref)
+    assert int(odd[0]) == int(odd[-1]) == -7
+    assert ctx.km1(d) == int(((ref > 0).sum(axis=1) - 1).clip(min=0).sum())
+    bad = part.copy()
+    bad[17] = k
+    with pytest.raises(J().JetError, match="part"):
+        ctx.km1(torch.from_numpy(bad).to("cuda"))
+    assert ctx.km1(d) == O.km1(hg, part)
+    ctx.close()
