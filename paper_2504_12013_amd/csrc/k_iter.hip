@@ -1220,6 +1220,7 @@ __device__ __forceinline__ void recount_mid(const int64_t *__restrict__ off, con
 
 // Net-centric, big nets: one block per net; per-block count changes gathered in LDS, then the
 // block rewrites the changed counts, the connectivity words and its metric contribution.
+constexpr int kBigU = 8;  // slices of a big net in flight
 template <int NW>
 struct NetLds {
   int32_t delta[kMaxK];
@@ -1243,22 +1244,22 @@ __device__ __forceinline__ void recount_nets(const int64_t *__restrict__ off, co
   if (threadIdx.x == 0) L.any = 0;
   if (threadIdx.x < 2 * NW) L.words[threadIdx.x] = ns[(int64_t)e * (2 * NW) + threadIdx.x];
   __syncthreads();
-  // four slices of the net at a time, each level of their dependent loads (pin, block
+  // kBigU slices of the net at a time, each level of their dependent loads (pin, block
   // left, block) issued for all before any is used
-  for (int64_t qb = q0; qb < q1; qb += 4 * kApplyBlock) {
-    int32_t v[4], nb[4];
-    uint8_t mf[4];
+  for (int64_t qb = q0; qb < q1; qb += kBigU * kApplyBlock) {
+    int32_t v[kBigU], nb[kBigU];
+    uint8_t mf[kBigU];
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kBigU; ++u) {
       const int64_t q = qb + u * kApplyBlock + threadIdx.x;
       v[u] = q < q1 ? pins[q] : -1;
     }
 #pragma unroll
-    for (int u = 0; u < 4; ++u) mf[u] = v[u] >= 0 ? mvfrom[v[u]] : (uint8_t)0xff;
+    for (int u = 0; u < kBigU; ++u) mf[u] = v[u] >= 0 ? mvfrom[v[u]] : (uint8_t)0xff;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) nb[u] = mf[u] != 0xff ? part[v[u]] : 0;
+    for (int u = 0; u < kBigU; ++u) nb[u] = mf[u] != 0xff ? part[v[u]] : 0;
 #pragma unroll
-    for (int u = 0; u < 4; ++u) {
+    for (int u = 0; u < kBigU; ++u) {
       if (mf[u] != 0xff) {
         atomicSub(&L.delta[mf[u]], 1);
         atomicAdd(&L.delta[nb[u]], 1);
@@ -1322,7 +1323,7 @@ __global__ __launch_bounds__(kApplyBlock) void k_apply(
   __shared__ ChunkLds<NW> chunk_lds[kApplyBlock / kWave];
   __shared__ NetLds<NW> net_lds;
   __shared__ int32_t mid_lds[kApplyBlock / kWave][kMaxK];
-  const int32_t cnt = st->n_moves;
+  const int32_t cnt = st->n_moves, nbigmv = st->n_bigmv;
   if (cnt == 0) return;
   const bool by_vertex = !net_centric(st, p, divisor);
   for (int b = threadIdx.x; b < k; b += blockDim.x) {
@@ -1372,6 +1373,18 @@ __global__ __launch_bounds__(kApplyBlock) void k_apply(
     i1 = by_vertex ? min((int64_t)cnt, (x + 1) * per * span) : 0;
     istep = (int64_t)(gridDim.x / 8) * span;
   }
+  // high-degree moves: an equal share of the grid each (several blocks per move while there are
+  // fewer such moves than blocks), the threads of the share striding over the move's nets.  This
+  // workgroup's is looked up before the light moves, beside their loads.
+  const bool share = by_vertex && nbigmv > 0 && nbigmv <= (int32_t)gridDim.x;
+  const int32_t bper = share ? (int32_t)gridDim.x / nbigmv : 1, bj = (int32_t)blockIdx.x / bper;
+  int4 bmv = make_int4(0, 0, 0, 0);
+  int64_t bq0 = 0, bq1 = 0;
+  if (share && bj < nbigmv) {
+    bmv = moves[bigmv[bj]];
+    bq0 = voff[bmv.x];
+    bq1 = voff[bmv.x + 1];
+  }
   for (int64_t i = i0; i < i1; i += istep) {
     const int4 mv = moves[i];
     const int32_t hg = un ? (int32_t)u.vhg[mv.x] : 0;
@@ -1400,22 +1413,16 @@ __global__ __launch_bounds__(kApplyBlock) void k_apply(
     }
   }
   if (by_vertex) {
-    // high-degree moves: an equal share of the grid each (several blocks per move while there are
-    // fewer such moves than blocks), the threads of the share striding over the move's nets
-    const int32_t nb = st->n_bigmv;
-    if (nb > 0 && nb <= (int32_t)gridDim.x) {
-      const int32_t per = (int32_t)gridDim.x / nb;
-      const int32_t j = (int32_t)blockIdx.x / per, sub = (int32_t)blockIdx.x % per;
-      if (j < nb) {
-        const int4 mv = moves[bigmv[j]];
-        const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
-        const int64_t d = apply_nets_of_move<NW>(inc, q0 + (int64_t)sub * blockDim.x + threadIdx.x, q1,
-                                                 (int64_t)per * blockDim.x, mv.y, mv.z, k, nw, phi, ns);
-        if (u.vhg) add_km1_hg(st, u.vhg[mv.x], d);
+    if (share) {
+      const int32_t sub = (int32_t)blockIdx.x % bper;
+      if (bj < nbigmv) {
+        const int64_t d = apply_nets_of_move<NW>(inc, bq0 + (int64_t)sub * blockDim.x + threadIdx.x, bq1,
+                                                 (int64_t)bper * blockDim.x, bmv.y, bmv.z, k, nw, phi, ns);
+        if (u.vhg) add_km1_hg(st, u.vhg[bmv.x], d);
         else dk += d;
       }
     } else {
-      for (int32_t j = blockIdx.x; j < nb; j += gridDim.x) {
+      for (int32_t j = blockIdx.x; j < nbigmv; j += gridDim.x) {
         const int4 mv = moves[bigmv[j]];
         const int64_t q0 = voff[mv.x], q1 = voff[mv.x + 1];
         const int64_t d = apply_nets_of_move<NW>(inc, q0 + threadIdx.x, q1, blockDim.x, mv.y, mv.z, k, nw, phi, ns);
