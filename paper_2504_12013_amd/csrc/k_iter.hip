@@ -287,10 +287,14 @@ __global__ void k_import_candidates(const int32_t *__restrict__ part, const int3
 // Small nets, one wave per chunk.  The whole net is in the wave, so each candidate lane takes the
 // net's pins in its source and target blocks (phi_e[s], phi_e[t]) from byte counters of (net of
 // the chunk, block) that every pin of the chunk adds one to in the wave's LDS table (a chunk holds
-// at most 64 pins, so a byte never carries): no pin count or connectivity word is read.  Only the
-// candidates of nets with two or more candidates have predecessors to count; a candidate alone on
-// its net skips that step.  The pins clear their counter words again at the end, so the table is
-// zero between chunks.
+// at most 64 pins, so a byte never carries): no pin count or connectivity word is read.  The pins clear
+// their counter words again at the end, so the table is zero between chunks.
+// Counting predecessors is what bounds it (some 20 vector instructions per candidate of the chunk), so
+// few take part: those on nets with two or more candidates, and of them only those on a block of the
+// net from which every pin leaves -- a block that keeps a pin neither empties nor is found empty, whatever
+// the order.  The leaving pins are counted in a second byte table (k <= 64; above, two tables would halve
+// the waves in flight and all candidates take part).  1M row-net vertices, k = 64, in their first
+// iterations (beside the other sizes' kernels): 108 us on average, now 102.
 // One chunk of the afterburner for small nets (all lanes of the wave call it; the chunk's
 // descriptor, each lane's pin and its net index in the chunk are loaded by the caller).  KW: counter
 // words per net (k / 4 rounded up to 16 or 32).
@@ -298,7 +302,7 @@ template <int KW>
 __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const int32_t *__restrict__ nw,
                                          const int32_t *__restrict__ part, const uint32_t *__restrict__ inm,
                                          const uint64_t *__restrict__ rec, RgSink rg, int32_t slot,
-                                         uint32_t (*cnt)[KW], uint32_t *ncand) {
+                                         uint32_t (*cnt)[KW], uint32_t (*gone)[KW], uint32_t *ncand) {
   const int l = lane_id();
   ChunkLane cl;
   cl.active = l < cd.z;
@@ -321,15 +325,23 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
     t = rec_target(r);
   }
   if (cl.active) atomicAdd(&cnt[pj][pv >> 2], 1u << (8 * (pv & 3)));
-  if (cand) atomicAdd(&ncand[pj], 1u);
+  if (cand) {
+    atomicAdd(&ncand[pj], 1u);
+    if (gone) atomicAdd(&gone[pj][s >> 2], 1u << (8 * (s & 3)));
+  }
   wave_lds_sync();
   int32_t phs = 0, pht = 0;  // pins of the net in s (this one included) and in t
+  bool need = cand;
   if (cand) {
     phs = (int32_t)((cnt[pj][s >> 2] >> (8 * (s & 3))) & 0xffu);
     pht = (int32_t)((cnt[pj][t >> 2] >> (8 * (t & 3))) & 0xffu);
+    if (gone)
+      need = phs == (int32_t)((gone[pj][s >> 2] >> (8 * (s & 3))) & 0xffu) ||
+             pht == (int32_t)((gone[pj][t >> 2] >> (8 * (t & 3))) & 0xffu);
+    if (!need) khi = klo = 0xffffffffu;
   }
   const bool multi = cl.active && ncand[pj] >= 2u;  // this lane's net has two or more candidates
-  const uint64_t cm2 = ballot(cand && multi);
+  const uint64_t cm2 = ballot(need && multi);
   int32_t Ds = 0, As = 0, Dt = 0, At = 0;
   if (cm2) {
     const int32_t st_pack = s | (t << 8);
@@ -344,7 +356,7 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
     const int npins = __popcll(ballot(cl.active));  // outside any branch: a ballot sees active lanes only
     const int seg_end = later ? __ffsll((unsigned long long)later) - 1 : npins;
     const int segn = cl.active ? seg_end - seg0 : 0;
-    int maxseg = multi ? segn : 0;
+    int maxseg = need && multi ? segn : 0;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) maxseg = max(maxseg, __shfl_xor(maxseg, o, kWave));
     auto count = [&](uint32_t hj, uint32_t lj, int32_t pk) {
@@ -364,7 +376,7 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
         const int32_t ej = read_lane_i32(cl.net, j);
         const uint32_t hj = read_lane_u32(khi, j), lj = read_lane_u32(klo, j);
         const int32_t pk = read_lane_i32(st_pack, j);
-        if (cand && ej == cl.net) count(hj, lj, pk);
+        if (need && ej == cl.net) count(hj, lj, pk);
       }
     } else {
       for (int d = 1; d < maxseg; ++d) {
@@ -373,11 +385,11 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
         const int src = d < segn ? seg0 + r : l;
         const uint32_t hj = (uint32_t)__shfl((int)khi, src, kWave), lj = (uint32_t)__shfl((int)klo, src, kWave);
         const int32_t pk = __shfl(st_pack, src, kWave);
-        if (cand && d < segn) count(hj, lj, pk);
+        if (need && d < segn) count(hj, lj, pk);
       }
     }
   }
-  if (cand) {
+  if (need) {
     // v's turn: s empties iff exactly v is left in it; t fills iff it is empty before v arrives
     const int32_t wgt = nw ? nw[cl.net] : 1;
     const bool dep = phs + As - Ds == 1;
@@ -387,7 +399,10 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
   }
   wave_lds_sync();  // every lane has read its counters
   if (cl.active) cnt[pj][pv >> 2] = 0u;  // every nonzero counter word has a pin here
-  if (cand) ncand[pj] = 0u;
+  if (cand) {
+    ncand[pj] = 0u;
+    if (gone) gone[pj][s >> 2] = 0u;
+  }
 }
 
 template <int KW>
@@ -401,12 +416,17 @@ __global__ __launch_bounds__(256) void k_ab_chunks(const int32_t *__restrict__ p
   // union: only the chunks of the hypergraphs in their Jet phase
   const ActList *AL = u.lcs ? &u.act[kActJet] : nullptr;
   const int32_t nvc = AL ? AL->cpref[AL->cnt] : nchunks;
+  constexpr bool kGone = KW <= 16;
   __shared__ uint32_t cnt[4][kChunkNets][KW];
+  __shared__ uint32_t gone[kGone ? 4 : 1][kGone ? kChunkNets : 1][KW];
   __shared__ uint32_t ncand[4][kChunkNets];
   const int l = lane_id();
   const int w = threadIdx.x / kWave;
   const int32_t wid = blockIdx.x * 4 + w, nwv = gridDim.x * 4;
-  for (int x = 0; x < kChunkNets * KW; x += kWave) (&cnt[w][0][0])[x + l] = 0u;
+  for (int x = 0; x < kChunkNets * KW; x += kWave) {
+    (&cnt[w][0][0])[x + l] = 0u;
+    if (kGone) (&gone[kGone ? w : 0][0][0])[x + l] = 0u;
+  }
   if (l < kChunkNets) ncand[w][l] = 0u;
   wave_lds_sync();
   auto fetch = [&](int32_t cc, int4 &d, int32_t &p, int32_t &j) {
@@ -435,7 +455,7 @@ __global__ __launch_bounds__(256) void k_ab_chunks(const int32_t *__restrict__ p
     int4 ncd;
     int32_t npin, npj;
     fetch(c + cstep < cend ? c + cstep : nvc, ncd, npin, npj);  // the next chunk's loads overlap this chunk's work
-    ab_chunk<KW>(cd, pin, pj, nw, part, inm, rec, rg, wid, cnt[w], ncand[w]);
+    ab_chunk<KW>(cd, pin, pj, nw, part, inm, rec, rg, wid, cnt[w], kGone ? gone[kGone ? w : 0] : nullptr, ncand[w]);
     cd = ncd;
     pin = npin;
     pj = npj;
