@@ -291,7 +291,7 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
 
 /* Move application (Algorithm 1) switches from per-move atomics to per-net recounting when the
  * listed moves' incident nets times this divisor reach the number of pins; 0 = always per move.
- * Default 16. */
+ * Default 32. */
 #define JET_OPT_APPLY_DIVISOR 1
 /* 1: launch the per-net application kernels with one wave per chunk / block per net when the
  * previous application of the same kind took that path; 0 (default): small grids always. */
@@ -300,9 +300,10 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * the order candidates, candidates_hub, afterburner, select_moves, apply, rebalance_gain,
  * rebalance_select); default all.  Fewer families, less host work per launch. */
 #define JET_OPT_PROF_FAMILIES 3
-/* Candidate selection with unit net weights and k <= 64 uses one lane per vertex (bit-sliced
- * block counts) when the mean degree of the non-hub vertices is below this value, a group of
- * lanes per vertex otherwise; default 24, 0 = always groups.  Results do not depend on it. */
+/* Candidate selection and rebalancing gains with unit net weights (bit-sliced block counts) use one
+ * lane per vertex on more than 32,768 vertices when the mean degree of the non-hub vertices is below
+ * this value, a group of lanes per vertex otherwise; default 24, 0 = always groups.  Results do not
+ * depend on it. */
 #define JET_OPT_CAND_LANE_DEGREE 4
 /* The rebalancing selection's first radix pass runs over all compute units (a histogram kernel
  * and a split kernel, several workgroups per overloaded block) on levels with at least this many

@@ -341,7 +341,7 @@ struct Ctx {
   int32_t stamp = 0;  // iteration stamp for locks
   // move application: net-centric when (incident nets of the moves) * apply_divisor >= p,
   // vertex-centric otherwise (0 = always vertex-centric); environment JET_APPLY_DIVISOR overrides
-  int32_t apply_divisor = 16;
+  int32_t apply_divisor = 32;
   // the path the device took at the last application of each kind (Jet moves, rebalancing moves),
   // used to size the next launch of that kind
   bool wide_hint[2] = {false, false};
@@ -480,6 +480,10 @@ int64_t resident_grid(int block) {
   }(block);
   return g;
 }
+template <auto K>
+struct KernelTag {  // a kernel as a type
+  static constexpr auto value = K;
+};
 // Launches K with one workgroup per `blocks`, at most as many as are resident and c.grid_cap allows.
 template <auto K, typename... A>
 void launch_resident(Ctx &c, int64_t blocks, int block, A... args) {
@@ -488,8 +492,14 @@ void launch_resident(Ctx &c, int64_t blocks, int block, A... args) {
 }
 
 // Unit net weights: one lane per vertex (the candidate and rebalancing gain passes) instead of eight.
-// One lane is right while the vertices are light (mean degree below lane_degree).
-inline bool light_lanes(const Ctx &c) { return c.p_low < (int64_t)c.lane_degree * c.n_low; }
+// One lane is right while the vertices are light (mean degree below lane_degree) and more than a few:
+// 2,000 to 30,000 vertices are 32 to 500 waves of one-lane vertices on 1,024 SIMDs, and their refinement
+// took 2 to 8% longer than with eight lanes; from 65,000 on local hypergraphs are 1% (260,000: 18%) faster
+// with one.
+constexpr int32_t kFewVertices = 1 << 15;
+inline bool light_lanes(const Ctx &c) {
+  return c.n > kFewVertices && c.p_low < (int64_t)c.lane_degree * c.n_low;
+}
 
 // the union view of a context for the kernels
 inline Union union_of(const Ctx &c) {

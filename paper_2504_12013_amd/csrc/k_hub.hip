@@ -9,23 +9,11 @@
 // instructions.  Eight lanes per net with four exchanges and 24 instructions each bound the passes by
 // vector instructions (four cycles each): on levels of 1M
 // row-net vertices candidates took 49 us (now 40) and a rebalancing pass 38 us in three launches (25).
-#include <algorithm>
-
-#include "chunk.h"
-#include "conn.h"
-#include "dev_util.h"
-#include "entry.h"
-#include "jet_internal.h"
-#include "rec.h"
+#include "hub.h"
 
 namespace jet {
 
 namespace {
-
-constexpr int kHubBlock = 256;
-constexpr int kHubWaves = kHubBlock / kWave;
-constexpr int kHubShares = 16;   // most workgroups on one hub
-constexpr int kHubSegment = 508; // nets one lane takes before its nine planes are emptied
 
 // Union: the hubs that may move, by their index in the hub list (one hypergraph: k_rb_list).
 __global__ __launch_bounds__(256) void k_rb_hub_list(const int32_t *__restrict__ part, const int32_t *__restrict__ vw,
@@ -50,227 +38,10 @@ __global__ __launch_bounds__(256) void k_rb_hub_list(const int32_t *__restrict__
   if (e) hlist[base + rank_below(mm)] = i;
 }
 
-// max over 64 lanes of a 64-bit key
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long x) {
-#pragma unroll
-  for (int o = 32; o >= 1; o >>= 1) {
-    const uint32_t lo = (uint32_t)__shfl_xor((int)(uint32_t)x, o, kWave);
-    const uint32_t hi = (uint32_t)__shfl_xor((int)(uint32_t)(x >> 32), o, kWave);
-    const unsigned long long y = ((unsigned long long)hi << 32) | lo;
-    x = y > x ? y : x;
-  }
-  return x;
-}
-
-struct HubArgs {
-  const int32_t *part, *inc, *nw, *sumw, *vw, *hubs;
-  const int64_t *voff;
-  const uint64_t *ns;
-  int32_t nhubs, k;
-  int32_t *rows, *done;  // [workgroups * (k + 1)] sums, [nhubs] arrivals (zero between launches)
-  DevStatus *st;
-  const LoopCtl *lc;
-  Union u;
-  // candidates
-  const int32_t *lockstamp;
-  const uint8_t *lock_bytes;
-  int32_t locked_stamp, tau_q;
-  uint64_t *rec;
-  uint32_t *inm;
-  // rebalancing
-  const int32_t *hlist;
-  int64_t lmax, dz;
-  uint32_t *entries;
-};
-
-// The workgroup's share of a hub's nets (incidences q0 + its threads, step threads, ... below q1) into
-// row[0..k) and row[k] (benefit), which it clears first.  Every thread calls it; ends with a barrier.
-// G: lane group of the weighted form; HW: words of the bit-sliced form (unit net weights).
-template <int G, int HW, bool UNIT>
-__device__ __forceinline__ void hub_sums(const HubArgs &a, int64_t q0, int64_t q1, int64_t threads, int32_t s,
-                                         int32_t *row) {
-  const int tid = threadIdx.x, l = lane_id();
-  for (int b = tid; b <= a.k; b += kHubBlock) row[b] = 0;
-  __syncthreads();
-  int32_t ben = 0;
-  if (UNIT) {
-    constexpr int N = 9, M = 15;  // a wave sums 64 lanes of at most 511
-    int32_t total = 0;
-    for (int64_t qs = q0; qs < q1; qs += kHubSegment * threads) {  // block-uniform trip count
-      uint32_t pl[HW][N] = {}, w[M];
-      ben = 0;
-      planes_accumulate<HW, N>(a.inc, qs + tid, min(q1, qs + kHubSegment * threads), threads, a.ns, s, pl, ben);
-      const int x = planes_combine<kWave, HW, N, M>(pl, w, ben, l);
-      total += ben;
-      // lane l holds the sums of word x: blocks 32 x + j, spread over the lanes that hold that word
-      constexpr int SH = HW == 1 ? 0 : HW == 2 ? 1 : 2;
-      for (int j = l >> SH; j < 32; j += kWave >> SH) {
-        int32_t c = 0;
-#pragma unroll
-        for (int p = 0; p < M; ++p) c |= (int32_t)((w[p] >> j) & 1u) << p;
-        if (c) atomicAdd(&row[32 * x + j], c);  // blocks of k and above have no pins
-      }
-    }
-    if (l == 0 && total) atomicAdd(&row[a.k], total);
-  } else {
-    constexpr int NG = kWave / G;
-    const int lg = l % G, gi = tid / G;  // group of the workgroup
-    int32_t conn[8];
-#pragma unroll
-    for (int b = 0; b < 8; ++b) conn[b] = 0;
-    if (G == 1)
-      conn_accumulate_strided<G, false>(a.inc, q0 + tid, q1, threads, a.nw, a.ns, lg, s, conn, ben);
-    else
-      conn_accumulate<G, false>(a.inc, q0 + (int64_t)gi * G, q1, threads, a.nw, a.ns, lg, s, conn, ben);
-#pragma unroll
-    for (int o = G; o < kWave; o <<= 1) {  // sums over the wave's groups, in every lane
-#pragma unroll
-      for (int b = 0; b < 8; ++b) conn[b] += __shfl_xor(conn[b], o, kWave);
-      ben += __shfl_xor(ben, o, kWave);
-    }
-#pragma unroll
-    for (int b = 0; b < 8; ++b)
-      if (b % NG == (l / G) % NG && lg * 8 + b < a.k && conn[b]) atomicAdd(&row[lg * 8 + b], conn[b]);
-    if (l == 0 && ben) atomicAdd(&row[a.k], ben);
-  }
-  __syncthreads();
-}
-
-// RB: the hubs listed in hlist; otherwise all unlocked hubs.
 template <int G, int HW, bool UNIT, bool RB>
 __global__ __launch_bounds__(kHubBlock) void k_hub(HubArgs a) {
   JET_GATE(a.lc, RB ? kPhRb : kPhJet);
-  __shared__ int32_t row[kMaxK + 1];
-  __shared__ int32_t s_last;
-  const int32_t nh = RB ? a.st->rb_nhub : a.nhubs;
-  if (nh == 0) return;
-  const int tid = threadIdx.x, l = lane_id(), k = a.k;
-  const bool un = a.u.lcs != nullptr;
-  int32_t ls0 = a.locked_stamp, tq0 = a.tau_q, unw0 = 0;
-  int64_t dz0 = a.dz;
-  if (a.lc && !un) {
-    ls0 = a.lc->stamp - 1;
-    tq0 = a.lc->tau_q;
-    dz0 = a.lc->dz;
-    unw0 = a.lc->rb_unw;
-  }
-  const int32_t per = max(1, min(kHubShares, (int32_t)gridDim.x / nh));  // workgroups of a hub
-  unsigned long long scanned = 0ull, examined = 0ull, emitted = 0ull;     // thread 0
-  for (int64_t i = blockIdx.x; i < (int64_t)nh * per; i += gridDim.x) {   // block-uniform trip count
-    const int32_t j = (int32_t)(i / per), sub = (int32_t)(i % per);
-    const int32_t hi = RB ? a.hlist[j] : j;
-    const int32_t v = a.hubs[hi];
-    const int32_t s = a.part[v];
-    const LoopCtl *h = un ? &a.u.lcs[a.u.vhg[v]] : nullptr;  // the hub's own hypergraph (union)
-    if (!RB) {
-      const int32_t ls = un ? h->stamp - 1 : ls0;
-      const bool off = un && h->phase != kPhJet;
-      if (off || (a.lock_bytes ? a.lock_bytes[v] != 0 : a.lockstamp[v] == ls)) {
-        if (sub == 0 && tid == 0) a.rec[v] = pack_rec(0, 0xff, s);
-        continue;
-      }
-    }
-    const int64_t q0 = a.voff[v], q1 = a.voff[v + 1];
-    hub_sums<G, HW, UNIT>(a, q0 + (int64_t)sub * kHubBlock, q1, (int64_t)per * kHubBlock, s, row);
-    if (per > 1) {
-      int32_t *mine = a.rows + i * (k + 1);  // i < the grid: one pass when workgroups share hubs
-      for (int b = tid; b <= k; b += kHubBlock)
-        __hip_atomic_store(&mine[b], row[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // the row is in device-wide order before the arrival is counted, and the last workgroup reads
-      // the rows with atomic loads, so no cache has to be written back or invalidated
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-      __syncthreads();
-      if (tid == 0) s_last = atomicAdd(&a.done[hi], 1) == per - 1;
-      __syncthreads();
-      if (!s_last) continue;  // block-uniform
-      for (int b = tid; b <= k; b += kHubBlock) {
-        int32_t c = 0;
-        for (int x = 0; x < per; ++x)
-          c += __hip_atomic_load(&a.rows[((int64_t)j * per + x) * (k + 1) + b], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
-        row[b] = c;
-      }
-      if (tid == 0) a.done[hi] = 0;
-      __syncthreads();
-    }
-    if (tid < kWave) {
-      const int64_t sg0 = un ? (int64_t)a.u.vhg[v] * k : 0;
-      const int32_t c = RB && a.vw ? a.vw[v] : 1;
-      const int64_t lm = un ? h->lmax : a.lmax, dzz = un ? h->dz : dz0;
-      // best target by conn, lowest block on ties: candidates need an adjacent block, a rebalancing move
-      // one with room for v outside the deadzone
-      unsigned long long key = 0ull;
-      for (int b = l; b < k; b += kWave) {
-        const int32_t cb = row[b];
-        bool ok = b != s && (RB || cb > 0);
-        if (RB && ok) {
-          const int64_t bwb = a.st->bw[sg0 + b];
-          ok = bwb + c <= lm && bwb < dzz;
-        }
-        const unsigned long long kb =
-            ok ? ((unsigned long long)(uint32_t)(cb + 1) << 32) | (uint32_t)(0xffffffffu - (uint32_t)b) : 0ull;
-        key = kb > key ? kb : key;
-      }
-      key = wave_max_u64(key);
-      if (tid == 0) {
-        const int32_t bestc = (int32_t)(uint32_t)(key >> 32) - 1, bestb = (int32_t)(0xffffffffu - (uint32_t)key);
-        const int32_t benefit = row[k];
-        scanned += (unsigned long long)(q1 - q0);
-        examined += 1ull;
-        if (RB) {
-          if (bestc >= 0) {
-            const int32_t slot = atomicAdd(&a.st->rb_count[sg0 + s], 1);
-            write_entry(a.entries + (a.st->rb_off[sg0 + s] + slot) * kEntryWords, true,
-                        bestc - (a.sumw[v] - benefit), c, v, bestb, un ? h->rb_unw : unw0);
-            emitted += 1ull;
-          }
-        } else {
-          bool cand = false;
-          finish_candidate(v, s, bestc > 0 ? bestc : 0, bestb, a.sumw[v], benefit, un ? h->tau_q : tq0, a.rec, &cand);
-          if (cand) {
-            atomicOr(&a.inm[v >> 5], 1u << (v & 31));
-            emitted += 1ull;
-          }
-        }
-      }
-    }
-    __syncthreads();  // the row is rewritten for the next hub
-  }
-  if (tid != 0 || examined == 0ull) return;
-  if (RB) {
-    count_add(a.st, blockIdx.x, &CtrSlot::rb_inc, (long long)scanned);
-    count_add(a.st, blockIdx.x, &CtrSlot::rb_elig, (long long)examined);
-    count_add(a.st, blockIdx.x, &CtrSlot::rb_ent, (long long)emitted);
-  } else {
-    count_add(a.st, blockIdx.x, &CtrSlot::inc_hub, (long long)scanned);
-    count_add(a.st, blockIdx.x, &CtrSlot::n_cand, (long long)emitted);
-  }
-}
-
-HubArgs hub_args(Ctx &c, const int32_t *part, const LoopCtl *lc) {
-  HubArgs a{};
-  a.part = part;
-  a.inc = c.inc;
-  a.nw = c.nw;
-  a.sumw = c.sumw;
-  a.vw = c.vw;
-  a.hubs = c.hubs;
-  a.voff = c.voff;
-  a.ns = c.ns;
-  a.nhubs = c.nhubs;
-  a.k = c.k;
-  a.rows = c.hub_rows;
-  a.done = c.hub_done;
-  a.st = c.st;
-  a.lc = lc;
-  a.u = union_of(c);
-  a.lockstamp = c.lockstamp;
-  a.rec = c.rec;
-  a.inm = c.inm;
-  a.hlist = c.rb_hlist;
-  a.lmax = c.lmax;
-  a.entries = c.rb_keys;
-  return a;
+  hub_work<G, HW, UNIT, RB>(a, (int32_t)blockIdx.x, (int32_t)gridDim.x);
 }
 
 template <bool RB>
@@ -305,7 +76,7 @@ hipError_t launch_candidates_hub(Ctx &c, const int32_t *part, int32_t locked_sta
 }
 
 hipError_t launch_rb_hubs(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *lc) {
-  if (c.nhubs == 0) return hipSuccess;
+  if (c.nhubs == 0 || hubs_beside_gains(c)) return hipSuccess;
   if (c.H > 1)
     hipLaunchKernelGGL(k_rb_hub_list, dim3((unsigned)((c.nhubs + 255) / 256)), dim3(256), 0, c.stream, part, c.vw,
                        c.hubs, c.nhubs, c.st, c.rb_hlist, lc, c.k, union_of(c));

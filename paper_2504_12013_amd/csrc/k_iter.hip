@@ -10,6 +10,7 @@
 #include "chunk.h"
 #include "dev_util.h"
 #include "moves.h"
+#include "hub.h"
 #include "jet_internal.h"
 #include "rec.h"
 #include "conn.h"
@@ -135,14 +136,19 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
 // a word cleared before the launch.  GRAPH (G = 1): every net has two pins and inc holds the other pin of
 // each, so the neighbours' blocks, which stay in the caches, take the place of 16 to 32 bytes per net: a
 // mesh of 4M vertices at k = 64 went from 114 us, the time of its 400 MB, to 47.
-template <int G, int HW, int N, bool GRAPH>
+template <int G, int HW, int N, bool GRAPH, bool HUBS>
 __global__ __launch_bounds__(256) void k_candidates_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw, const int32_t *__restrict__ lockstamp,
     int32_t locked_stamp, const uint8_t *__restrict__ lock_bytes, int32_t n, int32_t tau_q,
     uint64_t *__restrict__ rec, uint32_t *__restrict__ inm, int32_t *__restrict__ best, DevStatus *st,
-    const LoopCtl *lc, Union u, int32_t xcd) {
+    const LoopCtl *lc, Union u, int32_t xcd, HubArgs hubs, int32_t hub_blocks) {
   JET_GATE(lc, kPhJet);
+  if (HUBS && (int32_t)blockIdx.x < hub_blocks) {
+    hub_work<1, HW, true, false>(hubs, (int32_t)blockIdx.x, hub_blocks);
+    return;
+  }
+  const int32_t bid = (int32_t)blockIdx.x - hub_blocks, nblk = (int32_t)gridDim.x - hub_blocks;
   bool snap = false;  // the partition is the round's best so far: the rollback point (Algorithm 1)
   if (lc && !u.lcs) {
     locked_stamp = lc->stamp - 1;
@@ -161,15 +167,15 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
   // Workgroups go to the eight XCDs round robin.  With xcd set, the workgroups of one XCD walk one
   // contiguous eighth of the vertex range, so the nets of neighbouring vertices are fetched into
   // that XCD's L2 once instead of into all eight.
-  int64_t vstart = ((int64_t)blockIdx.x * 4 + w) * VPW, vend = nv, vstep = (int64_t)gridDim.x * 4 * VPW;
-  if (xcd && !AL && gridDim.x % 8 == 0) {
+  int64_t vstart = ((int64_t)bid * 4 + w) * VPW, vend = nv, vstep = (int64_t)nblk * 4 * VPW;
+  if (xcd && !AL && nblk % 8 == 0) {
     const int64_t span = 4 * VPW;                      // vertices of one workgroup step
     const int64_t steps = (nv + span - 1) / span;
     const int64_t per = (steps + 7) / 8;               // workgroup steps of one XCD
-    const int64_t x = blockIdx.x % 8, j = blockIdx.x / 8;
+    const int64_t x = bid % 8, j = bid / 8;
     vstart = (x * per + j) * span + w * VPW;
     vend = std::min<int64_t>(nv, (x + 1) * per * span);
-    vstep = (int64_t)(gridDim.x / 8) * span;
+    vstep = (int64_t)(nblk / 8) * span;
   }
   for (int64_t vbase = vstart; vbase < vend; vbase += vstep) {  // wave-uniform trip count
     const int64_t base =
@@ -240,8 +246,8 @@ __global__ __launch_bounds__(256) void k_candidates_bits(
       ts += wscan[i];
       tc += wcand[i];
     }
-    count_add(st, blockIdx.x, &CtrSlot::n_cand, tc);
-    count_add(st, blockIdx.x, &CtrSlot::inc_low, (long long)ts);
+    count_add(st, bid, &CtrSlot::n_cand, tc);
+    count_add(st, bid, &CtrSlot::inc_low, (long long)ts);
   }
 }
 
@@ -1499,30 +1505,42 @@ hipError_t cand_launch(Ctx &c, const int32_t *part, int32_t locked_stamp, const 
     }
     const bool few = c.max_low_degree < 32;
     const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
-#define JET_CAND(GG, HW, N, GRAPH)                                                                                   \
-  launch_resident<k_candidates_bits<GG, HW, N, GRAPH>>(                                                              \
-      c, ((int64_t)c.n + 256 / GG - 1) / (256 / GG), 256, part, c.voff, GRAPH ? c.adj : c.inc, c.ns, c.sumw,         \
-      c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc, union_of(c), c.cand_xcd)
-    if (!light_lanes(c)) {
-      if (hw == 1) few ? JET_CAND(8, 1, 5, false) : JET_CAND(8, 1, 9, false);
-      else if (hw == 2) few ? JET_CAND(8, 2, 5, false) : JET_CAND(8, 2, 9, false);
-      else few ? JET_CAND(8, 4, 5, false) : JET_CAND(8, 4, 9, false);
-    } else if (graph) {
-      if (hw == 1) few ? JET_CAND(1, 1, 5, true) : JET_CAND(1, 1, 9, true);
-      else if (hw == 2) few ? JET_CAND(1, 2, 5, true) : JET_CAND(1, 2, 9, true);
-      else few ? JET_CAND(1, 4, 5, true) : JET_CAND(1, 4, 9, true);
-    } else {
-      if (hw == 1) few ? JET_CAND(1, 1, 5, false) : JET_CAND(1, 1, 9, false);
-      else if (hw == 2) few ? JET_CAND(1, 2, 5, false) : JET_CAND(1, 2, 9, false);
-      else few ? JET_CAND(1, 4, 5, false) : JET_CAND(1, 4, 9, false);
+    const bool hubs = hubs_beside_candidates(c);
+    HubArgs ha{};
+    if (hubs) {
+      ha = hub_args(c, part, lc);
+      ha.locked_stamp = locked_stamp;
+      ha.lock_bytes = lock_bytes;
+      ha.tau_q = tau_q;
     }
+    const int32_t hb = hubs ? hub_blocks(c) : 0;
+    auto go = [&](auto tag, int64_t per) {
+      constexpr auto K = decltype(tag)::value;
+      const int64_t g = std::max<int64_t>(
+          1, std::min<int64_t>({((int64_t)c.n + per - 1) / per, c.grid_cap, resident_grid<K>(256)}));
+      hipLaunchKernelGGL(K, dim3((unsigned)(hb + g)), dim3(256), 0, c.stream, part, c.voff, graph ? c.adj : c.inc,
+                         c.ns, c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st,
+                         lc, union_of(c), c.cand_xcd, ha, hb);
+    };
+#define JET_CAND(GG, HW, N, GRAPH, HUBS) go(KernelTag<k_candidates_bits<GG, HW, N, GRAPH, HUBS>>{}, 256 / GG)
+#define JET_CANDS(GG, GRAPH, HUBS)                                                                        \
+  do {                                                                                                    \
+    if (hw == 1) few ? JET_CAND(GG, 1, 5, GRAPH, HUBS) : JET_CAND(GG, 1, 9, GRAPH, HUBS);                 \
+    else if (hw == 2) few ? JET_CAND(GG, 2, 5, GRAPH, HUBS) : JET_CAND(GG, 2, 9, GRAPH, HUBS);            \
+    else few ? JET_CAND(GG, 4, 5, GRAPH, HUBS) : JET_CAND(GG, 4, 9, GRAPH, HUBS);                         \
+  } while (0)
+    if (hubs) JET_CANDS(8, false, true);
+    else if (!light_lanes(c)) JET_CANDS(8, false, false);
+    else if (graph) JET_CANDS(1, true, false);
+    else JET_CANDS(1, false, false);
+#undef JET_CANDS
 #undef JET_CAND
   } else
     hipLaunchKernelGGL((k_candidates<G>), dim3(grid), dim3(BLOCK), 0, c.stream, part, c.voff, c.inc, c.nw, c.ns,
                        c.sumw, c.lockstamp, locked_stamp, lock_bytes, c.n, tau_q, c.rec, c.inm, c.best, c.st, lc,
                        union_of(c));
-  prof_end(c, tok, lc, want, 18.0 * c.n_low, per_inc);  // plus per_inc per scanned incidence (device count)
-  if (c.nhubs > 0) {
+  prof_end(c, tok, lc, want, 18.0 * (hubs_beside_candidates(c) ? c.n : c.n_low), per_inc);  // plus per_inc per scanned incidence (device count)
+  if (c.nhubs > 0 && !hubs_beside_candidates(c)) {
     tok = prof_begin(c, kProfCandidatesHub, lc, want);
     const hipError_t he = launch_candidates_hub(c, part, locked_stamp, lock_bytes, tau_q, lc);
     if (he != hipSuccess) return he;

@@ -336,7 +336,7 @@ __global__ void k_prof_mark(DevProf *dp, const DevStatus *st, const LoopCtl *lc,
   auto total = [&](long long x) { return (double)wave_sum(x); };
   double b = bytes;
   switch (fam) {
-  case kProfCandidates: b += per_inc * total(c.inc_low); break;
+  case kProfCandidates: b += per_inc * (total(c.inc_low) + total(c.inc_hub)); break;  // hubs: if beside
   case kProfCandidatesHub: b += per_inc * total(c.inc_hub); break;
   case kProfAfterburner:  // per_inc is nonzero for the graph afterburner only
     if (per_inc > 0.0) b += per_inc * total(c.ab_inc) + 24.0 * total(c.n_cand);

@@ -23,6 +23,7 @@
 #include "conn.h"
 #include "dev_util.h"
 #include "entry.h"
+#include "hub.h"
 #include "jet_internal.h"
 #include "moves.h"
 
@@ -432,13 +433,19 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
 // weight, outside the deadzone); the best is the lowest block of largest count in it (counts of zero
 // included, as for the lane-group kernel).  k = 128 took 16 lanes per vertex with six exchanges and 24
 // instructions per net on each: 85 us per pass on 300,000 SAT-like vertices against 30 us now.
-template <int G, int HW, int N>
+template <int G, int HW, int N, bool HUBS>
 __global__ __launch_bounds__(256) void k_rb_gain_bits(
     const int32_t *__restrict__ part, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
     const uint64_t *__restrict__ ns, const int32_t *__restrict__ sumw, const int32_t *__restrict__ vw,
     const int32_t *__restrict__ list, const int32_t *__restrict__ slot, int32_t k, int64_t lmax, int64_t dz,
-    DevStatus *st, uint32_t *__restrict__ entries, const LoopCtl *lc, Union u, int32_t xcd) {
+    DevStatus *st, uint32_t *__restrict__ entries, const LoopCtl *lc, Union u, int32_t xcd, HubArgs hubs,
+    int32_t hub_blocks) {
   JET_GATE(lc, kPhRb);
+  if (HUBS && (int32_t)blockIdx.x < hub_blocks) {
+    hub_work<1, HW, true, true>(hubs, (int32_t)blockIdx.x, hub_blocks);
+    return;
+  }
+  const int32_t bid = (int32_t)blockIdx.x - hub_blocks, nblk = (int32_t)gridDim.x - hub_blocks;
   const bool un = u.lcs != nullptr;
   if (lc && !un) dz = lc->dz;
   const int32_t unw0 = lc && !un ? lc->rb_unw : 0;
@@ -465,13 +472,13 @@ __global__ __launch_bounds__(256) void k_rb_gain_bits(
   const int l = lane_id(), lg = l % G;
   unsigned long long scanned = 0ull, examined = 0ull, emitted = 0ull;
   // with xcd set, the workgroups of one XCD take one contiguous eighth of the list (as k_rb_gain)
-  int64_t bstart = ((int64_t)blockIdx.x * 4 + threadIdx.x / kWave) * VPW, bend = nl;
-  int64_t bstep = (int64_t)gridDim.x * 4 * VPW;
-  if (xcd && !un && gridDim.x % 8 == 0) {
-    const int64_t span = 4 * VPW, steps = (nl + span - 1) / span, per = (steps + 7) / 8, x = blockIdx.x % 8;
-    bstart = (x * per + blockIdx.x / 8) * span + (threadIdx.x / kWave) * VPW;
+  int64_t bstart = ((int64_t)bid * 4 + threadIdx.x / kWave) * VPW, bend = nl;
+  int64_t bstep = (int64_t)nblk * 4 * VPW;
+  if (xcd && !un && nblk % 8 == 0) {
+    const int64_t span = 4 * VPW, steps = (nl + span - 1) / span, per = (steps + 7) / 8, x = bid % 8;
+    bstart = (x * per + bid / 8) * span + (threadIdx.x / kWave) * VPW;
     bend = min(nl, (x + 1) * per * span);
-    bstep = (int64_t)(gridDim.x / 8) * span;
+    bstep = (int64_t)(nblk / 8) * span;
   }
   for (int64_t base = bstart; base < bend; base += bstep) {  // wave-uniform trip count
     const int64_t i = base + l / G;
@@ -1205,10 +1212,23 @@ hipError_t gain_launch(Ctx &c, const int32_t *part, int64_t dz, const LoopCtl *l
   if (c.unit_nw) {
     const bool few = c.max_low_degree < 32;
     const int hw = c.k <= 32 ? 1 : c.k <= 64 ? 2 : 4;
-#define JET_GAIN(GG, HW, N)                                                                                         \
-  launch_resident<k_rb_gain_bits<GG, HW, N>>(c, ((int64_t)c.n + 256 / GG - 1) / (256 / GG), 256, part, c.voff,      \
-                                             c.inc, c.ns, c.sumw, c.vw, c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st, \
-                                             c.rb_keys, lc, u, c.rb_xcd)
+    const bool hubs = hubs_beside_gains(c);
+    HubArgs ha{};
+    if (hubs) {
+      ha = hub_args(c, part, lc);
+      ha.dz = dz;
+    }
+    const int32_t hb = hubs ? hub_blocks(c) : 0;
+    auto go = [&](auto tag, int64_t per) {
+      constexpr auto K = decltype(tag)::value;
+      const int64_t g = std::max<int64_t>(
+          1, std::min<int64_t>({((int64_t)c.n + per - 1) / per, c.grid_cap, resident_grid<K>(256)}));
+      hipLaunchKernelGGL(K, dim3((unsigned)(hb + g)), dim3(256), 0, c.stream, part, c.voff, c.inc, c.ns, c.sumw, c.vw,
+                         c.rb_list, c.rb_slot, c.k, c.lmax, dz, c.st, c.rb_keys, lc, u, c.rb_xcd, ha, hb);
+    };
+#define JET_GAIN(GG, HW, N)                                                                     \
+  (hubs ? go(KernelTag<k_rb_gain_bits<GG, HW, N, true>>{}, 256 / GG)                            \
+        : go(KernelTag<k_rb_gain_bits<GG, HW, N, false>>{}, 256 / GG))
     if (light_lanes(c)) {
       if (hw == 1) few ? JET_GAIN(1, 1, 5) : JET_GAIN(1, 1, 9);
       else if (hw == 2) few ? JET_GAIN(1, 2, 5) : JET_GAIN(1, 2, 9);
