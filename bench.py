@@ -132,18 +132,17 @@ def build_workload(args):
 # once per family launch, the other kernels of the family)
 FAMILIES = {
     "candidates": (("k_candidates", "k_candidates_bits"), ()),
-    "candidates_hub": (("k_candidates_hub",), ()),
+    "candidates_hub": (("k_hub",), ()),  # where hubs are not beside the candidates (weighted nets, light levels)
     "afterburner": (("k_ab_chunks", "k_ab_graph"), ("k_ab_nets", "k_ab_overflow", "k_rg_reduce")),
     "select_moves": (("k_select_moves",), ()),
-    "apply": (("k_apply",), ("k_apply_chunks", "k_apply_nets")),
-    "rebalance_gain": (("k_rb_list", "k_rb_list_union"), ("k_rb_gain", "k_rb_gain_bits", "k_rb_hub_list",
-                                                          "k_rb_hub_accum", "k_rb_hub_finish")),
+    "apply": (("k_apply",), ("k_apply_chunks", "k_apply_nets")),  # the latter in traces of older builds
+    "rebalance_gain": (("k_rb_list", "k_rb_list_union"), ("k_rb_gain", "k_rb_gain_bits", "k_rb_hub_list")),
     "rebalance_select": (("k_rb_select",), ("k_rb_sel_hist", "k_rb_sel_split")),
-    "clustering_subround": (("k_co_join", "k_co_settle_small"), ("k_co_rate", "k_co_swap", "k_co_group", "k_co_scan",
-                                                                 "k_co_scatter", "k_co_approve", "k_co_apply")),
+    "clustering_subround": (("k_co_group", "k_co_settle_small"), ("k_co_rate", "k_co_offsets", "k_co_scatter",
+                                                                  "k_co_approve", "k_co_apply")),
     # one launch per maximum-flow iteration of the piercing loop: the side weights
-    "flow_iteration": (("k_fl_sidew",), ("k_fl_reach", "k_fl_reach_init", "k_fl_gr_level", "k_fl_gr_init",
-                                         "k_fl_gr_rest", "k_fl_sweep", "k_fl_active", "k_fl_saturate", "k_fl_sinkflow",
+    "flow_iteration": (("k_fl_sidew",), ("k_fl_first", "k_fl_level", "k_fl_deep", "k_fl_reach_init",
+                                         "k_fl_gr_init", "k_fl_gr_rest", "k_fl_sweep", "k_fl_active", "k_fl_saturate", "k_fl_sinkflow",
                                          "k_fl_absorb", "k_fl_cand", "k_fl_pierce")),
 }
 
@@ -258,15 +257,16 @@ def summarize(directory, copy_mib):
 
 def summarize_levels(path, top=6):
     """Kernel time per level refinement from a *_kernel_trace.csv: each refinement starts with the
-    state build of its level (k_build_ns), so with --steps 1 --warmup 0 the groups are the levels
+    state build of its level (k_block_weights; k_build_ns in older traces), so with --steps 1 --warmup 0 the groups are the levels
     refined coarsest first, numbered as in the bench's level lines (0 = finest); kernels before
     the first group are set-up."""
     import csv
     rows = sorted(csv.DictReader(open(path)), key=lambda r: int(r["Start_Timestamp"]))
     groups, cur = [], {}
-    for r in rows:
-        name = kernel_base_name(r["Kernel_Name"])
-        if name == "k_build_ns":
+    names = [kernel_base_name(r["Kernel_Name"]) for r in rows]
+    opener = "k_build_ns" if "k_build_ns" in names else "k_block_weights"
+    for r, name in zip(rows, names):
+        if name == opener:
             groups.append(cur)
             cur = {}
         d = (int(r["End_Timestamp"]) - int(r["Start_Timestamp"])) / 1e3

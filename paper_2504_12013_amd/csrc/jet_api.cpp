@@ -9,7 +9,6 @@
 #include <cmath>
 #include <cstdlib>
 #include <cstring>
-#include <deque>
 #include <new>
 #include <string>
 #include <thread>
@@ -644,21 +643,22 @@ int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_sta
                                ((double)prm->max_rebalance_rounds + 3.0) + 16.0;
   int64_t pieces = 0;
   c.polls = 0;
-  const size_t lead = (size_t)std::min<int32_t>(c.replays, 2);
+  const int32_t lead = std::min<int32_t>(c.replays, 2);
   Ahead guess(rb_only);
-  std::deque<int32_t> flight;  // phases of the launched pieces that have not reported
+  // phases of the launched control kernels that have not reported: at most three pieces of up to 64
+  int32_t flight[256], nflight = 0;
   jet::LoopMail m{};           // the last report looked at; before the first one, what it is likely to say
   m.phase = rb_only ? jet::kPhRb : jet::kPhJet;
   uint32_t seen = 0;
-  flight.push_back(jet::kPhAny);  // the set-up's control kernel reports too
+  flight[nflight++] = jet::kPhAny;  // the set-up's control kernel reports too
   while (m.phase != jet::kPhDone && !m.err) {
     // the piece of the current phase, then the one behind it
-    const bool has = std::find(flight.begin(), flight.end(), m.phase) != flight.end();
-    const int32_t add = !has ? m.phase : flight.size() < lead && flight.back() == m.phase ? guess.next(m) : -1;
-    if (add >= 0) {
+    const bool has = std::find(flight, flight + nflight, m.phase) != flight + nflight;
+    const int32_t add = !has ? m.phase : nflight < lead && flight[nflight - 1] == m.phase ? guess.next(m) : -1;
+    if (add >= 0 && nflight + reports_of(c, add) <= 256) {
       rc = launch_piece(c, piece_of(add));
       if (rc != JET_OK) return rc;
-      for (int32_t i = 0; i < reports_of(c, add); ++i) flight.push_back(add);
+      for (int32_t i = 0; i < reports_of(c, add); ++i) flight[nflight++] = add;
       pieces += 1;
       continue;
     }
@@ -668,10 +668,10 @@ int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_sta
     if (rc != JET_OK) return rc;
     c.polls += 1;
     bool ran = false;  // a piece of the phase we knew of has run
-    for (uint32_t i = (m.seq - seen) & jet::kMailSeqMask; i > 0 && !flight.empty(); --i) {
-      ran = ran || flight.front() == was.phase;
-      flight.pop_front();
-    }
+    const int32_t got = std::min<int32_t>((int32_t)((m.seq - seen) & jet::kMailSeqMask), nflight);
+    for (int32_t i = 0; i < got; ++i) ran = ran || flight[i] == was.phase;
+    std::copy(flight + got, flight + nflight, flight);
+    nflight -= got;
     seen = m.seq;
     if (ran && !rb_only && was.phase != jet::kPhRoll && m.phase != jet::kPhRb) guess.learn(m.rb_rounds);
   }

@@ -244,7 +244,7 @@ enum : int32_t {
 // kernel families timed by the optional instrumentation
 enum ProfFamily : int {
   kProfCandidates = 0,   // k_candidates (vertices with at most kHubDegree incident nets)
-  kProfCandidatesHub,    // k_candidates_hub
+  kProfCandidatesHub,    // k_hub where hubs are not beside the light vertices
   kProfAfterburner,      // k_ab_chunks + k_ab_nets + k_ab_overflow
   kProfSelect,           // k_select_moves
   kProfApply,            // k_apply
@@ -342,6 +342,8 @@ struct Ctx {
   int32_t stamp = 0;  // iteration stamp for locks
   // move application: net-centric when (incident nets of the moves) * apply_divisor >= p,
   // vertex-centric otherwise (0 = always vertex-centric); environment JET_APPLY_DIVISOR overrides
+  // (16 against 32 on one card: row-net 1M 11.07 / 10.92 ms, rebalancing 1M 1.24 / 1.20, a V-cycle 513 /
+  // 504, SAT-like 300k 127.7 / 128.4; 64 is slower than 32 on all four)
   int32_t apply_divisor = 32;
   // the path the device took at the last application of each kind (Jet moves, rebalancing moves),
   // used to size the next launch of that kind
@@ -565,8 +567,7 @@ hipError_t launch_rebalance_round(Ctx &c, int32_t *part, int64_t dz, int32_t *se
                                   const LoopCtl *lc = nullptr);
 
 // the device-resident loop (k_loop.hip)
-// the launches of one piece of an iteration (kTickAll: every phase, rb_slots rebalancing rounds),
-// gated by c.lc
+// the launches of one piece of an iteration, gated by c.lc
 hipError_t launch_tick(Ctx &c, int kind);
 // loop records for a call: the host wrote each hypergraph's parameters into c.lcs; this completes
 // them from the status block (metric, overload, first phase) and sets the gate record
