@@ -314,8 +314,8 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * pieces (Jet phase, rebalancing round, rollback), launched as the loop's state asks for them;
  * 0: the same kernels are launched one by one (same results). */
 #define JET_OPT_GRAPH 6
-/* Rebalancing rounds (Section 4.3) launched at a time, 1..64, default 1.  Results do not depend on
- * it. */
+/* Rebalancing rounds (Section 4.3) launched at a time, 1..64; default 1, in a batch 3.  Results do not
+ * depend on it. */
 #define JET_OPT_RB_SLOTS 7
 /* Pieces of the loop in flight at once, 1..1024, default 2: one runs, one more (at most) waits
  * behind it when the host can foresee which it will be.  Results do not depend on it. */

@@ -30,10 +30,10 @@ KNOBS = {
     "replays": (2, 8, 32),
     "grid": (1024, 2048, 4096),
     "lane_degree": (0, 24),
-    "apply_divisor": (4, 16, 64),
-    "rb_slots": (1, 2),
+    "apply_divisor": (4, 16, 32, 64),
+    "rb_slots": (1, 2, 3, 4),
 }
-DEFAULTS = {"replays": 8, "grid": 2048, "lane_degree": 24, "apply_divisor": 16, "rb_slots": 1}
+DEFAULTS = {"replays": 8, "grid": 2048, "lane_degree": 24, "apply_divisor": 32, "rb_slots": 3}
 _OPTION = {"grid": JET_OPT_GRID, "lane_degree": JET_OPT_CAND_LANE_DEGREE, "apply_divisor": JET_OPT_APPLY_DIVISOR,
            "rb_slots": JET_OPT_RB_SLOTS}
 

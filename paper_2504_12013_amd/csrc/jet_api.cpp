@@ -1485,6 +1485,7 @@ int make_union(const std::vector<HostHg> &hh, const std::vector<int32_t> &ids, h
   c.k = k;
   c.eps = hh[ids[0]].eps;
   c.H = (int32_t)ids.size();
+  if (c.H > 1) c.rb_slots = jet::kUnionRounds;
   // every hypergraph's vertices start on a tile; the padding vertices up to the next start belong
   // to the pseudo-hypergraph H (no nets, block 0, never in a phase)
   // (a lone hypergraph of its k is a plain context: no padding, its record is the gate record)
@@ -1645,7 +1646,7 @@ int jet_batch_set_option(jet_batch *b, int32_t option, int64_t value) {
 // are in, once its last step has reported; while one union's report travels the others compute.  Replaying
 // one graph of every phase and four rebalancing rounds, all unions in turn, until the slowest hypergraph
 // was done launched more than half of its kernels for nothing: 96 hypergraphs of up to 30,000 vertices
-// took 200 ms, now 166.
+// took 200 ms, 166 with one rebalancing round per step and 126 with three.
 static int batch_loops(jet_batch *b, const jet_params *params) {
   struct Run {
     uint32_t seen = 0;
