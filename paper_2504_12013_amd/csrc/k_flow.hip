@@ -11,7 +11,8 @@
 //               neighbour or relabels, with atomics on residuals and excesses only, and global
 //               relabels (breadth-first distances to the sinks, then to the sources above N, by
 //               the same frontier searches) at the start and whenever the sweeps since the last
-//               one took twice its time; after a piercing step that may open augmenting paths
+//               one took twice its time; a flow is maximum once the sources reach no sink (checked
+//               with the cuts), else it goes on; after a piercing step that may open augmenting paths
 //               the flow is augmented from the previous one;
 //   cuts        the nodes the sources reach in the residual network (S_r) and those that reach the
 //               sinks (T_r), by breadth-first search (first level arc-parallel, then a wave per
@@ -34,6 +35,7 @@
 #include <vector>
 
 #include "dev_util.h"
+#include "flow_sweep.h"
 #include "jet_internal.h"
 
 namespace jet {
@@ -41,7 +43,6 @@ namespace {
 
 constexpr int kFB = 256;
 constexpr int64_t kFGridCap = 1 << 14;
-constexpr int kPushCycles = 64;        // push or relabel steps of one node per sweep
 constexpr int kSweepsPerCheck = 8;     // sweeps between two counts of the active nodes
 constexpr int kLevelBatch = 2;         // wide breadth-first levels launched before the next look, doubling
 constexpr int kLevelBatchMax = 64;     // up to this while the frontier stays wide
@@ -61,16 +62,11 @@ inline unsigned fgrid(int64_t work) {
 // scalar slots of FlowState::sc
 enum : int {
   kScCut = 0, kScBwA, kScBwB, kScLw, kScCnt, kScWsum, kScFlow, kScW1, kScW2, kScActive, kScChanged,
-  kScBest, kScMoved, kScErr, kScN
+  kScBest, kScMoved, kScStuck, kScOpen, kScN
 };
 
 __device__ __forceinline__ int64_t cv(const int32_t *vw, int32_t v) { return vw ? (int64_t)vw[v] : 1; }
 __device__ __forceinline__ int64_t wn(const int32_t *nw, int32_t e) { return nw ? (int64_t)nw[e] : 1; }
-
-template <typename T>
-__device__ __forceinline__ T ld(const T *p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
 
 __device__ __forceinline__ void add_sc(int64_t *sc, int slot, int64_t x) {
   x = wave_sum(x);
@@ -344,13 +340,6 @@ __device__ __forceinline__ void for_out(int64_t u, int32_t nv, const int64_t *vo
   }
 }
 
-__device__ __forceinline__ void push(int64_t a, int32_t u, int32_t v, int64_t d, int64_t *res, int64_t *ex) {
-  atomicAdd((unsigned long long *)&res[a], (unsigned long long)(-d));
-  atomicAdd((unsigned long long *)&res[a ^ 1], (unsigned long long)d);
-  atomicAdd((unsigned long long *)&ex[u], (unsigned long long)(-d));
-  atomicAdd((unsigned long long *)&ex[v], (unsigned long long)d);
-}
-
 // every residual arc from a source to a non-source node is saturated
 __global__ void k_fl_saturate(int64_t A, const int32_t *__restrict__ tail, const int32_t *__restrict__ head,
                               const uint8_t *__restrict__ term, int64_t *__restrict__ res, int64_t *__restrict__ ex) {
@@ -529,91 +518,18 @@ __global__ void k_fl_seed_one(uint8_t *flag, int32_t node, int32_t *front, int32
   cnt[1] = 0;
 }
 
-// Out-arcs of node u by index, in for_out's order.
-struct OutArcs {
-  int64_t base;  // first adjacency entry of a vertex node, arc block of a net node
-  int32_t count;
-  bool vertex, out;
-};
-__device__ __forceinline__ OutArcs out_arcs(int64_t u, int32_t nv, const int64_t *voffn, const int64_t *rbase,
-                                            const int32_t *rends) {
-  if (u < nv) {
-    const int64_t lo = voffn[u];
-    return OutArcs{lo, (int32_t)(2 * (voffn[u + 1] - lo)), true, false};
-  }
-  const int64_t r = (u - nv) >> 1;
-  return OutArcs{rbase[r], 1 + rends[r], false, ((u - nv) & 1) != 0};
-}
-__device__ __forceinline__ int64_t out_arc(const OutArcs &o, const int64_t *vadj, int32_t i) {
-  if (o.vertex) return vadj[o.base + (i >> 1)] + (i & 1 ? 3 : 0);
-  if (i == 0) return o.base + (o.out ? 1 : 0);
-  return o.base + 2 + 4 * (int64_t)(i - 1) + (o.out ? 2 : 1);
-}
-
-// Push-relabel sweep: every active node (free, positive excess, height below 2N) pushes to its
-// lowest residual neighbour if it is higher, else relabels to one above it.  Only u's thread lowers
-// u's excess and the residuals of u's arcs, so a push never takes more than is there.  A step is a
-// chain of loads past the caches (residual, head, height), issued for kSweepU arcs at a time: a round of
-// flow refinement on 20,000 VLSI-like vertices, k = 8, took 240 ms with one arc after the other, 227 with
-// eight.
-constexpr int kSweepU = 8;
+// Push-relabel sweep, a thread per node: 20,000 VLSI-like vertices, k = 8, took 240 ms a round with one arc
+// after the other in a node's turn, 227 with eight.
 __global__ __launch_bounds__(kFB) void k_fl_sweep(int64_t N, int32_t nv, const uint8_t *__restrict__ term,
                                                   int32_t *__restrict__ h, int64_t *__restrict__ ex,
                                                   int64_t *__restrict__ res, const int32_t *__restrict__ head,
                                                   const int64_t *__restrict__ voffn, const int64_t *__restrict__ vadj,
-                                                  const int64_t *__restrict__ rbase, const int32_t *__restrict__ rends,
-                                                  int64_t *sc) {
-  const int32_t h2n = (int32_t)(2 * N);
-  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < N; u += (int64_t)gridDim.x * blockDim.x) {
-    const uint8_t tu = term[u];
-    int64_t e = ld(&ex[u]);
-    int32_t hu = h[u];
-    if (tu != 0 || e <= 0 || hu >= h2n) continue;
-    const OutArcs o = out_arcs(u, nv, voffn, rbase, rends);
-    for (int c = 0; c < kPushCycles; ++c) {
-      int64_t best_a = -1, best_r = 0;
-      int32_t best_h = INT32_MAX, best_v = 0;
-      for (int32_t i0 = 0; i0 < o.count; i0 += kSweepU) {
-        int64_t a[kSweepU], r[kSweepU];
-        int32_t v[kSweepU], hv[kSweepU];
-#pragma unroll
-        for (int i = 0; i < kSweepU; ++i) a[i] = i0 + i < o.count ? out_arc(o, vadj, i0 + i) : -1;
-#pragma unroll
-        for (int i = 0; i < kSweepU; ++i) {
-          r[i] = a[i] >= 0 ? ld(&res[a[i]]) : 0;
-          v[i] = a[i] >= 0 ? head[a[i]] : 0;
-        }
-#pragma unroll
-        for (int i = 0; i < kSweepU; ++i) hv[i] = r[i] > 0 ? ld(&h[v[i]]) : INT32_MAX;
-#pragma unroll
-        for (int i = 0; i < kSweepU; ++i)
-          if (r[i] > 0 && hv[i] < best_h) {
-            best_h = hv[i];
-            best_a = a[i];
-            best_r = r[i];
-            best_v = v[i];
-          }
-      }
-      if (best_a < 0) {  // cannot happen for a node with excess; reported, never left looping
-        atomicAdd((unsigned long long *)&sc[kScErr], 1ull);
-        __hip_atomic_store(&h[u], h2n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        break;
-      }
-      if (hu > best_h) {
-        const int64_t d = e < best_r ? e : best_r;  // the residual can only have grown since it was read
-        push(best_a, (int32_t)u, best_v, d, res, ex);
-      } else {
-        hu = best_h + 1 < h2n ? best_h + 1 : h2n;
-        __hip_atomic_store(&h[u], hu, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      e = ld(&ex[u]);
-      if (e <= 0 || hu >= h2n) break;
-    }
-  }
+                                                  const int64_t *__restrict__ rbase, const int32_t *__restrict__ rends) {
+  for (int64_t u = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; u < N; u += (int64_t)gridDim.x * blockDim.x)
+    sweep_node(u, N, nv, term, h, ex, res, head, voffn, vadj, rbase, rends);
 }
 
-// active nodes; a free node left with excess at height 2N would leave no valid flow: counted as an
-// error
+// active nodes, and free nodes left with excess at height 2N
 __global__ void k_fl_active(int64_t N, const uint8_t *__restrict__ term, const int32_t *__restrict__ h,
                             const int64_t *__restrict__ ex, int64_t *sc) {
   const int32_t h2n = (int32_t)(2 * N);
@@ -624,7 +540,7 @@ __global__ void k_fl_active(int64_t N, const uint8_t *__restrict__ term, const i
     else ++stuck;
   }
   add_sc(sc, kScActive, cnt);
-  add_sc(sc, kScErr, stuck);
+  add_sc(sc, kScStuck, stuck);
 }
 
 __global__ void k_fl_sinkflow(int64_t N, const uint8_t *__restrict__ term, const int64_t *__restrict__ ex,
@@ -638,22 +554,27 @@ __global__ void k_fl_sinkflow(int64_t N, const uint8_t *__restrict__ term, const
 // ---- residual reachability ----
 
 // weights of the vertices on the source side (S_r) and on the sink side (T_r): the region vertices'
-// nodes, and the contracted terminals (weight cs on node 0, ct on node 1)
-__global__ void k_fl_sidew(const int32_t *__restrict__ nvert, const int32_t *__restrict__ vw, int32_t nv,
-                           const uint8_t *__restrict__ rs, const uint8_t *__restrict__ rt, int64_t cs, int64_t ct,
-                           int64_t *sc) {
-  int64_t w1 = 0, w2 = 0;
+// nodes, and the contracted terminals (weight cs on node 0, ct on node 1); and the sinks the sources reach
+// (none once the flow is maximum)
+__global__ void k_fl_sidew(const int32_t *__restrict__ nvert, const int32_t *__restrict__ vw, int64_t N, int32_t nv,
+                           const uint8_t *__restrict__ term, const uint8_t *__restrict__ rs,
+                           const uint8_t *__restrict__ rt, int64_t cs, int64_t ct, int64_t *sc) {
+  int64_t w1 = 0, w2 = 0, open = 0;
   if (blockIdx.x == 0 && threadIdx.x == 0) {  // the contracted terminals: cs on node 0, ct on node 1
     w1 += (rs[0] ? cs : 0) + (rs[1] ? ct : 0);
     w2 += (rt[0] ? cs : 0) + (rt[1] ? ct : 0);
   }
-  for (int64_t x = 2 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < nv; x += (int64_t)gridDim.x * blockDim.x) {
+  for (int64_t x = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; x < N; x += (int64_t)gridDim.x * blockDim.x) {
+    const bool s = rs[x] != 0;
+    open += s && term[x] == 2;
+    if (x < 2 || x >= nv) continue;
     const int64_t w = cv(vw, nvert[x - 2]);
-    if (rs[x]) w1 += w;
+    if (s) w1 += w;
     if (rt[x]) w2 += w;
   }
   add_sc(sc, kScW1, w1);
   add_sc(sc, kScW2, w2);
+  add_sc(sc, kScOpen, open);
 }
 
 // piercing candidates: free vertex endpoints outside `mine` of nets with endpoints on both sides of
@@ -873,17 +794,10 @@ int read_sc(Ctx &c) {
   return JET_OK;
 }
 
-// Clears the scalar slots except the error count, which lasts for the whole call.  The host
-// mirror is cleared with them: it always holds the value a slot had at its last read (or clear),
-// so the loops of the piercing step take differences of sums instead of clearing the device slots
-// before every launch.
+// Clears the scalar slots.  The host mirror is cleared with them: it always holds the value a slot had at
+// its last read (or clear), so the loops of the piercing step take differences of sums instead of
+// clearing the device slots before every launch.
 int zero_sc(Ctx &c) {
-  FL_OK(hipMemsetAsync(c.fl->sc, 0, sizeof(int64_t) * kScErr, c.stream));
-  for (int i = 0; i < kScErr; ++i) c.fl->hsc[i] = 0;
-  return JET_OK;
-}
-
-int start_call(Ctx &c) {
   FL_OK(hipMemsetAsync(c.fl->sc, 0, sizeof(int64_t) * kScN, c.stream));
   for (int i = 0; i < kScN; ++i) c.fl->hsc[i] = 0;
   return JET_OK;
@@ -1064,6 +978,18 @@ int global_relabel(Ctx &c, const Net &net) {
   return JET_OK;
 }
 
+// nodes that can push, and free nodes with excess at height 2N
+int count_active(Ctx &c, const Net &net, int64_t *active, int64_t *stuck) {
+  FlowState &s = *c.fl;
+  const int64_t a = s.hsc[kScActive], b = s.hsc[kScStuck];
+  hipLaunchKernelGGL(k_fl_active, dim3(fgrid(net.N)), dim3(kFB), 0, c.stream, net.N, s.term, s.h, s.ex, s.sc);
+  FL_OK(hipGetLastError());
+  FL_RC(read_sc(c));
+  *active = s.hsc[kScActive] - a;
+  *stuck = s.hsc[kScStuck] - b;
+  return JET_OK;
+}
+
 // maximum flow from the current one for the current terminals; its value in *flow
 int max_flow(Ctx &c, const Net &net, int64_t *flow) {
   FlowState &s = *c.fl;
@@ -1091,17 +1017,19 @@ int max_flow(Ctx &c, const Net &net, int64_t *flow) {
     t0 = clock::now();
     for (int i = 0; i < kSweepsPerCheck; ++i)
       hipLaunchKernelGGL(k_fl_sweep, dim3(fgrid(net.N)), dim3(kFB), 0, c.stream, net.N, net.nv, s.term, s.h, s.ex,
-                         s.res, s.head, s.voffn, s.vadj, s.rbase, s.rends, s.sc);
-    const int64_t before = s.hsc[kScActive];
-    hipLaunchKernelGGL(k_fl_active, dim3(fgrid(net.N)), dim3(kFB), 0, c.stream, net.N, s.term, s.h, s.ex, s.sc);
-    FL_OK(hipGetLastError());
-    FL_RC(read_sc(c));
+                         s.res, s.head, s.voffn, s.vadj, s.rbase, s.rends);
+    int64_t active = 0, stuck = 0;
+    FL_RC(count_active(c, net, &active, &stuck));
     sweeps_s += std::chrono::duration<double>(clock::now() - t0).count();
-    if (s.hsc[kScErr] != 0) {
-      c.last_error = "flow: a node with excess cannot push";
-      return JET_EHIP;
+    if (stuck > 0) {  // relabelled past an arc that was not visible yet; exact heights are below 2N
+      FL_RC(global_relabel(c, net));
+      FL_RC(count_active(c, net, &active, &stuck));
+      if (stuck > 0) {
+        c.last_error = "flow: a node with excess cannot push";
+        return JET_EHIP;
+      }
     }
-    if (s.hsc[kScActive] == before) break;
+    if (active == 0) break;
   }
   const int64_t before = s.hsc[kScFlow];
   hipLaunchKernelGGL(k_fl_sinkflow, dim3(fgrid(net.N)), dim3(kFB), 0, c.stream, net.N, s.term, s.ex, s.sc);
@@ -1132,14 +1060,21 @@ int reach(Ctx &c, const Net &net, int32_t dir, int32_t from = -1) {
   return JET_OK;
 }
 
-int check_err(Ctx &c) {
+// The side weights and, in *open, the sinks the sources reach.
+int sides(Ctx &c, const Net &net, int64_t cs, int64_t ct, int64_t *w1, int64_t *w2, int64_t *open) {
+  FlowState &s = *c.fl;
+  const int64_t b1 = s.hsc[kScW1], b2 = s.hsc[kScW2], b3 = s.hsc[kScOpen];
+  hipLaunchKernelGGL(k_fl_sidew, dim3(fgrid(net.N)), dim3(kFB), 0, c.stream, s.nvert, c.vw, net.N, net.nv, s.term,
+                     s.rs, s.rt, cs, ct, s.sc);
+  FL_OK(hipGetLastError());
   FL_RC(read_sc(c));
-  if (c.fl->hsc[kScErr] != 0) {
-    c.last_error = "flow: a node with excess had no residual arc";
-    return JET_EHIP;
-  }
+  *w1 = s.hsc[kScW1] - b1;
+  *w2 = s.hsc[kScW2] - b2;
+  *open = s.hsc[kScOpen] - b3;
   return JET_OK;
 }
+
+constexpr int kMaxAgain = 64;  // times a flow goes on because a sink was still in the sources' reach
 
 }  // namespace
 
@@ -1161,7 +1096,7 @@ void flow_free(Ctx &c) {
 
 int flow_region(Ctx &c, const int32_t *part, int32_t a, int32_t b, int32_t alpha, int8_t *region) {
   FL_RC(ensure_state(c));
-  FL_RC(start_call(c));
+  FL_RC(zero_sc(c));
   FL_RC(pair_scalars(c, part, a, b));
   FlowState &s = *c.fl;
   int32_t ra = 0, rb = 0;
@@ -1174,22 +1109,30 @@ int flow_region(Ctx &c, const int32_t *part, int32_t a, int32_t b, int32_t alpha
 int flow_mincut(Ctx &c, const int32_t *part, int32_t a, int32_t b, const int8_t *term, int64_t *flow,
                 uint8_t *in_sr, uint8_t *in_tr) {
   FL_RC(ensure_state(c));
-  FL_RC(start_call(c));
+  FL_RC(zero_sc(c));
   FlowState &s = *c.fl;
   Net net;
   FL_RC(build_net(c, part, a, b, term, &net));
-  FL_RC(max_flow(c, net, flow));
-  FL_RC(reach(c, net, 3));
+  int64_t w1 = 0, w2 = 0, open = 1;
+  for (int again = 0; open > 0; ++again) {
+    if (again > kMaxAgain) {
+      c.last_error = "flow: push-relabel left augmenting paths";
+      return JET_EHIP;
+    }
+    FL_RC(max_flow(c, net, flow));
+    FL_RC(reach(c, net, 3));
+    FL_RC(sides(c, net, 0, 0, &w1, &w2, &open));
+  }
   hipLaunchKernelGGL(k_fl_export, dim3(fgrid(c.n)), dim3(kFB), 0, c.stream, s.vnode, c.n, s.rs, s.rt, in_sr, in_tr);
   FL_OK(hipGetLastError());
-  FL_RC(check_err(c));
+  FL_OK(hipStreamSynchronize(c.stream));
   return JET_OK;
 }
 
 // Algorithm 3 for the pair (a, b); readings F1-F3 of the design notes
 int flow_pair(Ctx &c, int32_t *part, int32_t a, int32_t b, int32_t alpha, FlowPairResult *out) {
   FL_RC(ensure_state(c));
-  FL_RC(start_call(c));
+  FL_RC(zero_sc(c));
   FlowState &s = *c.fl;
   FlowPairResult r;
   FL_RC(pair_scalars(c, part, a, b));
@@ -1219,13 +1162,19 @@ int flow_pair(Ctx &c, int32_t *part, int32_t a, int32_t b, int32_t alpha, FlowPa
     }
     ++r.iterations;
     r.arcs += net.A;
+    if (F > r.old_cut) break;  // also if it is not maximum yet
+    int64_t w1 = 0, w2 = 0, open = 0;
+    FL_RC(sides(c, net, bwa - rwa, bwb - rwb, &w1, &w2, &open));
+    for (int again = 0; open > 0 && F <= r.old_cut; ++again) {
+      if (again == kMaxAgain) {
+        c.last_error = "flow: push-relabel left augmenting paths";
+        return JET_EHIP;
+      }
+      FL_RC(max_flow(c, net, &F));
+      FL_RC(reach(c, net, 3));
+      FL_RC(sides(c, net, bwa - rwa, bwb - rwb, &w1, &w2, &open));
+    }
     if (F > r.old_cut) break;
-    const int64_t w1_before = s.hsc[kScW1], w2_before = s.hsc[kScW2];
-    hipLaunchKernelGGL(k_fl_sidew, dim3(fgrid(net.nv)), dim3(kFB), 0, c.stream, s.nvert, c.vw, net.nv, s.rs, s.rt,
-                       bwa - rwa, bwb - rwb, s.sc);
-    FL_OK(hipGetLastError());
-    FL_RC(read_sc(c));
-    const int64_t w1 = s.hsc[kScW1] - w1_before, w2 = s.hsc[kScW2] - w2_before;
     const int64_t h1 = std::max(w1, wab - w1), h2 = std::max(w2, wab - w2);
     const bool bal1 = w1 <= lmax && wab - w1 <= lmax;
     const bool bal2 = w2 <= lmax && wab - w2 <= lmax;
@@ -1264,7 +1213,6 @@ int flow_pair(Ctx &c, int32_t *part, int32_t a, int32_t b, int32_t alpha, FlowPa
     FL_OK(hipMemcpyAsync(&pierced, s.vnode + (key & 0x7fffffff), sizeof(int32_t), hipMemcpyDeviceToHost, c.stream));
     FL_OK(hipStreamSynchronize(c.stream));
   }
-  FL_RC(check_err(c));
   *out = r;
   return JET_OK;
 }
@@ -1290,7 +1238,7 @@ int km1_quot(Ctx &c, const int32_t *part, uint8_t *quot_dev, std::vector<uint8_t
 // k-way refinement with the matching schedule of Section 5.2 (reading F4 of the design notes)
 int flow_refine(Ctx &c, int32_t *part, int32_t alpha, int32_t max_rounds, FlowRefineResult *out) {
   FL_RC(ensure_state(c));
-  FL_RC(start_call(c));
+  FL_RC(zero_sc(c));
   const int32_t k = c.k;
   FlowRefineResult r;
   uint8_t *quot_dev = nullptr;
