@@ -301,9 +301,9 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * rebalance_select); default all.  Fewer families, less host work per launch. */
 #define JET_OPT_PROF_FAMILIES 3
 /* Candidate selection and rebalancing gains with unit net weights (bit-sliced block counts) use one
- * lane per vertex on more than 32,768 vertices when the mean degree of the non-hub vertices is below
- * this value, a group of lanes per vertex otherwise; default 24, 0 = always groups.  Results do not
- * depend on it. */
+ * lane per vertex when the mean degree of the non-hub vertices is below this value, a group of lanes per
+ * vertex otherwise; 0 = always groups.  The default 24 also keeps groups on up to 32,768 vertices; any
+ * other value decides at every size.  Results do not depend on it. */
 #define JET_OPT_CAND_LANE_DEGREE 4
 /* The rebalancing selection's first radix pass runs over all compute units (a histogram kernel
  * and a split kernel, several workgroups per overloaded block) on levels with at least this many

@@ -5,7 +5,7 @@ Knobs (none of them changes any result, only the time):
   replays        bound of a union's steps in flight (one is launched at a time, so more change nothing);
   grid           workgroups of the persistent kernels (tiles per workgroup = work / grid);
   lane_degree    lanes per vertex of the bit-sliced candidate kernel: one lane below this mean degree,
-                 eight above (0: always eight);
+                 eight above (0: always eight; 24 is the library's rule);
   apply_divisor  switch point of move application from per-move atomics to per-net recounting;
   rb_slots       rebalancing rounds launched at a time.
 

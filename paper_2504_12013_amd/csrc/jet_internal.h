@@ -336,6 +336,8 @@ constexpr int kSides = 3;
 constexpr int32_t kUnionRounds = 3;
 constexpr int64_t kForkPins = 1 << 19;  // pins from which the afterburner's kernels run beside each other
 
+constexpr int32_t kLaneDegreeDefault = 24;  // JET_OPT_CAND_LANE_DEGREE unless set
+
 struct Ctx {
   hipStream_t stream = nullptr;
   int32_t n = 0, m = 0, k = 0, nw_words = 1;  // nw_words = ceil(k/64) words per mask
@@ -353,7 +355,7 @@ struct Ctx {
   // used to size the next launch of that kind
   bool wide_hint[2] = {false, false};
   bool wide_enabled = false;  // JET_OPT_APPLY_WIDE
-  int32_t lane_degree = 24;   // JET_OPT_CAND_LANE_DEGREE
+  int32_t lane_degree = kLaneDegreeDefault;  // JET_OPT_CAND_LANE_DEGREE
   int32_t cand_xcd = 1;       // JET_OPT_CAND_XCD: contiguous vertex ranges per XCD in the candidate kernels
   int32_t rb_xcd = 1;         // JET_OPT_RB_XCD: contiguous list ranges per XCD in the rebalancing gain pass
   int32_t apply_xcd = 0;      // JET_OPT_APPLY_XCD: contiguous move and chunk ranges per XCD in the application
@@ -502,10 +504,10 @@ void launch_resident(Ctx &c, int64_t blocks, int block, A... args) {
 // One lane is right while the vertices are light (mean degree below lane_degree) and more than a few:
 // 2,000 to 30,000 vertices are 32 to 500 waves of one-lane vertices on 1,024 SIMDs, and their refinement
 // took 2 to 8% longer than with eight lanes; from 65,000 on local hypergraphs are 1% (260,000: 18%) faster
-// with one.
+// with one.  A lane degree other than the default decides at every size.
 constexpr int32_t kFewVertices = 1 << 15;
 inline bool light_lanes(const Ctx &c) {
-  return c.n > kFewVertices && c.p_low < (int64_t)c.lane_degree * c.n_low;
+  return (c.n > kFewVertices || c.lane_degree != kLaneDegreeDefault) && c.p_low < (int64_t)c.lane_degree * c.n_low;
 }
 
 // the union view of a context for the kernels
