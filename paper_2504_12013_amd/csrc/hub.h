@@ -14,7 +14,13 @@ namespace jet {
 
 constexpr int kHubBlock = 256;
 constexpr int kHubWaves = kHubBlock / kWave;
-constexpr int kHubShares = 16;   // most workgroups on one hub
+// Workgroups of one hub: one per kHubShare nets (the four of a thread that are in flight together), at most
+// kHubShares.  The release and acquire between them write back and invalidate caches, 3 to 4 us a pass: with
+// 16 workgroups on every hub a V-cycle on 1M row-net vertices took 1.5% longer (shares of 256 nets 1%), with
+// these as long as with an unordered hand-over.  What pays is a level of few listed hubs of thousands of
+// nets (8,000 hubs of 3,000 nets: 17 -> 21 us a rebalancing pass).
+constexpr int kHubShares = 16;
+constexpr int kHubShare = 1024;
 constexpr int kHubSegment = 508; // nets one lane takes before its nine planes are emptied
 
 // max over 64 lanes of a 64-bit key
@@ -120,7 +126,7 @@ __device__ __forceinline__ void hub_work(const HubArgs &a, int32_t bid, int32_t 
     dz0 = a.lc->dz;
     unw0 = a.lc->rb_unw;
   }
-  const int32_t per = max(1, min(kHubShares, nblk / nh));  // workgroups of a hub
+  const int32_t per = max(1, min(kHubShares, nblk / nh));  // most workgroups of a hub
   unsigned long long scanned = 0ull, examined = 0ull, emitted = 0ull;     // thread 0
   for (int64_t i = bid; i < (int64_t)nh * per; i += nblk) {   // block-uniform trip count
     const int32_t j = (int32_t)(i / per), sub = (int32_t)(i % per);
@@ -137,23 +143,25 @@ __device__ __forceinline__ void hub_work(const HubArgs &a, int32_t bid, int32_t 
       }
     }
     const int64_t q0 = a.voff[v], q1 = a.voff[v + 1];
-    hub_sums<G, HW, UNIT>(a, q0 + (int64_t)sub * kHubBlock, q1, (int64_t)per * kHubBlock, s, row);
-    if (per > 1) {
+    const int32_t shares =  // uniform
+        __builtin_amdgcn_readfirstlane(min(per, (int32_t)(q1 - q0 + kHubShare - 1) / kHubShare));
+    if (sub >= shares) continue;  // block-uniform
+    hub_sums<G, HW, UNIT>(a, q0 + (int64_t)sub * kHubBlock, q1, (int64_t)shares * kHubBlock, s, row);
+    if (shares > 1) {
       int32_t *mine = a.rows + i * (k + 1);  // i < the grid: one pass when workgroups share hubs
-      for (int b = tid; b <= k; b += kHubBlock)
-        __hip_atomic_store(&mine[b], row[b], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      // the row is in device-wide order before the arrival is counted, and the last workgroup reads
-      // the rows with atomic loads, so no cache has to be written back or invalidated
-      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      for (int b = tid; b <= k; b += kHubBlock) mine[b] = row[b];
       __syncthreads();
-      if (tid == 0) s_last = atomicAdd(&a.done[hi], 1) == per - 1;
+      // the barrier and the release put every thread's stores before the arrival, the acquire and the next
+      // barrier the arrivals before the last workgroup's loads
+      if (tid == 0) {
+        s_last = __hip_atomic_fetch_add(&a.done[hi], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == shares - 1;
+        if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      }
       __syncthreads();
       if (!s_last) continue;  // block-uniform
       for (int b = tid; b <= k; b += kHubBlock) {
         int32_t c = 0;
-        for (int x = 0; x < per; ++x)
-          c += __hip_atomic_load(&a.rows[((int64_t)j * per + x) * (k + 1) + b], __ATOMIC_RELAXED,
-                                 __HIP_MEMORY_SCOPE_AGENT);
+        for (int x = 0; x < shares; ++x) c += a.rows[((int64_t)j * per + x) * (k + 1) + b];
         row[b] = c;
       }
       if (tid == 0) a.done[hi] = 0;

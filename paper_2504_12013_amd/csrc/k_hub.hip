@@ -2,8 +2,8 @@
 // gains (Section 4.3).
 //
 // Both need conn(v, b) over all incident nets of every hub.  A workgroup takes a hub, or while there
-// are fewer hubs than workgroups a share of one; then the workgroups of a hub store their sums in rows
-// and the last one to arrive adds the rows and finishes the hub (best target, record or entry), so no
+// are fewer hubs than workgroups a share of a long one; then the workgroups of a hub store their sums in
+// rows and the last one to arrive adds the rows and finishes the hub (best target, record or entry), so no
 // second launch waits for the sums.  With unit net weights a lane takes whole nets into bit-sliced
 // counts (conn.h), which the wave sums at the end: a net costs a lane a gather and some 15
 // instructions.  Eight lanes per net with four exchanges and 24 instructions each bound the passes by
