@@ -709,16 +709,6 @@ int refine_impl(Ctx &c, int32_t *part, const jet_params *prm, jet_stats *out, je
 
 // ---- synchronous clustering (Section 6, Algorithm 4): host side ----
 
-// rating-table slots of a vertex with d = sum of (|e| - 1) over its nets: a power of two at least
-// twice the number of clusters it can meet (at most min(d, n)), so probing stays short
-int64_t co_table(int64_t d, int64_t n) {
-  if (d <= 0) return 0;
-  const int64_t want = std::max<int64_t>(16, 2 * std::min(d, n));
-  int64_t t = 16;
-  while (t < want) t <<= 1;
-  return t;
-}
-
 // (first position, length) of every sub-round: initial_single of one vertex, then 2, 4, 8, ... up
 // to max(1, n / cap_div) (Section 6, prefix doubling)
 std::vector<std::pair<int64_t, int64_t>> co_schedule(int64_t n, int32_t initial_single, int32_t cap_div) {
@@ -813,7 +803,7 @@ int co_reserve(Ctx &c, int64_t cap, int64_t ptab_len, int64_t slots) {
 }
 
 // some vertex's rating table does not fit the LDS of the rating kernel
-bool co_large_tables(const Ctx &c) { return co_table(c.co->max_deg, c.n) > jet::kCoLdsTable; }
+bool co_large_tables(const Ctx &c) { return jet::co_table(c.co->max_deg, c.n) > jet::kCoLdsTable; }
 
 // Sub-rounds `rounds` over the device list d_list (host copy hlist, needed if co_large_tables): offsets
 // of the tables in global scratch, launches.
@@ -835,7 +825,7 @@ int co_run(Ctx &c, const int32_t *d_list, const std::vector<int32_t> &hlist,
   const int64_t len = (int64_t)hlist.size();
   std::vector<int64_t> P((size_t)len + 1, 0);
   for (int64_t i = 0; i < len; ++i) {
-    int64_t t = co_table(s.hdeg[(size_t)hlist[(size_t)i]], c.n);
+    int64_t t = jet::co_table(s.hdeg[(size_t)hlist[(size_t)i]], c.n);
     if (t <= jet::kCoLdsTable) t = 0;
     P[(size_t)i + 1] = P[(size_t)i] + t;
     biggest = std::max(biggest, t);

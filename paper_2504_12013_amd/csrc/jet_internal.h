@@ -593,7 +593,15 @@ hipError_t launch_build_adj(Ctx &c);
 bool graph_afterburner(const Ctx &c);
 hipError_t launch_ab_graph(Ctx &c, const int32_t *part, const LoopCtl *lc, int32_t want);
 
-constexpr int64_t kCoLdsTable = 512;  // largest rating table (slots) that needs no global scratch
+constexpr int kCoLdsTable = 512;  // largest rating table (slots) that needs no global scratch
+// Rating-table slots of a vertex with d = sum of (|e| - 1) over its nets: a power of two at least twice the
+// number of clusters it can meet (at most min(d, n)), so probing stays short.  The host lays out the
+// tables above kCoLdsTable by it, the rating kernel finds its own by it.
+__host__ __device__ inline int64_t co_table(int64_t d, int64_t n) {
+  if (d <= 0) return 0;
+  const int64_t want = 2 * (d < n ? d : n);
+  return want <= 16 ? 16 : (int64_t)1 << (64 - __builtin_clzll((unsigned long long)(want - 1)));
+}
 // k_coarsen.hip: synchronous clustering (Section 6, Algorithm 4)
 hipError_t launch_co_prepare(Ctx &c);
 hipError_t launch_co_init(Ctx &c, int32_t *label, int64_t *cw);

@@ -189,15 +189,7 @@ __device__ __forceinline__ void rate_vertex(int64_t t, int gl, const int32_t *__
 
 constexpr int kCoGroup = 8;      // lanes per vertex for the smallest tables
 constexpr int kCoLdsSmall = 64;  // largest table (slots) rated by kCoGroup lanes in LDS
-constexpr int kCoLdsLarge = 512; // largest table rated by a wave in LDS
-static_assert(kCoLdsSmall * (kWave / kCoGroup) == kCoLdsLarge, "both forms use the same LDS");
-
-// Slots of the table of a vertex with D = d: a power of two at least twice the number of clusters it
-// can meet (as the host's co_table).
-__device__ __forceinline__ int32_t co_slots(int64_t d, int64_t n) {
-  const int64_t want = max((int64_t)16, 2 * min(d, n));
-  return want <= 16 ? 16 : (int32_t)min((int64_t)1 << 30, (int64_t)1 << (64 - __clzll(want - 1)));
-}
+static_assert(kCoLdsSmall * (kWave / kCoGroup) == kCoLdsTable, "both forms use the same LDS");
 
 // Rating by G lanes in an LDS table of cap slots (G = 8 or 64 lanes, aligned in the wave).  The lanes
 // load the offsets of G nets at once and the first G pins and labels of NB nets at once, so a vertex
@@ -309,18 +301,18 @@ __global__ __launch_bounds__(kCoBlock) void k_co_rate(
     const int64_t *__restrict__ cw, int64_t wmax, CoSlot *__restrict__ tab, int32_t *__restrict__ tp,
     unsigned long long *__restrict__ jw, int32_t *__restrict__ ctr) {
   if (blockIdx.x == 0 && threadIdx.x == 0) ctr[0] = ctr[3] = 0;  // the sub-round's group counters
-  __shared__ int32_t key[kCoBlock / kWave][kCoLdsLarge], mark[kCoBlock / kWave][kCoLdsLarge];
-  __shared__ unsigned long long val[kCoBlock / kWave][kCoLdsLarge];
+  __shared__ int32_t key[kCoBlock / kWave][kCoLdsTable], mark[kCoBlock / kWave][kCoLdsTable];
+  __shared__ unsigned long long val[kCoBlock / kWave][kCoLdsTable];
   const int w = (int)(threadIdx.x / kWave), l = lane_id();
   if (blockIdx.x >= small_blocks) {  // workgroup-uniform
     const int64_t t = a + (int64_t)(blockIdx.x - small_blocks) * (kCoBlock / kWave) + w;
     if (t >= b) return;
     const int32_t u = verts[t];
-    const int64_t d = deg[u];
-    const int32_t cap = d > 0 ? co_slots(d, n) : 0;
+    const int64_t cap = co_table(deg[u], n);
     if (cap <= kCoLdsSmall) return;
-    if (cap <= kCoLdsLarge)
-      rate_lds<kWave>(u, cap, l, voff, inc, off, pins, qnet, vw, label, cw, wmax, key[w], mark[w], val[w], tp, jw);
+    if (cap <= kCoLdsTable)
+      rate_lds<kWave>(u, (int32_t)cap, l, voff, inc, off, pins, qnet, vw, label, cw, wmax, key[w], mark[w], val[w], tp,
+                      jw);
     else
       rate_vertex<kWave>(t, l, verts, ptab, base, voff, inc, off, pins, qnet, vw, label, cw, wmax, tab, tp, jw);
     return;
@@ -329,14 +321,13 @@ __global__ __launch_bounds__(kCoBlock) void k_co_rate(
   const int64_t t = a + ((int64_t)blockIdx.x * (kCoBlock / kWave) + w) * (kWave / kCoGroup) + g;
   if (t >= b) return;
   const int32_t u = verts[t];
-  const int64_t d = deg[u];
-  const int32_t cap = d > 0 ? co_slots(d, n) : 0;
+  const int64_t cap = co_table(deg[u], n);
   if (cap > kCoLdsSmall) return;
   if (cap == 0) {  // no neighbour
     if (l % kCoGroup == 0) tp[u] = -1;
     return;
   }
-  rate_lds<kCoGroup>(u, cap, l % kCoGroup, voff, inc, off, pins, qnet, vw, label, cw, wmax,
+  rate_lds<kCoGroup>(u, (int32_t)cap, l % kCoGroup, voff, inc, off, pins, qnet, vw, label, cw, wmax,
                      key[w] + g * kCoLdsSmall, mark[w] + g * kCoLdsSmall, val[w] + g * kCoLdsSmall, tp, jw);
 }
 
