@@ -402,7 +402,8 @@ int jet_prof_enable(jet_ctx *ctx, int32_t on);
 /* Writes up to cap [host] entries (one per kernel family that ran) and the count to *count.
  * Synchronises the stream. */
 int jet_prof_read(jet_ctx *ctx, jet_prof_entry *out, int32_t cap, int32_t *count);
-/* Instrumentation of every union context (as jet_prof_enable / jet_prof_read; entries summed). */
+/* Instrumentation of every union context (as jet_prof_enable / jet_prof_read; entries summed).  While it is
+ * on the unions run one kernel at a time on the batch's stream, so the times add up. */
 int jet_batch_prof_enable(jet_batch *b, int32_t on);
 int jet_batch_prof_read(jet_batch *b, jet_prof_entry *out, int32_t cap, int32_t *count);
 

@@ -1632,7 +1632,7 @@ int jet_batch_set_option(jet_batch *b, int32_t option, int64_t value) {
 }
 
 // The loops of a batch's unions, each on a stream of its own when there are several (their kernels are
-// small and overlap).  A step of a union launches a piece for every phase that some of its hypergraphs
+// small and overlap; instrumented batches stay on the caller's stream, so that the families' times add up).  A step of a union launches a piece for every phase that some of its hypergraphs
 // are in, once its last step has reported; while one union's report travels the others compute.  Replaying
 // one graph of every phase and four rebalancing rounds, all unions in turn, until the slowest hypergraph
 // was done launched more than half of its kernels for nothing: 96 hypergraphs of up to 30,000 vertices
@@ -1649,7 +1649,7 @@ static int batch_loops(jet_batch *b, const jet_params *params) {
     Ctx &c = b->uctx[i]->c;
     Run &r = runs[i];
     c.use_graph = b->use_graph;
-    if (runs.size() > 1) c.stream = c.gstream;  // the state is built and the caller's stream has been waited for
+    if (runs.size() > 1 && !c.prof) c.stream = c.gstream;  // the state is built, the caller's stream waited for
     if (c.H == 1) *c.mail = 0ull;               // its record starts anew, a union's gate record counts on
     r.seen = jet::read_mail(*c.mail).seq;
     r.cap = 2.0 * c.H * params->num_tau * ((double)params->max_iters + 2.0) *
