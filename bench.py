@@ -136,7 +136,8 @@ FAMILIES = {
     "afterburner": (("k_ab_chunks", "k_ab_graph"), ("k_ab_nets", "k_ab_overflow", "k_rg_reduce")),
     "select_moves": (("k_select_moves",), ()),
     "apply": (("k_apply",), ("k_apply_chunks", "k_apply_nets")),  # the latter in traces of older builds
-    "rebalance_gain": (("k_rb_list", "k_rb_list_union"), ("k_rb_gain", "k_rb_gain_bits", "k_rb_hub_list")),
+    "rebalance_gain": (("k_rb_list", "k_rb_list_union"), ("k_rb_gain", "k_rb_gain_bits", "k_rb_hub_list",
+                                                             "k_rb_hub")),
     "rebalance_select": (("k_rb_select",), ("k_rb_sel_hist", "k_rb_sel_split")),
     "clustering_subround": (("k_co_group", "k_co_settle_small"), ("k_co_rate", "k_co_offsets", "k_co_scatter",
                                                                   "k_co_approve", "k_co_apply")),

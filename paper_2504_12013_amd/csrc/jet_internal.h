@@ -243,13 +243,13 @@ enum : int32_t {
 
 // kernel families timed by the optional instrumentation
 enum ProfFamily : int {
-  kProfCandidates = 0,   // k_candidates (vertices with at most kHubDegree incident nets)
-  kProfCandidatesHub,    // k_hub where hubs are not beside the light vertices
-  kProfAfterburner,      // k_ab_chunks + k_ab_nets + k_ab_overflow
+  kProfCandidates = 0,   // k_candidates or k_candidates_bits (hubs too where they are beside the others)
+  kProfCandidatesHub,    // k_hub where hubs are not beside the others
+  kProfAfterburner,      // k_ab_chunks + k_ab_nets + k_ab_overflow + k_rg_reduce, or k_ab_graph
   kProfSelect,           // k_select_moves
   kProfApply,            // k_apply
-  kProfRbGain,           // k_rb_gain + k_rb_gain_hub
-  kProfRbSelect,         // k_rb_prepare + k_rb_select
+  kProfRbGain,           // k_rb_list(_union) + k_rb_gain(_bits) + k_rb_hub_list + k_rb_hub
+  kProfRbSelect,         // k_rb_sel_hist + k_rb_sel_split + k_rb_select
   kProfFamilies
 };
 

@@ -38,17 +38,31 @@ __global__ __launch_bounds__(256) void k_rb_hub_list(const int32_t *__restrict__
   if (e) hlist[base + rank_below(mm)] = i;
 }
 
-template <int G, int HW, bool UNIT, bool RB>
+// candidates
+template <int G, int HW, bool UNIT>
 __global__ __launch_bounds__(kHubBlock) void k_hub(HubArgs a) {
-  JET_GATE(a.lc, RB ? kPhRb : kPhJet);
-  hub_work<G, HW, UNIT, RB>(a, (int32_t)blockIdx.x, (int32_t)gridDim.x);
+  JET_GATE(a.lc, kPhJet);
+  hub_work<G, HW, UNIT, false>(a, (int32_t)blockIdx.x, (int32_t)gridDim.x);
+}
+
+// rebalancing gains
+template <int G, int HW, bool UNIT>
+__global__ __launch_bounds__(kHubBlock) void k_rb_hub(HubArgs a) {
+  JET_GATE(a.lc, kPhRb);
+  hub_work<G, HW, UNIT, true>(a, (int32_t)blockIdx.x, (int32_t)gridDim.x);
+}
+
+template <bool RB, int G, int HW, bool UNIT>
+void hub_launch_form(Ctx &c, int64_t blocks, const HubArgs &a) {
+  if constexpr (RB) launch_resident<k_rb_hub<G, HW, UNIT>>(c, blocks, kHubBlock, a);
+  else launch_resident<k_hub<G, HW, UNIT>>(c, blocks, kHubBlock, a);
 }
 
 template <bool RB>
 hipError_t hub_launch(Ctx &c, const HubArgs &a) {
   // rows: one per workgroup while workgroups share hubs
   const int64_t blocks = std::min<int64_t>(kHubGrid, (int64_t)c.nhubs * kHubShares);
-#define JET_HUB(G, HW, UNIT) launch_resident<k_hub<G, HW, UNIT, RB>>(c, blocks, kHubBlock, a)
+#define JET_HUB(G, HW, UNIT) hub_launch_form<RB, G, HW, UNIT>(c, blocks, a)
   if (c.unit_nw) {
     if (c.k <= 32) JET_HUB(1, 1, true);
     else if (c.k <= 64) JET_HUB(1, 2, true);
