@@ -317,8 +317,10 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
 /* Rebalancing rounds (Section 4.3) launched at a time, 1..64; default 1, in a batch 3.  Results do not
  * depend on it. */
 #define JET_OPT_RB_SLOTS 7
-/* Pieces of the loop in flight at once, 1..1024, default 2: one runs, one more (at most) waits
- * behind it when the host can foresee which it will be.  Results do not depend on it. */
+/* Pieces of the loop in flight at once, 1..1024 (256 at most), default 2: one runs, the others wait
+ * behind it as far as the host can foresee which they will be.  More than two help where the host is
+ * slow to follow; a piece that was foreseen wrongly costs its empty launches.  Results do not depend on
+ * it. */
 #define JET_OPT_REPLAYS 8
 /* Workgroups of the persistent (grid-stride) kernels: candidates, afterburner chunks, move
  * selection, rebalancing gains; 64..65536, default 2048.  Results do not depend on it. */

@@ -540,41 +540,6 @@ int launch_piece(Ctx &c, int kind) {
   return JET_OK;
 }
 
-// Which piece the host launches ahead of the device: the phase that follows the current one.  The
-// number of rebalancing rounds of an iteration is guessed from the number of the iteration before it
-// (what followed that number last time); the guess is acted on while the last one of its kind was right.
-struct Ahead {
-  static constexpr int kKinds = 17;  // rounds of the iteration before: 0..15, more
-  int32_t guess[kKinds] = {};
-  bool sure[kKinds];
-  int32_t prev = 0;  // rounds of the last finished iteration
-  bool rb_only;      // rebalancing alone: another round is the likely thing
-  explicit Ahead(bool rb) : rb_only(rb) { std::fill(sure, sure + kKinds, true); }
-  static int slot(int32_t rounds) { return std::min<int32_t>(rounds, kKinds - 1); }
-  // an iteration with this many rounds has ended
-  void learn(int32_t rounds) {
-    const int s = slot(prev);
-    sure[s] = guess[s] == rounds;
-    guess[s] = rounds;
-    prev = rounds;
-  }
-  // the phase after the one running (its rounds done so far, the round's last chance), -1: wait and see
-  int32_t next(const jet::LoopMail &m) const {
-    if (rb_only) return jet::kPhRb;
-    const int s = slot(prev);
-    if (m.phase == jet::kPhJet) {
-      if (!sure[s]) return -1;
-      if (guess[s] > 0) return jet::kPhRb;
-      return m.last ? -1 : jet::kPhJet;
-    }
-    if (m.phase == jet::kPhRb) {
-      if (m.rb_rounds + 1 < guess[s]) return jet::kPhRb;
-      if (m.rb_rounds + 1 == guess[s] && sure[s] && !m.last) return jet::kPhJet;
-    }
-    return -1;
-  }
-};
-
 int piece_of(int32_t phase) {
   return phase == jet::kPhJet ? jet::kTickJet : phase == jet::kPhRb ? jet::kTickRb : jet::kTickRoll;
 }
@@ -605,8 +570,8 @@ int wait_mail(Ctx &c, uint32_t seen, jet::LoopMail *m) {
 
 // The Jet loop (Algorithm 1) for every temperature, or (rb_only) the rebalancing rounds alone, on
 // the device.  The host launches pieces -- a Jet phase, a rebalancing round, a rollback -- and follows
-// the word each one's control kernel stores in pinned memory.  One piece runs, one more waits behind
-// it when Ahead can name it; what is launched only decides how much work is in flight, never what is
+// the word each one's control kernel stores in pinned memory.  One piece runs, one more (JET_OPT_REPLAYS:
+// several) waits behind it when Ahead can name it; what is launched only decides how much work is in flight, never what is
 // computed: a piece whose phase the record is not in does nothing, but its five to nine launches take
 // 15 to 40 us.  Iterations replayed in batches of eight with four rounds each, and a copy and a
 // synchronisation between batches, left two thirds of the launched rounds empty: 263 of 292 on a 4M
@@ -639,41 +604,26 @@ int run_loop(Ctx &c, int32_t *part, const jet_params *prm, bool rb_only, jet_sta
     rc = ensure_graphs(c);
     if (rc != JET_OK) return rc;
   }
-  const double piece_cap = 2.0 * (rb_only ? 1 : prm->num_tau) * ((double)prm->max_iters + 2.0) *
-                               ((double)prm->max_rebalance_rounds + 3.0) + 16.0;
+  const double piece_cap = (double)std::max(2, c.replays) * (rb_only ? 1 : prm->num_tau) *
+                               ((double)prm->max_iters + 2.0) * ((double)prm->max_rebalance_rounds + 3.0) + 16.0;
   int64_t pieces = 0;
   c.polls = 0;
-  const int32_t lead = std::min<int32_t>(c.replays, 2);
-  Ahead guess(rb_only);
-  // phases of the launched control kernels that have not reported: at most three pieces of up to 64
-  int32_t flight[256], nflight = 0;
-  jet::LoopMail m{};           // the last report looked at; before the first one, what it is likely to say
-  m.phase = rb_only ? jet::kPhRb : jet::kPhJet;
-  uint32_t seen = 0;
-  flight[nflight++] = jet::kPhAny;  // the set-up's control kernel reports too
-  while (m.phase != jet::kPhDone && !m.err) {
-    // the piece of the current phase, then the one behind it
-    const bool has = std::find(flight, flight + nflight, m.phase) != flight + nflight;
-    const int32_t add = !has ? m.phase : nflight < lead && flight[nflight - 1] == m.phase ? guess.next(m) : -1;
-    if (add >= 0 && nflight + reports_of(c, add) <= 256) {
+  jet::Ahead ahead(rb_only, c.replays);
+  while (!ahead.done()) {
+    const int32_t add = ahead.want();  // the piece of the current phase, then those behind it
+    if (add >= 0 && ahead.room(reports_of(c, add))) {
       rc = launch_piece(c, piece_of(add));
       if (rc != JET_OK) return rc;
-      for (int32_t i = 0; i < reports_of(c, add); ++i) flight[nflight++] = add;
+      ahead.launched(add, reports_of(c, add));
       pieces += 1;
       continue;
     }
     if ((double)pieces > piece_cap) return fail(&c, JET_EHIP, "the device loop did not finish within its bound");
-    const jet::LoopMail was = m;
-    rc = wait_mail(c, seen, &m);
+    jet::LoopMail m;
+    rc = wait_mail(c, ahead.seen, &m);
     if (rc != JET_OK) return rc;
     c.polls += 1;
-    bool ran = false;  // a piece of the phase we knew of has run
-    const int32_t got = std::min<int32_t>((int32_t)((m.seq - seen) & jet::kMailSeqMask), nflight);
-    for (int32_t i = 0; i < got; ++i) ran = ran || flight[i] == was.phase;
-    std::copy(flight + got, flight + nflight, flight);
-    nflight -= got;
-    seen = m.seq;
-    if (ran && !rb_only && was.phase != jet::kPhRoll && m.phase != jet::kPhRb) guess.learn(m.rb_rounds);
+    ahead.report(m);
   }
   HIP_OR_FAIL(&c, hipMemcpyAsync(c.hlc, c.lc, sizeof(jet::LoopCtl), hipMemcpyDeviceToHost, c.stream));
   rc = read_status(c);

@@ -9,6 +9,7 @@
 #include <vector>
 
 #include "../../include/jet.h"
+#include "ahead.h"
 
 namespace jet {
 
@@ -65,19 +66,6 @@ struct DevStatus {
   int32_t rb_seg[kMaxSeg];   // union: the overloaded segments of the round
 };
 
-// Device-resident Jet loop (Algorithm 1).  One record per context holds the state the loop's
-// decisions need; small control kernels advance it between the phases of an iteration, and every
-// kernel of a phase returns at once unless the record is in that phase, so one captured iteration
-// can be replayed without the host looking at the device in between.
-enum LoopPhase : int32_t {
-  kPhJet = 0,    // candidates, afterburner, selection and application of the kept moves
-  kPhRb = 1,     // rebalancing rounds (Section 4.3)
-  kPhEnd = 2,    // quality key, snapshot, iteration limit
-  kPhRoll = 3,   // rollback to the best partition of the temperature round
-  kPhDone = 4,
-  kPhAny = -1,   // a launch outside the loop (inspection calls): never gated
-};
-
 struct LoopCtl {
   int32_t phase;
   int32_t phase_mask;     // bit p set iff a hypergraph of the record is in phase p (1 << phase for one)
@@ -106,25 +94,6 @@ struct LoopCtl {
   int32_t trace_cap;
   int64_t lmax, dz, A;    // balance limit, deadzone threshold, ceil(W/k) of the hypergraph
 };
-
-// What the host follows of a running loop: one word per control kernel, stored by it in pinned memory.
-struct LoopMail {
-  uint32_t seq;       // low kMailSeqBits bits of LoopCtl::seq
-  int32_t mask;       // phases the record (a union: any of its hypergraphs) is in
-  int32_t phase;      // the lowest of them
-  int32_t rb_rounds;  // of the current iteration, once the next Jet phase runs of the last one (clipped)
-  bool last;          // the round ends with the current iteration unless that improves
-  bool err;           // a kernel reported an error
-};
-constexpr int kMailSeqBits = 24, kMailMaskSh = 24, kMailMaskBits = 5;
-constexpr int kMailRbSh = 29, kMailRbBits = 16, kMailLastSh = 45, kMailErrSh = 46;
-constexpr uint32_t kMailSeqMask = (1u << kMailSeqBits) - 1u;
-inline LoopMail read_mail(unsigned long long w) {
-  const int32_t mask = (int32_t)((w >> kMailMaskSh) & ((1u << kMailMaskBits) - 1u));
-  return LoopMail{(uint32_t)w & kMailSeqMask, mask, mask ? __builtin_ctz((unsigned)mask) : 0,
-                  (int32_t)((w >> kMailRbSh) & ((1u << kMailRbBits) - 1u)), ((w >> kMailLastSh) & 1u) != 0,
-                  ((w >> kMailErrSh) & 1u) != 0};
-}
 
 // A launch of a phase returns at once unless some hypergraph of the gate record is in it.
 #define JET_GATE(lc, want)                                                      \
@@ -452,7 +421,7 @@ struct Ctx {
   hipGraphExec_t gexec[kTickPieces] = {};
   bool use_graph = true;         // JET_OPT_GRAPH
   int32_t rb_slots = 1;          // JET_OPT_RB_SLOTS: rounds of one rebalancing piece (a union: kUnionRounds)
-  int32_t replays = 2;           // JET_OPT_REPLAYS: most pieces in flight
+  int32_t replays = 2;           // JET_OPT_REPLAYS: control kernels in flight while another piece is launched ahead
   int64_t polls = 0;             // host polls of the last call (diagnostic)
   int64_t replays_done = 0;      // graph replays or eager ticks of the last call
   DevProf *dprof = nullptr;      // device timing accumulators
