@@ -497,7 +497,7 @@ def run_batch(args):
     def step():
         parts = [p.clone() for p in starts]
         torch.cuda.synchronize()
-        rc, stats, rcs = batch.refine(parts, replays=knobs["replays"], **kw)
+        rc, stats, rcs = batch.refine(parts, **kw)
         return parts, stats
 
     # warm-up with every family marked (breakdown; the unions then share a stream), the timed steps without

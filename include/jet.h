@@ -370,7 +370,7 @@ typedef struct jet_batch jet_batch;
  * kept per (hypergraph, block), one loop record per hypergraph.  Synchronises stream.  On failure
  * no batch is returned and jet_last_error(NULL) has the message (naming the hypergraph). */
 int jet_batch_init(jet_batch **out, int32_t count, const jet_hg_desc *descs, void *stream);
-/* Applies jet_set_option to every union context of the batch (JET_OPT_GRAPH: the batch graph). */
+/* Applies jet_set_option to every union context of the batch (JET_OPT_GRAPH: of all of them). */
 int jet_batch_set_option(jet_batch *b, int32_t option, int64_t value);
 /* Refines every hypergraph i in place in parts[i] ([host] array of device pointers) exactly as
  * jet_refine would (Algorithm 1 per hypergraph, its own balance limit, key, limit and rollback):
@@ -378,8 +378,8 @@ int jet_batch_set_option(jet_batch *b, int32_t option, int64_t value);
  * launch covers all hypergraphs of a union context, each hypergraph's vertices and nets taking part
  * only while its own loop is in the launch's phase; the phases some hypergraph is in are launched
  * (as captured HIP graphs) until every hypergraph's loop is done, the unions beside each other.
- * `replays` (1..1024) bounds the steps of a union in flight; one is enough and more are not
- * launched.  The caller's order holds on the stream given to jet_batch_init.
+ * `replays` (1..1024) is checked and has no effect: a union launches one step at a time (more in flight
+ * launch mostly empty phases).  The caller's order holds on the stream given to jet_batch_init.
  * stats and rcs ([host][count], may be NULL) receive each hypergraph's statistics and return code.
  * Returns a negative code on failure, else JET_IMBALANCED if any hypergraph is, else JET_OK. */
 int jet_batch_refine(jet_batch *b, int32_t *const *parts, const jet_params *params, int32_t replays,

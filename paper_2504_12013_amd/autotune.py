@@ -2,12 +2,13 @@
 caches the choice as JSON keyed by (GPU architecture, shape bucket).
 
 Knobs (none of them changes any result, only the time):
-  replays        bound of a union's steps in flight (one is launched at a time, so more change nothing);
   grid           workgroups of the persistent kernels (tiles per workgroup = work / grid);
   lane_degree    lanes per vertex of the bit-sliced candidate kernel: one lane below this mean degree,
                  eight above (0: always eight; 24 is the library's rule);
   apply_divisor  switch point of move application from per-move atomics to per-net recounting;
   rb_slots       rebalancing rounds launched at a time.
+
+(The `replays` argument of a batch refinement is not among them: a union launches one step at a time.)
 
 The sweep is coordinate descent from the library defaults: each knob in turn is timed at every
 value with the others fixed at their best so far (one refinement of copies of the batch's starting
@@ -27,13 +28,13 @@ from .jet import JET_OPT_APPLY_DIVISOR, JET_OPT_CAND_LANE_DEGREE, JET_OPT_GRID, 
 
 DEFAULT_CACHE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "autotune.json")
 KNOBS = {
-    "replays": (2, 8, 32),
     "grid": (1024, 2048, 4096),
     "lane_degree": (0, 24),
     "apply_divisor": (4, 16, 32, 64),
     "rb_slots": (1, 2, 3, 4),
 }
-DEFAULTS = {"replays": 8, "grid": 2048, "lane_degree": 24, "apply_divisor": 32, "rb_slots": 3}
+DEFAULTS = {"grid": 2048, "lane_degree": 24, "apply_divisor": 32, "rb_slots": 3}
+REPLAYS = 8  # settings still carry the argument, for callers that pass it on
 _OPTION = {"grid": JET_OPT_GRID, "lane_degree": JET_OPT_CAND_LANE_DEGREE, "apply_divisor": JET_OPT_APPLY_DIVISOR,
            "rb_slots": JET_OPT_RB_SLOTS}
 
@@ -56,18 +57,18 @@ def _load(path):
 
 
 def apply(batch, settings):
-    """Sets the batch's launch options (everything but replays, which is a refine argument)."""
+    """Sets the batch's launch options."""
     for name, opt in _OPTION.items():
         batch.set_option(opt, int(settings[name]))
 
 
 def _time(batch, parts, settings, kw):
     apply(batch, settings)
-    batch.refine([p.clone() for p in parts], replays=settings["replays"], **kw)  # graph capture, untimed
+    batch.refine([p.clone() for p in parts], **kw)  # graph capture, untimed
     work = [p.clone() for p in parts]
     torch.cuda.synchronize()
     t0 = time.perf_counter()
-    batch.refine(work, replays=settings["replays"], **kw)
+    batch.refine(work, **kw)
     torch.cuda.synchronize()
     return time.perf_counter() - t0
 
@@ -97,7 +98,7 @@ def sweep(batch, parts, knobs=None, passes=2, log=None, **kw):
 
 def tuned(batch, hgs, parts, cache_path: str = DEFAULT_CACHE, retune: bool = False, log=None, **kw):
     """Settings for this batch from the cache, sweeping (and storing) them when absent; the batch's
-    options are set to them."""
+    options are set to them.  Entries of the cache may hold more than the knobs, which is ignored."""
     key = shape_key(hgs)
     cache = _load(cache_path)
     if key in cache and not retune and all(k in cache[key] for k in DEFAULTS):
@@ -110,4 +111,4 @@ def tuned(batch, hgs, parts, cache_path: str = DEFAULT_CACHE, retune: bool = Fal
             json.dump(cache, f, indent=1, sort_keys=True)
         os.replace(tmp, cache_path)
     apply(batch, settings)
-    return key, settings
+    return key, dict(settings, replays=REPLAYS)

@@ -457,8 +457,8 @@ class JetBatch:
             raise JetError(rc, lib().jet_batch_last_error(self.h).decode())
 
     def refine(self, parts, replays: int = 8, **kw):
-        """parts: list of device int32 tensors (refined in place); replays: bound
-        of the steps of a union in flight.  Returns (rc, [stats], [rc_i])."""
+        """parts: list of device int32 tensors (refined in place); replays: 1..1024, without effect (a union
+        launches one step at a time).  Returns (rc, [stats], [rc_i])."""
         if len(parts) != self.count:
             raise ValueError("one partition per hypergraph")
         arr = (ctypes.c_void_p * self.count)(*[_ptr(p) for p in parts])
