@@ -16,6 +16,7 @@
 
 #include "jet_internal.h"
 #include "phi.h"
+#include "spin.h"
 
 using jet::Ctx;
 using jet::DevStatus;
@@ -564,7 +565,7 @@ int wait_mail(Ctx &c, uint32_t seen, jet::LoopMail *m) {
       *m = jet::read_mail(__atomic_load_n(c.mail, __ATOMIC_ACQUIRE));
       return m->seq != (seen & jet::kMailSeqMask) ? JET_OK : fail(&c, JET_EHIP, "the device loop did not report");
     }
-    __builtin_ia32_pause();
+    jet::cpu_relax();
   }
 }
 
@@ -1653,7 +1654,7 @@ static int batch_loops(jet_batch *b, const jet_params *params) {
     }
     if (news) spin = 0;
     else if (spin % 4096 == 0) std::this_thread::yield();
-    else __builtin_ia32_pause();
+    else jet::cpu_relax();
   }
   return JET_OK;
 }
