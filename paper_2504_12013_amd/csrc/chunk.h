@@ -8,31 +8,6 @@
 
 namespace jet {
 
-struct ChunkLane {
-  int32_t net;      // net ID of this lane's pin (valid only if active)
-  int64_t q;        // pin index
-  bool active;      // lane holds a pin
-  uint64_t starts;  // lanes that hold the first pin of a net (wave-uniform)
-};
-
-// Must be called by all 64 lanes of the wave (wave-level only); has_chunk must be wave-uniform.
-__device__ __forceinline__ ChunkLane chunk_lane(int4 cd, const uint8_t *__restrict__ pnet, bool has_chunk) {
-  const int l = lane_id();
-  ChunkLane r;
-  r.active = has_chunk && l < cd.z;
-  r.net = 0;
-  r.q = 0;
-  int32_t j = -1;
-  if (r.active) {
-    r.q = (int64_t)cd.w + l;
-    j = pnet[r.q];
-    r.net = cd.x + j;
-  }
-  const int32_t jprev = __shfl_up(j, 1, kWave);
-  r.starts = ballot(r.active && (l == 0 || jprev != j));
-  return r;
-}
-
 // Orders this wave's LDS accesses before the following ones (for LDS private to the wave).
 __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "workgroup");

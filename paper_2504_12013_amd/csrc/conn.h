@@ -1,4 +1,5 @@
-// Per-vertex block connectivity, shared by the candidate and rebalancing kernels.
+// Per-vertex block connectivity, shared by the candidate and rebalancing kernels: with net weights first,
+// with unit weights (bit-sliced) below.
 //
 // G lanes cooperate on one vertex v; lane j of the group owns blocks 8j .. 8j+7 and accumulates
 //     conn[b] = sum of w(e) over incident nets e that have a pin in block b
@@ -19,7 +20,7 @@ namespace jet {
 // the mask word holding its byte).  Batches start at q0, q0 + stride, ... below q1.  The
 // arguments are equal for the G lanes of a group, so the shuffles only ever read lanes of the
 // same group that run the same iteration.
-template <int G, bool UNIT>
+template <int G>
 __device__ __forceinline__ void conn_accumulate(const int32_t *__restrict__ inc, int64_t q0, int64_t q1,
                                                 int64_t stride, const int32_t *__restrict__ nw,
                                                 const uint64_t *__restrict__ ns, int lg, int32_t s,
@@ -49,7 +50,7 @@ __device__ __forceinline__ void conn_accumulate(const int32_t *__restrict__ inc,
         hi[u][x] = 0u;
       }
       if (e[u] >= 0) {
-        w[u] = UNIT ? 1 : nw[e[u]];
+        w[u] = nw[e[u]];
         const uint64_t *nse = ns + (int64_t)e[u] * (2 * NW);
         uint64_t one;
         if (NW == 1) {  // mask and "one pin" word in one access
@@ -93,7 +94,6 @@ __device__ __forceinline__ void conn_accumulate(const int32_t *__restrict__ inc,
 }
 
 // Sequential form for one lane per vertex (G = 1): four incident nets per step.
-template <bool UNIT>
 __device__ __forceinline__ void conn_accumulate_lane(const int32_t *__restrict__ inc, int64_t q0, int64_t q1,
                                                      const int32_t *__restrict__ nw,
                                                      const uint64_t *__restrict__ ns, int32_t s, int32_t conn[8],
@@ -112,7 +112,7 @@ __device__ __forceinline__ void conn_accumulate_lane(const int32_t *__restrict__
     const uint64_t *n2 = ns + (int64_t)e2 * 2, *n3 = ns + (int64_t)e3 * 2;
     const uint64_t m0 = n0[0], m1 = n1[0], m2 = n2[0], m3 = n3[0];
     const uint64_t o0 = n0[1], o1 = n1[1], o2 = n2[1], o3 = n3[1];
-    const int32_t w0 = UNIT ? 1 : nw[e0], w1 = UNIT ? 1 : nw[e1], w2 = UNIT ? 1 : nw[e2], w3 = UNIT ? 1 : nw[e3];
+    const int32_t w0 = nw[e0], w1 = nw[e1], w2 = nw[e2], w3 = nw[e3];
     add(m0, o0, w0);
     add(m1, o1, w1);
     add(m2, o2, w2);
@@ -120,13 +120,13 @@ __device__ __forceinline__ void conn_accumulate_lane(const int32_t *__restrict__
   }
   for (; q < q1; ++q) {
     const int32_t e = inc[q];
-    add(ns[(int64_t)e * 2], ns[(int64_t)e * 2 + 1], UNIT ? 1 : nw[e]);
+    add(ns[(int64_t)e * 2], ns[(int64_t)e * 2 + 1], nw[e]);
   }
 }
 
 // Strided form: each lane of the group walks q0, q0 + step, ... itself (all lanes of the group load
 // the same incident net); four nets per step.  Used by the workgroup-per-vertex kernels with G = 1.
-template <int G, bool UNIT>
+template <int G>
 __device__ __forceinline__ void conn_accumulate_strided(const int32_t *__restrict__ inc, int64_t q0, int64_t q1,
                                                         int64_t step, const int32_t *__restrict__ nw,
                                                         const uint64_t *__restrict__ ns, int lg, int32_t s,
@@ -149,7 +149,7 @@ __device__ __forceinline__ void conn_accumulate_strided(const int32_t *__restric
     const uint64_t *n2 = ns + (int64_t)e2 * (2 * NW), *n3 = ns + (int64_t)e3 * (2 * NW);
     const uint64_t m0 = n0[word], m1 = n1[word], m2 = n2[word], m3 = n3[word];
     const uint64_t o0 = n0[NW + sw], o1 = n1[NW + sw], o2 = n2[NW + sw], o3 = n3[NW + sw];
-    const int32_t w0 = UNIT ? 1 : nw[e0], w1 = UNIT ? 1 : nw[e1], w2 = UNIT ? 1 : nw[e2], w3 = UNIT ? 1 : nw[e3];
+    const int32_t w0 = nw[e0], w1 = nw[e1], w2 = nw[e2], w3 = nw[e3];
     add(m0, o0, w0);
     add(m1, o1, w1);
     add(m2, o2, w2);
@@ -158,17 +158,17 @@ __device__ __forceinline__ void conn_accumulate_strided(const int32_t *__restric
   for (; q < q1; q += step) {
     const int32_t e = inc[q];
     const uint64_t *nse = ns + (int64_t)e * (2 * NW);
-    add(nse[word], nse[NW + sw], UNIT ? 1 : nw[e]);
+    add(nse[word], nse[NW + sw], nw[e]);
   }
 }
 
 // Dispatch: conn[] and benefit of v over the incidences [q0, q1) walked in batches (see above).
-template <int G, bool UNIT>
+template <int G>
 __device__ __forceinline__ void vertex_conn(const int32_t *__restrict__ inc, int64_t q0, int64_t q1, int64_t stride,
                                             const int32_t *__restrict__ nw, const uint64_t *__restrict__ ns, int lg,
                                             int32_t s, int32_t conn[8], int32_t &benefit) {
-  if (G == 1) conn_accumulate_lane<UNIT>(inc, q0, q1, nw, ns, s, conn, benefit);
-  else conn_accumulate<G, UNIT>(inc, q0, q1, stride, nw, ns, lg, s, conn, benefit);
+  if (G == 1) conn_accumulate_lane(inc, q0, q1, nw, ns, s, conn, benefit);
+  else conn_accumulate<G>(inc, q0, q1, stride, nw, ns, lg, s, conn, benefit);
 }
 
 // ---- bit-sliced counts (unit net weights) ----

@@ -92,9 +92,9 @@ __device__ __forceinline__ void hub_sums(const HubArgs &a, int64_t q0, int64_t q
 #pragma unroll
     for (int b = 0; b < 8; ++b) conn[b] = 0;
     if (G == 1)
-      conn_accumulate_strided<G, false>(a.inc, q0 + tid, q1, threads, a.nw, a.ns, lg, s, conn, ben);
+      conn_accumulate_strided<G>(a.inc, q0 + tid, q1, threads, a.nw, a.ns, lg, s, conn, ben);
     else
-      conn_accumulate<G, false>(a.inc, q0 + (int64_t)gi * G, q1, threads, a.nw, a.ns, lg, s, conn, ben);
+      conn_accumulate<G>(a.inc, q0 + (int64_t)gi * G, q1, threads, a.nw, a.ns, lg, s, conn, ben);
 #pragma unroll
     for (int o = G; o < kWave; o <<= 1) {  // sums over the wave's groups, in every lane
 #pragma unroll

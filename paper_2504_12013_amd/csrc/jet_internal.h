@@ -532,7 +532,7 @@ enum : int32_t { kResetCandidates = 1, kResetMoves = 2 };
 hipError_t launch_reset_counters(Ctx &c, int32_t what);
 hipError_t launch_afterburner_overflow(Ctx &c, RgSink sink, const LoopCtl *lc);  // k_ab_large.hip
 bool ab_branches(const Ctx &c);
-hipError_t launch_select_moves(Ctx &c, int32_t *part, int32_t stamp, const LoopCtl *lc = nullptr);
+hipError_t launch_select_moves(Ctx &c, int32_t *part, const LoopCtl *lc);
 // wide: size the net-centric grids for that path (a performance hint; the device decides the path)
 hipError_t launch_apply_moves(Ctx &c, int32_t *part, bool wide, const LoopCtl *lc = nullptr, int32_t want = kPhAny);
 hipError_t launch_diff_moves(Ctx &c, int32_t *part, const int32_t *target, const LoopCtl *lc);

@@ -320,26 +320,6 @@ __global__ void k_fl_init_nodes(int64_t N, uint8_t *__restrict__ term, int32_t *
 
 // ---- maximum flow ----
 
-// the arcs out of node u: f(arc)
-template <typename F>
-__device__ __forceinline__ void for_out(int64_t u, int32_t nv, const int64_t *voffn, const int64_t *vadj,
-                                        const int64_t *rbase, const int32_t *rends, F f) {
-  if (u < nv) {
-    for (int64_t i = voffn[u]; i < voffn[u + 1]; ++i) {
-      const int64_t a0 = vadj[i];
-      f(a0);      // x -> e_in
-      f(a0 + 3);  // x -> e_out (reverse of e_out -> x)
-    }
-  } else {
-    const int64_t r = (u - nv) >> 1;
-    const bool out = ((u - nv) & 1) != 0;
-    const int64_t B = rbase[r];
-    const int32_t E = rends[r];
-    f(out ? B + 1 : B);
-    for (int32_t j = 0; j < E; ++j) f(B + 2 + 4 * (int64_t)j + (out ? 2 : 1));
-  }
-}
-
 // every residual arc from a source to a non-source node is saturated
 __global__ void k_fl_saturate(int64_t A, const int32_t *__restrict__ tail, const int32_t *__restrict__ head,
                               const uint8_t *__restrict__ term, int64_t *__restrict__ res, int64_t *__restrict__ ex) {
@@ -381,24 +361,6 @@ __global__ void k_fl_reach_init(int64_t N, const uint8_t *__restrict__ term, int
 // (terminal nodes can have a great many arcs); later levels take a wave per frontier node.  The
 // frontier sizes live on the device in three rotating counters: a level reads one, appends to the
 // next and clears the one after, so levels are launched back to back without the host looking.
-
-// arcs out of node u by index: vertex-type nodes (u < nv) have two per adjacency entry (x -> e_in,
-// x -> e_out), net nodes one to their partner node and one per endpoint
-__device__ __forceinline__ int64_t out_degree(int64_t u, int32_t nv, const int64_t *voffn, const int32_t *rends) {
-  return u < nv ? 2 * (voffn[u + 1] - voffn[u]) : 1 + (int64_t)rends[(u - nv) >> 1];
-}
-
-__device__ __forceinline__ int64_t out_arc(int64_t u, int64_t i, int32_t nv, const int64_t *voffn,
-                                           const int64_t *vadj, const int64_t *rbase) {
-  if (u < nv) {
-    const int64_t a0 = vadj[voffn[u] + (i >> 1)];
-    return (i & 1) ? a0 + 3 : a0;
-  }
-  const bool out = ((u - nv) & 1) != 0;
-  const int64_t B = rbase[(u - nv) >> 1];
-  if (i == 0) return out ? B + 1 : B;
-  return B + 2 + 4 * (i - 1) + (out ? 2 : 1);
-}
 
 // claims node v for the search; true for the one thread that claims it
 template <bool REACH>
@@ -443,10 +405,9 @@ __global__ __launch_bounds__(kFB) void k_fl_level(
   const int l = lane_id();
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / kWave; i < count;
        i += (int64_t)gridDim.x * blockDim.x / kWave) {
-    const int64_t u = front_in[i];
-    const int64_t deg = out_degree(u, nv, voffn, rends);
-    for (int64_t j = l; j < deg; j += kWave) {
-      const int64_t a = out_arc(u, j, nv, voffn, vadj, rbase);
+    const OutArcs o = out_arcs(front_in[i], nv, voffn, rbase, rends);
+    for (int32_t j = l; j < o.count; j += kWave) {
+      const int64_t a = out_arc(o, vadj, j);
       if ((BACK ? res[a ^ 1] : res[a]) <= 0) continue;
       const int32_t v = head[a];
       if (claim<REACH>(v, term, flag, h, L)) front_out[atomicAdd(cnt_out, 1)] = v;
@@ -482,10 +443,9 @@ __global__ __launch_bounds__(kDeepBlock) void k_fl_deep(
     const int out = (cur + 1) % 3;
     int32_t *front = out == 0 ? f0 : out == 1 ? f1 : f2;
     for (int32_t i = g; i < count; i += kDeepBlock / kDeepLanes) {
-      const int64_t u = ahead[i];
-      const int64_t deg = out_degree(u, nv, voffn, rends);
-      for (int64_t j = lg; j < deg; j += kDeepLanes) {
-        const int64_t a = out_arc(u, j, nv, voffn, vadj, rbase);
+      const OutArcs o = out_arcs(ahead[i], nv, voffn, rbase, rends);
+      for (int32_t j = lg; j < o.count; j += kDeepLanes) {
+        const int64_t a = out_arc(o, vadj, j);
         if ((BACK ? res[a ^ 1] : res[a]) <= 0) continue;
         const int32_t v = head[a];
         if (claim<REACH>(v, term, flag, h, L)) front[atomicAdd(&next[par], 1)] = v;

@@ -89,7 +89,7 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_candidates(
 #pragma unroll
     for (int j = 0; j < 8; ++j) conn[j] = 0;
     int32_t benefit = 0;
-    if (!skip) vertex_conn<G, false>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
+    if (!skip) vertex_conn<G>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
     int32_t bestc = 0, bestb = INT32_MAX;
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
@@ -310,19 +310,17 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
                                          const uint64_t *__restrict__ rec, RgSink rg, int32_t slot,
                                          uint32_t (*cnt)[KW], uint32_t (*gone)[KW], uint32_t *ncand) {
   const int l = lane_id();
-  ChunkLane cl;
-  cl.active = l < cd.z;
-  cl.q = (int64_t)cd.w + l;
-  cl.net = cd.x + pj;
+  const bool active = l < cd.z;       // the lane holds a pin
+  const int32_t net = cd.x + pj;      // of this net
   const int32_t jprev = __shfl_up(pj, 1, kWave);
-  cl.starts = ballot(cl.active && (l == 0 || jprev != pj));
+  const uint64_t starts = ballot(active && (l == 0 || jprev != pj));  // lanes that hold the first pin of a net
   const int32_t v = pin;
-  const bool cand = cl.active && inm_bit(inm, v);
+  const bool cand = active && inm_bit(inm, v);
   const uint64_t cm = ballot(cand);
   if (cm == 0) return;
   uint32_t khi = 0xffffffffu, klo = 0xffffffffu;
   int32_t s = 0, t = 0, pv = 0;
-  if (cl.active) pv = part[v];
+  if (active) pv = part[v];
   if (cand) {
     const uint64_t r = rec[v];
     khi = order_hi(rec_gain(r));
@@ -330,7 +328,7 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
     s = rec_source(r);
     t = rec_target(r);
   }
-  if (cl.active) atomicAdd(&cnt[pj][pv >> 2], 1u << (8 * (pv & 3)));
+  if (active) atomicAdd(&cnt[pj][pv >> 2], 1u << (8 * (pv & 3)));
   if (cand) {
     atomicAdd(&ncand[pj], 1u);
     if (gone) atomicAdd(&gone[pj][s >> 2], 1u << (8 * (s & 3)));
@@ -346,7 +344,7 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
              pht == (int32_t)((gone[pj][t >> 2] >> (8 * (t & 3))) & 0xffu);
     if (!need) khi = klo = 0xffffffffu;
   }
-  const bool multi = cl.active && ncand[pj] >= 2u;  // this lane's net has two or more candidates
+  const bool multi = active && ncand[pj] >= 2u;  // this lane's net has two or more candidates
   const uint64_t cm2 = ballot(need && multi);
   int32_t Ds = 0, As = 0, Dt = 0, At = 0;
   if (cm2) {
@@ -355,13 +353,12 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
     // Two ways to visit the pairs, chosen per wave: broadcast each of those candidates in turn (one
     // step per candidate), or rotate the lanes of every such net past each other (one step per pin
     // of the longest of them).
-    const uint64_t starts = cl.starts;
     const uint64_t upto = (l == 63) ? ~0ull : ((2ull << l) - 1ull);
     const int seg0 = 63 - __clzll((long long)(starts & upto));  // first lane of this lane's net
     const uint64_t later = starts & ~upto;
-    const int npins = __popcll(ballot(cl.active));  // outside any branch: a ballot sees active lanes only
+    const int npins = __popcll(ballot(active));  // outside any branch: a ballot sees active lanes only
     const int seg_end = later ? __ffsll((unsigned long long)later) - 1 : npins;
-    const int segn = cl.active ? seg_end - seg0 : 0;
+    const int segn = active ? seg_end - seg0 : 0;
     int maxseg = need && multi ? segn : 0;
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) maxseg = max(maxseg, __shfl_xor(maxseg, o, kWave));
@@ -379,10 +376,10 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
       while (rem) {
         const int j = __ffsll((unsigned long long)rem) - 1;
         rem &= rem - 1;
-        const int32_t ej = read_lane_i32(cl.net, j);
+        const int32_t ej = read_lane_i32(net, j);
         const uint32_t hj = read_lane_u32(khi, j), lj = read_lane_u32(klo, j);
         const int32_t pk = read_lane_i32(st_pack, j);
-        if (need && ej == cl.net) count(hj, lj, pk);
+        if (need && ej == net) count(hj, lj, pk);
       }
     } else {
       for (int d = 1; d < maxseg; ++d) {
@@ -397,14 +394,14 @@ __device__ __forceinline__ void ab_chunk(int4 cd, int32_t pin, int32_t pj, const
   }
   if (need) {
     // v's turn: s empties iff exactly v is left in it; t fills iff it is empty before v arrives
-    const int32_t wgt = nw ? nw[cl.net] : 1;
+    const int32_t wgt = nw ? nw[net] : 1;
     const bool dep = phs + As - Ds == 1;
     const bool arr = pht + At - Dt == 0;
     const int32_t delta = (dep ? wgt : 0) - (arr ? wgt : 0);
     if (delta) rg_add(rg, slot, v, delta);
   }
   wave_lds_sync();  // every lane has read its counters
-  if (cl.active) cnt[pj][pv >> 2] = 0u;  // every nonzero counter word has a pin here
+  if (active) cnt[pj][pv >> 2] = 0u;  // every nonzero counter word has a pin here
   if (cand) {
     ncand[pj] = 0u;
     if (gone) gone[pj][s >> 2] = 0u;
@@ -806,14 +803,14 @@ __global__ __launch_bounds__(kSelBlock) void k_select_moves(int32_t *__restrict_
                                                             uint32_t *__restrict__ inm,
                                                             const uint64_t *__restrict__ rec,
                                                             int32_t *__restrict__ rg,
-                                                            const int32_t *__restrict__ vw, int32_t n, int32_t stamp,
+                                                            const int32_t *__restrict__ vw, int32_t n,
                                                             int32_t *__restrict__ lockstamp,
                                                             int4 *__restrict__ moves, uint8_t *__restrict__ mvfrom,
                                                             const int64_t *__restrict__ voff, DevStatus *st,
                                                             int32_t *__restrict__ bigmv, const LoopCtl *lc,
                                                             Union u) {
   JET_GATE(lc, kPhJet);
-  if (lc && !u.lcs) stamp = lc->stamp;
+  const int32_t stamp = lc->stamp;  // (a union's hypergraphs have their own)
   // recomputed gains start from zero in the next iteration: each candidate's entry is cleared here
   auto pred = [&](int64_t v) {
     mvfrom[v] = 0xff;
@@ -827,11 +824,7 @@ __global__ __launch_bounds__(kSelBlock) void k_select_moves(int32_t *__restrict_
     moves[pos] = make_int4((int32_t)v, from, t, vw ? vw[v] : 1);
     mvfrom[v] = (uint8_t)from;
     part[v] = t;
-    if (u.lcs) {  // union: the hypergraph's own stamp (its move count is added per sub-tile)
-      lockstamp[v] = u.lcs[u.vhg[v]].stamp;
-    } else {
-      lockstamp[v] = stamp;
-    }
+    lockstamp[v] = u.lcs ? u.lcs[u.vhg[v]].stamp : stamp;
     return (unsigned long long)(voff[v + 1] - voff[v]);
   };
   // the candidate bits of the walked tiles are cleared once read, so a hypergraph that leaves its
@@ -873,7 +866,7 @@ __global__ __launch_bounds__(kSelBlock) void k_diff_moves(int32_t *__restrict__ 
   JET_GATE(lc, kPhRoll);
   // union: only the hypergraphs whose round ended roll back; a partition that is its round's best
   // without a snapshot yet stays (target holds an older one)
-  const bool stay = !u.lcs && lc && lc->improved != 0;
+  const bool stay = !u.lcs && lc->improved != 0;
   auto pred = [&](int64_t v) {
     mvfrom[v] = 0xff;
     if (stay || part[v] == target[v]) return false;
@@ -1172,7 +1165,6 @@ __device__ __forceinline__ void recount_mid(const int64_t *__restrict__ off, con
   int32_t *D = delta[w];
   const int32_t wid = blockIdx.x * (kApplyBlock / kWave) + w, nwaves = gridDim.x * (kApplyBlock / kWave);
   int64_t dk = 0;  // metric change of this wave's nets (every lane)
-#pragma unroll
   for (int b = l; b < kMaxK; b += kWave) D[b] = 0;
   int32_t e1 = wid < nnets ? nets[wid] : 0;
   int64_t lo = wid < nnets ? off[e1] : 0, hi = wid < nnets ? off[e1 + 1] : 0;
@@ -1712,14 +1704,13 @@ hipError_t launch_afterburner(Ctx &c, const int32_t *part, const LoopCtl *lc) {
   return err;
 }
 
-hipError_t launch_select_moves(Ctx &c, int32_t *part, int32_t stamp, const LoopCtl *lc) {
-  // the move counters were cleared with the candidate counters
-  const int32_t want = lc ? (int32_t)kPhJet : (int32_t)kPhAny;
-  const int tok = prof_begin(c, kProfSelect, lc, want);
+// only in the loop; the move counters were cleared with the candidate counters
+hipError_t launch_select_moves(Ctx &c, int32_t *part, const LoopCtl *lc) {
+  const int tok = prof_begin(c, kProfSelect, lc, kPhJet);
   hipLaunchKernelGGL(k_select_moves, dim3(grid_for(c.n, kSelBlock * kCompactPer, c.grid_cap)), dim3(kSelBlock), 0,
-                     c.stream, part, c.inm, c.rec,
-                     c.rg, c.vw, c.n, stamp, c.lockstamp, c.moves, c.mvfrom, c.voff, c.st, c.bigmv, lc, union_of(c));
-  prof_end(c, tok, lc, want, 8.5 * c.n, 0.0);
+                     c.stream, part, c.inm, c.rec, c.rg, c.vw, c.n, c.lockstamp, c.moves, c.mvfrom, c.voff, c.st,
+                     c.bigmv, lc, union_of(c));
+  prof_end(c, tok, lc, kPhJet, 8.5 * c.n, 0.0);
   return hipGetLastError();
 }
 

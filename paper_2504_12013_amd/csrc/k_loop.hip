@@ -400,7 +400,7 @@ hipError_t launch_tick(Ctx &c, int kind) {
     // Jet phase: candidates, afterburner, kept moves (locks), their application
     e = launch_candidates(c, c.cpart, 0, nullptr, 0, lc);
     if (e == hipSuccess) e = launch_afterburner(c, c.cpart, lc);
-    if (e == hipSuccess) e = launch_select_moves(c, c.cpart, 0, lc);
+    if (e == hipSuccess) e = launch_select_moves(c, c.cpart, lc);
     if (e == hipSuccess) e = launch_apply_moves(c, c.cpart, false, lc, kPhJet);
     if (e == hipSuccess) e = launch_control(c, kPhJet);
     if (e != hipSuccess) return e;

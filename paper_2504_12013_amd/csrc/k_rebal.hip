@@ -393,7 +393,7 @@ __global__ __launch_bounds__(G == 16 ? 512 : 256) void k_rb_gain(
 #pragma unroll
     for (int j = 0; j < 8; ++j) conn[j] = 0;
     int32_t benefit = 0;
-    if (elig) vertex_conn<G, false>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
+    if (elig) vertex_conn<G>(inc, q0, q1, G, nw, ns, lg, s, conn, benefit);
     // best valid target by conn (gain = conn - aff), lowest block on ties; -1 = none
     int32_t bestc = -1, bestb = INT32_MAX;
     if (elig) {
