@@ -479,6 +479,16 @@ inline bool light_lanes(const Ctx &c) {
   return (c.n > kFewVertices || c.lane_degree != kLaneDegreeDefault) && c.p_low < (int64_t)c.lane_degree * c.n_low;
 }
 
+// Workgroups of a move application: those that fit (at most kApplyGrid), more for `groups` groups of chunks,
+// and never fewer than the kWeightBlocks that sum the block weights of a list (a card partition of 32
+// CUs may fit fewer).
+constexpr int kApplyGrid = 2048;
+constexpr unsigned kWeightBlocks = 64;
+inline int64_t apply_grid(int64_t fits, int64_t groups) {
+  const int64_t g = std::min<int64_t>(kApplyGrid, fits);
+  return std::max<int64_t>({g, std::min<int64_t>(groups, 1 << 20), (int64_t)kWeightBlocks});
+}
+
 // the union view of a context for the kernels
 inline Union union_of(const Ctx &c) {
   return c.H > 1 ? Union{c.lcs, c.vhg, c.nhg, c.act, c.ht0, c.hch0}

@@ -1324,7 +1324,6 @@ __device__ __forceinline__ void recount_nets(const int64_t *__restrict__ off, co
 // kApplyLanes-th incident net of a move with few nets, so a move's chain of dependent atomics is
 // that many times shorter.
 constexpr int kApplyLanes = 8;
-constexpr unsigned kWeightBlocks = 64;  // workgroups that sum the block weights of a list
 template <int NW, typename T>
 __global__ __launch_bounds__(kApplyBlock) void k_apply(
     const int4 *__restrict__ moves, const int64_t *__restrict__ voff, const int32_t *__restrict__ inc,
@@ -1550,8 +1549,6 @@ hipError_t cand_dispatch(Ctx &c, const int32_t *part, int32_t locked_stamp, cons
   return cand_launch<16>(c, part, locked_stamp, lock_bytes, tau_q, lc);
 }
 
-constexpr int kApplyGrid = 2048;
-
 }  // namespace
 
 // One launch clears the per-iteration counters (instead of a fill per field) of a launch outside the
@@ -1727,8 +1724,7 @@ void apply_launch(Ctx &c, int32_t *part, bool wide, T *phi, const LoopCtl *lc, i
   // `wide` only sizes the grid: one wave per group of chunks when the host expects the net-centric
   // path (either grid gives the same result)
   const int64_t groups = ((int64_t)c.nchunks + 4 * kApplyU - 1) / (4 * kApplyU);
-  const int64_t fits = std::min<int64_t>(kApplyGrid, resident_grid<k_apply<NW, T>>(kApplyBlock));
-  const unsigned grid = (unsigned)(wide ? std::max<int64_t>(fits, std::min<int64_t>(groups, 1 << 20)) : fits);
+  const unsigned grid = (unsigned)apply_grid(resident_grid<k_apply<NW, T>>(kApplyBlock), wide ? groups : 0);
   hipLaunchKernelGGL((k_apply<NW, T>), dim3(grid), dim3(kApplyBlock), 0, c.stream, c.moves, c.voff, c.inc, c.off,
                      c.pins, c.chunks, c.pnet, c.nchunks, c.mid_nets, c.nmid, c.big_nets, c.nbig, c.nw, c.p, c.k, part,
                      phi, c.ns, c.mvfrom, c.bigmv, c.apply_divisor, c.st, lc, want, union_of(c), c.apply_xcd);
