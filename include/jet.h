@@ -296,7 +296,7 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
 /* 1: launch the per-net application kernels with one wave per chunk / block per net when the
  * previous application of the same kind took that path; 0 (default): small grids always. */
 #define JET_OPT_APPLY_WIDE 2
-/* Bit mask of the kernel families that jet_prof_enable brackets with events (bit i = family i in
+/* Bit mask of the kernel families that jet_prof_enable brackets with marks (bit i = family i in
  * the order candidates, candidates_hub, afterburner, select_moves, apply, rebalance_gain,
  * rebalance_select); default all.  Fewer families, less host work per launch. */
 #define JET_OPT_PROF_FAMILIES 3
@@ -322,8 +322,9 @@ int jet_flow_refine(jet_ctx *ctx, int32_t *part, int32_t alpha, int32_t max_roun
  * slow to follow; a piece that was foreseen wrongly costs its empty launches.  Results do not depend on
  * it. */
 #define JET_OPT_REPLAYS 8
-/* Workgroups of the persistent (grid-stride) kernels: candidates, afterburner chunks, move
- * selection, rebalancing gains; 64..65536, default 2048.  Results do not depend on it. */
+/* Most workgroups of the persistent (grid-stride) kernels: candidates, afterburner chunks, move
+ * selection, rebalancing gains; 64..65536, default 2048.  Candidates, gains and the hub passes never
+ * launch more than fit the chip at once.  Results do not depend on it. */
 #define JET_OPT_GRID 9
 /* Rating-table slots (16 bytes each) of one clustering launch (jet_coarsen): a sub-round whose
  * vertices need more is rated in several launches; at least one vertex's table always fits.  The
@@ -389,17 +390,17 @@ const char *jet_batch_last_error(const jet_batch *b);
 
 /* ---- instrumentation ---- */
 
-/* [host] accumulated HIP-event timing of one kernel family on the context's stream */
+/* [host] accumulated device timing of one kernel family on the context's stream */
 typedef struct {
   char name[24];       /* kernel family */
   int64_t launches;    /* timed launches */
-  double total_ms;     /* summed event-to-event duration */
+  double total_ms;     /* summed duration between the marks */
   double alg_bytes;    /* summed algorithmic bytes (0 when data dependent) */
 } jet_prof_entry;
 
-/* on != 0: bracket every kernel launch of the context (of the families JET_OPT_PROF_FAMILIES
- * selects) with HIP events from now on (counters are reset); on == 0: stop.  Adds a few
- * microseconds of host work per bracketed launch; the durations are read at jet_prof_read. */
+/* on != 0: bracket every kernel family of the context (of those JET_OPT_PROF_FAMILIES selects) with marks
+ * of the device clock from now on (counters are reset); on == 0: stop.  A mark is a small kernel, a few
+ * microseconds per bracketed family; the sums are read at jet_prof_read. */
 int jet_prof_enable(jet_ctx *ctx, int32_t on);
 /* Writes up to cap [host] entries (one per kernel family that ran) and the count to *count.
  * Synchronises the stream. */

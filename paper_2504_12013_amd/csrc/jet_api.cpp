@@ -1265,7 +1265,7 @@ int jet_set_option(jet_ctx *ctx, int32_t option, int64_t value) {
     c.rb_slots = (int32_t)value;
     return JET_OK;
   case JET_OPT_REPLAYS:
-    if (value < 1 || value > 1024) return fail(&c, JET_EINVAL, "replays per poll outside [1, 1024]");
+    if (value < 1 || value > 1024) return fail(&c, JET_EINVAL, "pieces in flight outside [1, 1024]");
     c.replays = (int32_t)value;
     return JET_OK;
   case JET_OPT_GRID:
@@ -1326,8 +1326,8 @@ const char *jet_last_error(const jet_ctx *ctx) {
 }
 
 
-// ---- batches: one context per hypergraph; lanes of streams, each driven by a host thread, take
-// the hypergraphs largest first.  A hypergraph's result depends only on its own inputs.
+// ---- batches: one union context per k, driven together by the calling thread.  A hypergraph's result
+// depends only on its own inputs.
 
 struct jet_batch {
   std::vector<jet_ctx *> uctx;          // union contexts: hypergraphs of one k, concatenated

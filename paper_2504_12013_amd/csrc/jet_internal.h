@@ -303,7 +303,10 @@ constexpr int kSides = 3;
 // of them finish theirs the next Jet launches cover the others only.  96 hypergraphs with 1 / 2 / 3 / 4
 // rounds: 168 / 142 / 126 / 139 ms.
 constexpr int32_t kUnionRounds = 3;
-constexpr int64_t kForkPins = 1 << 19;  // pins from which the afterburner's kernels run beside each other
+// Pins from which the afterburner's kernels run beside each other.  It pays on smaller levels too (beside /
+// after each other, row-net k = 64: 10,000 rows 46 / 55 ms, 40,000 15.7 / 18.8, 250,000 8.5 / 10.5; SAT-like
+// k = 32: 10,000 40.5 / 42.9, 100,000 104 / 117); the line spares small contexts the three streams.
+constexpr int64_t kForkPins = 1 << 19;
 
 constexpr int32_t kLaneDegreeDefault = 24;  // JET_OPT_CAND_LANE_DEGREE unless set
 
@@ -413,10 +416,10 @@ struct Ctx {
   jet_trace *dtrace = nullptr;   // device iteration records
   int32_t dtrace_cap = 0;
   hipStream_t gstream = nullptr; // stream the iteration graph is captured on
-  // captured pieces of an iteration (TickKind): Jet phase + end, Jet phase + rebalancing slots +
-  // end, rebalancing slots + end, rollback
   hipStream_t side[kSides] = {};  // branches of the afterburner beside `stream`
   hipEvent_t fork = nullptr, join[kSides] = {};
+  // captured pieces of the loop (TickKind): Jet phase, rb_slots rebalancing rounds, rollback, each with
+  // its control kernel
   hipGraph_t graph[kTickPieces] = {};
   hipGraphExec_t gexec[kTickPieces] = {};
   bool use_graph = true;         // JET_OPT_GRAPH

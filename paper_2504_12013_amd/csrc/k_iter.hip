@@ -1638,9 +1638,9 @@ void ab_nets_launch(Ctx &c, RgSink sink, const T *phi, const LoopCtl *lc, const 
 
 // The kernels of the net sizes run beside each other: a net of 10,000 pins keeps one workgroup busy for
 // 80 us while the others leave the chip, so it starts first.  On 1M row-net vertices at
-// k = 64 a full iteration's kernels took 314 us one after the other, 159 us beside each other.
-// Levels with few pins finish each within the 10 us that a fork and a join cost, and the unions of a
-// batch already run beside each other (166 ms for 96 hypergraphs, 195 ms with branches, at one rebalancing round per step).
+// k = 64 a full iteration's kernels took 314 us one after the other, 159 us beside each other.  The
+// unions of a batch already run beside each other (166 ms for 96 hypergraphs, 195 ms with branches, at
+// one rebalancing round per step).
 bool ab_branches(const Ctx &c) {
   const int kinds = (c.nchunks > 0) + (c.nbig > 0) + (c.nmid_large > 0) + (c.nmid > c.nmid_large);
   return c.H == 1 && kinds > 1 && c.p >= kForkPins && !graph_afterburner(c);
