@@ -7,6 +7,7 @@
 #include "conn.h"
 #include "dev_util.h"
 #include "entry.h"
+#include "hand_over.h"
 #include "jet_internal.h"
 #include "rec.h"
 
@@ -15,10 +16,7 @@ namespace jet {
 constexpr int kHubBlock = 256;
 constexpr int kHubWaves = kHubBlock / kWave;
 // Workgroups of one hub: one per kHubShare nets (the four of a thread that are in flight together), at most
-// kHubShares.  The release and acquire between them write back and invalidate caches, 3 to 4 us a pass: with
-// 16 workgroups on every hub a V-cycle on 1M row-net vertices took 1.5% longer (shares of 256 nets 1%), with
-// these as long as with an unordered hand-over.  What pays is a level of few listed hubs of thousands of
-// nets (8,000 hubs of 3,000 nets: 17 -> 21 us a rebalancing pass).
+// kHubShares.
 constexpr int kHubShares = 16;
 constexpr int kHubShare = 1024;
 constexpr int kHubSegment = 508; // nets one lane takes before its nine planes are emptied
@@ -40,7 +38,7 @@ struct HubArgs {
   const int64_t *voff;
   const uint64_t *ns;
   int32_t nhubs, k;
-  int32_t *rows, *done;  // [workgroups * (k + 1)] sums, [nhubs] arrivals (zero between launches)
+  unsigned long long *words;  // [kHubGrid / 2 * (k + 1)] sums of shared hubs (hand_over.h), zero between launches
   DevStatus *st;
   const LoopCtl *lc;
   Union u;
@@ -147,24 +145,16 @@ __device__ __forceinline__ void hub_work(const HubArgs &a, int32_t bid, int32_t 
         __builtin_amdgcn_readfirstlane(min(per, (int32_t)(q1 - q0 + kHubShare - 1) / kHubShare));
     if (sub >= shares) continue;  // block-uniform
     hub_sums<G, HW, UNIT>(a, q0 + (int64_t)sub * kHubBlock, q1, (int64_t)shares * kHubBlock, s, row);
-    if (shares > 1) {
-      int32_t *mine = a.rows + i * (k + 1);  // i < the grid: one pass when workgroups share hubs
-      for (int b = tid; b <= k; b += kHubBlock) mine[b] = row[b];
-      __syncthreads();
-      // the barrier and the release put every thread's stores before the arrival, the acquire and the next
-      // barrier the arrivals before the last workgroup's loads
-      if (tid == 0) {
-        s_last = __hip_atomic_fetch_add(&a.done[hi], 1, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT) == shares - 1;
-        if (s_last) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (shares > 1) {  // so every hub has a workgroup of its own or several: j < kHubGrid / 2
+      unsigned long long *words = a.words + (int64_t)j * (k + 1);
+      if (tid <= k) {
+        const bool last = word_add(&words[tid], row[tid], shares);
+        if (tid == k) s_last = last;
       }
       __syncthreads();
       if (!s_last) continue;  // block-uniform
-      for (int b = tid; b <= k; b += kHubBlock) {
-        int32_t c = 0;
-        for (int x = 0; x < shares; ++x) c += a.rows[((int64_t)j * per + x) * (k + 1) + b];
-        row[b] = c;
-      }
-      if (tid == 0) a.done[hi] = 0;
+      if (tid <= k && !word_take(&words[tid], shares, &row[tid]))
+        if (atomicCAS(&a.st->err, 0, kErrHandOver) == 0) a.st->err_arg = v;
       __syncthreads();
     }
     if (tid < kWave) {
@@ -233,8 +223,7 @@ inline HubArgs hub_args(Ctx &c, const int32_t *part, const LoopCtl *lc) {
   a.ns = c.ns;
   a.nhubs = c.nhubs;
   a.k = c.k;
-  a.rows = c.hub_rows;
-  a.done = c.hub_done;
+  a.words = c.hub_words;
   a.st = c.st;
   a.lc = lc;
   a.u = union_of(c);

@@ -177,8 +177,7 @@ void free_ctx(Ctx &c) {
   void *ptrs[] = {c.off,  c.pins, c.nw,   c.vw,        c.voff, c.inc,   c.sumw, c.adj,    c.chunks,    c.pnet, c.mid_nets,
                   c.big_nets, c.phi, c.phi16, c.ns, c.rec, c.inm, c.rg, c.lockstamp, c.best, c.moves, c.rb_keys,
                   c.rb_target, c.st, c.scan_tmp, c.ovf_list, c.ovf_off, c.ovf_ka, c.ovf_kb, c.ovf_ma,
-                  c.ovf_mb, c.hubs, c.mvfrom, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.hub_rows,
-                  c.hub_done,
+                  c.ovf_mb, c.hubs, c.mvfrom, c.bigmv, c.rb_list, c.rb_slot, c.lstat, c.tau_io, c.rgx, c.rb_hlist, c.hub_words,
                   c.rb_keys2, c.rb_gw, c.rb_gc};
   for (void *p : ptrs)
     if (p) (void)hipFree(p);
@@ -300,11 +299,11 @@ int init_impl(Ctx &c, int32_t n, int32_t m, int64_t num_pins, const int64_t *net
     c.nhubs = (int32_t)hh.size();
     HIP_OR_FAIL(&c, dalloc(&c.hubs, hh.size()));
     HIP_OR_FAIL(&c, dalloc(&c.rb_hlist, hh.size()));
-    HIP_OR_FAIL(&c, dalloc(&c.hub_rows, hh.empty() ? 0 : (size_t)jet::kHubGrid * (size_t)(c.k + 1)));
-    HIP_OR_FAIL(&c, dalloc(&c.hub_done, hh.size()));
+    const size_t words = hh.empty() ? 0 : (size_t)(jet::kHubGrid / 2) * (size_t)(c.k + 1);
+    HIP_OR_FAIL(&c, dalloc(&c.hub_words, words));
     if (!hh.empty()) {
       HIP_OR_FAIL(&c, hipMemcpyAsync(c.hubs, hh.data(), sizeof(int32_t) * hh.size(), hipMemcpyHostToDevice, c.stream));
-      HIP_OR_FAIL(&c, hipMemsetAsync(c.hub_done, 0, sizeof(int32_t) * hh.size(), c.stream));
+      HIP_OR_FAIL(&c, hipMemsetAsync(c.hub_words, 0, sizeof(unsigned long long) * words, c.stream));
     }
   }
   // net schedule: chunks of consecutive small nets (<= 64 pins in total), medium and big net lists

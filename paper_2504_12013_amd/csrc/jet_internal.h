@@ -208,6 +208,7 @@ enum : int32_t {
   kErrWeight = 6,         // weight < 1
   kErrOverflow = 7,       // a vertex's incident weight sum >= 2^31
   kErrTarget = 8,         // inspection input: candidate target outside [0,k) or equal to its block
+  kErrHandOver = 9,       // a workgroup waited for another one's sums in vain
 };
 
 // kernel families timed by the optional instrumentation
@@ -359,7 +360,6 @@ struct Ctx {
   int32_t nbig_over = 0;        // leading entries of big_nets with |e| > kBigCap
   int32_t *hubs = nullptr;      // vertices with more than kHubDegree incident nets
   int32_t nhubs = 0;
-  int32_t *hub_done = nullptr;  // [nhubs] workgroups of the running hub pass that stored their sums (zero between)
   int2 *ovf_list = nullptr;     // [nbig_over] (index into big_nets, net) needing the scratch path
   int64_t *ovf_off = nullptr;   // [nbig_over + 1] scratch offsets: 2 |e| event slots per net
   unsigned long long *ovf_ka = nullptr, *ovf_kb = nullptr;  // event keys (ping-pong)
@@ -382,7 +382,7 @@ struct Ctx {
   int32_t *rb_list = nullptr; // [n] non-hub vertices that may move in the current rebalancing round
   int32_t *rb_slot = nullptr; // [n] the entry slot of each listed vertex (its block's region)
   int32_t *rb_hlist = nullptr; // [nhubs] hubs (indices into hubs) that may move in the current rebalancing round
-  int32_t *hub_rows = nullptr; // [kHubGrid * (k + 1)] sums of the workgroups that share a hub in the running hub pass
+  unsigned long long *hub_words = nullptr; // [kHubGrid / 2 * (k + 1)] sums of shared hubs in the running hub pass
   int64_t *lstat = nullptr;   // [5] level statistics scratch
   float *tau_io = nullptr;    // [17] learned temperature: features in, temperature out
 

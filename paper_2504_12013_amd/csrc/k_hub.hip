@@ -2,10 +2,10 @@
 // gains (Section 4.3).
 //
 // Both need conn(v, b) over all incident nets of every hub.  A workgroup takes a hub, or while there
-// are fewer hubs than workgroups a share of a long one; then the workgroups of a hub store their sums in
-// rows and the last one to arrive adds the rows and finishes the hub (best target, record or entry), so no
-// second launch waits for the sums.  With unit net weights a lane takes whole nets into bit-sliced
-// counts (conn.h), which the wave sums at the end: a net costs a lane a gather and some 15
+// are fewer hubs than workgroups a share of a long one; then the workgroups of a hub add their sums into
+// words (hand_over.h) and the one that completes the last word finishes the hub (best target, record or
+// entry), so no second launch waits for the sums.  With unit net weights a lane takes whole nets into
+// bit-sliced counts (conn.h), which the wave sums at the end: a net costs a lane a gather and some 15
 // instructions.  Eight lanes per net with four exchanges and 24 instructions each bound the passes by
 // vector instructions (four cycles each): on levels of 1M
 // row-net vertices candidates took 49 us (now 40) and a rebalancing pass 38 us in three launches (25).
@@ -60,7 +60,6 @@ void hub_launch_form(Ctx &c, int64_t blocks, const HubArgs &a) {
 
 template <bool RB>
 hipError_t hub_launch(Ctx &c, const HubArgs &a) {
-  // rows: one per workgroup while workgroups share hubs
   const int64_t blocks = std::min<int64_t>(kHubGrid, (int64_t)c.nhubs * kHubShares);
 #define JET_HUB(G, HW, UNIT) hub_launch_form<RB, G, HW, UNIT>(c, blocks, a)
   if (c.unit_nw) {
