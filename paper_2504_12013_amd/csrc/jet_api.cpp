@@ -76,6 +76,8 @@ int map_device_error(Ctx &c, int32_t err, int32_t arg) {
     return fail(&c, JET_EINVAL, "candidate " + std::to_string(arg) + " has a target outside [0,k) or equal to its block");
   case jet::kErrOverflow:
     return fail(&c, JET_EOVERFLOW, "incident net weight of vertex " + std::to_string(arg) + " reaches 2^31");
+  case jet::kErrHandOver:
+    return fail(&c, JET_EHIP, "vertex " + std::to_string(arg) + ": sums of another workgroup did not arrive");
   default: return fail(&c, JET_EINVAL, "device reported error " + std::to_string(err));
   }
 }
