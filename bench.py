@@ -160,16 +160,25 @@ def kernel_base_name(name):
 # the headers of the kernel directory.  Per launch it is divided by the launches that ran (the
 # device loop also dispatches gated launches that return at once; the counters see those too).
 TRAFFIC_RECORDS = [
-    {"family": "rebalance_gain", "workload": "rownet-4000000-k64", "sources": ["k_rebal.hip"],
-     "sources_sha256": "eef8d73e95e5e1be22057613aec8e8888654eb623a815b500085538c59fd30e1", "bytes_per_step": (4193624.4 + 126110.7) * 1e6 / 3},
+    {"family": "afterburner", "workload": "rownet-4000000-k64", "sources": ["k_ab_large.hip", "k_iter.hip"],
+     "sources_sha256": "11da624e46a5a59c77a38a6af6967e1cea072536bcdaf13872040b8caf7aa507",
+     "bytes_per_step": (601593.8 + 191236.1) * 1e6 / 3},
     {"family": "apply", "workload": "rownet-4000000-k64", "sources": ["k_iter.hip"],
-     "sources_sha256": "af9ebc85d5c34ab5edb617c60d490e4d70860a9d5b5993983667048ec65fdf30", "bytes_per_step": (548190.9 + 807364.5) * 1e6 / 3},
+     "sources_sha256": "453d33eb21dabcbcd4bca82f229426e52fe399b64bd6620198d5aaed30dc9b1e",
+     "bytes_per_step": (867376.3 + 654593.8) * 1e6 / 3},
+    {"family": "rebalance_gain", "workload": "rownet-4000000-k64", "sources": ["k_rebal.hip"],
+     "sources_sha256": "4ea0e4d2219f5dd67e43cf4c7d6adb8f4633af65fc72f4e5341a4098d302f091",
+     "bytes_per_step": (4191594.9 + 66916.2) * 1e6 / 3},
     {"family": "candidates", "workload": "rownet-4000000-k64", "sources": ["k_iter.hip"],
-     "sources_sha256": "af9ebc85d5c34ab5edb617c60d490e4d70860a9d5b5993983667048ec65fdf30", "bytes_per_step": (804338.3 + 17651.3) * 1e6 / 3},
+     "sources_sha256": "453d33eb21dabcbcd4bca82f229426e52fe399b64bd6620198d5aaed30dc9b1e",
+     "bytes_per_step": (3387744.6 + 21857.7) * 1e6 / 3},
+    # the graph form alone (seven of the nine steps)
     {"family": "candidates", "workload": "mesh-4194304-k64", "sources": ["k_iter.hip"],
-     "sources_sha256": "af9ebc85d5c34ab5edb617c60d490e4d70860a9d5b5993983667048ec65fdf30", "bytes_per_step": (309890.1 + 21371.1) * 1e6 / 9},
+     "sources_sha256": "453d33eb21dabcbcd4bca82f229426e52fe399b64bd6620198d5aaed30dc9b1e",
+     "bytes_per_step": (82577.4 + 22487.1) * 1e6 / 7},
     {"family": "candidates", "workload": "vlsi-1000000-k8", "sources": ["k_iter.hip"],
-     "sources_sha256": "af9ebc85d5c34ab5edb617c60d490e4d70860a9d5b5993983667048ec65fdf30", "bytes_per_step": (3516.3 + 575.4) * 1e6 / 5},
+     "sources_sha256": "453d33eb21dabcbcd4bca82f229426e52fe399b64bd6620198d5aaed30dc9b1e",
+     "bytes_per_step": (3516.8 + 634.8) * 1e6 / 5},
 ]
 
 

@@ -28,9 +28,8 @@
 // the phases of one workgroup, k_co_settle_small, with barriers between the phases.
 // All weight updates are integer atomics: the result is the same for any schedule of the waves.
 // The pass is a chain of some 200 dependent sub-rounds, bound by the latency of each: 1M VLSI-like
-// vertices took 27.8 ms with global tables, a workgroup per group and six more passes per sub-round;
-// now 6.2 ms,
-// 2.9 of them the ratings (13 us a launch).
+// vertices took 27.8 ms with global tables, a workgroup per group and six more passes per sub-round; now
+// 6.2 ms, 2.9 of them the ratings (13 us a launch).
 #include <hip/hip_runtime.h>
 
 #include "dev_util.h"

@@ -7,8 +7,8 @@
 // entry), so no second launch waits for the sums.  With unit net weights a lane takes whole nets into
 // bit-sliced counts (conn.h), which the wave sums at the end: a net costs a lane a gather and some 15
 // instructions.  Eight lanes per net with four exchanges and 24 instructions each bound the passes by
-// vector instructions (four cycles each): on levels of 1M
-// row-net vertices candidates took 49 us (now 40) and a rebalancing pass 38 us in three launches (25).
+// vector instructions (four cycles each): on levels of 1M row-net vertices candidates took 49 us (now 40)
+// and a rebalancing pass 38 us in three launches (25).
 #include "hub.h"
 
 namespace jet {

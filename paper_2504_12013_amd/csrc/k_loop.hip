@@ -6,8 +6,7 @@
 // followed by its control kernel, are the pieces of an iteration; the host captures each in a HIP
 // graph once per context and launches them by what the control kernel last reported in pinned memory.
 // A union's hypergraphs may be in several phases at once: a piece then works on those in its phase.
-// Pieces after the loop finished do nothing.  The sequence of
-// states is exactly that of the host loop it replaces (one Jet phase, then rebalancing rounds while a
+// Pieces after the loop finished do nothing.  The sequence of states is exactly that of the host loop it replaces (one Jet phase, then rebalancing rounds while a
 // block is overloaded, a round moved something and the cap allows, then the key), so results and
 // per-iteration records do not depend on which pieces were launched ahead.
 //

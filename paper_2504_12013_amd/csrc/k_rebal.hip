@@ -605,8 +605,7 @@ __device__ __forceinline__ void pass_threshold(const unsigned long long *hw, con
 // it, when that completes the selection) and compacts the entries on the threshold digit into the
 // block's region of keep2.  The single-workgroup selection then continues over the kept entries, which
 // still differ anywhere in the key; it clears hist[b] again.
-// A block that holds half of 300,000 vertices took 140 us on the two slices that suit an average block;
-// now
+// A block that holds half of 300,000 vertices took 140 us on the two slices that suit an average block, now
 // 27 us, and a round's histogram and split 15 us on average (34).
 constexpr int kSplitThreads = 256;  // one thread per histogram bin
 
